@@ -153,9 +153,8 @@ typedef struct {
 
 /* Validates the description (before any device work), computes the per-mode
  * recursion coefficients in FP64 (paper: Sec. 3.2, the Stormer-Verlet and
- * transfer-function updates of each modal oscillator) and stores them as
- * float-float pairs,
- * partitions the batch into per-workgroup work, allocates device memory and
+ * transfer-function updates of each modal oscillator), in which the state is
+ * kept and stepped too, partitions the batch into per-workgroup work, allocates device memory and
  * uploads the coupling tensors and initial states on `stream`.
  * Shared-tensor path: when every instance is VK with n_t <= 64 and
  * n_in <= 64, the
@@ -238,7 +237,7 @@ int modal_check(modal_ctx *c, void *stream);
 int modal_reset(modal_ctx *c, void *stream);
 
 /* Copies the current state of every instance (the modal displacements of
- * Sec. 3.2's recursion, recombined from their float-float pairs) to host
+ * Sec. 3.2's recursion, held in FP64) to host
  * FP64 arrays laid out as the concatenation of the instances' modes:
  * x = q^n, xm1 = q^{n-1}
  * (each [sum n_t]).  Waits for `stream`. */
@@ -277,7 +276,7 @@ int modal_set_tangent(modal_ctx *c, int32_t inst, const float *Hd, void *stream)
  * every instance, run from the initial state (paper: Sec. 4.3, fitting by
  * propagating gradients through the time integrator).  dL_dy is device
  * memory [batch][y_stride] (FP32).  The forward pass is recomputed from
- * float-float checkpoints taken every ckpt_every steps (0 = 512); each
+ * FP64 checkpoints taken every ckpt_every steps (0 = 512); each
  * segment is re-run, recorded, and swept backwards by the adjoint kernel.
  * Outputs (host, FP64, modes concatenated over instances; NULL to skip):
  *   g_omega, g_gamma  dL/d omega_k, dL/d gamma_k (through the scheme's

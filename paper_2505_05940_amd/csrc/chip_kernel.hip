@@ -15,15 +15,15 @@
 // tensor, whose entries vanish unless the parity classes of the two columns
 // and the row match (Sec. 5, sparsity), only the partner class, a quarter of
 // them.  Per sample (paper: Sec. 3.1 modal forces, Sec. 3.2 modal update)
-//   1. wave 0 publishes q^n (fp32 high part, lane order) to LDS and writes
+//   1. wave 0 publishes q^n (rounded to FP32, lane order) to LDS and writes
 //      the output y^n = sum_k c_k q_k^n;
 //   2. every wave forms, for its rows, V[n, p] = sum_t h[r][t] q[jb + t]
 //      (a wave's rows share jb, so each q read serves all of them),
 //      eta_n = sum_p V[n, p] q_p (a DPP sum over the wave) and its partial
 //      force F_p = sum_n eta_n V[n, p];
 //   3. wave 0 adds the waves' partial forces (LDS) and advances its lane's
-//      mode in float-float arithmetic, d+ = m X - p d + r (b e - F),
-//      X+ = X + d+, exactly as the streaming kernel does.
+//      mode in FP64, d+ = m X - p d + r (b e - F), X+ = X + d+, exactly as
+//      the streaming kernel does.
 // Tension-modulated instances need no tensor: wave 0 forms
 // F_k = kappa lambda_k q_k sum_j lambda_j q_j^2 itself.  Linear instances
 // have F = 0.  Two workgroup barriers per sample and no global memory
@@ -62,7 +62,7 @@ __device__ __forceinline__ void wave_sums(float (&v)[R]) {
 // R: rows per wave (>= every wave's row count).
 template <int W, int R>
 __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) {
-  // q^n (high parts) in lane order, zero past the last lane so that a run of
+  // q^n (FP32) in lane order, zero past the last lane so that a run of
   // W columns from any jb reads zeros beyond the modes
   __shared__ float4 xc4[(kWave + 64) / 4];
   __shared__ float red[kChipWaves][kWave];  // per-wave partial forces
@@ -92,21 +92,17 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
   __syncthreads();
 
   // wave 0: its lane's mode, state and coefficients
-  float xh = 0.f, xl = 0.f, dh = 0.f, dl = 0.f;
-  float mh = 0.f, ml = 0.f, ph = 0.f, pl = 0.f, rh = 0.f, rl = 0.f, bx = 0.f, cw = 0.f, lam = 0.f;
+  double x = 0., d = 0., m = 0., p = 0., r = 0.;
+  float xh = 0.f, bx = 0.f, cw = 0.f, lam = 0.f;  // xh: x rounded to FP32
   if (wave == 0) {
     if (k >= 0) {
       const int so = U.state_off + k, mo = I.mode_off + k;
-      xh = P.x_hi[so];
-      xl = P.x_lo[so];
-      dh = P.d_hi[so];
-      dl = P.d_lo[so];
-      mh = P.m_hi[mo];
-      ml = P.m_lo[mo];
-      ph = P.p_hi[mo];
-      pl = P.p_lo[mo];
-      rh = P.r_hi[mo];
-      rl = P.r_lo[mo];
+      x = P.x[so];
+      d = P.d[so];
+      m = P.m[mo];
+      p = P.p[mo];
+      r = P.r[mo];
+      xh = (float)x;
       bx = P.b_ext[mo];
       cw = P.c_out[mo];
       lam = P.lam[mo];
@@ -160,7 +156,8 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
       F = lam * xh * S;
     }
     if (wave == 0) {
-      ff_step(xh, xl, dh, dl, mh, ml, ph, pl, rh, rl, fmaf(bx, e, -F));
+      mode_step(x, d, m, p, r, fmaf(bx, e, -F));
+      xh = (float)x;
       bad |= !isfinite(xh);
       if (k >= 0) Xc[lane] = xh;
     }
@@ -168,10 +165,8 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
   if (wave == 0) {
     if (k >= 0) {
       const int so = U.state_off + k;
-      P.x_hi[so] = xh;
-      P.x_lo[so] = xl;
-      P.d_hi[so] = dh;
-      P.d_lo[so] = dl;
+      P.x[so] = x;
+      P.d[so] = d;
     }
     if (__any(bad) && lane == 0) atomicOr(&P.flags[1], 1);
   }
@@ -181,7 +176,7 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
 // of up to 64 M modes (M <= kChipWaveModes / 64), one wave each: lane p
 // steps modes p, p + 64, ..., p + 64 (M - 1).  Per sample: the output and, for the tension
 // force F_k = kappa lam_k q_k sum_j lam_j q_j^2, one more sum over the wave
-// (DPP), then every mode's float-float update; no barrier and no memory
+// (DPP), then every mode's FP64 update; no barrier and no memory
 // traffic but the output and the excitation, read 64 samples ahead.
 template <int M>
 __global__ void __launch_bounds__(kWave) chip_wave_kernel(StepParams P) {
@@ -190,22 +185,19 @@ __global__ void __launch_bounds__(kWave) chip_wave_kernel(StepParams P) {
   const InstDev I = P.inst[U.inst];
   const int nt = I.nt;
   const bool tension = I.kind == KIND_TENSION;
-  float xh[M], xl[M], dh[M], dl[M], mh[M], ml[M], ph[M], pl[M], rh[M], rl[M], bx[M], cw[M], lam[M];
+  double x[M], d[M], m[M], p[M], r[M];
+  float xh[M], bx[M], cw[M], lam[M];  // xh: x rounded to FP32
 #pragma unroll
   for (int i = 0; i < M; ++i) {
     const int k = lane + kWave * i;
     const bool live = k < nt;
     const int so = U.state_off + k, mo = I.mode_off + k;
-    xh[i] = live ? P.x_hi[so] : 0.f;
-    xl[i] = live ? P.x_lo[so] : 0.f;
-    dh[i] = live ? P.d_hi[so] : 0.f;
-    dl[i] = live ? P.d_lo[so] : 0.f;
-    mh[i] = live ? P.m_hi[mo] : 0.f;
-    ml[i] = live ? P.m_lo[mo] : 0.f;
-    ph[i] = live ? P.p_hi[mo] : 0.f;
-    pl[i] = live ? P.p_lo[mo] : 0.f;
-    rh[i] = live ? P.r_hi[mo] : 0.f;
-    rl[i] = live ? P.r_lo[mo] : 0.f;
+    x[i] = live ? P.x[so] : 0.;
+    d[i] = live ? P.d[so] : 0.;
+    m[i] = live ? P.m[mo] : 0.;
+    p[i] = live ? P.p[mo] : 0.;
+    r[i] = live ? P.r[mo] : 0.;
+    xh[i] = (float)x[i];
     bx[i] = live ? P.b_ext[mo] : 0.f;
     cw[i] = live ? P.c_out[mo] : 0.f;
     lam[i] = live ? P.lam[mo] : 0.f;
@@ -215,8 +207,8 @@ __global__ void __launch_bounds__(kWave) chip_wave_kernel(StepParams P) {
   // c; each chunk's loads are issued a chunk ahead, and the steps of a chunk
   // read no memory, so no step waits on the vector-memory counter
   auto chunk = [&](long long n0) {
-    const long long m = n0 + lane;
-    return m < I.n_exc ? P.e_ext[I.e_off + m] : 0.f;
+    const long long t = n0 + lane;
+    return t < I.n_exc ? P.e_ext[I.e_off + t] : 0.f;
   };
   float en = chunk(base);
   bool bad = false;
@@ -238,7 +230,8 @@ __global__ void __launch_bounds__(kWave) chip_wave_kernel(StepParams P) {
 #pragma unroll
       for (int i = 0; i < M; ++i) {
         const float F = lam[i] * xh[i] * S;
-        ff_step(xh[i], xl[i], dh[i], dl[i], mh[i], ml[i], ph[i], pl[i], rh[i], rl[i], fmaf(bx[i], e, -F));
+        mode_step(x[i], d[i], m[i], p[i], r[i], fmaf(bx[i], e, -F));
+        xh[i] = (float)x[i];
         bad |= !isfinite(xh[i]);
       }
     }
@@ -248,10 +241,8 @@ __global__ void __launch_bounds__(kWave) chip_wave_kernel(StepParams P) {
     const int k = lane + kWave * i;
     if (k < nt) {
       const int so = U.state_off + k;
-      P.x_hi[so] = xh[i];
-      P.x_lo[so] = xl[i];
-      P.d_hi[so] = dh[i];
-      P.d_lo[so] = dl[i];
+      P.x[so] = x[i];
+      P.d[so] = d[i];
     }
   }
   if (__any(bad) && lane == 0) atomicOr(&P.flags[1], 1);

@@ -50,20 +50,13 @@ __device__ __forceinline__ ff ff_mul_f(ff a, float b) {
   return fast_two_sum(p, e);
 }
 
-// d+ = m X - p d + r fe ;  X+ = X + d+
-__device__ __forceinline__ void ff_step(float& xh, float& xl, float& dh, float& dl,
-                                        float mh, float ml, float ph, float pl,
-                                        float rh, float rl, float fe) {
-  ff X{xh, xl}, D{dh, dl};
-  ff a = ff_mul({mh, ml}, X);
-  ff b = ff_mul({ph, pl}, D);
-  ff t = ff_add(a, {-b.hi, -b.lo});
-  t = ff_add(t, ff_mul_f({rh, rl}, fe));
-  X = ff_add(X, t);
-  xh = X.hi;
-  xl = X.lo;
-  dh = t.hi;
-  dl = t.lo;
+// d+ = m X - p d + r fe ;  X+ = X + d+, in FP64: four instructions at the
+// FP32 issue rate (gfx950 runs FP64 vector code at the rate of unpacked
+// FP32), where the float-float form of this update took about 80 and filled
+// most of a small instance's step (one-wave string: 0.30 us a step before).
+__device__ __forceinline__ void mode_step(double& x, double& d, double m, double p, double r, float fe) {
+  d = fma(m, x, fma(-p, d, r * (double)fe));
+  x += d;
 }
 
 // ------------------------------------------------------------------ helpers
@@ -99,6 +92,24 @@ __device__ __forceinline__ float dot4(float4 a, float4 b) {
   return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)));
 }
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+
+typedef double v2d __attribute__((ext_vector_type(2)));
+// four consecutive doubles (two 16-byte accesses; p on a multiple of 16 bytes)
+struct f64x4 {
+  double v[4];
+};
+__device__ __forceinline__ f64x4 ld4d(const double* p) {
+  const v2d a = reinterpret_cast<const v2d*>(p)[0], b = reinterpret_cast<const v2d*>(p)[1];
+  return {{a.x, a.y, b.x, b.y}};
+}
+__device__ __forceinline__ void st4d(double* p, const f64x4& v) {
+  reinterpret_cast<v2d*>(p)[0] = (v2d){v.v[0], v.v[1]};
+  reinterpret_cast<v2d*>(p)[1] = (v2d){v.v[2], v.v[3]};
+}
+// their FP32 roundings
+__device__ __forceinline__ float4 to_f4(const f64x4& v) {
+  return make_float4((float)v.v[0], (float)v.v[1], (float)v.v[2], (float)v.v[3]);
+}
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 // Raw buffer resource over `bytes` bytes at p (stride 0).  Loads at byte

@@ -6,7 +6,7 @@
 //   qb^n     = ybar^n c + qb^{n+1} + m db^{n+1} - J(q^n) u^n,
 // with J = dF/dq symmetric.  For the von Karman force one pass over a row of
 // Ht with two right-hand sides gives V = Ht q and W = Ht u, eta = V.q,
-// w = V.u and (J u) += 2 w V + eta W, F += eta V.  Per-mode float-float
+// w = V.u and (J u) += 2 w V + eta W, F += eta V.  Per-mode FP64
 // accumulators collect dL/dm, dL/dp, dL/dr, dL/dc and the force-scale term
 // u.F; an optional tangent tensor Hd adds the directional derivative
 // -(Vd.q) (V.u) - eta (Vd.u) per row, Vd = Hd q.  Work partition, slab
@@ -352,37 +352,22 @@ __device__ void vk_rows2_finish(const float* xv, const int* xr, int nw, int wave
   }
 }
 
-__device__ __forceinline__ void acc_add(float* acc, int k, int sf, int i, ff v) {
-  ff a{acc[(2 * k) * (long long)sf + i], acc[(2 * k + 1) * (long long)sf + i]};
-  a = ff_add(a, v);
-  acc[(2 * k) * (long long)sf + i] = a.hi;
-  acc[(2 * k + 1) * (long long)sf + i] = a.lo;
-}
-
 // u^n = r db^{n+1}, db^{n+1} = qb^{n+1} - p db^{n+2}, of four consecutive
-// modes from the adjoint state (the high parts of u).
+// modes from the adjoint state (rounded to FP32).
 __device__ __forceinline__ float4 adj_u4(const GradParams& P, int so, int mo) {
-  const float4 qh4 = ld4(P.qb_hi + so), ql4 = ld4(P.qb_lo + so);
-  const float4 dh4 = ld4(P.db_hi + so), dl4 = ld4(P.db_lo + so);
-  const float4 ph4 = ld4(P.p_hi + mo), pl4 = ld4(P.p_lo + mo);
-  const float4 rh4 = ld4(P.r_hi + mo), rl4 = ld4(P.r_lo + mo);
-  const float qh[4] = {qh4.x, qh4.y, qh4.z, qh4.w}, ql[4] = {ql4.x, ql4.y, ql4.z, ql4.w};
-  const float dh[4] = {dh4.x, dh4.y, dh4.z, dh4.w}, dl[4] = {dl4.x, dl4.y, dl4.z, dl4.w};
-  const float ph[4] = {ph4.x, ph4.y, ph4.z, ph4.w}, pl[4] = {pl4.x, pl4.y, pl4.z, pl4.w};
-  const float rh[4] = {rh4.x, rh4.y, rh4.z, rh4.w}, rl[4] = {rl4.x, rl4.y, rl4.z, rl4.w};
-  float us[4];
+  const f64x4 qb = ld4d(P.qb + so), db = ld4d(P.db + so);
+  const f64x4 p = ld4d(P.p + mo), r = ld4d(P.r + mo);
+  f64x4 u;
 #pragma unroll
-  for (int e4 = 0; e4 < 4; ++e4) {
-    const ff t = ff_mul({ph[e4], pl[e4]}, {dh[e4], dl[e4]});
-    const ff db = ff_add({qh[e4], ql[e4]}, {-t.hi, -t.lo});
-    us[e4] = ff_mul({rh[e4], rl[e4]}, db).hi;
-  }
-  return make_float4(us[0], us[1], us[2], us[3]);
+  for (int i = 0; i < 4; ++i) u.v[i] = r.v[i] * fma(-p.v[i], db.v[i], qb.v[i]);
+  return to_f4(u);
 }
 
 // Finishes step n for the modes of one unit given the full J u and F.  The
 // adjoint state, coefficients and accumulators of a lane's four modes move
-// as float4 (per-unit state and per-mode arrays start on multiples of 4).
+// as 16-byte accesses (per-unit state and per-mode arrays start on multiples
+// of 4); all of it in FP64, about 10 instructions a mode where float-float
+// pairs took 250.
 template <int GM>
 __device__ void adj_post(const GradParams& P, const InstDev& I, const UnitDev& U, long long n,
                          const float4 (&Ju)[GM], const float4 (&F)[GM], int G, int lane) {
@@ -400,72 +385,38 @@ __device__ void adj_post(const GradParams& P, const InstDev& I, const UnitDev& U
     const int mo = I.mode_off + 4 * k4;
     const float4 x4 = ld4(P.rec_x + ro + 4 * k4), d4 = ld4(P.rec_d + ro + 4 * k4);
     const float4 b4 = ld4(P.b_ext + mo), c4 = ld4(P.c_out + mo);
-    const float4 qh4 = ld4(P.qb_hi + so), ql4 = ld4(P.qb_lo + so);
-    const float4 dh4 = ld4(P.db_hi + so), dl4 = ld4(P.db_lo + so);
-    const float4 ph4 = ld4(P.p_hi + mo), pl4 = ld4(P.p_lo + mo);
-    const float4 rh4 = ld4(P.r_hi + mo), rl4 = ld4(P.r_lo + mo);
-    const float4 mh4 = ld4(P.m_hi + mo), ml4 = ld4(P.m_lo + mo);
-    float4 ah[5], al[5];
+    const f64x4 p = ld4d(P.p + mo), r = ld4d(P.r + mo), m = ld4d(P.m + mo);
+    f64x4 qb = ld4d(P.qb + so), db = ld4d(P.db + so);
+    f64x4 a[5];
     if (accumulate) {
 #pragma unroll
-      for (int k = 0; k < 5; ++k) {
-        ah[k] = ld4(P.acc + (2 * k) * sf + so);
-        al[k] = ld4(P.acc + (2 * k + 1) * sf + so);
-      }
+      for (int k = 0; k < 5; ++k) a[k] = ld4d(P.acc + k * sf + so);
     }
     const float xs[4] = {x4.x, x4.y, x4.z, x4.w}, ds[4] = {d4.x, d4.y, d4.z, d4.w};
     const float bs[4] = {b4.x, b4.y, b4.z, b4.w}, cs[4] = {c4.x, c4.y, c4.z, c4.w};
     const float js[4] = {Ju[g].x, Ju[g].y, Ju[g].z, Ju[g].w};
     const float fs[4] = {F[g].x, F[g].y, F[g].z, F[g].w};
-    const float qh[4] = {qh4.x, qh4.y, qh4.z, qh4.w}, ql[4] = {ql4.x, ql4.y, ql4.z, ql4.w};
-    const float dh[4] = {dh4.x, dh4.y, dh4.z, dh4.w}, dl[4] = {dl4.x, dl4.y, dl4.z, dl4.w};
-    const float phs[4] = {ph4.x, ph4.y, ph4.z, ph4.w}, pls[4] = {pl4.x, pl4.y, pl4.z, pl4.w};
-    const float rhs[4] = {rh4.x, rh4.y, rh4.z, rh4.w}, rls[4] = {rl4.x, rl4.y, rl4.z, rl4.w};
-    const float mhs[4] = {mh4.x, mh4.y, mh4.z, mh4.w}, mls[4] = {ml4.x, ml4.y, ml4.z, ml4.w};
-    float ahs[5][4], als[5][4];
 #pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      ahs[k][0] = ah[k].x; ahs[k][1] = ah[k].y; ahs[k][2] = ah[k].z; ahs[k][3] = ah[k].w;
-      als[k][0] = al[k].x; als[k][1] = al[k].y; als[k][2] = al[k].z; als[k][3] = al[k].w;
-    }
-    float oqh[4], oql[4], odh[4], odl[4];
-#pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {
+    for (int i = 0; i < 4; ++i) {
       // db^{n+1} = qb^{n+1} - p db^{n+2},  u^n = r db^{n+1}
-      const ff t = ff_mul({phs[e4], pls[e4]}, {dh[e4], dl[e4]});
-      const ff db = ff_add({qh[e4], ql[e4]}, {-t.hi, -t.lo});
-      const ff u = ff_mul({rhs[e4], rls[e4]}, db);
+      const double dn = fma(-p.v[i], db.v[i], qb.v[i]);
       if (accumulate) {
-        const ff v[5] = {ff_mul_f(db, xs[e4]), ff_mul_f(db, -ds[e4]), ff_mul_f(db, fmaf(bs[e4], e, -fs[e4])),
-                         two_prod(yb, xs[e4]), ff_mul_f(u, -fs[e4])};
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          const ff a = ff_add({ahs[k][e4], als[k][e4]}, v[k]);
-          ahs[k][e4] = a.hi;
-          als[k][e4] = a.lo;
-        }
+        a[0].v[i] = fma(dn, (double)xs[i], a[0].v[i]);
+        a[1].v[i] = fma(-dn, (double)ds[i], a[1].v[i]);
+        a[2].v[i] = fma(dn, (double)fmaf(bs[i], e, -fs[i]), a[2].v[i]);
+        a[3].v[i] = fma((double)yb, (double)xs[i], a[3].v[i]);
+        a[4].v[i] = fma(-(r.v[i] * dn), (double)fs[i], a[4].v[i]);
       }
       // qb^n = ybar c + qb^{n+1} + m db^{n+1} - (J u)
-      ff qb = {qh[e4], ql[e4]};
-      qb = ff_add(qb, ff_mul({mhs[e4], mls[e4]}, db));
-      qb = ff_add(qb, two_prod(yb, cs[e4]));
-      qb = ff_add(qb, {-js[e4], 0.f});
-      oqh[e4] = qb.hi;
-      oql[e4] = qb.lo;
-      odh[e4] = db.hi;
-      odl[e4] = db.lo;
+      qb.v[i] = fma(m.v[i], dn, qb.v[i]) + fma((double)yb, (double)cs[i], -(double)js[i]);
+      db.v[i] = dn;
     }
     if (accumulate) {
 #pragma unroll
-      for (int k = 0; k < 5; ++k) {
-        st4(P.acc + (2 * k) * sf + so, make_float4(ahs[k][0], ahs[k][1], ahs[k][2], ahs[k][3]));
-        st4(P.acc + (2 * k + 1) * sf + so, make_float4(als[k][0], als[k][1], als[k][2], als[k][3]));
-      }
+      for (int k = 0; k < 5; ++k) st4d(P.acc + k * sf + so, a[k]);
     }
-    st4(P.qb_hi + so, make_float4(oqh[0], oqh[1], oqh[2], oqh[3]));
-    st4(P.qb_lo + so, make_float4(oql[0], oql[1], oql[2], oql[3]));
-    st4(P.db_hi + so, make_float4(odh[0], odh[1], odh[2], odh[3]));
-    st4(P.db_lo + so, make_float4(odl[0], odl[1], odl[2], odl[3]));
+    st4d(P.qb + so, qb);
+    st4d(P.db + so, db);
   }
 }
 
@@ -575,7 +526,7 @@ __global__ void __launch_bounds__(kWave * NW) grad_kernel(GradParams P) {
         }
         if (TAN && wave == 0 && lane == 0) {
           // theta partial of this unit: mode slot 0 of its theta accumulator
-          acc_add(P.acc, 5, P.state_floats, U.state_off, {tsum, 0.f});
+          P.acc[5LL * P.state_floats + U.state_off] += (double)tsum;
         }
       } else if (I.kind == KIND_TENSION && wave == 0) {
         // F = kappa lam x S, J u = kappa lam (u S + 2 x sum(lam x u))
@@ -777,30 +728,41 @@ hipError_t launch_tensor_grad(const TGradJob* jobs, int n_jobs, int max_nin, int
   return hipGetLastError();
 }
 
-// Adds the per-row records of one segment (steps in record order) to the
-// float-float row accumulators acc[2][rows].
-__global__ void row_sum_kernel(const float* rrec, int seg_len, int rows, float* acc) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  ff a{acc[r], acc[rows + r]};
-  for (int s = 0; s < seg_len; ++s) a = ff_add(a, ff{rrec[(long long)s * rows + r], 0.f});
-  acc[r] = a.hi;
-  acc[rows + r] = a.lo;
+// Adds the per-row records of one segment to the FP64 row accumulators.  A
+// workgroup sums kRowSumRows rows, its threads in kRowSumWays ways of
+// interleaved steps each, joined in a fixed order through LDS: 512 steps of
+// 2560 rows in 5 us where one thread a row, a serial chain of loads, took 130.
+constexpr int kRowSumRows = 32, kRowSumWays = 16;
+__global__ void __launch_bounds__(kRowSumRows* kRowSumWays) row_sum_kernel(const float* rrec, int seg_len,
+                                                                           int rows, double* acc) {
+  __shared__ double part[kRowSumWays][kRowSumRows];
+  const int tr = threadIdx.x % kRowSumRows, w = threadIdx.x / kRowSumRows;
+  const int r = blockIdx.x * kRowSumRows + tr;
+  double a = 0.;
+  if (r < rows)
+#pragma unroll 8
+    for (int s = w; s < seg_len; s += kRowSumWays) a += (double)rrec[(long long)s * rows + r];
+  part[w][tr] = a;
+  __syncthreads();
+  if (w == 0 && r < rows) {
+    for (int i = 1; i < kRowSumWays; ++i) a += part[i][tr];
+    acc[r] += a;
+  }
 }
 
-// Copies checkpoint `slot` ([4][mode_floats]) into every unit's state and
+// Copies checkpoint `slot` ([2][mode_floats]) into every unit's state and
 // rewinds the step counter and the forward arrival words to `step`.
-__global__ void restore_kernel(const float* ckpt, long long slot, int mode_floats, const InstDev* inst,
-                               const UnitDev* unit, int n_units, float* state, int state_floats,
+__global__ void restore_kernel(const double* ckpt, long long slot, int mode_floats, const InstDev* inst,
+                               const UnitDev* unit, int n_units, double* state, int state_floats,
                                long long* step_base, long long step, unsigned int* ctr) {
   const int u = blockIdx.x;
   if (u >= n_units) return;
   const UnitDev U = unit[u];
   const InstDev I = inst[U.inst];
   if (threadIdx.x == 0) ctr[I.ctr_off + U.slab] = (unsigned int)step;
-  const float* src = ckpt + slot * 4LL * mode_floats + I.mode_off;
+  const double* src = ckpt + slot * 2LL * mode_floats + I.mode_off;
   for (int k = threadIdx.x; k < I.ntp; k += blockDim.x)
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 2; ++a)
       state[(long long)a * state_floats + U.state_off + k] = src[(long long)a * mode_floats + k];
   if (u == 0 && threadIdx.x == 0) *step_base = step;
 }
@@ -849,14 +811,15 @@ hipError_t grad_occupancy(int* blocks, int gm, bool tangent, int nw, bool split,
 #undef GO
 }
 
-hipError_t launch_row_sum(const float* rrec, int seg_len, int rows, float* acc, hipStream_t s) {
+hipError_t launch_row_sum(const float* rrec, int seg_len, int rows, double* acc, hipStream_t s) {
   if (rows < 1) return hipSuccess;
-  hipLaunchKernelGGL(row_sum_kernel, dim3((rows + 255) / 256), dim3(256), 0, s, rrec, seg_len, rows, acc);
+  hipLaunchKernelGGL(row_sum_kernel, dim3((rows + kRowSumRows - 1) / kRowSumRows), dim3(kRowSumRows * kRowSumWays),
+                     0, s, rrec, seg_len, rows, acc);
   return hipGetLastError();
 }
 
-hipError_t launch_restore(const float* ckpt, long long slot, int mode_floats, const InstDev* inst,
-                          const UnitDev* unit, int n_units, float* state, int state_floats,
+hipError_t launch_restore(const double* ckpt, long long slot, int mode_floats, const InstDev* inst,
+                          const UnitDev* unit, int n_units, double* state, int state_floats,
                           long long* step_base, long long step, unsigned int* ctr, hipStream_t s) {
   hipLaunchKernelGGL(restore_kernel, dim3(n_units), dim3(256), 0, s, ckpt, slot, mode_floats, inst,
                      unit, n_units, state, state_floats, step_base, step, ctr);

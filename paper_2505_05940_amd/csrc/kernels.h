@@ -63,8 +63,8 @@ struct UnitDev {
 // (red_floats >= 2 ntp for every instance), where wave 0 sums them.
 // A workgroup that owns a single unit for the whole launch may also keep that
 // unit's state and its instance's per-mode coefficients resident in LDS: 13
-// arrays of res_stride floats after the reduction regions (X hi, X lo, d hi,
-// d lo, m hi, m lo, p hi, p lo, r hi, r lo, b, c, lambda).
+// res_stride floats after the reduction regions (FP64 X, d, m, p, r, two
+// floats a value; FP32 b, c, lambda).
 constexpr int kResArrays = 13;
 // Exchange words of the waves that share an in-plane row (one-unit
 // workgroups, whose waves divide the unit's row blocks rather than its rows):
@@ -131,12 +131,12 @@ struct StepParams {
   const UnitDev* unit;
   const int* wg_begin;  // [n_wg + 1] unit ranges per workgroup
   const float* H;       // tensor pool
-  // per-mode float-float coefficients of d+ = m X - p d + r (f_ext - f)
-  const float *m_hi, *m_lo, *p_hi, *p_lo, *r_hi, *r_lo;
+  // per-mode FP64 coefficients of d+ = m X - p d + r (f_ext - f)
+  const double *m, *p, *r;
   const float *c_out, *lam, *b_ext;
   const float* e_ext;
-  // per-unit state (float-float X = q^n and d = q^n - q^{n-1})
-  float *x_hi, *x_lo, *d_hi, *d_lo;
+  // per-unit FP64 state (X = q^n and d = q^n - q^{n-1})
+  double *x, *d;
   float* part;              // partial forces of split instances
   unsigned int* ctr;        // arrival words of split instances' slabs (InstDev.ctr_off)
   int* flags;               // [0] barrier timeout, [1] non-finite state
@@ -151,9 +151,9 @@ struct StepParams {
   // coefficients in LDS (kResArrays arrays of res_stride >= ntp floats) from
   // the start of the launch, writing the state back at its end
   int res_stride;
-  // checkpoints of the float-float state at steps that are multiples of
-  // ckpt_every: [slot][4][mode_floats] (X hi, X lo, d hi, d lo); NULL = none
-  float* ckpt;
+  // checkpoints of the state at steps that are multiples of ckpt_every:
+  // [slot][2][mode_floats] (X, d); NULL = none
+  double* ckpt;
   int ckpt_every;
   // per-step record of q^n and d^n (fp32) for steps rec_base.. : [step][mode_floats]
   float *rec_x, *rec_d;
@@ -168,7 +168,7 @@ struct GradParams {
   const int* wg_begin;
   const float* H;
   const float* Hd;  // tangent tensor pool (same layout as H) or NULL
-  const float *m_hi, *m_lo, *p_hi, *p_lo, *r_hi, *r_lo;
+  const double *m, *p, *r;
   const float *c_out, *lam, *b_ext;
   const float* e_ext;
   const float *rec_x, *rec_d;  // recorded q^n, d^n of the segment
@@ -177,11 +177,11 @@ struct GradParams {
   int mode_floats;
   const float* ybar;           // dL/dy [batch][ybar_stride], absolute steps
   long long ybar_stride;
-  // adjoint state per unit: qb = dL/dq^{n+1}, db = dL/dd^{n+2} (float-float)
-  float *qb_hi, *qb_lo, *db_hi, *db_lo;
-  // per-unit accumulators, float-float pairs [10][state floats]:
+  // adjoint state per unit: qb = dL/dq^{n+1}, db = dL/dd^{n+2} (FP64)
+  double *qb, *db;
+  // per-unit FP64 accumulators [6][state floats]:
   // m, p, r, c, s (u.F per mode), theta (per mode)
-  float* acc;
+  double* acc;
   int state_floats;
   float* part;           // partial (J u, F) of split instances, [2][nslab][2 ntp] at 2 part_off
   unsigned int* ctr;
@@ -241,8 +241,9 @@ struct SharedParams {
   const float* s2;           // [n_wg][nin_max][cols] squared row scales
   int nin_max, cols, ktot;   // cols = 64 JT, ktot = 16 KT
   // per (column, mode), layout [n_wg * cols][ktot]
-  float *x_hi, *x_lo, *d_hi, *d_lo;
-  const float *m_hi, *m_lo, *p_hi, *p_lo, *r_hi, *r_lo, *c_out, *b_ext;
+  double *x, *d;
+  const double *m, *p, *r;
+  const float *c_out, *b_ext;
   const float* e_ext;
   float* y;
   long long y_stride;

@@ -34,11 +34,11 @@ bool chip_shape(int max_nt, int max_rows, int& nt_tile, int& rows);
 hipError_t launch_grad(const GradParams& P, int gm, bool tangent, int nw, bool split, int n_wg, size_t lds,
                        hipStream_t s);
 hipError_t grad_occupancy(int* blocks, int gm, bool tangent, int nw, bool split, size_t lds);
-hipError_t launch_restore(const float* ckpt, long long slot, int mode_floats, const InstDev* inst,
-                          const UnitDev* unit, int n_units, float* state, int state_floats,
+hipError_t launch_restore(const double* ckpt, long long slot, int mode_floats, const InstDev* inst,
+                          const UnitDev* unit, int n_units, double* state, int state_floats,
                           long long* step_base, long long step, unsigned int* ctr, hipStream_t s);
 hipError_t launch_shared(const SharedParams& P, int kt, int kc, int jt, int n_wg, hipStream_t s);
-hipError_t launch_row_sum(const float* rrec, int seg_len, int rows, float* acc, hipStream_t s);
+hipError_t launch_row_sum(const float* rrec, int seg_len, int rows, double* acc, hipStream_t s);
 hipError_t launch_tf_response(const float2* coef, const int* mode_off, int batch, const FFc* z, int n_freq,
                               FFc* H, hipStream_t s);
 hipError_t launch_tf_grad(const float2* coef, const int* mode_off, int batch, int max_modes, const FFc* z,
@@ -228,12 +228,12 @@ struct modal_ctx {
   long long coupling_bytes = 0, padded_bytes = 0, steps = 0;
   int state_floats = 0, mode_floats = 0;
   std::vector<int> nt, unit_state_of_inst, inst_mode_off;
-  std::vector<float> state0;  // x_hi, x_lo, d_hi, d_lo concatenated
+  std::vector<double> state0;  // X, d concatenated
   // device
   float* dH = nullptr;
   void* dMeta = nullptr;     // InstDev, UnitDev, wg_begin
-  float* dCoef = nullptr;    // 9 per-mode arrays
-  float* dState = nullptr;   // 4 per-unit arrays
+  double* dCoef = nullptr;   // per-mode arrays: FP64 m, p, r, then FP32 c, lambda, b
+  double* dState = nullptr;  // per-unit arrays X, d
   float* dPart = nullptr;
   unsigned int* dCtr = nullptr;  // arrival words, n_ctr of them (one per slab)
   int n_ctr = 0;
@@ -248,10 +248,10 @@ struct modal_ctx {
   std::vector<double> omega, gamma;  // concatenated over instances
   std::vector<int> kind;
   // gradient buffers (allocated on first modal_grad)
-  float *dHd = nullptr, *dCkpt = nullptr, *dRec = nullptr, *dAdj = nullptr, *dAcc = nullptr,
-        *dGPart = nullptr;
+  float *dHd = nullptr, *dRec = nullptr, *dGPart = nullptr;
+  double *dCkpt = nullptr, *dAdj = nullptr, *dAcc = nullptr;
   unsigned int* dGCtr = nullptr;
-  long long ckpt_floats = 0, rec_floats = 0;
+  long long ckpt_vals = 0, rec_floats = 0;
   // Checkpoints recorded by the forward runs of a gradient context, every
   // kRunCkpt steps from step 0: valid for the steps [0, ckpt_upto) run with
   // the current tensors unless broken (a gap, or a buffer that had to grow
@@ -273,7 +273,8 @@ struct modal_ctx {
   bool tangent = false;
   // per-row (in-plane) gradient pools: rows of all VK instances
   int rows_total = 0;
-  float *dRrec = nullptr, *dRacc = nullptr;
+  float* dRrec = nullptr;
+  double* dRacc = nullptr;
   long long rrec_floats = 0;
   // full tensor gradient: u and (eta, V.u) records of a segment, job list
   float *dUrec = nullptr, *dTrec = nullptr;
@@ -1208,8 +1209,9 @@ int init_shared(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& gro
   std::vector<SharedWg> wgs;
   std::vector<SharedSlot> slots(ncol, SharedSlot{-1, 0, 0, 0});
   std::vector<float> apool, s2((size_t)n_wg * nin_max * cols, 0.f);
-  std::vector<float> coef(8 * (size_t)ncolk, 0.f);
-  c->state0.assign(4 * (size_t)ncolk, 0.f);
+  std::vector<double> coef(3 * (size_t)ncolk, 0.);  // m, p, r
+  std::vector<float> cb(2 * (size_t)ncolk, 0.f);    // output and force weights
+  c->state0.assign(2 * (size_t)ncolk, 0.);
   c->unit_state_of_inst.assign(d->batch, 0);
   std::vector<float> epool(1, 0.f);
   for (auto& g : groups) {
@@ -1270,13 +1272,13 @@ int init_shared(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& gro
         c->unit_state_of_inst[b] = (int)o;
         for (int k = 0; k < I.n_t; ++k) {
           const Coef q = coefficients(d->scheme, I.omega[k], I.gamma[k], T);
-          split(q.m, coef[o + k], coef[ncolk + o + k]);
-          split(q.p, coef[2 * ncolk + o + k], coef[3 * ncolk + o + k]);
-          split(q.r, coef[4 * ncolk + o + k], coef[5 * ncolk + o + k]);
-          coef[6 * ncolk + o + k] = (float)I.c_out[k];
-          coef[7 * ncolk + o + k] = I.b_ext ? (float)I.b_ext[k] : 0.f;
-          split(I.x0[k], c->state0[o + k], c->state0[ncolk + o + k]);
-          split(I.x0[k] - I.xm1[k], c->state0[2 * ncolk + o + k], c->state0[3 * ncolk + o + k]);
+          coef[o + k] = q.m;
+          coef[ncolk + o + k] = q.p;
+          coef[2 * ncolk + o + k] = q.r;
+          cb[o + k] = (float)I.c_out[k];
+          cb[ncolk + o + k] = I.b_ext ? (float)I.b_ext[k] : 0.f;
+          c->state0[o + k] = I.x0[k];
+          c->state0[ncolk + o + k] = I.x0[k] - I.xm1[k];
         }
         c->flops += 2LL * g.nin * g.nt * g.nt + 4LL * g.nin * g.nt;
       }
@@ -1300,8 +1302,8 @@ int init_shared(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& gro
   int r = dalloc(&c->dShA, sizeof(float) * (apool.size() + 64));
   if (!r) r = dalloc(&c->dMeta, meta_bytes);
   if (!r) r = dalloc(&c->dShS2, sizeof(float) * s2.size());
-  if (!r) r = dalloc(&c->dCoef, sizeof(float) * coef.size());
-  if (!r) r = dalloc(&c->dState, sizeof(float) * c->state0.size());
+  if (!r) r = dalloc(&c->dCoef, sizeof(double) * coef.size() + sizeof(float) * cb.size());
+  if (!r) r = dalloc(&c->dState, sizeof(double) * c->state0.size());
   c->n_ctr = d->batch;
   if (!r) r = dalloc(&c->dCtr, sizeof(unsigned int) * d->batch);
   if (!r) r = dalloc(&c->dFlags, sizeof(int) * 2);
@@ -1315,7 +1317,8 @@ int init_shared(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& gro
   HIP_TRY(hipMemcpyAsync(dWg, wgs.data(), sizeof(SharedWg) * wgs.size(), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(dSlot, slots.data(), sizeof(SharedSlot) * slots.size(), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(c->dShS2, s2.data(), sizeof(float) * s2.size(), hipMemcpyHostToDevice, stream));
-  HIP_TRY(hipMemcpyAsync(c->dCoef, coef.data(), sizeof(float) * coef.size(), hipMemcpyHostToDevice, stream));
+  HIP_TRY(hipMemcpyAsync(c->dCoef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice, stream));
+  HIP_TRY(hipMemcpyAsync(c->dCoef + coef.size(), cb.data(), sizeof(float) * cb.size(), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipMemcpyAsync(c->dE, epool.data(), sizeof(float) * epool.size(), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipStreamSynchronize(stream));
   SharedParams& P = c->SP;
@@ -1326,17 +1329,12 @@ int init_shared(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& gro
   P.nin_max = nin_max;
   P.cols = cols;
   P.ktot = ktot;
-  P.x_hi = c->dState;
-  P.x_lo = P.x_hi + ncolk;
-  P.d_hi = P.x_lo + ncolk;
-  P.d_lo = P.d_hi + ncolk;
-  P.m_hi = c->dCoef;
-  P.m_lo = P.m_hi + ncolk;
-  P.p_hi = P.m_lo + ncolk;
-  P.p_lo = P.p_hi + ncolk;
-  P.r_hi = P.p_lo + ncolk;
-  P.r_lo = P.r_hi + ncolk;
-  P.c_out = P.r_lo + ncolk;
+  P.x = c->dState;
+  P.d = P.x + ncolk;
+  P.m = c->dCoef;
+  P.p = P.m + ncolk;
+  P.r = P.p + ncolk;
+  P.c_out = (const float*)(P.r + ncolk);
   P.b_ext = P.c_out + ncolk;
   P.e_ext = c->dE;
   P.step_base = c->dStep;
@@ -1821,13 +1819,11 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   }
 
   // ---------------- coefficients, initial state
-  std::vector<float> coef(9 * (size_t)mode_floats, 0.f);
-  float *m_hi = &coef[0], *m_lo = m_hi + mode_floats, *p_hi = m_lo + mode_floats,
-        *p_lo = p_hi + mode_floats, *r_hi = p_lo + mode_floats, *r_lo = r_hi + mode_floats,
-        *cw = r_lo + mode_floats, *lam = cw + mode_floats, *bx = lam + mode_floats;
+  const size_t mfs = (size_t)mode_floats;
+  std::vector<double> coef(3 * mfs, 0.), xinit(2 * mfs, 0.);  // m, p, r; X, d
+  std::vector<float> clb(3 * mfs, 0.f);                       // c, lambda, b
   c->nt.resize(d->batch);
   c->inst_mode_off.resize(d->batch);
-  std::vector<float> xinit(4 * (size_t)mode_floats, 0.f);
   for (int b = 0; b < d->batch; ++b) {
     const modal_instance& I = d->inst[b];
     const int o = inst[b].mode_off;
@@ -1837,22 +1833,22 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     for (int k = 0; k < I.n_t; ++k) {
       const int e = o + (ms.empty() ? k : ms[k]);  // internal slot of caller mode k
       const Coef q = coefficients(d->scheme, I.omega[k], I.gamma[k], T);
-      split(q.m, m_hi[e], m_lo[e]);
-      split(q.p, p_hi[e], p_lo[e]);
-      split(q.r, r_hi[e], r_lo[e]);
-      cw[e] = (float)I.c_out[k];
-      lam[e] = I.lambda ? (float)I.lambda[k] : 0.f;
-      bx[e] = I.b_ext ? (float)I.b_ext[k] : 0.f;
-      split(I.x0[k], xinit[e], xinit[mode_floats + e]);
-      split(I.x0[k] - I.xm1[k], xinit[2 * mode_floats + e], xinit[3 * mode_floats + e]);
+      coef[e] = q.m;
+      coef[mfs + e] = q.p;
+      coef[2 * mfs + e] = q.r;
+      clb[e] = (float)I.c_out[k];
+      clb[mfs + e] = I.lambda ? (float)I.lambda[k] : 0.f;
+      clb[2 * mfs + e] = I.b_ext ? (float)I.b_ext[k] : 0.f;
+      xinit[e] = I.x0[k];
+      xinit[mfs + e] = I.x0[k] - I.xm1[k];
     }
   }
-  c->state0.assign(4 * (size_t)state_floats, 0.f);
+  c->state0.assign(2 * (size_t)state_floats, 0.);
   for (const UnitDev& U : udev) {
     const int o = inst[U.inst].mode_off, n = inst[U.inst].ntp;
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 2; ++a)
       std::memcpy(&c->state0[(size_t)a * state_floats + U.state_off], &xinit[(size_t)a * mode_floats + o],
-                  sizeof(float) * n);
+                  sizeof(double) * n);
   }
 
   // ---------------- device memory
@@ -1868,8 +1864,8 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   } while (0)
   ALLOC(c->dH, sizeof(float) * (size_t)(h_floats + 64));
   ALLOC(c->dMeta, meta_bytes);
-  ALLOC(c->dCoef, sizeof(float) * coef.size());
-  ALLOC(c->dState, sizeof(float) * c->state0.size());
+  ALLOC(c->dCoef, sizeof(double) * coef.size() + sizeof(float) * clb.size());
+  ALLOC(c->dState, sizeof(double) * c->state0.size());
   ALLOC(c->dPart, sizeof(float) * (size_t)(part_floats + 64));
   ALLOC(c->dCtr, sizeof(unsigned int) * n_ctr);
   ALLOC(c->dFlags, sizeof(int) * (2 + 2 * d->batch));
@@ -1906,7 +1902,8 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   HIP_TRY_C(hipMemcpyAsync(dInst, inst.data(), sizeof(InstDev) * d->batch, hipMemcpyHostToDevice, stream));
   HIP_TRY_C(hipMemcpyAsync(dUnit, udev.data(), sizeof(UnitDev) * udev.size(), hipMemcpyHostToDevice, stream));
   HIP_TRY_C(hipMemcpyAsync(dWg, wg_begin.data(), sizeof(int) * (n_wg + 1), hipMemcpyHostToDevice, stream));
-  HIP_TRY_C(hipMemcpyAsync(c->dCoef, coef.data(), sizeof(float) * coef.size(), hipMemcpyHostToDevice, stream));
+  HIP_TRY_C(hipMemcpyAsync(c->dCoef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice, stream));
+  HIP_TRY_C(hipMemcpyAsync(c->dCoef + coef.size(), clb.data(), sizeof(float) * clb.size(), hipMemcpyHostToDevice, stream));
   {
     std::vector<float> epool((size_t)e_floats + 1, 0.f);
     for (int b = 0; b < d->batch; ++b)
@@ -1937,20 +1934,15 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   P.unit = dUnit;
   P.wg_begin = dWg;
   P.H = c->dH;
-  P.m_hi = c->dCoef;
-  P.m_lo = P.m_hi + mode_floats;
-  P.p_hi = P.m_lo + mode_floats;
-  P.p_lo = P.p_hi + mode_floats;
-  P.r_hi = P.p_lo + mode_floats;
-  P.r_lo = P.r_hi + mode_floats;
-  P.c_out = P.r_lo + mode_floats;
+  P.m = c->dCoef;
+  P.p = P.m + mode_floats;
+  P.r = P.p + mode_floats;
+  P.c_out = (const float*)(P.r + mode_floats);
   P.lam = P.c_out + mode_floats;
   P.b_ext = P.lam + mode_floats;
   P.e_ext = c->dE;
-  P.x_hi = c->dState;
-  P.x_lo = P.x_hi + state_floats;
-  P.d_hi = P.x_lo + state_floats;
-  P.d_lo = P.d_hi + state_floats;
+  P.x = c->dState;
+  P.d = P.x + state_floats;
   P.part = c->dPart;
   P.ctr = c->dCtr;
   P.flags = c->dFlags;
@@ -1976,7 +1968,7 @@ int modal_reset(modal_ctx* c, void* stream_) {
     c->steps = 0;
     return MODAL_OK;
   }
-  HIP_TRY(hipMemcpyAsync(c->dState, c->state0.data(), sizeof(float) * c->state0.size(),
+  HIP_TRY(hipMemcpyAsync(c->dState, c->state0.data(), sizeof(double) * c->state0.size(),
                          hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemsetAsync(c->dCtr, 0, sizeof(unsigned int) * c->n_ctr, s));
   HIP_TRY(hipMemsetAsync(c->dFlags, 0, sizeof(int) * 2, s));
@@ -2052,18 +2044,18 @@ int modal_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* s
     if (c->ckpt_broken || c->steps > c->ckpt_upto) {
       c->ckpt_broken = true;
     } else {
-      const long long need = (c->steps + n_steps + kRunCkpt - 1) / kRunCkpt * 4LL * c->mode_floats;
-      if (c->ckpt_floats < need && c->steps > 0) {
+      const long long need = (c->steps + n_steps + kRunCkpt - 1) / kRunCkpt * 2LL * c->mode_floats;
+      if (c->ckpt_vals < need && c->steps > 0) {
         c->ckpt_broken = true;  // growing would lose the slots already taken
       } else {
-        if (c->ckpt_floats < need) {
+        if (c->ckpt_vals < need) {
           if (c->dCkpt) HIP_TRY(hipFree(c->dCkpt));
           c->dCkpt = nullptr;
-          c->ckpt_floats = 0;
+          c->ckpt_vals = 0;
           c->ckpt_upto = 0;
-          int r = dalloc(&c->dCkpt, sizeof(float) * (size_t)need);
+          int r = dalloc(&c->dCkpt, sizeof(double) * (size_t)need);
           if (r) return r;
-          c->ckpt_floats = need;
+          c->ckpt_vals = need;
         }
         c->run_ckpt = true;
       }
@@ -2352,16 +2344,16 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   // checkpoints of the last forward runs, if they cover the steps with this
   // spacing, replace the forward pass
   const bool reuse = K == kRunCkpt && !c->ckpt_broken && c->ckpt_upto >= n_steps &&
-                     !(c->flags & MODAL_FLAG_GRAPH) && c->ckpt_floats >= nseg * 4LL * mf;
+                     !(c->flags & MODAL_FLAG_GRAPH) && c->ckpt_vals >= nseg * 2LL * mf;
   // buffers (grown on demand)
-  if (c->ckpt_floats < nseg * 4LL * mf) {
+  if (c->ckpt_vals < nseg * 2LL * mf) {
     if (c->dCkpt) HIP_TRY(hipFree(c->dCkpt));
     c->dCkpt = nullptr;
-    c->ckpt_floats = 0;
+    c->ckpt_vals = 0;
     c->ckpt_upto = 0;
-    int r = dalloc(&c->dCkpt, sizeof(float) * (size_t)(nseg * 4LL * mf));
+    int r = dalloc(&c->dCkpt, sizeof(double) * (size_t)(nseg * 2LL * mf));
     if (r) return r;
-    c->ckpt_floats = nseg * 4LL * mf;
+    c->ckpt_vals = nseg * 2LL * mf;
   }
   if (c->rec_floats < 2LL * K * mf) {
     if (c->dRec) HIP_TRY(hipFree(c->dRec));
@@ -2376,7 +2368,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
     c->dRrec = nullptr;
     c->rrec_floats = 0;
     int r = dalloc(&c->dRrec, sizeof(float) * (size_t)K * c->rows_total);
-    if (!r && !c->dRacc) r = dalloc(&c->dRacc, sizeof(float) * 2 * (size_t)c->rows_total);
+    if (!r && !c->dRacc) r = dalloc(&c->dRacc, sizeof(double) * (size_t)c->rows_total);
     if (r) return r;
     c->rrec_floats = (long long)K * c->rows_total;
   }
@@ -2424,8 +2416,8 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
       HIP_TRY(hipMemsetAsync(j.out, 0, sizeof(float) * (size_t)j.nin * j.nt * j.nt, s));
   }
   if (!c->dAdj) {
-    int r = dalloc(&c->dAdj, sizeof(float) * 4 * (size_t)sf);
-    if (!r) r = dalloc(&c->dAcc, sizeof(float) * 12 * (size_t)sf);
+    int r = dalloc(&c->dAdj, sizeof(double) * 2 * (size_t)sf);
+    if (!r) r = dalloc(&c->dAcc, sizeof(double) * 6 * (size_t)sf);
     if (!r) r = dalloc(&c->dGPart, sizeof(float) * (size_t)(2 * c->part_floats + 64));
     if (!r) r = dalloc(&c->dGCtr, sizeof(unsigned int) * c->n_ctr);
     if (r) return r;
@@ -2463,11 +2455,11 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
     c->ckpt_upto = K == kRunCkpt ? std::max<long long>(c->ckpt_upto, n_steps) : 0;
     c->rec_upto = rec_now ? n_steps : 0;
   }
-  HIP_TRY(hipMemsetAsync(c->dAdj, 0, sizeof(float) * 4 * (size_t)sf, s));
-  HIP_TRY(hipMemsetAsync(c->dAcc, 0, sizeof(float) * 12 * (size_t)sf, s));
+  HIP_TRY(hipMemsetAsync(c->dAdj, 0, sizeof(double) * 2 * (size_t)sf, s));
+  HIP_TRY(hipMemsetAsync(c->dAcc, 0, sizeof(double) * 6 * (size_t)sf, s));
   HIP_TRY(hipMemsetAsync(c->dGCtr, 0, sizeof(unsigned int) * c->n_ctr, s));
   const bool rows_on = g_row && c->rows_total > 0;
-  if (rows_on) HIP_TRY(hipMemsetAsync(c->dRacc, 0, sizeof(float) * 2 * (size_t)c->rows_total, s));
+  if (rows_on) HIP_TRY(hipMemsetAsync(c->dRacc, 0, sizeof(double) * (size_t)c->rows_total, s));
   GradParams G{};
   const StepParams& F = c->P;
   G.inst = F.inst;
@@ -2475,8 +2467,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   G.wg_begin = F.wg_begin;
   G.H = F.H;
   G.Hd = c->tangent ? c->dHd : nullptr;
-  G.m_hi = F.m_hi; G.m_lo = F.m_lo; G.p_hi = F.p_hi; G.p_lo = F.p_lo;
-  G.r_hi = F.r_hi; G.r_lo = F.r_lo;
+  G.m = F.m; G.p = F.p; G.r = F.r;
   G.c_out = F.c_out; G.lam = F.lam; G.b_ext = F.b_ext; G.e_ext = F.e_ext;
   // the whole trajectory recorded by the last runs, if it covers the steps,
   // replaces the segment recomputes
@@ -2484,7 +2475,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   G.mode_floats = mf;
   G.ybar = ybar;
   G.ybar_stride = y_stride;
-  G.qb_hi = c->dAdj; G.qb_lo = c->dAdj + sf; G.db_hi = c->dAdj + 2 * (size_t)sf; G.db_lo = c->dAdj + 3 * (size_t)sf;
+  G.qb = c->dAdj; G.db = c->dAdj + sf;
   G.acc = c->dAcc;
   G.state_floats = sf;
   G.part = c->dGPart;
@@ -2528,18 +2519,15 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   r = modal_check(c, stream_);
   if (r) return r;
   if (g_row) {
-    std::vector<float> ra(2 * (size_t)c->rows_total);
     if (rows_on)
-      HIP_TRY(hipMemcpyAsync(ra.data(), c->dRacc, sizeof(float) * ra.size(), hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipMemcpyAsync(g_row, c->dRacc, sizeof(double) * (size_t)c->rows_total, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    for (int i = 0; i < c->rows_total; ++i)
-      g_row[i] = (double)ra[i] + (double)ra[(size_t)c->rows_total + i];
   }
-  std::vector<float> acc(12 * (size_t)sf), adj(4 * (size_t)sf);
-  HIP_TRY(hipMemcpyAsync(acc.data(), c->dAcc, sizeof(float) * acc.size(), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(adj.data(), c->dAdj, sizeof(float) * adj.size(), hipMemcpyDeviceToHost, s));
+  std::vector<double> acc(6 * (size_t)sf), adj(2 * (size_t)sf);
+  HIP_TRY(hipMemcpyAsync(acc.data(), c->dAcc, sizeof(double) * acc.size(), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(adj.data(), c->dAdj, sizeof(double) * adj.size(), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  auto A = [&](int k, int i) { return (double)acc[(size_t)(2 * k) * sf + i] + (double)acc[(size_t)(2 * k + 1) * sf + i]; };
+  auto A = [&](int k, int i) { return acc[(size_t)k * sf + i]; };
   // per instance: its slab-0 unit holds the accumulators; every unit its theta partial
   std::vector<int> slab0(c->batch, -1);
   std::vector<double> theta(c->batch, 0.0);
@@ -2561,8 +2549,8 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
       if (g_c) g_c[o] = A(3, so + k);
       gs += A(4, so + k);
       const Coef q = coefficients(c->scheme, c->omega[o], c->gamma[o], T);
-      const double qb0 = (double)adj[so + k] + (double)adj[(size_t)sf + so + k];
-      const double db1 = (double)adj[2 * (size_t)sf + so + k] + (double)adj[3 * (size_t)sf + so + k];
+      const double qb0 = adj[so + k];
+      const double db1 = adj[(size_t)sf + so + k];
       const double d0b = -q.p * db1;  // d^0 = q^0 - q^-1 only feeds d^1
       if (g_x0) g_x0[o] = qb0 + d0b;
       if (g_xm1) g_xm1[o] = -d0b;
@@ -2597,8 +2585,8 @@ int modal_get_state(modal_ctx* c, double* x, double* xm1, void* stream_) {
       }
     return MODAL_OK;
   }
-  std::vector<float> st(c->state0.size());
-  HIP_TRY(hipMemcpyAsync(st.data(), c->dState, sizeof(float) * st.size(), hipMemcpyDeviceToHost, s));
+  std::vector<double> st(c->state0.size());
+  HIP_TRY(hipMemcpyAsync(st.data(), c->dState, sizeof(double) * st.size(), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   const size_t S = c->state_floats;
   size_t o = 0;
@@ -2607,8 +2595,7 @@ int modal_get_state(modal_ctx* c, double* x, double* xm1, void* stream_) {
     const std::vector<int>* ms = b < (int)c->mode_slot.size() && !c->mode_slot[b].empty() ? &c->mode_slot[b] : nullptr;
     for (int k = 0; k < c->nt[b]; ++k, ++o) {
       const int so = so0 + (ms ? (*ms)[k] - k : 0);
-      const double xv = (double)st[so + k] + (double)st[S + so + k];
-      const double dv = (double)st[2 * S + so + k] + (double)st[3 * S + so + k];
+      const double xv = st[so + k], dv = st[S + so + k];
       x[o] = xv;
       xm1[o] = xv - dv;
     }

@@ -14,11 +14,11 @@
 // with each lane's four operands adjacent, so that a workgroup stages one
 // row n with coalesced 16-byte loads into LDS (double-buffered; rows are
 // loaded two ahead of the one multiplied) and a wave reads its operands
-// with 16-byte LDS reads; X (FP32 high part of the float-float state) is the
+// with 16-byte LDS reads; X (the FP64 state rounded to FP32) is the
 // B operand, held in registers for the whole step, and also kept in LDS in
 // accumulator order for the eta reductions; the squared row scales of the
 // workgroup's columns sit in LDS for the whole launch.  Every column keeps its own
-// float-float state and coefficients and the update is the increment form of
+// FP64 state and coefficients and the update is the increment form of
 // the forward kernel, so the only difference from it is the order of the
 // FP32 sums inside the contraction.
 #include <hip/hip_runtime.h>
@@ -69,14 +69,14 @@ __global__ void __launch_bounds__(kWave * kSharedWaves, (KT == 4 && JT == 2) ? 1
     S2[i] = P.s2[(long long)blockIdx.x * P.nin_max * P.cols + i];
   for (int i = lane; i < 16 * KT * CW; i += kWave) {
     const int k = i / CW, cc = i % CW;
-    xs[i] = P.x_hi[(col0 + cc) * P.ktot + k];
+    xs[i] = (float)P.x[(col0 + cc) * P.ktot + k];
   }
 #pragma unroll
   for (int j = 0; j < JT; ++j)
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
       const long long o = (col0 + 16 * j + col16) * P.ktot + 16 * t + 4 * quad;
-      const float4 x = ld4(P.x_hi + o);
+      const float4 x = to_f4(ld4d(P.x + o));
       xdl[(j * KT + t) * 64 + lane] = (v4f){x.x, x.y, x.z, x.w};
     }
   SharedSlot sl[JT];
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(kWave * kSharedWaves, (KT == 4 && JT == 2) ? 1
 #undef SH_ROW
 #undef SH_LOAD
 #undef SH_STORE
-    // output y^n = c . X^n and the float-float update of every (mode, column):
+    // output y^n = c . X^n and the FP64 update of every (mode, column):
     // one 4-mode group per (column tile j, row tile t), its state and
     // coefficients loaded one group ahead of the arithmetic
     bool bad = false;
@@ -169,7 +169,8 @@ __global__ void __launch_bounds__(kWave * kSharedWaves, (KT == 4 && JT == 2) ? 1
       eo[j] = nabs < sl[j].n_exc ? P.e_ext[sl[j].e_off + nabs] : 0.f;
     }
     struct Grp {
-      float4 xh, xl, dh, dl, mh, ml, ph, pl, rh, rl, b, cw;
+      f64x4 x, d, m, p, r;
+      float4 b, cw;
     };
     auto grp_off = [&](int u) -> long long {
       const int j = u / KT, t = u % KT;
@@ -177,9 +178,9 @@ __global__ void __launch_bounds__(kWave * kSharedWaves, (KT == 4 && JT == 2) ? 1
     };
     auto grp_load = [&](long long o) -> Grp {
       Grp g;
-      g.xh = ld4(P.x_hi + o); g.xl = ld4(P.x_lo + o); g.dh = ld4(P.d_hi + o); g.dl = ld4(P.d_lo + o);
-      g.mh = ld4(P.m_hi + o); g.ml = ld4(P.m_lo + o); g.ph = ld4(P.p_hi + o); g.pl = ld4(P.p_lo + o);
-      g.rh = ld4(P.r_hi + o); g.rl = ld4(P.r_lo + o); g.b = ld4(P.b_ext + o); g.cw = ld4(P.c_out + o);
+      g.x = ld4d(P.x + o); g.d = ld4d(P.d + o);
+      g.m = ld4d(P.m + o); g.p = ld4d(P.p + o); g.r = ld4d(P.r + o);
+      g.b = ld4(P.b_ext + o); g.cw = ld4(P.c_out + o);
       return g;
     };
     Grp cur = grp_load(grp_off(0));
@@ -190,21 +191,16 @@ __global__ void __launch_bounds__(kWave * kSharedWaves, (KT == 4 && JT == 2) ? 1
       if (u + 1 < JT * KT) nxt = grp_load(grp_off(u + 1));
       const long long o = grp_off(u);
       const float e = eo[j];
-      float4 xh = cur.xh, xl = cur.xl, dh = cur.dh, dl = cur.dl;
-      ypart[j] += dot4(cur.cw, xh);
-      ff_step(xh.x, xl.x, dh.x, dl.x, cur.mh.x, cur.ml.x, cur.ph.x, cur.pl.x, cur.rh.x, cur.rl.x,
-              fmaf(cur.b.x, e, -F[j][t][0]));
-      ff_step(xh.y, xl.y, dh.y, dl.y, cur.mh.y, cur.ml.y, cur.ph.y, cur.pl.y, cur.rh.y, cur.rl.y,
-              fmaf(cur.b.y, e, -F[j][t][1]));
-      ff_step(xh.z, xl.z, dh.z, dl.z, cur.mh.z, cur.ml.z, cur.ph.z, cur.pl.z, cur.rh.z, cur.rl.z,
-              fmaf(cur.b.z, e, -F[j][t][2]));
-      ff_step(xh.w, xl.w, dh.w, dl.w, cur.mh.w, cur.ml.w, cur.ph.w, cur.pl.w, cur.rh.w, cur.rl.w,
-              fmaf(cur.b.w, e, -F[j][t][3]));
+      f64x4 x = cur.x, d = cur.d;
+      ypart[j] += dot4(cur.cw, to_f4(x));
+      const float b[4] = {cur.b.x, cur.b.y, cur.b.z, cur.b.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        mode_step(x.v[i], d.v[i], cur.m.v[i], cur.p.v[i], cur.r.v[i], fmaf(b[i], e, -F[j][t][i]));
+      const float4 xh = to_f4(x);
       bad |= !(isfinite(xh.x) && isfinite(xh.y) && isfinite(xh.z) && isfinite(xh.w));
-      st4(P.x_hi + o, xh);
-      st4(P.x_lo + o, xl);
-      st4(P.d_hi + o, dh);
-      st4(P.d_lo + o, dl);
+      st4d(P.x + o, x);
+      st4d(P.d + o, d);
       float* xr = xs + (16 * t + 4 * quad) * CW + 16 * j + col16;
       xr[0] = xh.x;
       xr[CW] = xh.y;

@@ -5,14 +5,14 @@
 // in-plane rows of a von Karman instance whose coupling tensor is split over
 // several workgroups; the waves of a workgroup share a unit's rows.  Per audio sample (paper: Sec. 3.2, modal oscillator
 // update) each unit
-//   1. publishes q^n (fp32 high part) to LDS and writes the output sample
+//   1. publishes q^n (rounded to FP32) to LDS and writes the output sample
 //      y^n = sum_k c_k q_k^n (modal-to-physical transform at one point),
 //   2. evaluates its share of the nonlinear modal force (Sec. 3.1):
 //        von Karman, one pass over its rows of Ht:  V[n,k] = sum_j Ht[n][j][k] q_j
 //        (Ht symmetric in its last two indices), eta_n = sum_k V[n,k] q_k,
 //        F_k += eta_n V[n,k];
 //        tension-modulated: F_k = kappa lambda_k q_k sum_j lambda_j q_j^2,
-//   3. advances the state in float-float arithmetic in increment form
+//   3. advances the state in FP64 in increment form
 //        d^{n+1} = m q^n - p d^n + r (f_ext^n - F^n),  q^{n+1} = q^n + d^{n+1}
 //      (m = g + p - 1 = -r omega^2 for Stormer-Verlet), where instances split
 //      over several workgroups first exchange their partial forces through
@@ -466,8 +466,9 @@ __device__ void vk_rows_blk(const float* __restrict__ Hb, const int4* __restrict
 // Where one unit's state and its instance's per-mode coefficients live: in
 // global memory, or resident in LDS for the whole launch.
 struct ModeRefs {
-  float *xh, *xl, *dh, *dl;
-  const float *mh, *ml, *ph, *pl, *rh, *rl, *b, *c, *lam;
+  double *x, *d;
+  const double *m, *p, *r;
+  const float *b, *c, *lam;
 };
 
 // Per-mode state update of the float4 groups owned by this lane; e is this
@@ -482,22 +483,17 @@ __device__ __forceinline__ void update_groups(const ModeRefs& M, int nc, float e
     const int k4 = lane + kWave * g;
     if (g < G && k4 < nc) {
       const int o = 4 * k4;
-      float4 xh = ld4(M.xh + o), xl = ld4(M.xl + o);
-      float4 dh = ld4(M.dh + o), dl = ld4(M.dl + o);
-      const float4 mh = ld4(M.mh + o), ml = ld4(M.ml + o);
-      const float4 ph = ld4(M.ph + o), pl = ld4(M.pl + o);
-      const float4 rh = ld4(M.rh + o), rl = ld4(M.rl + o);
-      const float4 b = ld4(M.b + o);
-      const float4 f = F[g];
-      ff_step(xh.x, xl.x, dh.x, dl.x, mh.x, ml.x, ph.x, pl.x, rh.x, rl.x, fmaf(b.x, e, -f.x));
-      ff_step(xh.y, xl.y, dh.y, dl.y, mh.y, ml.y, ph.y, pl.y, rh.y, rl.y, fmaf(b.y, e, -f.y));
-      ff_step(xh.z, xl.z, dh.z, dl.z, mh.z, ml.z, ph.z, pl.z, rh.z, rl.z, fmaf(b.z, e, -f.z));
-      ff_step(xh.w, xl.w, dh.w, dl.w, mh.w, ml.w, ph.w, pl.w, rh.w, rl.w, fmaf(b.w, e, -f.w));
-      bad |= !(isfinite(xh.x) && isfinite(xh.y) && isfinite(xh.z) && isfinite(xh.w));
-      st4(M.xh + o, xh);
-      st4(M.xl + o, xl);
-      st4(M.dh + o, dh);
-      st4(M.dl + o, dl);
+      f64x4 x = ld4d(M.x + o), d = ld4d(M.d + o);
+      const f64x4 m = ld4d(M.m + o), p = ld4d(M.p + o), r = ld4d(M.r + o);
+      const float4 b4 = ld4(M.b + o);
+      const float b[4] = {b4.x, b4.y, b4.z, b4.w}, f[4] = {F[g].x, F[g].y, F[g].z, F[g].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        mode_step(x.v[i], d.v[i], m.v[i], p.v[i], r.v[i], fmaf(b[i], e, -f[i]));
+        bad |= !isfinite((float)x.v[i]);
+      }
+      st4d(M.x + o, x);
+      st4d(M.d + o, d);
     }
   }
   if (__any(bad) && lane == 0) atomicOr(&flags[1], 1);
@@ -533,30 +529,20 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
     if constexpr (RES) {
       float* R = L.res;
       const int S = P.res_stride;
-      M.xh = R;
-      M.xl = R + S;
-      M.dh = R + 2 * S;
-      M.dl = R + 3 * S;
-      M.mh = R + 4 * S;
-      M.ml = R + 5 * S;
-      M.ph = R + 6 * S;
-      M.pl = R + 7 * S;
-      M.rh = R + 8 * S;
-      M.rl = R + 9 * S;
+      M.x = reinterpret_cast<double*>(R);
+      M.d = reinterpret_cast<double*>(R + 2 * S);
+      M.m = reinterpret_cast<const double*>(R + 4 * S);
+      M.p = reinterpret_cast<const double*>(R + 6 * S);
+      M.r = reinterpret_cast<const double*>(R + 8 * S);
       M.b = R + 10 * S;
       M.c = R + 11 * S;
       M.lam = R + 12 * S;
     } else {
-      M.xh = P.x_hi + U.state_off;
-      M.xl = P.x_lo + U.state_off;
-      M.dh = P.d_hi + U.state_off;
-      M.dl = P.d_lo + U.state_off;
-      M.mh = P.m_hi + I.mode_off;
-      M.ml = P.m_lo + I.mode_off;
-      M.ph = P.p_hi + I.mode_off;
-      M.pl = P.p_lo + I.mode_off;
-      M.rh = P.r_hi + I.mode_off;
-      M.rl = P.r_lo + I.mode_off;
+      M.x = P.x + U.state_off;
+      M.d = P.d + U.state_off;
+      M.m = P.m + I.mode_off;
+      M.p = P.p + I.mode_off;
+      M.r = P.r + I.mode_off;
       M.b = P.b_ext + I.mode_off;
       M.c = P.c_out + I.mode_off;
       M.lam = P.lam + I.mode_off;
@@ -572,20 +558,24 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
     const int nc = I.ntp >> 2;
     float* R = L.res;
     const int S = P.res_stride;
-    float* gs[4] = {P.x_hi + U.state_off, P.x_lo + U.state_off, P.d_hi + U.state_off,
-                    P.d_lo + U.state_off};
-    const float* gc[9] = {P.m_hi, P.m_lo, P.p_hi, P.p_lo, P.r_hi, P.r_lo, P.b_ext, P.c_out, P.lam};
+    double* gs[2] = {P.x + U.state_off, P.d + U.state_off};
+    const double* gd[3] = {P.m + I.mode_off, P.p + I.mode_off, P.r + I.mode_off};
+    const float* gc[3] = {P.b_ext + I.mode_off, P.c_out + I.mode_off, P.lam + I.mode_off};
     for (int k4 = lane; k4 < nc; k4 += kWave) {
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
+      for (int a = 0; a < 2; ++a) {
+        double* l = reinterpret_cast<double*>(R + 2 * a * S) + 4 * k4;
         if (in)
-          st4(R + a * S + 4 * k4, ld4(gs[a] + 4 * k4));
+          st4d(l, ld4d(gs[a] + 4 * k4));
         else
-          st4(gs[a] + 4 * k4, ld4(R + a * S + 4 * k4));
+          st4d(gs[a] + 4 * k4, ld4d(l));
       }
       if (in) {
 #pragma unroll
-        for (int a = 0; a < 9; ++a) st4(R + (4 + a) * S + 4 * k4, ld4(gc[a] + I.mode_off + 4 * k4));
+        for (int a = 0; a < 3; ++a) {
+          st4d(reinterpret_cast<double*>(R + (4 + 2 * a) * S) + 4 * k4, ld4d(gd[a] + 4 * k4));
+          st4(R + (10 + a) * S + 4 * k4, ld4(gc[a] + 4 * k4));
+        }
       }
     }
   };
@@ -611,7 +601,7 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
         for (int g = 0; g < GM; ++g) {
           const int k4 = lane + kWave * g;
           if (g < G && k4 < nc) {
-            const float4 xh = ld4(M.xh + 4 * k4);
+            const float4 xh = to_f4(ld4d(M.x + 4 * k4));
             const float4 c = ld4(M.c + 4 * k4);
             ypart += dot4(c, xh);
             if (I.kind == KIND_VK) {
@@ -627,14 +617,12 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
           const float yv = wave_sum(ypart);
           if (lane == 0 && P.y) P.y[(long long)I.out_row * P.y_stride + s] = yv;
           if (P.ckpt && n % P.ckpt_every == 0) {
-            float* cp = P.ckpt + (n / P.ckpt_every) * 4LL * P.mode_floats + I.mode_off;
+            double* cp = P.ckpt + (n / P.ckpt_every) * 2LL * P.mode_floats + I.mode_off;
             for (int g = 0; g < GM; ++g) {
               const int k4 = lane + kWave * g;
               if (g < G && k4 < nc) {
-                st4(cp + 4 * k4, ld4(M.xh + 4 * k4));
-                st4(cp + P.mode_floats + 4 * k4, ld4(M.xl + 4 * k4));
-                st4(cp + 2 * P.mode_floats + 4 * k4, ld4(M.dh + 4 * k4));
-                st4(cp + 3 * P.mode_floats + 4 * k4, ld4(M.dl + 4 * k4));
+                st4d(cp + 4 * k4, ld4d(M.x + 4 * k4));
+                st4d(cp + P.mode_floats + 4 * k4, ld4d(M.d + 4 * k4));
               }
             }
           }
@@ -643,8 +631,8 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
             for (int g = 0; g < GM; ++g) {
               const int k4 = lane + kWave * g;
               if (g < G && k4 < nc) {
-                st4(P.rec_x + ro + 4 * k4, ld4(M.xh + 4 * k4));
-                st4(P.rec_d + ro + 4 * k4, ld4(M.dh + 4 * k4));
+                st4(P.rec_x + ro + 4 * k4, to_f4(ld4d(M.x + 4 * k4)));
+                st4(P.rec_d + ro + 4 * k4, to_f4(ld4d(M.d + 4 * k4)));
               }
             }
           }
@@ -705,7 +693,7 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
         for (int g = 0; g < GM; ++g) {
           const int k4 = lane + kWave * g;
           if (g < G && k4 < nc) {
-            const float4 xh = ld4(M.xh + 4 * k4);
+            const float4 xh = to_f4(ld4d(M.x + 4 * k4));
             const float4 l = ld4(M.lam + 4 * k4);
             Fa[g] = make_float4(l.x * xh.x * S, l.y * xh.y * S, l.z * xh.z * S, l.w * xh.w * S);
           }
