@@ -81,6 +81,31 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_mov<0x140>(v);  // row_mirror
   return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
+// Sums of v over each group of L consecutive lanes (L = 16, 32 or 64), the
+// same bits on every lane of a group: the DPP exchanges of wave_sum within a
+// row, then gfx950's lane swaps between rows and halves.
+template <int L>
+__device__ __forceinline__ float group_sum(float v) {
+  v += dpp_mov<0xB1>(v);
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0x141>(v);
+  v += dpp_mov<0x140>(v);
+  if constexpr (L >= 32) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  if constexpr (L >= 64) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  return v;
+}
+// Lane j of each group of L lanes (j the same for every group).
+template <int L>
+__device__ __forceinline__ float group_lane(float v, int j) {
+  if constexpr (L == 64) return lane_value(v, j);
+  return __shfl(v, j, L);
+}
 __device__ __forceinline__ float4 f4(float v) { return make_float4(v, v, v, v); }
 __device__ __forceinline__ float4 fma4(float4 a, float b, float4 c) {
   return make_float4(fmaf(a.x, b, c.x), fmaf(a.y, b, c.y), fmaf(a.z, b, c.z), fmaf(a.w, b, c.w));

@@ -29,7 +29,9 @@ hipError_t launch_ctr_fill(const InstDev* inst, int batch, const long long* step
 hipError_t launch_check(const float* H, const InstDev* inst, int batch, int* out, hipStream_t s);
 hipError_t step_occupancy(int* blocks_per_cu, int gm, int nw, size_t lds_bytes, bool res = false);
 hipError_t launch_chip(const StepParams& P, int nt_tile, int rows, int n_wg, hipStream_t s);
-hipError_t launch_chip_wave(const StepParams& P, int m, int n_wg, hipStream_t s);
+void wave_shape(int nt, int batch, int cus, int& lanes, int& m);
+hipError_t launch_wave_step(const StepParams& P, int lanes, int m, int batch, hipStream_t s);
+hipError_t launch_wave_grad(const GradParams& P, int lanes, int m, int batch, hipStream_t s);
 bool chip_shape(int max_nt, int max_rows, int& nt_tile, int& rows);
 hipError_t launch_grad(const GradParams& P, int gm, bool tangent, int nw, bool split, int n_wg, size_t lds,
                        hipStream_t s);
@@ -216,9 +218,9 @@ struct modal_ctx {
   // wave, and its register layouts (one ChipMap per instance)
   int chip_nt = 0, chip_rows = 0;
   ChipMap* dChip = nullptr;
-  // > 0: the on-chip kernel for instances without a tensor, one wave each,
-  // with this many modes per lane
-  int chip_wave = 0;
+  // > 0: the wave kernels (no instance has a tensor), with this many lanes
+  // per instance and modes per lane
+  int wave_lanes = 0, wave_m = 0;
   // waves of the reverse kernel without and with a tangent tensor (its
   // reduction space per wave holds two or three reduced vectors per row)
   int nw_grad[2] = {4, 4};
@@ -1520,12 +1522,23 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   // between workgroups.
   int chip_nt = 0, chip_rows = 0;
   std::vector<ChipMap> chip_maps;
-  // A batch with no tensor at all (tension-modulated and linear instances,
-  // each of at most kChipWaveModes modes) takes the one-wave variant.
-  bool chip_wave = latency && !(d->flags & MODAL_FLAG_GRAD);
-  for (int b = 0; b < d->batch && chip_wave; ++b)
-    chip_wave = d->inst[b].kind != MODAL_KIND_VK && d->inst[b].n_t <= kChipWaveModes;
-  if (latency && !(d->flags & MODAL_FLAG_GRAD) && !chip_wave) {
+  // A batch with no tensor at all (tension-modulated and linear instances)
+  // takes the wave kernels, whatever its size, forward and for gradients:
+  // their state stays in registers, and no step has a barrier or waits for
+  // memory (4096 strings of 12 modes, 2205 samples: 0.35 ms, and 30.5 on the
+  // streaming kernel; a gradient step of 64 strings of 30 modes 0.6 us, forward
+  // and reverse, and 6.8 there).  An explicit launch shape keeps the streaming kernel.
+  int wave_lanes = 0, wave_m = 0;
+  if (d->waves == 0 && d->max_workgroups == 0 && !(d->flags & MODAL_FLAG_SPLIT_ANY)) {
+    int nt_max = 1;
+    bool plain = true;
+    for (int b = 0; b < d->batch && plain; ++b) {
+      plain = d->inst[b].kind != MODAL_KIND_VK;
+      nt_max = std::max(nt_max, d->inst[b].n_t);
+    }
+    if (plain) wave_shape(nt_max, d->batch, prop0.multiProcessorCount, wave_lanes, wave_m);
+  }
+  if (latency && !(d->flags & MODAL_FLAG_GRAD) && !wave_lanes) {
     int max_w = 0, max_rows = 0;
     bool ok = true;
     chip_maps.resize(d->batch);
@@ -1686,7 +1699,14 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   std::vector<Unit> units;
   std::vector<int> bin_of;
   std::vector<double> load;
-  if (latency) {
+  if (wave_lanes) {  // one unit per instance, in instance order
+    for (int b = 0; b < d->batch; ++b) {
+      units.push_back({b, 0, 1, 0, fixed_cost[b]});
+      bin_of.push_back(b);
+      load.push_back(fixed_cost[b]);
+    }
+    n_bins = d->batch;
+  } else if (latency) {
     // one slab per workgroup, instances cut into slabs of about kLatencyRows
     // rows; only for a few instances: with many, the per-step exchanges of
     // all their slabs cost more than the rows they spread (64 plates at
@@ -1718,7 +1738,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
       latency = false;
     }
   }
-  if (!latency && !plan_batch(d, row_cost, fixed_cost, total, n_bins, units, bin_of, load)) {
+  if (!wave_lanes && !latency && !plan_batch(d, row_cost, fixed_cost, total, n_bins, units, bin_of, load)) {
     free_ctx(c);
     return fail(MODAL_EINVAL, "batch does not fit the workgroup budget");
   }
@@ -1783,15 +1803,15 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   // Berger plate in 2.4 us instead of 2.9).  Only
   // when the variant still fits every planned workgroup on the chip at once.
   c->res_stride = 0;
+  c->wave_lanes = wave_lanes;
+  c->wave_m = wave_m;
   if (latency && chip_nt && n_wg == d->batch) {
     c->chip_nt = chip_nt;
     c->chip_rows = chip_rows;
     c->nw = kChipWaves;
     c->lds_bytes = 0;
-  } else if (latency && chip_wave && n_wg == d->batch) {
-    int nt_max = 1;
-    for (int b = 0; b < d->batch; ++b) nt_max = std::max(nt_max, d->inst[b].n_t);
-    c->chip_wave = (nt_max + kWave - 1) / kWave;
+  } else if (wave_lanes && !(d->flags & MODAL_FLAG_GRAD)) {
+    c->n_wg = n_wg = (d->batch + kWave / wave_lanes - 1) / (kWave / wave_lanes);
     c->nw = 1;
     c->lds_bytes = 0;
   } else if (latency && n_wg == (int)udev.size() && (c->nw == 4 || c->nw == 8)) {
@@ -2003,8 +2023,8 @@ static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride
         P.rec_d = c->dRecAll + (size_t)c->recall_cap * c->mode_floats;
         P.rec_base = 0;
       }
-      if (c->chip_wave)
-        HIP_TRY(launch_chip_wave(P, c->chip_wave, c->n_wg, s));
+      if (c->wave_lanes)
+        HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
       else if (c->chip_nt)
         HIP_TRY(launch_chip(P, c->chip_nt, c->chip_rows, c->n_wg, s));
       else
@@ -2154,8 +2174,8 @@ int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride,
     P.y = y + done;
     P.y_stride = y_stride;
     P.n_steps = (int)k;
-    if (c->chip_wave)
-      HIP_TRY(launch_chip_wave(P, c->chip_wave, c->n_wg, s));
+    if (c->wave_lanes)
+      HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
     else if (c->chip_nt)
       HIP_TRY(launch_chip(P, c->chip_nt, c->chip_rows, c->n_wg, s));
     else
@@ -2450,7 +2470,8 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
       P.rec_base = 0;
       rec_now = true;
     }
-    HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
+    if (c->wave_lanes) HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
+    else HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
     // slots now hold this spacing's checkpoints, and the record this run
     c->ckpt_upto = K == kRunCkpt ? std::max<long long>(c->ckpt_upto, n_steps) : 0;
     c->rec_upto = rec_now ? n_steps : 0;
@@ -2502,15 +2523,19 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
       P.rec_d = c->dRec + (size_t)K * mf;
       P.rec_base = s0;
       P.n_steps = len;
-      HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
+      if (c->wave_lanes) HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
+      else HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
       G.rec_x = c->dRec;
       G.rec_d = c->dRec + (size_t)K * mf;
     }
     G.seg_base = s0;
     G.seg_len = len;
     G.done_before = n_steps - s0 - len;
-    HIP_TRY(launch_grad(G, c->gm, c->tangent, c->nw_grad[c->tangent], c->res_stride > 0 && c->nw_grad[c->tangent] > 1,
-                        c->n_wg, c->grad_lds_v[c->tangent], s));
+    if (c->wave_lanes)
+      HIP_TRY(launch_wave_grad(G, c->wave_lanes, c->wave_m, c->batch, s));
+    else
+      HIP_TRY(launch_grad(G, c->gm, c->tangent, c->nw_grad[c->tangent],
+                          c->res_stride > 0 && c->nw_grad[c->tangent] > 1, c->n_wg, c->grad_lds_v[c->tangent], s));
     if (rows_on) HIP_TRY(launch_row_sum(c->dRrec, len, c->rows_total, c->dRacc, s));
     if (tens_on)
       HIP_TRY(launch_tensor_grad(c->dTJobs, (int)tjobs.size(), tj_nin, tj_nt, G.rec_x, c->dUrec, c->dTrec, mf,
@@ -2615,7 +2640,8 @@ int modal_info(const modal_ctx* c, int64_t info[15]) {
   info[7] = c->occ;
   info[8] = (int64_t)c->makespan;
   info[9] = (int64_t)c->mean_load;
-  info[10] = c->shared ? 1 : (c->linear ? 2 : (c->chip_nt || c->chip_wave ? 3 : 0));
+  const bool on_chip = (c->chip_nt || c->wave_lanes) && !(c->flags & MODAL_FLAG_GRAD);
+  info[10] = c->shared ? 1 : (c->linear ? 2 : (on_chip ? 3 : 0));
   info[11] = c->flops;
   info[12] = c->n_blocked;
   info[13] = c->shared ? c->coupling_bytes : c->dense_bytes;
