@@ -173,13 +173,16 @@ typedef struct {
  * excitation convolved with the impulse response); MODAL_FLAG_GRAPH has no
  * effect there.  A mode with a double root keeps the batch on the recursion.
  * On-chip path (paper: Sec. 4.2, the single small plate stepped in real
- * time): a latency-bound batch (below) without MODAL_FLAG_GRAD whose
- * instances all have n_t <= 64 and whose widest tensor fits one workgroup's
- * registers (ceil(n_in / 8) rows per wave times the column width, n_t
- * rounded up to 16, 32, 40, 48 or 64, at most 200: 40/40 and 64/24 fit)
- * steps each instance in one workgroup of 8 waves that loads its tensor
- * into registers at the start of each launch; no memory traffic between
- * workgroups, two workgroup barriers per step.
+ * time): a batch of any size (waves and max_workgroups 0, no
+ * MODAL_FLAG_SPLIT_ANY) whose instances all have n_t <= 64 and whose widest
+ * tensor fits one workgroup's registers (rows per wave, ceil(n_in / 8), times
+ * the column width, n_t rounded up to 8, 12, 16, 20, 24, 32, 40, 48 or 64, at
+ * most 200: 40/40 and 64/24 fit; with mode_class classes of a tensor that has
+ * their structure, the largest class counts instead of n_t) steps each
+ * instance in one workgroup of 8 waves that loads its tensor into registers
+ * at the start of each launch; no memory traffic between workgroups, one
+ * workgroup barrier per step.  modal_grad sweeps such a batch backwards the
+ * same way unless a tangent is set.
  * Wave path: a batch of any size with no tensor at all (MODAL_KIND_TENSION
  * and MODAL_KIND_LINEAR instances of n_t <= 256; waves and max_workgroups 0,
  * no MODAL_FLAG_SPLIT_ANY) steps each instance on 16, 32 or 64 lanes of one

@@ -15,151 +15,139 @@
 // tensor, whose entries vanish unless the parity classes of the two columns
 // and the row match (Sec. 5, sparsity), only the partner class, a quarter of
 // them.  Per sample (paper: Sec. 3.1 modal forces, Sec. 3.2 modal update)
-//   1. wave 0 publishes q^n (rounded to FP32, lane order) to LDS and writes
-//      the output y^n = sum_k c_k q_k^n;
-//   2. every wave forms, for its rows, V[n, p] = sum_t h[r][t] q[jb + t]
-//      (a wave's rows share jb, so each q read serves all of them),
-//      eta_n = sum_p V[n, p] q_p (a DPP sum over the wave) and its partial
-//      force F_p = sum_n eta_n V[n, p];
-//   3. wave 0 adds the waves' partial forces (LDS) and advances its lane's
-//      mode in FP64, d+ = m X - p d + r (b e - F), X+ = X + d+, exactly as
-//      the streaming kernel does.
-// Tension-modulated instances need no tensor: wave 0 forms
+//   1. every wave writes q^n (rounded to FP32, lane order) to its own LDS copy;
+//   2. forms, for its rows, V[n, p] = sum_t h[r][t] q[jb + t] (a wave's rows
+//      share jb, so each q read serves all of them), eta_n = sum_p V[n, p] q_p
+//      (row_sums) and its partial force F_p = sum_n eta_n V[n, p];
+//   3. writes the partial force to LDS and, after the step's one barrier,
+//      adds all waves' partials and advances its lane's mode in FP64,
+//      d+ = m X - p d + r (b e - F), X+ = X + d+.
+// Every wave keeps the whole state and takes the same update, to the same
+// bits, so that q^n need not cross a second barrier.  The output's products
+// c_k q_k^n go to LDS step by step and are summed 64 steps at a time, a step
+// per lane, by the last wave; excitation samples are read 64 ahead.
+// Tension-modulated instances need no tensor: each wave forms
 // F_k = kappa lambda_k q_k sum_j lambda_j q_j^2 itself.  Linear instances
-// have F = 0.  Two workgroup barriers per sample and no global memory
-// besides the excitation sample and the output.
+// have F = 0.
+//
+// Bound by vector issue (two waves per SIMD, W R multiply-adds a wave) and
+// the latency of the LDS round trips and the barrier: a 40/40 plate by class
+// (a tile of 12 columns and 5 or 6 rows) steps in 0.60 us.  With wave 0 alone
+// keeping the state, a second barrier for q^n, a full wave sum per row and the
+// output summed every step it took 0.84 us (0.95 with a float-float state).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
-#include "device_common.h"
-#include "kernels.h"
+#include "chip_common.h"
 
 namespace modal {
 
-namespace {
-
-// R sums over the 64 lanes at once (the DPP steps of wave_sum interleaved so
-// that their latencies overlap)
-template <int R>
-__device__ __forceinline__ void wave_sums(float (&v)[R]) {
-#pragma unroll
-  for (int r = 0; r < R; ++r) v[r] += dpp_mov<0xB1>(v[r]);
-#pragma unroll
-  for (int r = 0; r < R; ++r) v[r] += dpp_mov<0x4E>(v[r]);
-#pragma unroll
-  for (int r = 0; r < R; ++r) v[r] += dpp_mov<0x141>(v[r]);
-#pragma unroll
-  for (int r = 0; r < R; ++r) v[r] += dpp_mov<0x140>(v[r]);
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-    v[r] = (lane_value(v[r], 0) + lane_value(v[r], 16)) + (lane_value(v[r], 32) + lane_value(v[r], 48));
-}
-
-}  // namespace
-
 // W: tensor columns held per row and lane (>= every jl, multiple of 4);
-// R: rows per wave (>= every wave's row count).
-template <int W, int R>
+// R: rows per wave (>= every wave's row count); REC: also checkpoints of the
+// state and the trajectory for the reverse sweep.
+template <int W, int R, bool REC>
 __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) {
-  // q^n (FP32) in lane order, zero past the last lane so that a run of
-  // W columns from any jb reads zeros beyond the modes
-  __shared__ float4 xc4[(kWave + 64) / 4];
-  __shared__ float red[kChipWaves][kWave];  // per-wave partial forces
-  float* Xc = reinterpret_cast<float*>(xc4);
+  constexpr int kYStride = kWave + 4;
+  __shared__ __align__(16) float xs[kChipWaves][kChipVec];      // q^n, one copy per wave
+  __shared__ float red[2][kChipWaves][kWave];                   // partial forces, by step parity
+  __shared__ __align__(16) float ys[kWave][kYStride];           // c_k q_k^n of 64 steps
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform
-  const UnitDev U = P.unit[P.wg_begin[blockIdx.x]];
-  const InstDev I = P.inst[U.inst];
-  const ChipMap& M = P.chip[U.inst];
-  const int nt = I.nt;
+  const ChipMap& M = P.chip[blockIdx.x];
+  const UnitDev U = P.unit[M.unit];
+  const InstDev I = P.inst[blockIdx.x];
   const bool vk = I.kind == KIND_VK;
   const int k = M.perm[lane];  // this lane's mode (-1: none)
   const int jb = M.jb[wave][lane];
   const int jl = M.jl[wave][lane];
 
   float h[R][W];
-#pragma unroll
-  for (int t = 0; t < W; ++t) {
-    const int j = (vk && k >= 0 && t < jl) ? M.perm[jb + t] : -1;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int n = M.row[wave][r];
-      h[r][t] = (j >= 0 && n >= 0) ? P.H[I.h_off + ((long long)n * nt + j) * I.ntp + k] : 0.f;
-    }
-  }
-  for (int i = threadIdx.x; i < kWave + 64; i += kWave * kChipWaves) Xc[i] = 0.f;
-  __syncthreads();
+  chip_load<W, R>(M, I, P.H, wave, k, jb, jl, [&](int i, int t, float v) { h[i][t] = v; });
+  float* Xc = xs[wave];
+  Xc[kWave + lane] = 0.f;
 
-  // wave 0: its lane's mode, state and coefficients
   double x = 0., d = 0., m = 0., p = 0., r = 0.;
-  float xh = 0.f, bx = 0.f, cw = 0.f, lam = 0.f;  // xh: x rounded to FP32
-  if (wave == 0) {
-    if (k >= 0) {
-      const int so = U.state_off + k, mo = I.mode_off + k;
-      x = P.x[so];
-      d = P.d[so];
-      m = P.m[mo];
-      p = P.p[mo];
-      r = P.r[mo];
-      xh = (float)x;
-      bx = P.b_ext[mo];
-      cw = P.c_out[mo];
-      lam = P.lam[mo];
-    }
-    Xc[lane] = xh;
+  float bx = 0.f, cw = 0.f, lam = 0.f;
+  if (k >= 0) {
+    const int so = U.state_off + k, mo = I.mode_off + k;
+    x = P.x[so];
+    d = P.d[so];
+    m = P.m[mo];
+    p = P.p[mo];
+    r = P.r[mo];
+    bx = P.b_ext[mo];
+    cw = P.c_out[mo];
+    lam = P.lam[mo];
   }
-  const float4* xq = reinterpret_cast<const float4*>(Xc + jb);
+  float xh = (float)x;
   const long long base = *P.step_base;
+  auto chunk = [&](long long n0) {
+    const long long t = n0 + lane;
+    return t < I.n_exc ? P.e_ext[I.e_off + t] : 0.f;
+  };
+  float en = chunk(base);
   bool bad = false;
-  for (int s = 0; s < P.n_steps; ++s) {
-    const long long n = base + s;
-    __syncthreads();  // q^n in LDS; the previous step's partial forces consumed
-    float e = 0.f;
-    if (wave == 0) {
-      if (n < I.n_exc) e = P.e_ext[I.e_off + n];
-      const float yv = wave_sum(cw * xh);
-      if (lane == 0 && P.y) P.y[(long long)I.out_row * P.y_stride + s] = yv;
-    }
-    float F = 0.f;
-    if (vk) {
-      float V[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) V[r] = 0.f;
-#pragma unroll
-      for (int t4 = 0; t4 < W / 4; ++t4) {
-        const float4 q = xq[t4];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          V[r] = fmaf(h[r][4 * t4], q.x, V[r]);
-          V[r] = fmaf(h[r][4 * t4 + 1], q.y, V[r]);
-          V[r] = fmaf(h[r][4 * t4 + 2], q.z, V[r]);
-          V[r] = fmaf(h[r][4 * t4 + 3], q.w, V[r]);
+  int to_ckpt = 0;  // steps to the next checkpoint
+  if (REC && P.ckpt) to_ckpt = (int)((P.ckpt_every - base % P.ckpt_every) % P.ckpt_every);
+  for (int s0 = 0; s0 < P.n_steps; s0 += kWave) {
+    const float ec = en;
+    const bool driven = base + s0 < I.n_exc;
+    en = chunk(base + s0 + kWave);
+    const int js = min(kWave, P.n_steps - s0);
+    for (int j = 0; j < js; ++j) {
+      Xc[lane] = xh;
+      if (wave == kChipWaves - 1) ys[j][lane] = cw * xh;
+      if constexpr (REC) {
+        const long long n = base + s0 + j;
+        if (wave == kChipWaves - 2 && P.rec_x && k >= 0) {
+          const long long ro = (n - P.rec_base) * P.mode_floats + I.mode_off + k;
+          P.rec_x[ro] = xh;
+          P.rec_d[ro] = (float)d;
+        }
+        if (P.ckpt) {
+          if (to_ckpt == 0) {
+            if (wave == kChipWaves - 2 && k >= 0) {
+              double* cp = P.ckpt + (n / P.ckpt_every) * 2LL * P.mode_floats + I.mode_off + k;
+              cp[0] = x;
+              cp[P.mode_floats] = d;
+            }
+            to_ckpt = P.ckpt_every;
+          }
+          --to_ckpt;
         }
       }
-      const float qk = Xc[lane];
-      float eta[R];
+      float F = 0.f;
+      if (vk) {
+        wave_lds_sync();
+        float V[R], eta[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) eta[r] = V[r] * qk;
-      wave_sums<R>(eta);
+        for (int i = 0; i < R; ++i) V[i] = 0.f;
+        chip_mul<W, R>(V, h, Xc + jb);
 #pragma unroll
-      for (int r = 0; r < R; ++r) F = fmaf(eta[r], V[r], F);
-      red[wave][lane] = F;
-      __syncthreads();  // every wave's partial force
-      if (wave == 0) {
-        F = red[0][lane];
+        for (int i = 0; i < R; ++i) eta[i] = V[i] * xh;
+        const float es = row_sums<R>(eta, lane);
 #pragma unroll
-        for (int w = 1; w < kChipWaves; ++w) F += red[w][lane];
+        for (int i = 0; i < R; ++i) F = fmaf(lane_value(es, i), V[i], F);
+        red[j & 1][wave][lane] = F;
+        block_lds_sync();  // every wave's partial force
+        F = wave_join(red[j & 1], lane);
+      } else if (I.kind == KIND_TENSION) {
+        const float S = group_sum<kWave>(lam * xh * xh) * I.kappa;
+        F = lam * xh * S;
       }
-    } else if (I.kind == KIND_TENSION && wave == 0) {
-      const float S = wave_sum(lam * xh * xh) * I.kappa;
-      F = lam * xh * S;
-    }
-    if (wave == 0) {
+      const float e = driven ? lane_value(ec, j) : 0.f;
       mode_step(x, d, m, p, r, fmaf(bx, e, -F));
       xh = (float)x;
       bad |= !isfinite(xh);
-      if (k >= 0) Xc[lane] = xh;
+    }
+    if (wave == kChipWaves - 1) {
+      wave_lds_sync();
+      float4 a = f4(0.f);
+#pragma unroll 4
+      for (int i = 0; i < kWave / 4; ++i) a = add4(a, ld4(&ys[lane][4 * i]));
+      if (lane < js && P.y) P.y[(long long)I.out_row * P.y_stride + s0 + lane] = (a.x + a.y) + (a.z + a.w);
+      wave_lds_sync();
     }
   }
   if (wave == 0) {
@@ -172,44 +160,38 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
   }
 }
 
-// Widths and rows per wave with a kernel: W R <= 200 tensor floats per lane
-// (with the rest of the kernel's registers, at most two waves per SIMD).
+// The smallest tile with a kernel that holds max_w columns and max_rows rows
+// per wave.
 bool chip_shape(int max_w, int max_rows, int& w_tile, int& rows) {
-  static const int widths[] = {8, 16, 20, 24, 32, 40, 48, 64};
-  static const int counts[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12};
   int w = 0, r = 0;
-  for (int x : widths)
-    if (x >= max_w) {
-      w = x;
-      break;
-    }
-  for (int x : counts)
-    if (x >= std::max(1, max_rows)) {
-      r = x;
-      break;
-    }
-  if (!w || !r || w * r > 200) return false;
+  long best = -1;
+#define CHIP_FIT(WW, RR)                                                       \
+  if (WW >= max_w && RR >= max_rows && (best < 0 || WW * RR < best)) {         \
+    best = WW * RR;                                                            \
+    w = WW;                                                                    \
+    r = RR;                                                                    \
+  }
+  CHIP_SHAPES(CHIP_FIT)
+#undef CHIP_FIT
+  if (best < 0 || best > kChipTile) return false;
   w_tile = w;
   rows = r;
   return true;
 }
 
 hipError_t launch_chip(const StepParams& P, int w_tile, int rows, int n_wg, hipStream_t s) {
-  if (P.ckpt || P.rec_x || !P.chip) return hipErrorInvalidValue;  // forward-only contexts
-#define CL(WW, RR)                                                                               \
-  if (w_tile == WW && rows == RR) {                                                              \
-    hipLaunchKernelGGL((chip_kernel<WW, RR>), dim3(n_wg), dim3(kWave * kChipWaves), 0, s, P);    \
-    return hipGetLastError();                                                                    \
+  if (!P.chip) return hipErrorInvalidValue;
+  const bool rec = P.ckpt || P.rec_x;
+#define CHIP_RUN(WW, RR)                                                                                \
+  if (w_tile == WW && rows == RR) {                                                                     \
+    if (rec)                                                                                            \
+      hipLaunchKernelGGL((chip_kernel<WW, RR, true>), dim3(n_wg), dim3(kWave * kChipWaves), 0, s, P);   \
+    else                                                                                                \
+      hipLaunchKernelGGL((chip_kernel<WW, RR, false>), dim3(n_wg), dim3(kWave * kChipWaves), 0, s, P);  \
+    return hipGetLastError();                                                                           \
   }
-  CL(8, 1) CL(8, 2) CL(8, 3) CL(8, 4) CL(8, 5) CL(8, 6) CL(8, 7) CL(8, 8) CL(8, 10) CL(8, 12)
-  CL(16, 1) CL(16, 2) CL(16, 3) CL(16, 4) CL(16, 5) CL(16, 6) CL(16, 7) CL(16, 8) CL(16, 10) CL(16, 12)
-  CL(20, 1) CL(20, 2) CL(20, 3) CL(20, 4) CL(20, 5) CL(20, 6) CL(20, 7) CL(20, 8) CL(20, 10)
-  CL(24, 1) CL(24, 2) CL(24, 3) CL(24, 4) CL(24, 5) CL(24, 6) CL(24, 7) CL(24, 8)
-  CL(32, 1) CL(32, 2) CL(32, 3) CL(32, 4) CL(32, 5) CL(32, 6)
-  CL(40, 1) CL(40, 2) CL(40, 3) CL(40, 4) CL(40, 5)
-  CL(48, 1) CL(48, 2) CL(48, 3) CL(48, 4)
-  CL(64, 1) CL(64, 2) CL(64, 3)
-#undef CL
+  CHIP_SHAPES(CHIP_RUN)
+#undef CHIP_RUN
   return hipErrorInvalidValue;
 }
 

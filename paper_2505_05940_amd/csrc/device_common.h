@@ -277,6 +277,11 @@ __device__ __forceinline__ float4 buf_ld4(v4i r, int voff) {
   return make_float4(v.x, v.y, v.z, v.w);
 }
 
+// 4-byte load through a buffer resource (zero at out-of-range offsets)
+__device__ float llvm_raw_buffer_load_f32(v4i rsrc, int voffset, int soffset, int aux)
+    __asm("llvm.amdgcn.raw.buffer.load.f32");
+__device__ __forceinline__ float buf_ld1(v4i r, int voff) { return llvm_raw_buffer_load_f32(r, voff, 0, 0); }
+
 // Orders this wave's LDS writes before its later LDS reads by other lanes.
 // Workgroups are single waves, so no s_barrier is needed, and vector-memory
 // loads in flight are not waited for.

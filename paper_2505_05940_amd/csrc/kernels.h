@@ -119,6 +119,7 @@ __host__ __device__ inline GradLds grad_lds(float* base) {
 // from lane jb[w][p] (the one column class whose entries can be nonzero
 // against p's class; for a tensor without classes, all nt modes from 0).
 struct ChipMap {
+  int unit;  // the unit that holds the instance's state (its slab 0)
   short perm[kWave];
   short row[kChipWaves][kChipMaxRows];
   unsigned char jb[kChipWaves][kWave];
@@ -192,6 +193,10 @@ struct GradParams {
   // per-row record of -2 eta_n (V_n . u) for every reverse step of the
   // segment: [seg_len][rows_total] (rows of all VK instances); NULL = none
   float* rrec;
+  // on-chip reverse kernel: one map per instance, and the FP64 sums over the
+  // steps of -2 eta_n (V_n . u), added to (NULL = none), instead of rrec
+  const ChipMap* chip;
+  double* racc;
   int rows_total;
   // records for the full tensor gradient (NULL = none), in forward step order
   // like rec_x: u^n per mode [seg_len][mode_floats], and eta_n, V_n . u per

@@ -32,6 +32,7 @@ hipError_t launch_chip(const StepParams& P, int nt_tile, int rows, int n_wg, hip
 void wave_shape(int nt, int batch, int cus, int& lanes, int& m);
 hipError_t launch_wave_step(const StepParams& P, int lanes, int m, int batch, hipStream_t s);
 hipError_t launch_wave_grad(const GradParams& P, int lanes, int m, int batch, hipStream_t s);
+hipError_t launch_chip_grad(const GradParams& P, int w_tile, int rows, int n_wg, hipStream_t s);
 bool chip_shape(int max_nt, int max_rows, int& nt_tile, int& rows);
 hipError_t launch_grad(const GradParams& P, int gm, bool tangent, int nw, bool split, int n_wg, size_t lds,
                        hipStream_t s);
@@ -212,12 +213,22 @@ struct modal_ctx {
   int device = 0;  // the device current at modal_init
   double fs = 0;
   int n_wg = 0, n_units = 0, n_split = 0, occ = 0, gm = 1, nw = 4;
+  int nw_stream = 4;  // waves and LDS of the streaming kernel, should the
+  size_t lds_stream = 0;  // on-chip one be given up (set_tensor)
   int res_stride = 0;  // > 0: LDS-resident state (one unit per workgroup)
-  // > 0: the on-chip kernel (one workgroup per instance, tensor in
+  // > 0: the on-chip kernels (one workgroup per instance, tensor in
   // registers), with chip_nt tensor columns per lane and chip_rows rows per
-  // wave, and its register layouts (one ChipMap per instance)
+  // wave, and their register layouts (one ChipMap per instance, with the
+  // columns and rows it needs, and whether it leaves out the entries that
+  // the tensor's mode classes make zero)
   int chip_nt = 0, chip_rows = 0;
   ChipMap* dChip = nullptr;
+  struct Chip {
+    ChipMap map;
+    int w, r;
+    bool grouped;
+  };
+  std::vector<Chip> chips;
   // > 0: the wave kernels (no instance has a tensor), with this many lanes
   // per instance and modes per lane
   int wave_lanes = 0, wave_m = 0;
@@ -612,9 +623,11 @@ void plan_blocks(const modal_desc* d, std::vector<BlockPlan>& plans) {
 // each wave the rows of one column pattern, so a lane holds only the one
 // class of columns that can be nonzero against it; any other tensor is
 // held whole (all nt columns), its rows dealt to the waves in turn.
-bool chip_map(const modal_instance& I, ChipMap& m, int& w_need, int& r_need) {
+// bp: the tensor's class structure (analyze_blocks), not ok to hold it whole.
+bool chip_map(const modal_instance& I, const BlockPlan& bp, ChipMap& m, int& w_need, int& r_need) {
   const int nt = I.n_t;
   w_need = r_need = 0;
+  m.unit = 0;
   if (nt > kWave) return false;
   for (int p = 0; p < kWave; ++p) m.perm[p] = (short)(p < nt ? p : -1);
   for (int w = 0; w < kChipWaves; ++w) {
@@ -625,16 +638,6 @@ bool chip_map(const modal_instance& I, ChipMap& m, int& w_need, int& r_need) {
     }
   }
   if (I.kind != MODAL_KIND_VK) return true;
-  BlockPlan bp;
-  if (I.mode_class) {
-    hipPointerAttribute_t attr;
-    bool on_device = false;
-    if (hipPointerGetAttributes(&attr, I.H) == hipSuccess)
-      on_device = attr.type == hipMemoryTypeDevice;
-    else
-      (void)hipGetLastError();
-    if (!on_device) analyze_blocks(I, bp);
-  }
   const int nin = I.n_in;
   if (!bp.ok || bp.cls[4] > kWave) {  // whole tensor, rows dealt in turn
     r_need = (nin + kChipWaves - 1) / kChipWaves;
@@ -652,6 +655,7 @@ bool chip_map(const modal_instance& I, ChipMap& m, int& w_need, int& r_need) {
   for (int c = 0; c < 4; ++c)
     for (int p = bp.cls[c]; p < bp.cls[c + 1]; ++p) real[c] += bp.slot_mode[p] >= 0;
   std::map<std::array<int, 4>, std::vector<int>> by_pattern;
+  std::vector<int> zero;
   for (int n = 0; n < nin; ++n) {
     std::array<int, 4> part = {-1, -1, -1, -1};
     for (int i = 0; i < 4; ++i) {
@@ -660,9 +664,17 @@ bool chip_map(const modal_instance& I, ChipMap& m, int& w_need, int& r_need) {
       part[i] = je & 7;
       if (je & 8) part[je & 7] = i;
     }
-    if (part[0] < 0 && part[1] < 0 && part[2] < 0 && part[3] < 0) continue;  // a zero row
-    by_pattern[part].push_back(n);
+    if (part[0] < 0 && part[1] < 0 && part[2] < 0 && part[3] < 0) zero.push_back(n);
+    else by_pattern[part].push_back(n);
   }
+  // rows without entries go along with another pattern's (their records of
+  // eta and V.u are zeros that a tensor gradient reads)
+  if (by_pattern.empty()) by_pattern[{-1, -1, -1, -1}] = zero;
+  else
+    for (int n : zero)
+      std::min_element(by_pattern.begin(), by_pattern.end(), [](const auto& a, const auto& b) {
+        return a.second.size() < b.second.size();
+      })->second.push_back(n);
   const int npat = (int)by_pattern.size();
   if (npat > kChipWaves) return false;
   std::vector<const std::array<int, 4>*> pats;
@@ -706,6 +718,46 @@ bool chip_map(const modal_instance& I, ChipMap& m, int& w_need, int& r_need) {
     w0 += waves[i];
   }
   return true;
+}
+
+// The layouts of a batch whose instances all fit one workgroup's registers,
+// in a common tile; false if they do not.  Instances that pass the same
+// tensor and classes are analysed once.
+bool chip_plan(const modal_desc* d, std::vector<modal_ctx::Chip>& chips, int& w_tile, int& rows) {
+  for (int b = 0; b < d->batch; ++b) {  // before any analysis
+    const modal_instance& I = d->inst[b];
+    if (I.n_t > kWave || (I.kind == MODAL_KIND_VK && I.n_in > kChipWaves * kChipMaxRows)) return false;
+  }
+  chips.resize(d->batch);
+  std::map<std::tuple<const float*, int, int>, std::vector<int>> seen;
+  std::vector<BlockPlan> plans(d->batch);
+  int max_w = 0, max_r = 0;
+  for (int b = 0; b < d->batch; ++b) {
+    const modal_instance& I = d->inst[b];
+    int like = -1;
+    if (I.kind == MODAL_KIND_VK && I.mode_class) {
+      auto& same = seen[std::make_tuple(I.H, I.n_t, I.n_in)];
+      for (int o : same)
+        if (!std::memcmp(d->inst[o].mode_class, I.mode_class, I.n_t)) like = o;
+      if (like < 0) {
+        hipPointerAttribute_t attr;
+        bool on_device = false;
+        if (hipPointerGetAttributes(&attr, I.H) == hipSuccess)
+          on_device = attr.type == hipMemoryTypeDevice;
+        else
+          (void)hipGetLastError();
+        if (!on_device) analyze_blocks(I, plans[b]);
+        same.push_back(b);
+      }
+    }
+    modal_ctx::Chip& c = chips[b];
+    if (like >= 0) c = chips[like];
+    else if (!chip_map(I, plans[b], c.map, c.w, c.r)) return false;
+    else c.grouped = plans[b].ok;
+    max_w = std::max(max_w, c.w);
+    max_r = std::max(max_r, c.r);
+  }
+  return chip_shape(max_w, max_r, w_tile, rows);
 }
 
 // Planning cost of an instance in streamed-byte units: per in-plane row the
@@ -967,6 +1019,15 @@ int upload_tensors(modal_ctx* c, const modal_desc* d, const std::vector<InstDev>
   }
 #undef UP_TRY
   cleanup();
+  return MODAL_OK;
+}
+
+// The register layouts of the on-chip kernels, to the device.
+int upload_chips(modal_ctx* c, hipStream_t s) {
+  std::vector<ChipMap> m(c->chips.size());
+  for (size_t b = 0; b < m.size(); ++b) m[b] = c->chips[b].map;
+  HIP_TRY(hipMemcpyAsync(c->dChip, m.data(), sizeof(ChipMap) * m.size(), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipStreamSynchronize(s));
   return MODAL_OK;
 }
 
@@ -1515,13 +1576,6 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
       if (d->inst[b].kind == MODAL_KIND_VK) dense += 4.0 * d->inst[b].n_in * (double)d->inst[b].n_t * d->inst[b].n_t;
     latency = dense <= kLatencyBytes;
   }
-  // On-chip plan: a forward-only latency-bound batch whose instances each
-  // fit one workgroup's registers (at most 64 modes; a von Karman tensor of
-  // at most kChipWaves * rows in-plane rows) steps every instance in one
-  // workgroup that holds its tensor for the launch, with no exchange
-  // between workgroups.
-  int chip_nt = 0, chip_rows = 0;
-  std::vector<ChipMap> chip_maps;
   // A batch with no tensor at all (tension-modulated and linear instances)
   // takes the wave kernels, whatever its size, forward and for gradients:
   // their state stays in registers, and no step has a barrier or waits for
@@ -1538,24 +1592,19 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     }
     if (plain) wave_shape(nt_max, d->batch, prop0.multiProcessorCount, wave_lanes, wave_m);
   }
-  if (latency && !(d->flags & MODAL_FLAG_GRAD) && !wave_lanes) {
-    int max_w = 0, max_rows = 0;
-    bool ok = true;
-    chip_maps.resize(d->batch);
-    for (int b = 0; b < d->batch && ok; ++b) {
-      int w = 0, r = 0;
-      ok = chip_map(d->inst[b], chip_maps[b], w, r);
-      max_w = std::max(max_w, w);
-      max_rows = std::max(max_rows, r);
-    }
-    ok = ok && chip_shape(max_w, max_rows, chip_nt, chip_rows);
-    if (!ok) {
-      chip_nt = chip_rows = 0;
-      chip_maps.clear();
-    }
+  // On-chip plan: a batch of any size whose instances each fit one
+  // workgroup's registers (at most 64 modes; chip_plan) steps every instance
+  // in one workgroup that holds its tensor for the launch, with no exchange
+  // between workgroups; so does its reverse sweep, unless a tangent tensor is
+  // set.
+  int chip_nt = 0, chip_rows = 0;
+  if (d->waves == 0 && d->max_workgroups == 0 && !(d->flags & MODAL_FLAG_SPLIT_ANY) && !wave_lanes &&
+      !chip_plan(d, c->chips, chip_nt, chip_rows)) {
+    chip_nt = chip_rows = 0;
+    c->chips.clear();
   }
   std::vector<BlockPlan> plans;
-  if (!latency) plan_blocks(d, plans);
+  if (!latency && !chip_nt) plan_blocks(d, plans);
   else plans.assign(d->batch, BlockPlan{});
   std::vector<int> jmap_pool;
   c->mode_slot.assign(d->batch, {});
@@ -1699,11 +1748,17 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   std::vector<Unit> units;
   std::vector<int> bin_of;
   std::vector<double> load;
-  if (wave_lanes) {  // one unit per instance, in instance order
+  // one unit per instance, in instance order, where no streaming plan is kept
+  // (a gradient context keeps one: a tangent or a replaced tensor may need it)
+  const bool grad = d->flags & MODAL_FLAG_GRAD;
+  const bool one_each = wave_lanes || (chip_nt && !grad);
+  if (one_each) {
     for (int b = 0; b < d->batch; ++b) {
-      units.push_back({b, 0, 1, 0, fixed_cost[b]});
+      const int rows = inst[b].kind == KIND_VK ? inst[b].nin : 1;
+      const double cost = fixed_cost[b] + rows * row_cost[b];
+      units.push_back({b, 0, rows, 0, cost});
       bin_of.push_back(b);
-      load.push_back(fixed_cost[b]);
+      load.push_back(cost);
     }
     n_bins = d->batch;
   } else if (latency) {
@@ -1720,7 +1775,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
       const int by_rows = (rows + kLatencyRows / 2) / kLatencyRows;
       const double slab_bytes = bytes > kLatencyBigTensor ? 0.5 * kLatencySlabBytes : kLatencySlabBytes;
       const int by_bytes = (int)std::ceil(bytes / slab_bytes);
-      const int S = inst[b].kind == KIND_VK && !chip_nt
+      const int S = inst[b].kind == KIND_VK
                         ? std::max(1, std::min({cap_slabs, rows, std::max(by_rows, by_bytes)}))
                         : 1;
       for (int sl = 0; sl < S; ++sl) {
@@ -1738,7 +1793,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
       latency = false;
     }
   }
-  if (!wave_lanes && !latency && !plan_batch(d, row_cost, fixed_cost, total, n_bins, units, bin_of, load)) {
+  if (!one_each && !latency && !plan_batch(d, row_cost, fixed_cost, total, n_bins, units, bin_of, load)) {
     free_ctx(c);
     return fail(MODAL_EINVAL, "batch does not fit the workgroup budget");
   }
@@ -1773,7 +1828,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     U.row1 = u.row1;
     U.slab = u.slab;
     U.state_off = state_floats;
-    if (c->unit_state_of_inst[u.inst] < 0) c->unit_state_of_inst[u.inst] = state_floats;
+    if (u.slab == 0) c->unit_state_of_inst[u.inst] = state_floats;
     state_floats += inst[u.inst].ntp;
     U.qs = qs_of[u.inst];
     U.J = J_of[u.inst];
@@ -1805,12 +1860,14 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   c->res_stride = 0;
   c->wave_lanes = wave_lanes;
   c->wave_m = wave_m;
-  if (latency && chip_nt && n_wg == d->batch) {
-    c->chip_nt = chip_nt;
-    c->chip_rows = chip_rows;
+  c->chip_nt = chip_nt;
+  c->chip_rows = chip_rows;
+  c->nw_stream = c->nw;
+  c->lds_stream = c->lds_bytes;
+  if (chip_nt && !grad) {
     c->nw = kChipWaves;
     c->lds_bytes = 0;
-  } else if (wave_lanes && !(d->flags & MODAL_FLAG_GRAD)) {
+  } else if (wave_lanes && !grad) {
     c->n_wg = n_wg = (d->batch + kWave / wave_lanes - 1) / (kWave / wave_lanes);
     c->nw = 1;
     c->lds_bytes = 0;
@@ -1892,7 +1949,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   ALLOC(c->dStep, sizeof(long long));
   ALLOC(c->dE, sizeof(float) * (size_t)(e_floats + 1));
   ALLOC(c->dJmap, sizeof(int) * (jmap_pool.size() + 4));
-  if (c->chip_nt) ALLOC(c->dChip, sizeof(ChipMap) * chip_maps.size());
+  if (c->chip_nt) ALLOC(c->dChip, sizeof(ChipMap) * d->batch);
 #undef ALLOC
   auto bail = [&](int r) {
     free_ctx(c);
@@ -1911,9 +1968,12 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     if (!jmap_pool.empty())
       HIP_TRY_C(hipMemcpyAsync(c->dJmap, jmap_pool.data(), sizeof(int) * jmap_pool.size(),
                                hipMemcpyHostToDevice, stream));
-    if (c->chip_nt)
-      HIP_TRY_C(hipMemcpyAsync(c->dChip, chip_maps.data(), sizeof(ChipMap) * chip_maps.size(),
-                               hipMemcpyHostToDevice, stream));
+    if (c->chip_nt) {
+      for (int u = 0; u < c->n_units; ++u)
+        if (udev[u].slab == 0) c->chips[udev[u].inst].map.unit = u;
+      r = upload_chips(c, stream);
+      if (r) return bail(r);
+    }
   }
   char* meta = (char*)c->dMeta;
   InstDev* dInst = (InstDev*)meta;
@@ -1999,6 +2059,17 @@ int modal_reset(modal_ctx* c, void* stream_) {
   return MODAL_OK;
 }
 
+// One launch of P.n_steps forward steps.
+static int launch_forward(modal_ctx* c, const StepParams& P, hipStream_t s) {
+  if (c->wave_lanes)
+    HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
+  else if (c->chip_nt)
+    HIP_TRY(launch_chip(P, c->chip_nt, c->chip_rows, c->batch, s));
+  else
+    HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
+  return MODAL_OK;
+}
+
 static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, hipStream_t s) {
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
   for (int64_t done = 0; done < n_steps; done += chunk) {
@@ -2023,12 +2094,8 @@ static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride
         P.rec_d = c->dRecAll + (size_t)c->recall_cap * c->mode_floats;
         P.rec_base = 0;
       }
-      if (c->wave_lanes)
-        HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
-      else if (c->chip_nt)
-        HIP_TRY(launch_chip(P, c->chip_nt, c->chip_rows, c->n_wg, s));
-      else
-        HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
+      int r = launch_forward(c, P, s);
+      if (r) return r;
     }
     HIP_TRY(launch_advance(c->dStep, (int)k, s));
   }
@@ -2174,12 +2241,8 @@ int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride,
     P.y = y + done;
     P.y_stride = y_stride;
     P.n_steps = (int)k;
-    if (c->wave_lanes)
-      HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
-    else if (c->chip_nt)
-      HIP_TRY(launch_chip(P, c->chip_nt, c->chip_rows, c->n_wg, s));
-    else
-      HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
+    int r = launch_forward(c, P, s);
+    if (r) return r;
     HIP_TRY(launch_advance(c->dStep, (int)k, s));
   }
   // no checkpoints were recorded: a gradient context's recorded checkpoints
@@ -2306,6 +2369,49 @@ int modal_tf_grad(const double* coef, const int32_t* mode_off, int32_t batch, in
   return MODAL_OK;
 }
 
+// A tensor about to replace one whose on-chip layout leaves out the entries
+// that mode classes make zero may have entries there: instance b's tensor is
+// held whole from now on, where the tile allows it; else the batch goes back
+// to the streaming kernel, every slab of an instance starting from the state
+// that its slab 0 holds.
+static int chip_ungroup(modal_ctx* c, int b, hipStream_t s) {
+  modal_instance I{};
+  I.kind = MODAL_KIND_VK;
+  I.n_t = c->inst_host[b].nt;
+  I.n_in = c->inst_host[b].nin;
+  modal_ctx::Chip& C = c->chips[b];
+  const int unit = C.map.unit;
+  bool ok = chip_map(I, BlockPlan{}, C.map, C.w, C.r);
+  C.map.unit = unit;
+  C.grouped = false;
+  int w = 0, r = 0;
+  for (const modal_ctx::Chip& o : c->chips) {
+    w = std::max(w, o.w);
+    r = std::max(r, o.r);
+  }
+  ok = ok && chip_shape(w, r, c->chip_nt, c->chip_rows);
+  // recorded graphs hold launches of the tile that is given up
+  HIP_TRY(hipStreamSynchronize(s));
+  for (auto& g : c->graphs) HIP_TRY(hipGraphExecDestroy(g.exec));
+  c->graphs.clear();
+  if (ok) return upload_chips(c, s);
+  c->chip_nt = c->chip_rows = 0;
+  if (!(c->flags & MODAL_FLAG_GRAD)) {
+    c->nw = c->nw_stream;
+    c->lds_bytes = c->lds_stream;
+  }
+  for (const UnitDev& U : c->units) {
+    const int from = c->unit_state_of_inst[U.inst], n = c->inst_host[U.inst].ntp;
+    if (U.state_off == from) continue;
+    for (int a = 0; a < 2; ++a)
+      HIP_TRY(hipMemcpyAsync(c->dState + (size_t)a * c->state_floats + U.state_off,
+                             c->dState + (size_t)a * c->state_floats + from, sizeof(double) * n,
+                             hipMemcpyDeviceToDevice, s));
+  }
+  c->ctr_stale = true;
+  return MODAL_OK;
+}
+
 int modal_set_tensor(modal_ctx* c, int32_t b, const float* H, void* stream_) {
   if (!c || !H) return fail(MODAL_EINVAL, "NULL argument");
   if (c->shared || c->linear) return fail(MODAL_ESTATE, "the context keeps no per-instance tensor");
@@ -2341,6 +2447,10 @@ int modal_set_tensor(modal_ctx* c, int32_t b, const float* H, void* stream_) {
           }
   }
   if (!symmetric) return fail(MODAL_EINVAL, "tensor is not symmetric in its last two indices");
+  if (c->chip_nt && c->chips[b].grouped) {
+    int r = chip_ungroup(c, b, s);
+    if (r) return r;
+  }
   HIP_TRY(hipMemcpy2DAsync(c->dH + D.h_off, sizeof(float) * D.ntp, H, sizeof(float) * D.nt,
                            sizeof(float) * D.nt, (size_t)D.nin * D.nt, hipMemcpyDefault, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -2470,8 +2580,8 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
       P.rec_base = 0;
       rec_now = true;
     }
-    if (c->wave_lanes) HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
-    else HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
+    r = launch_forward(c, P, s);
+    if (r) return r;
     // slots now hold this spacing's checkpoints, and the record this run
     c->ckpt_upto = K == kRunCkpt ? std::max<long long>(c->ckpt_upto, n_steps) : 0;
     c->rec_upto = rec_now ? n_steps : 0;
@@ -2504,13 +2614,20 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   G.flags = F.flags;
   G.timeout_ticks = F.timeout_ticks;
   G.red_floats = (c->tangent ? 3 : 2) * c->red_floats;
-  G.rrec = rows_on ? c->dRrec : nullptr;
+  // on chip unless a tangent tensor is set; there the sums over the rows stay
+  // in the kernel, and with the whole trajectory recorded one launch sweeps it
+  const bool on_chip = c->wave_lanes || (c->chip_nt && !c->tangent);
+  const long long K_rev = on_chip && reuse_rec && !tens_on ? n_steps : K;
+  const long long nrev = (n_steps + K_rev - 1) / K_rev;
+  G.rrec = rows_on && !on_chip ? c->dRrec : nullptr;
+  G.chip = c->dChip;
+  G.racc = rows_on ? c->dRacc : nullptr;
   G.rows_total = c->rows_total;
   G.urec = tens_on ? c->dUrec : nullptr;
   G.trec = tens_on ? c->dTrec : nullptr;
-  for (long long seg = nseg - 1; seg >= 0; --seg) {
-    const long long s0 = seg * K;
-    const int len = (int)std::min<long long>(K, n_steps - s0);
+  for (long long seg = nrev - 1; seg >= 0; --seg) {
+    const long long s0 = seg * K_rev;
+    const int len = (int)std::min<long long>(K_rev, n_steps - s0);
     if (reuse_rec) {
       G.rec_x = c->dRecAll + (size_t)s0 * mf;
       G.rec_d = c->dRecAll + (size_t)(c->recall_cap + s0) * mf;
@@ -2523,8 +2640,8 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
       P.rec_d = c->dRec + (size_t)K * mf;
       P.rec_base = s0;
       P.n_steps = len;
-      if (c->wave_lanes) HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
-      else HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
+      r = launch_forward(c, P, s);
+      if (r) return r;
       G.rec_x = c->dRec;
       G.rec_d = c->dRec + (size_t)K * mf;
     }
@@ -2533,10 +2650,12 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
     G.done_before = n_steps - s0 - len;
     if (c->wave_lanes)
       HIP_TRY(launch_wave_grad(G, c->wave_lanes, c->wave_m, c->batch, s));
+    else if (on_chip)
+      HIP_TRY(launch_chip_grad(G, c->chip_nt, c->chip_rows, c->batch, s));
     else
       HIP_TRY(launch_grad(G, c->gm, c->tangent, c->nw_grad[c->tangent],
                           c->res_stride > 0 && c->nw_grad[c->tangent] > 1, c->n_wg, c->grad_lds_v[c->tangent], s));
-    if (rows_on) HIP_TRY(launch_row_sum(c->dRrec, len, c->rows_total, c->dRacc, s));
+    if (rows_on && !on_chip) HIP_TRY(launch_row_sum(c->dRrec, len, c->rows_total, c->dRacc, s));
     if (tens_on)
       HIP_TRY(launch_tensor_grad(c->dTJobs, (int)tjobs.size(), tj_nin, tj_nt, G.rec_x, c->dUrec, c->dTrec, mf,
                                  c->rows_total, len, s));

@@ -145,7 +145,8 @@ def plate_instance_shared(setup: PlateSetup, theta):
     pref = math.sqrt(6.0 * (1.0 - setup.nu ** 2) * Dh / setup.h ** 2)
     x0, c = _excitation_cached(setup, a)
     return dict(kind="vk", omega=omega, gamma=gamma, lam=lam, Ht=base_tensor(setup),
-                h_row_scale=pref / zeta2, x0=x0, xm1=x0.copy(), c=c, zeta2=zeta2)
+                h_row_scale=pref / zeta2, x0=x0, xm1=x0.copy(), c=c, zeta2=zeta2,
+                mode_class=physics.mode_classes(m, q))
 
 
 def aspect_tangent(setup, inst, a):
