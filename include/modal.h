@@ -169,7 +169,7 @@ typedef struct {
  * MODAL_FLAG_GRAD nor MODAL_FLAG_RECURSE is set), each mode's recursion is
  * solved in closed form from the roots of its characteristic polynomial
  * (FP64 on the host) and modal_run evaluates the outputs of all requested
- * steps in parallel in float-float arithmetic (free response plus the
+ * steps in parallel in FP64 (free response plus the
  * excitation convolved with the impulse response); MODAL_FLAG_GRAPH has no
  * effect there.  A mode with a double root keeps the batch on the recursion.
  * On-chip path (paper: Sec. 4.2, the single small plate stepped in real

@@ -268,8 +268,9 @@ __host__ __device__ inline size_t shared_lds_bytes(int kt, int kc, int jt, int n
 }
 
 // ---------------------------------------------------------- linear batches
-constexpr int kLinWaves = 2;  // waves per closed-form workgroup
-constexpr int kLinRun = 32;   // steps per lane (strided by 64)
+constexpr int kLinWaves = 4;  // waves per closed-form workgroup
+constexpr int kLinCols = 64;  // samples per row of a wave's tile
+constexpr int kLinConv = 256;  // steps per wave of the window convolution
 
 // A float-float complex number: real and imaginary parts as (high, low)
 // FP32 pairs whose sum carries about 48 bits.
@@ -277,38 +278,42 @@ struct FFc {
   float rh, rl, ih, il;
 };
 
-// One mode: both roots of z^2 - g z - p, their 64th powers, and the
-// recurrence y(n + 64) = a y(n) - b y(n - 64) that every combination of the
-// two root terms satisfies (a = Re(z1^64 + z2^64), b = Re((z1 z2)^64)), all
-// float-float, rounded from the host's FP64 values.  conj: z2 = conj(z1),
-// only root 1 is evaluated (its amplitude carries the factor 2).
+// One mode's roots of z^2 - g z - p.  conj: z2 = conj(z1), only root 1 is
+// evaluated (its amplitude carries the factor 2); else both are real.
 struct LinMode {
-  FFc z1, z2, s1, s2;
-  float ah, al, bh, bl;
+  double2 z1, z2;
   int conj, pad[3];
 };
 
-// A run of output samples of one instance from one amplitude set: sample i
-// (< len) is the sum over modes [m0, m1) of Re(P1 z1^(e0+i) + P2 z2^(e0+i)),
-// written to out[out_off + i].
-struct LinSeg {
-  int m0, mc, m1, pad;  // modes [m0, mc) complex-conjugate pairs, [mc, m1) real pairs
-  long long amp_off;
-  long long e0;
-  long long out_off;
-  long long len;
+// Modes [m0, m1) of one instance and its excitation's length.
+struct LinInst {
+  int m0, m1;
+  long long n_exc;
 };
 
-// Per mode, what the amplitude sets are built from (float-float).
+// Per mode, what the amplitude sets are built from.
 struct LinInit {
-  FFc z1, z2, A, B, C;
-  float ch, cl, bh, bl;  // output weight c and force weight b
+  double2 A, B, C;
+  double c, b;  // output and force weights
   long long e_off, n_exc;
-  int conj, pad[3];
 };
 
 struct LinForced {
   long long inst, e_off, n_exc;
+};
+
+struct LinParams {
+  const LinMode* mode;
+  const LinInst* inst;
+  const LinForced* forced;
+  const double2* amp;  // [3 sets][modes]
+  const double* z;     // [modes][2][kLinCols]
+  const double2* s64;  // [modes][32]
+  long long modes;
+  int batch;
+  long long base, n;     // steps [base, base + n)
+  long long out_stride;  // of an instance (or of a forced one's impulse response)
+  bool impulse;
 };
 
 }  // namespace modal

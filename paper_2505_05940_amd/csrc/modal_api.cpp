@@ -50,13 +50,11 @@ hipError_t launch_sym_check(const float* H, int nin, int nt, int* bad, hipStream
 hipError_t launch_tensor_grad(const TGradJob* jobs, int n_jobs, int max_nin, int max_nt, const float* rec_x,
                               const float* urec, const float* trec, int mode_floats, int rows_total,
                               int seg_len, hipStream_t s);
-hipError_t launch_lin_sum(const LinMode* modes, const FFc* amp, const FFc* ztab, const LinSeg* segs,
-                          int n_segs, long long max_len, float* out, hipStream_t s);
-hipError_t launch_lin_sum_ff(const LinMode* modes, const FFc* amp, const FFc* ztab, const LinSeg* segs,
-                             int n_segs, long long max_len, float2* out, hipStream_t s);
-hipError_t launch_lin_amp(const LinInit* init, const LinMode* modes, int M, const float* e_ext, FFc* amp,
-                          FFc* ztab, hipStream_t s);
-hipError_t launch_lin_conv(const LinForced* forced, int n_forced, const float2* h, long long h_stride,
+hipError_t launch_lin_sum(const LinParams& P, int n_forced, float* out, hipStream_t s);
+hipError_t launch_lin_impulse(const LinParams& P, int n_forced, long long max_len, double* out, hipStream_t s);
+hipError_t launch_lin_init(const LinInit* init, const LinMode* modes, int M, const float* e_ext, double2* amp,
+                           double* z, double2* s64, hipStream_t s);
+hipError_t launch_lin_conv(const LinForced* forced, int n_forced, const double* h, long long h_stride,
                            const float* e_ext, long long base, long long n_steps, long long window,
                            float* y, long long y_stride, hipStream_t s);
 }  // namespace modal
@@ -307,14 +305,16 @@ struct modal_ctx {
   std::vector<double> lc, lb;                               // output and force weights
   std::vector<char> lconj;                                  // complex-conjugate root pair
   std::vector<std::vector<float>> le;                       // excitation per instance
-  std::vector<int> lin_moff, lin_mc;  // device mode ranges; [moff, mc) conjugate pairs
+  std::vector<int> lin_moff;  // mode ranges
   LinMode* dLinModes = nullptr;
   LinInit* dLinInit = nullptr;
-  FFc* dLinAmp = nullptr;      // [3 sets][modes][2 roots]
-  FFc* dLinTab = nullptr;      // z1^l, l < 64, per mode
-  LinSeg* dLinSeg = nullptr;
+  LinInst* dLinInst = nullptr;
+  double2* dLinAmp = nullptr;  // [3 sets][modes]
+  double* dLinZ = nullptr;     // z^b, b < 64, per mode
+  double2* dLinS = nullptr;    // z^(64 a), a < 32, per mode
   LinForced* dLinForced = nullptr;
-  float2* dLinH = nullptr;     // float-float impulse responses of forced instances
+  double* dLinH = nullptr;     // impulse responses of forced instances
+  LinParams LP{};
   int n_forced = 0;
   long long lin_h_stride = 1, lin_max_exc = 0;
   // shared-tensor path
@@ -341,8 +341,8 @@ void free_ctx(modal_ctx* c) {
   void* ptrs[] = {c->dH,   c->dMeta, c->dCoef, c->dState, c->dPart, c->dCtr, c->dFlags,
                   c->dStep, c->dE,   c->dHd,   c->dCkpt,  c->dRec,  c->dAdj, c->dAcc,
                   c->dGPart, c->dGCtr, c->dShA, c->dShS2, c->dJmap, c->dRrec, c->dRacc,
-                  c->dLinModes, c->dLinInit, c->dLinAmp, c->dLinSeg, c->dLinForced, c->dLinH,
-                  c->dLinTab, c->dUrec, c->dTrec, c->dTJobs, c->dRecAll, c->dChip};
+                  c->dLinModes, c->dLinInit, c->dLinInst, c->dLinAmp, c->dLinZ, c->dLinS, c->dLinForced,
+                  c->dLinH, c->dUrec, c->dTrec, c->dTJobs, c->dRecAll, c->dChip};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   delete c;
@@ -1083,63 +1083,28 @@ int init_linear(modal_ctx* c, const modal_desc* d, hipStream_t stream) {
     if (ne > 0) forced.push_back({b, eoff[b], ne});
     c->lin_max_exc = std::max(c->lin_max_exc, ne);
   }
-  // device order within an instance: complex-conjugate pairs first
-  std::vector<int> src;
-  src.reserve(M);
-  c->lin_mc.assign(B, 0);
-  for (int b = 0; b < B; ++b) {
-    for (int k = c->lin_moff[b]; k < c->lin_moff[b + 1]; ++k)
-      if (c->lconj[k]) src.push_back(k);
-    c->lin_mc[b] = (int)src.size();
-    for (int k = c->lin_moff[b]; k < c->lin_moff[b + 1]; ++k)
-      if (!c->lconj[k]) src.push_back(k);
-  }
+  auto d2 = [](cd v) { return make_double2(v.real(), v.imag()); };
   std::vector<LinMode> modes(M);
   std::vector<LinInit> init(M);
-  for (int b = 0; b < B; ++b)
-    for (int slot = c->lin_moff[b]; slot < c->lin_moff[b + 1]; ++slot) {
-      const int k = src[slot];
-      const cd z1 = c->lz1[k], z2 = c->lz2[k];
-      const double lm1 = std::log(std::abs(z1)), lm2 = std::log(std::abs(z2));
-      const cd s1 = std::polar(std::exp(64.0 * lm1), 64.0 * std::arg(z1));
-      const cd s2 = std::polar(std::exp(64.0 * lm2), 64.0 * std::arg(z2));
-      LinMode& m = modes[slot];
-      m.z1 = ffc(z1);
-      m.z2 = ffc(z2);
-      m.s1 = ffc(s1);
-      m.s2 = ffc(s2);
-      split((s1 + s2).real(), m.ah, m.al);
-      split((s1 * s2).real(), m.bh, m.bl);
-      m.conj = c->lconj[k];
-      m.pad[0] = m.pad[1] = m.pad[2] = 0;
-      LinInit& I = init[slot];
-      I.z1 = ffc(z1);
-      I.z2 = ffc(z2);
-      I.A = ffc(c->lA[k]);
-      I.B = ffc(c->lB[k]);
-      I.C = ffc(c->lC[k]);
-      split(c->lc[k], I.ch, I.cl);
-      split(c->lb[k], I.bh, I.bl);
-      I.e_off = eoff[b];
-      I.n_exc = (long long)c->le[b].size();
-      I.conj = c->lconj[k];
-      I.pad[0] = I.pad[1] = I.pad[2] = 0;
+  std::vector<LinInst> insts(B);
+  for (int b = 0; b < B; ++b) {
+    const long long ne = (long long)c->le[b].size();
+    insts[b] = {c->lin_moff[b], c->lin_moff[b + 1], ne};
+    for (int k = c->lin_moff[b]; k < c->lin_moff[b + 1]; ++k) {
+      modes[k] = {d2(c->lz1[k]), d2(c->lz2[k]), c->lconj[k], {0, 0, 0}};
+      init[k] = {d2(c->lA[k]), d2(c->lB[k]), d2(c->lC[k]), c->lc[k], c->lb[k], eoff[b], ne};
     }
+  }
   c->n_forced = (int)forced.size();
   c->lin_h_stride = std::max<long long>(1, c->lin_max_exc);
-  std::vector<LinSeg> hseg;
-  for (int f = 0; f < c->n_forced; ++f) {
-    const int b = (int)forced[f].inst;
-    hseg.push_back({c->lin_moff[b], c->lin_mc[b], c->lin_moff[b + 1], 0, 2 * (long long)M, 1,
-                    f * c->lin_h_stride, forced[f].n_exc - 1});
-  }
   int r = dalloc(&c->dLinModes, sizeof(LinMode) * std::max<size_t>(M, 1));
   if (!r) r = dalloc(&c->dLinInit, sizeof(LinInit) * std::max<size_t>(M, 1));
-  if (!r) r = dalloc(&c->dLinAmp, sizeof(FFc) * 2 * 3 * std::max<size_t>(M, 1));
-  if (!r) r = dalloc(&c->dLinTab, sizeof(FFc) * 64 * std::max<size_t>(M, 1));
-  if (!r) r = dalloc(&c->dLinSeg, sizeof(LinSeg) * std::max<size_t>(2 * (size_t)B, hseg.size()));
+  if (!r) r = dalloc(&c->dLinInst, sizeof(LinInst) * B);
+  if (!r) r = dalloc(&c->dLinAmp, sizeof(double2) * 3 * std::max<size_t>(M, 1));
+  if (!r) r = dalloc(&c->dLinZ, sizeof(double) * 2 * kLinCols * (M + 8));
+  if (!r) r = dalloc(&c->dLinS, sizeof(double2) * 32 * (M + 8));
   if (!r) r = dalloc(&c->dLinForced, sizeof(LinForced) * std::max<size_t>(forced.size(), 1));
-  if (!r) r = dalloc(&c->dLinH, sizeof(float2) * std::max<size_t>(1, forced.size() * c->lin_h_stride));
+  if (!r) r = dalloc(&c->dLinH, sizeof(double) * std::max<size_t>(1, forced.size() * c->lin_h_stride));
   if (!r) r = dalloc(&c->dE, sizeof(float) * epool.size());
   if (!r) r = dalloc(&c->dFlags, sizeof(int) * 2);
   if (r) return r;
@@ -1149,12 +1114,24 @@ int init_linear(modal_ctx* c, const modal_desc* d, hipStream_t stream) {
   if (!forced.empty())
     HIP_TRY(hipMemcpyAsync(c->dLinForced, forced.data(), sizeof(LinForced) * forced.size(),
                            hipMemcpyHostToDevice, stream));
-  if (!hseg.empty())
-    HIP_TRY(hipMemcpyAsync(c->dLinSeg, hseg.data(), sizeof(LinSeg) * hseg.size(), hipMemcpyHostToDevice,
-                           stream));
-  HIP_TRY(launch_lin_amp(c->dLinInit, c->dLinModes, (int)M, c->dE, c->dLinAmp, c->dLinTab, stream));
-  HIP_TRY(launch_lin_sum_ff(c->dLinModes, c->dLinAmp, c->dLinTab, c->dLinSeg, (int)hseg.size(), c->lin_max_exc - 1,
-                            c->dLinH, stream));
+  HIP_TRY(hipMemcpyAsync(c->dLinInst, insts.data(), sizeof(LinInst) * B, hipMemcpyHostToDevice, stream));
+  // the tables' ends, read ahead of an odd last mode
+  HIP_TRY(hipMemsetAsync(c->dLinZ + 2 * kLinCols * M, 0, sizeof(double) * 2 * kLinCols * 8, stream));
+  HIP_TRY(hipMemsetAsync(c->dLinS + 32 * M, 0, sizeof(double2) * 32 * 8, stream));
+  HIP_TRY(launch_lin_init(c->dLinInit, c->dLinModes, (int)M, c->dE, c->dLinAmp, c->dLinZ, c->dLinS, stream));
+  LinParams& P = c->LP;
+  P.mode = c->dLinModes;
+  P.inst = c->dLinInst;
+  P.forced = c->dLinForced;
+  P.amp = c->dLinAmp;
+  P.z = c->dLinZ;
+  P.s64 = c->dLinS;
+  P.modes = (long long)M;
+  P.batch = B;
+  LinParams H = P;
+  H.impulse = true;
+  H.out_stride = c->lin_h_stride;
+  HIP_TRY(launch_lin_impulse(H, c->n_forced, c->lin_max_exc - 1, c->dLinH, stream));
   HIP_TRY(hipStreamSynchronize(stream));
   for (int b = 0; b < B; ++b) {
     c->kind.push_back(d->inst[b].kind);
@@ -1172,31 +1149,16 @@ int init_linear(modal_ctx* c, const modal_desc* d, hipStream_t stream) {
 // left (the post amplitude set).
 int run_linear(modal_ctx* c, int64_t n, float* y, int64_t y_stride, hipStream_t s) {
   if (n <= 0) return MODAL_OK;
-  const int B = c->batch;
   const long long base = c->steps, end = base + n;
-  const long long M = (long long)c->lz1.size();
-  std::vector<LinSeg> seg;
-  seg.reserve(2 * (size_t)B);
-  for (int b = 0; b < B; ++b) {
-    const int m0 = c->lin_moff[b], mc = c->lin_mc[b], m1 = c->lin_moff[b + 1];
-    const long long row = (long long)b * y_stride;
-    const long long ne = (long long)c->le[b].size();
-    if (ne == 0) {
-      seg.push_back({m0, mc, m1, 0, 0, base, row, n});
-      continue;
-    }
-    const long long w_end = std::min(end, ne);
-    if (w_end > base) seg.push_back({m0, mc, m1, 0, 0, base, row, w_end - base});
-    const long long p0 = std::max(base, ne);
-    if (end > p0) seg.push_back({m0, mc, m1, 0, M, p0 - ne, row + (p0 - base), end - p0});
-  }
-  HIP_TRY(hipMemcpyAsync(c->dLinSeg, seg.data(), sizeof(LinSeg) * seg.size(), hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_lin_sum(c->dLinModes, c->dLinAmp, c->dLinTab, c->dLinSeg, (int)seg.size(), n, y, s));
+  LinParams P = c->LP;
+  P.base = base;
+  P.n = n;
+  P.out_stride = y_stride;
+  HIP_TRY(launch_lin_sum(P, c->n_forced, y, s));
   const long long window = std::min(end, c->lin_max_exc) - base;
   HIP_TRY(launch_lin_conv(c->dLinForced, c->n_forced, c->dLinH, c->lin_h_stride, c->dE, base, n, window, y,
                           y_stride, s));
-  // the host segment list must outlive the asynchronous copy
-  HIP_TRY(hipStreamSynchronize(s));
+  if (!(c->flags & MODAL_FLAG_ASYNC)) HIP_TRY(hipStreamSynchronize(s));
   return MODAL_OK;
 }
 
