@@ -46,7 +46,7 @@ def build(verbose: bool = False) -> str:
     hipcc = _hipcc()
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
-    srcs = [("step_kernel.hip", True), ("grad_kernel.hip", True), ("shared_kernel.hip", True),
+    srcs = [("step_kernel.hip", True), ("grad_kernel.hip", True), ("shared_kernel.hip", True), ("shared_class_kernel.hip", True),
             ("linear_kernel.hip", True), ("tf_kernel.hip", True), ("chip_kernel.hip", True), ("chip_grad_kernel.hip", True),
             ("wave_kernel.hip", True),
             ("modal_api.cpp", True),

@@ -100,6 +100,13 @@ __device__ __forceinline__ float group_sum(float v) {
   }
   return v;
 }
+// Sum of v over the four lanes l, l^16, l^32, l^48 (gfx950 lane swaps).
+__device__ __forceinline__ float quad_sum(float v) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
 // Lane j of each group of L lanes (j the same for every group).
 template <int L>
 __device__ __forceinline__ float group_lane(float v, int j) {

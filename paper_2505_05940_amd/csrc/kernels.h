@@ -256,6 +256,35 @@ struct SharedParams {
   const long long* step_base;
   int* flags;
 };
+// The same with the tensor in registers (shared_class_kernel.hip), for tensors
+// with mode classes of at most 16 modes: one workgroup per 16 columns, whose
+// waves share a group's rows.
+constexpr int kScWaves = 8;
+constexpr int kScChunk = 32;  // steps whose outputs are written at once
+struct ScWg {
+  int group, pad;
+};
+struct ScWave {
+  int part[4];  // partner class of each class in the wave's rows (-1: none; their A operands are zero)
+};
+struct ScParams {
+  const ScWg* wg;
+  const ScWave* wave;      // [group][kScWaves]
+  const SharedSlot* slot;  // [n_wg * 16]
+  const float* A;          // [group][wave][row][class][K step][64]
+  const float* s2;         // [n_wg][wave][row][16] squared row scales
+  // per (column, slot): [n_wg * 16][64], slot 16 c + i for mode i of class c
+  double *x, *d;
+  const double *m, *p, *r;
+  const float *c_out, *b_ext;
+  const float* e_ext;
+  float* y;
+  long long y_stride;
+  int n_steps;
+  const long long* step_base;
+  int* flags;
+};
+
 // LDS: two staged tensor rows (each padded to whole rounds of the
 // workgroup's 16-byte loads), X of every wave in two layouts, squared row
 // scales [nin][cols]

@@ -41,6 +41,8 @@ hipError_t launch_restore(const double* ckpt, long long slot, int mode_floats, c
                           const UnitDev* unit, int n_units, double* state, int state_floats,
                           long long* step_base, long long step, unsigned int* ctr, hipStream_t s);
 hipError_t launch_shared(const SharedParams& P, int kt, int kc, int jt, int n_wg, hipStream_t s);
+bool shared_class_shape(int ks, int rows, int& r_tile);
+hipError_t launch_shared_class(const ScParams& P, int ks, int r, int n_wg, hipStream_t s);
 hipError_t launch_row_sum(const float* rrec, int seg_len, int rows, double* acc, hipStream_t s);
 hipError_t launch_tf_response(const float2* coef, const int* mode_off, int batch, const FFc* z, int n_freq,
                               FFc* H, hipStream_t s);
@@ -323,6 +325,10 @@ struct modal_ctx {
   long long flops = 0;
   float *dShA = nullptr, *dShS2 = nullptr;
   SharedParams SP{};
+  // > 0: the shared tensor in registers by mode class, with this many K steps
+  // and rows per wave, on sc_wg workgroups
+  int sc_ks = 0, sc_rows = 0, sc_wg = 0;
+  ScParams SC{};
   hipStream_t cap_stream = nullptr;  // private stream used only for graph capture
   struct Graph {
     int64_t n, stride;
@@ -615,6 +621,69 @@ void plan_blocks(const modal_desc* d, std::vector<BlockPlan>& plans) {
   for (auto& t : th) t.join();
 }
 
+// A class-structured tensor's in-plane rows dealt to the waves of a
+// workgroup, every wave's rows having the same pattern (the partner class of
+// each class, -1: none), a stored transposed pair counted for both of its
+// blocks.  False if there are more patterns than waves.
+struct WaveRows {
+  std::array<int, 4> part;
+  std::vector<int> rows;
+};
+bool deal_rows(const BlockPlan& bp, int nin, std::vector<WaveRows>& waves) {
+  std::map<std::array<int, 4>, std::vector<int>> by_pattern;
+  std::vector<int> zero;
+  for (int n = 0; n < nin; ++n) {
+    std::array<int, 4> part = {-1, -1, -1, -1};
+    for (int i = 0; i < 4; ++i) {
+      const int je = bp.jmap[(size_t)n * 4 + i];
+      if (je < 0) continue;
+      part[i] = je & 7;
+      if (je & 8) part[je & 7] = i;
+    }
+    if (part[0] < 0 && part[1] < 0 && part[2] < 0 && part[3] < 0) zero.push_back(n);
+    else by_pattern[part].push_back(n);
+  }
+  // rows without entries go along with another pattern's (their records of
+  // eta and V.u are zeros that a tensor gradient reads)
+  if (by_pattern.empty()) by_pattern[{-1, -1, -1, -1}] = zero;
+  else
+    for (int n : zero)
+      std::min_element(by_pattern.begin(), by_pattern.end(), [](const auto& a, const auto& b) {
+        return a.second.size() < b.second.size();
+      })->second.push_back(n);
+  const int npat = (int)by_pattern.size();
+  if (npat > kChipWaves) return false;
+  std::vector<const std::array<int, 4>*> pats;
+  std::vector<const std::vector<int>*> rows;
+  for (auto& kv : by_pattern) {
+    pats.push_back(&kv.first);
+    rows.push_back(&kv.second);
+  }
+  // one wave per pattern, the rest where the most rows per wave remain
+  std::vector<int> n_waves(npat, 1);
+  for (int left = kChipWaves - npat; left > 0; --left) {
+    int best = -1;
+    double most = -1;
+    for (int i = 0; i < npat; ++i) {
+      const double per = (double)rows[i]->size() / n_waves[i];
+      if (per > most) {
+        most = per;
+        best = i;
+      }
+    }
+    if (best < 0) break;
+    n_waves[best]++;
+  }
+  waves.clear();
+  for (int i = 0; i < npat; ++i) {
+    const int w0 = (int)waves.size();
+    waves.resize(w0 + n_waves[i], WaveRows{*pats[i], {}});
+    for (size_t t = 0; t < rows[i]->size(); ++t) waves[w0 + (int)(t % n_waves[i])].rows.push_back((*rows[i])[t]);
+  }
+  waves.resize(kChipWaves, WaveRows{{-1, -1, -1, -1}, {}});
+  return true;
+}
+
 // On-chip register layout of one instance (see ChipMap), with the columns
 // per lane (w_need) and rows per wave (r_need) it takes; false if it does
 // not fit one workgroup (more than kWave lanes, or more than kChipMaxRows
@@ -654,68 +723,22 @@ bool chip_map(const modal_instance& I, const BlockPlan& bp, ChipMap& m, int& w_n
   int real[4] = {0, 0, 0, 0};
   for (int c = 0; c < 4; ++c)
     for (int p = bp.cls[c]; p < bp.cls[c + 1]; ++p) real[c] += bp.slot_mode[p] >= 0;
-  std::map<std::array<int, 4>, std::vector<int>> by_pattern;
-  std::vector<int> zero;
-  for (int n = 0; n < nin; ++n) {
-    std::array<int, 4> part = {-1, -1, -1, -1};
-    for (int i = 0; i < 4; ++i) {
-      const int je = bp.jmap[(size_t)n * 4 + i];
-      if (je < 0) continue;
-      part[i] = je & 7;
-      if (je & 8) part[je & 7] = i;
-    }
-    if (part[0] < 0 && part[1] < 0 && part[2] < 0 && part[3] < 0) zero.push_back(n);
-    else by_pattern[part].push_back(n);
-  }
-  // rows without entries go along with another pattern's (their records of
-  // eta and V.u are zeros that a tensor gradient reads)
-  if (by_pattern.empty()) by_pattern[{-1, -1, -1, -1}] = zero;
-  else
-    for (int n : zero)
-      std::min_element(by_pattern.begin(), by_pattern.end(), [](const auto& a, const auto& b) {
-        return a.second.size() < b.second.size();
-      })->second.push_back(n);
-  const int npat = (int)by_pattern.size();
-  if (npat > kChipWaves) return false;
-  std::vector<const std::array<int, 4>*> pats;
-  std::vector<const std::vector<int>*> rows;
-  for (auto& kv : by_pattern) {
-    pats.push_back(&kv.first);
-    rows.push_back(&kv.second);
-  }
-  // one wave per pattern, the rest where the most rows per wave remain
-  std::vector<int> waves(npat, 1);
-  for (int left = kChipWaves - npat; left > 0; --left) {
-    int best = -1;
-    double most = -1;
-    for (int i = 0; i < npat; ++i) {
-      const double per = (double)rows[i]->size() / waves[i];
-      if (per > most) {
-        most = per;
-        best = i;
+  std::vector<WaveRows> waves;
+  if (!deal_rows(bp, nin, waves)) return false;
+  for (int w = 0; w < kChipWaves; ++w) {
+    const std::vector<int>& rs = waves[w].rows;
+    if ((int)rs.size() > kChipMaxRows) return false;
+    r_need = std::max(r_need, (int)rs.size());
+    for (size_t t = 0; t < rs.size(); ++t) m.row[w][t] = (short)rs[t];
+    for (int c = 0; c < 4; ++c) {
+      const int cj = waves[w].part[c];
+      if (cj < 0) continue;
+      for (int p = bp.cls[c]; p < bp.cls[c + 1]; ++p) {
+        m.jb[w][p] = (unsigned char)bp.cls[cj];
+        m.jl[w][p] = (unsigned char)real[cj];
       }
+      w_need = std::max(w_need, real[cj]);
     }
-    if (best < 0) break;
-    waves[best]++;
-  }
-  int w0 = 0;
-  for (int i = 0; i < npat; ++i) {
-    const std::vector<int>& rs = *rows[i];
-    const int per = ((int)rs.size() + waves[i] - 1) / waves[i];
-    if (per > kChipMaxRows) return false;
-    r_need = std::max(r_need, per);
-    for (size_t t = 0; t < rs.size(); ++t) m.row[w0 + (int)(t % waves[i])][t / waves[i]] = (short)rs[t];
-    for (int w = w0; w < w0 + waves[i]; ++w)
-      for (int c = 0; c < 4; ++c) {
-        const int cj = (*pats[i])[c];
-        if (cj < 0) continue;
-        for (int p = bp.cls[c]; p < bp.cls[c + 1]; ++p) {
-          m.jb[w][p] = (unsigned char)bp.cls[cj];
-          m.jl[w][p] = (unsigned char)real[cj];
-        }
-        w_need = std::max(w_need, real[cj]);
-      }
-    w0 += waves[i];
   }
   return true;
 }
@@ -1192,6 +1215,184 @@ std::vector<SharedGroup> shared_groups(const modal_desc* d) {
   return g;
 }
 
+// The shared-tensor path with the tensors in registers, by mode class: taken
+// when every group's tensor has the structure of its mode_class hint with at
+// most 16 modes a class and a tile of the kernel holds every wave's rows.
+// Measured (us a step, the dense product -> this): plates at 40/40, 512 of
+// them 29.1 -> 4.0, 4096 30.0 -> 5.2, 16 384 33.0 -> 18.5 (four rounds of
+// workgroups); 1024 at 20/20 10.1 -> 2.5; 4096 at 48/48 38.3 -> 6.6.
+// Returns 1 if it was taken, 0 if not, or a negative status.
+int init_shared_class(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& groups, hipStream_t stream) {
+  const double T = 1.0 / d->fs;
+  struct Plan {
+    BlockPlan bp;
+    std::vector<WaveRows> waves;
+    std::vector<float> H;
+    int slot[16 * 4];               // mode slots, 16 a class: the mode, or -1
+    std::vector<int> mode_slot;
+  };
+  std::vector<Plan> plans(groups.size());
+  int ks = 1, rows = 1;
+  for (size_t g = 0; g < groups.size(); ++g) {
+    const SharedGroup& G = groups[g];
+    Plan& p = plans[g];
+    const uint8_t* cls = nullptr;
+    for (int b : G.members)
+      if (!cls) cls = d->inst[b].mode_class;
+    if (!cls) return 0;
+    const size_t hn = (size_t)G.nin * G.nt * G.nt;
+    p.H.resize(hn);
+    HIP_TRY(hipMemcpy(p.H.data(), G.H, sizeof(float) * hn, hipMemcpyDefault));
+    modal_instance I = d->inst[G.members[0]];
+    I.H = p.H.data();
+    I.mode_class = cls;
+    analyze_blocks(I, p.bp);
+    if (!p.bp.ok || !deal_rows(p.bp, G.nin, p.waves)) return 0;
+    int n_of[4] = {0, 0, 0, 0};
+    std::fill(p.slot, p.slot + 64, -1);
+    p.mode_slot.resize(G.nt);
+    for (int k = 0; k < G.nt; ++k) {
+      const int q = cls[k];
+      if (n_of[q] == 16) return 0;
+      p.mode_slot[k] = 16 * q + n_of[q];
+      p.slot[16 * q + n_of[q]++] = k;
+    }
+    for (int q = 0; q < 4; ++q) ks = std::max(ks, (n_of[q] + 3) / 4);
+    for (auto& w : p.waves) rows = std::max(rows, (int)w.rows.size());
+  }
+  int R = 0;
+  if (!shared_class_shape(ks, rows, R)) return 0;
+  const int NG = (int)groups.size();
+  long long n_wg = 0;
+  for (auto& g : groups) n_wg += ((long long)g.members.size() + 15) / 16;
+  const long long ncol = n_wg * 16, ncolk = ncol * 64;
+  std::vector<float> A((size_t)NG * kScWaves * R * 4 * ks * 64, 0.f), s2((size_t)n_wg * kScWaves * R * 16, 0.f);
+  std::vector<ScWave> wv((size_t)NG * kScWaves);
+  std::vector<ScWg> wgs;
+  std::vector<SharedSlot> slots(ncol, SharedSlot{-1, 0, 0, 0});
+  std::vector<double> coef(3 * (size_t)ncolk, 0.);
+  std::vector<float> cb(2 * (size_t)ncolk, 0.f), epool(1, 0.f);
+  c->state0.assign(2 * (size_t)ncolk, 0.);
+  c->unit_state_of_inst.assign(d->batch, 0);
+  c->mode_slot.assign(d->batch, {});
+  for (int g = 0; g < NG; ++g) {
+    const SharedGroup& G = groups[g];
+    const Plan& p = plans[g];
+    for (int w = 0; w < kScWaves; ++w) {
+      const WaveRows& W = p.waves[w];
+      for (int t = 0; t < 4; ++t) wv[(size_t)g * kScWaves + w].part[t] = W.part[t];
+      for (size_t r = 0; r < W.rows.size(); ++r)
+        for (int t = 0; t < 4; ++t) {
+          if (W.part[t] < 0) continue;
+          for (int s = 0; s < ks; ++s)
+            for (int l = 0; l < 64; ++l) {
+              const int k = p.slot[16 * t + l % 16], j = p.slot[16 * W.part[t] + 4 * s + l / 16];
+              if (k >= 0 && j >= 0)
+                A[(((((size_t)g * kScWaves + w) * R + r) * 4 + t) * ks + s) * 64 + l] =
+                    p.H[((size_t)W.rows[r] * G.nt + k) * G.nt + j];
+            }
+        }
+    }
+    c->coupling_bytes += 4LL * G.nin * G.nt * G.nt * (long long)G.members.size();
+    const long long wg0 = (long long)wgs.size();
+    for (size_t i = 0; i < G.members.size(); ++i) {
+      const int b = G.members[i];
+      const modal_instance& I = d->inst[b];
+      if (i % 16 == 0) wgs.push_back(ScWg{g, 0});
+      SharedSlot& sl = slots[wg0 * 16 + (long long)i];
+      sl.out_row = b;
+      sl.n_exc = I.n_exc;
+      sl.e_off = (long long)epool.size();
+      if (I.n_exc > 0) epool.insert(epool.end(), I.e_ext, I.e_ext + I.n_exc);
+      c->unit_state_of_inst[b] = (int)((wg0 * 16 + (long long)i) * 64);
+      c->flops += 2LL * G.nin * G.nt * G.nt + 4LL * G.nin * G.nt;
+    }
+    // coefficients, states and scales, on the host's threads for a large group
+    auto fill = [&](size_t a, size_t z) {
+      for (size_t i = a; i < z; ++i) {
+        const int b = G.members[i];
+        const modal_instance& I = d->inst[b];
+        const long long col = wg0 * 16 + (long long)i;
+        for (int w = 0; w < kScWaves; ++w)
+          for (size_t r = 0; r < p.waves[w].rows.size(); ++r) {
+            const double sc = I.h_row_scale ? I.h_row_scale[p.waves[w].rows[r]] : 1.0;
+            s2[((((size_t)(col / 16) * kScWaves + w) * R) + r) * 16 + col % 16] = (float)(sc * sc);
+          }
+        c->mode_slot[b] = p.mode_slot;
+        for (int k = 0; k < I.n_t; ++k) {
+          const size_t e = (size_t)col * 64 + p.mode_slot[k];
+          const Coef q = coefficients(d->scheme, I.omega[k], I.gamma[k], T);
+          coef[e] = q.m;
+          coef[ncolk + e] = q.p;
+          coef[2 * ncolk + e] = q.r;
+          cb[e] = (float)I.c_out[k];
+          cb[ncolk + e] = I.b_ext ? (float)I.b_ext[k] : 0.f;
+          c->state0[e] = I.x0[k];
+          c->state0[ncolk + e] = I.x0[k] - I.xm1[k];
+        }
+      }
+    };
+    const size_t nm = G.members.size();
+    const size_t nth = std::min<size_t>({16, std::max(1u, std::thread::hardware_concurrency()), (nm + 1023) / 1024});
+    std::vector<std::thread> th;
+    for (size_t t = 1; t < nth; ++t) th.emplace_back(fill, nm * t / nth, nm * (t + 1) / nth);
+    fill(0, nm / nth);
+    for (auto& t : th) t.join();
+  }
+  for (int b = 0; b < d->batch; ++b) {
+    c->kind.push_back(d->inst[b].kind);
+    c->nt.push_back(d->inst[b].n_t);
+  }
+  c->shared = true;
+  c->sc_ks = ks;
+  c->sc_rows = R;
+  c->sc_wg = (int)n_wg;
+  c->state_floats = (int)ncolk;
+  const size_t wv_bytes = (sizeof(ScWave) * wv.size() + 63) & ~(size_t)63;
+  const size_t wg_bytes = (sizeof(ScWg) * wgs.size() + 63) & ~(size_t)63;
+  int r = dalloc(&c->dShA, sizeof(float) * A.size());
+  if (!r) r = dalloc(&c->dMeta, wv_bytes + wg_bytes + sizeof(SharedSlot) * slots.size());
+  if (!r) r = dalloc(&c->dShS2, sizeof(float) * s2.size());
+  if (!r) r = dalloc(&c->dCoef, sizeof(double) * coef.size() + sizeof(float) * cb.size());
+  if (!r) r = dalloc(&c->dState, sizeof(double) * c->state0.size());
+  c->n_ctr = d->batch;
+  if (!r) r = dalloc(&c->dCtr, sizeof(unsigned int) * d->batch);
+  if (!r) r = dalloc(&c->dFlags, sizeof(int) * 2);
+  if (!r) r = dalloc(&c->dStep, sizeof(long long));
+  if (!r) r = dalloc(&c->dE, sizeof(float) * epool.size());
+  if (r) return r;
+  char* meta = (char*)c->dMeta;
+  auto up = [&](void* to, const void* from, size_t n) {
+    return hipMemcpyAsync(to, from, n, hipMemcpyHostToDevice, stream);
+  };
+  HIP_TRY(up(c->dShA, A.data(), sizeof(float) * A.size()));
+  HIP_TRY(up(meta, wv.data(), sizeof(ScWave) * wv.size()));
+  HIP_TRY(up(meta + wv_bytes, wgs.data(), sizeof(ScWg) * wgs.size()));
+  HIP_TRY(up(meta + wv_bytes + wg_bytes, slots.data(), sizeof(SharedSlot) * slots.size()));
+  HIP_TRY(up(c->dShS2, s2.data(), sizeof(float) * s2.size()));
+  HIP_TRY(up(c->dCoef, coef.data(), sizeof(double) * coef.size()));
+  HIP_TRY(up(c->dCoef + coef.size(), cb.data(), sizeof(float) * cb.size()));
+  HIP_TRY(up(c->dE, epool.data(), sizeof(float) * epool.size()));
+  HIP_TRY(hipStreamSynchronize(stream));
+  ScParams& P = c->SC;
+  P.wave = (const ScWave*)meta;
+  P.wg = (const ScWg*)(meta + wv_bytes);
+  P.slot = (const SharedSlot*)(meta + wv_bytes + wg_bytes);
+  P.A = c->dShA;
+  P.s2 = c->dShS2;
+  P.x = c->dState;
+  P.d = P.x + ncolk;
+  P.m = c->dCoef;
+  P.p = P.m + ncolk;
+  P.r = P.p + ncolk;
+  P.c_out = (const float*)(P.r + ncolk);
+  P.b_ext = P.c_out + ncolk;
+  P.e_ext = c->dE;
+  P.step_base = c->dStep;
+  P.flags = c->dFlags;
+  return 1;
+}
+
 // Builds a context on the shared-tensor path: packs each group's tensor
 // once in the MFMA operand order, lays every instance out as one column of
 // its group's workgroups and uploads coefficients, scales and state.
@@ -1229,6 +1430,19 @@ int init_shared(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& gro
   for (auto& g : groups) n_wg += ((long long)g.members.size() + cols - 1) / cols;
   if (n_wg > (1 << 30) / cols) return fail(MODAL_EINVAL, "batch too large");
   const long long ncol = n_wg * cols, ncolk = ncol * ktot;
+  {
+    int r = init_shared_class(c, d, groups, stream);
+    if (r < 0) return r;
+    if (r > 0) {  // described like the dense tiling it replaces
+      c->n_wg = (int)n_wg;
+      c->n_units = (int)ncol;
+      for (auto& g : groups)
+        for (size_t i = 0; i < g.members.size(); i += cols)
+          c->padded_bytes += 4LL * g.nin * (long long)((size_t)kt * kc4 * 64 * 4);
+      c->lds_bytes = shared_lds_bytes(kt, kc, jt, nin_max);
+      return MODAL_OK;
+    }
+  }
 
   // packed tensors: A[n][t][c][l] = H[n][16 t + l%16][4 c + l/16]
   std::vector<SharedWg> wgs;
@@ -2036,7 +2250,13 @@ static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
   for (int64_t done = 0; done < n_steps; done += chunk) {
     const int64_t k = std::min<int64_t>(chunk, n_steps - done);
-    if (c->shared) {
+    if (c->sc_ks) {
+      ScParams P = c->SC;
+      P.y = y + done;
+      P.y_stride = y_stride;
+      P.n_steps = (int)k;
+      HIP_TRY(launch_shared_class(P, c->sc_ks, c->sc_rows, c->sc_wg, s));
+    } else if (c->shared) {
       SharedParams P = c->SP;
       P.y = y + done;
       P.y_stride = y_stride;

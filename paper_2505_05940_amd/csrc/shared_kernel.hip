@@ -30,14 +30,6 @@ namespace modal {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// Sum of v over the four lanes l, l^16, l^32, l^48 (gfx950 lane swaps).
-__device__ __forceinline__ float quad_sum(float v) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
-}
-
 // KT: 16-row tiles; KC: 4-wide K steps (compile time, packed rows padded to
 // a multiple of 4 steps); JT: 16-column tiles per wave.
 template <int KT, int KC, int JT>

@@ -132,6 +132,19 @@ def base_tensor(setup: PlateSetup):
     return _BASE_TENSORS[key][1]
 
 
+_CLASSES = {}
+
+
+def _classes(setup):
+    """Parity classes of the setup's transverse modes (one object per setup,
+    cached; the batch's instances share it)."""
+    if id(setup) not in _CLASSES:
+        if len(_CLASSES) > 256:
+            _CLASSES.clear()
+        _CLASSES[id(setup)] = (setup, physics.mode_classes(setup.modes[0], setup.modes[1]))
+    return _CLASSES[id(setup)][1]
+
+
 def plate_instance_shared(setup: PlateSetup, theta):
     """The plate of ``plate_instance`` expressed as the setup's base tensor
     with per-row scales pref / zeta_n^2(a): batches of such instances share
@@ -146,7 +159,7 @@ def plate_instance_shared(setup: PlateSetup, theta):
     x0, c = _excitation_cached(setup, a)
     return dict(kind="vk", omega=omega, gamma=gamma, lam=lam, Ht=base_tensor(setup),
                 h_row_scale=pref / zeta2, x0=x0, xm1=x0.copy(), c=c, zeta2=zeta2,
-                mode_class=physics.mode_classes(m, q))
+                mode_class=_classes(setup))
 
 
 def aspect_tangent(setup, inst, a):

@@ -142,6 +142,7 @@ def _build_desc(instances, fs, scheme="sv", flags=0, max_workgroups=0, chunk_ste
     arr = (modal_instance * batch)()
     keep.append(arr)
     n_t = []
+    hosts = {}  # id of an array given by an instance -> (the array, its C copy, pointer), for this call
     for i, inst in enumerate(instances):
         n = len(inst["omega"])
         n_t.append(n)
@@ -171,9 +172,12 @@ def _build_desc(instances, fs, scheme="sv", flags=0, max_workgroups=0, chunk_ste
                 assert H.dtype.itemsize == 4 and H.is_contiguous() and tuple(H.shape[1:]) == (n, n)
                 s.H = C.cast(C.c_void_p(H.data_ptr()), _fp)
             else:
-                H = np.ascontiguousarray(H, dtype=np.float32)
+                if id(H) not in hosts:  # (an array that instances share is converted once)
+                    A = np.ascontiguousarray(H, dtype=np.float32)
+                    hosts[id(H)] = (H, A, A.ctypes.data_as(_fp))
+                H, ptr = hosts[id(H)][1:]
                 assert H.ndim == 3 and H.shape[1:] == (n, n)
-                s.H = H.ctypes.data_as(_fp)
+                s.H = ptr
             s.n_in = H.shape[0]
             keep.append(H)
             if inst.get("h_row_scale") is not None:
@@ -181,10 +185,14 @@ def _build_desc(instances, fs, scheme="sv", flags=0, max_workgroups=0, chunk_ste
                 keep.append(sc)
                 s.h_row_scale = sc.ctypes.data_as(_dp)
             if inst.get("mode_class") is not None:
-                mc = np.ascontiguousarray(inst["mode_class"], dtype=np.uint8)
+                mc = inst["mode_class"]
+                if id(mc) not in hosts:
+                    A = np.ascontiguousarray(mc, dtype=np.uint8)
+                    hosts[id(mc)] = (mc, A, A.ctypes.data_as(C.POINTER(C.c_uint8)))
+                mc, ptr = hosts[id(mc)][1:]
                 assert mc.shape == (n,)
                 keep.append(mc)
-                s.mode_class = mc.ctypes.data_as(C.POINTER(C.c_uint8))
+                s.mode_class = ptr
         else:
             s.n_in = 0
         if inst.get("e_ext") is not None:
