@@ -342,9 +342,8 @@ int modal_set_tensor(modal_ctx *c, int32_t inst, const float *H, void *stream);
  * modes of instance b at [mode_off[b], mode_off[b+1]) (int32 [batch + 1],
  * non-decreasing); omega [n_freq] in radians per sample; H [batch][n_freq][2]
  * (real, imaginary) written.  The device evaluates the sums in float-float
- * arithmetic (FP32 pairs, about 48 bits) from the split inputs, and the host
- * adds the pairs back into FP64; near a lightly damped pole the relative
- * error grows like 2^-48 / (gamma T).  Synchronous on `stream` (device
+ * arithmetic (FP32 pairs, about 48 bits) of the split inputs; near a lightly
+ * damped pole the relative error grows like 2^-48 / (gamma T).  Synchronous on `stream` (device
  * buffers are allocated and freed within the call).  EINVAL for NULL
  * pointers, batch outside [1, 65535], n_freq < 1 or a decreasing mode_off. */
 int modal_tf_response(const double *coef, const int32_t *mode_off, int32_t batch,

@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
     lam = P.lam[mo];
   }
   float xh = (float)x;
-  const long long base = *P.step_base;
+  const long long base = step_first(P);
   auto chunk = [&](long long n0) {
     const long long t = n0 + lane;
     return t < I.n_exc ? P.e_ext[I.e_off + t] : 0.f;
@@ -156,7 +156,8 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
       P.x[so] = x;
       P.d[so] = d;
     }
-    if (__any(bad) && lane == 0) atomicOr(&P.flags[1], 1);
+    if (__any(bad) && lane == 0) P.flags[1] = 1;
+    step_done(P);
   }
 }
 

@@ -6,48 +6,17 @@
 
 namespace modal {
 
-// ---------------------------------------------------------------- float-float
-// Error-free transformations (Knuth's TwoSum, Dekker's Fast2Sum, and the
-// FMA-based exact product).  This file is compiled with -ffp-contract=off so
-// only the explicit fmaf calls fuse.
-struct ff {
-  float hi, lo;
-};
-__device__ __forceinline__ ff two_sum(float a, float b) {
-  float s = a + b;
-  float bb = s - a;
-  float e = (a - (s - bb)) + (b - bb);
-  return {s, e};
+// The absolute index of a launch's first step: given by the host, in which
+// case one thread stores the next launch's (step_done), or read from the
+// device's counter, which another launch then advances (captured launches,
+// whose replays the host does not see).
+template <class P>
+__device__ __forceinline__ long long step_first(const P& p) {
+  return p.base >= 0 ? p.base : *p.step_base;
 }
-__device__ __forceinline__ ff fast_two_sum(float a, float b) {
-  float s = a + b;
-  float e = b - (s - a);
-  return {s, e};
-}
-__device__ __forceinline__ ff two_prod(float a, float b) {
-  const float p = a * b;
-  return {p, fmaf(a, b, -p)};
-}
-__device__ __forceinline__ ff ff_add(ff a, ff b) {
-  ff s = two_sum(a.hi, b.hi);
-  ff t = two_sum(a.lo, b.lo);
-  float e = s.lo + t.hi;
-  s = fast_two_sum(s.hi, e);
-  e = s.lo + t.lo;
-  return fast_two_sum(s.hi, e);
-}
-__device__ __forceinline__ ff ff_mul(ff a, ff b) {
-  float p = a.hi * b.hi;
-  float e = fmaf(a.hi, b.hi, -p);
-  e = fmaf(a.hi, b.lo, e);
-  e = fmaf(a.lo, b.hi, e);
-  return fast_two_sum(p, e);
-}
-__device__ __forceinline__ ff ff_mul_f(ff a, float b) {
-  float p = a.hi * b;
-  float e = fmaf(a.hi, b, -p);
-  e = fmaf(a.lo, b, e);
-  return fast_two_sum(p, e);
+template <class P>
+__device__ __forceinline__ void step_done(const P& p) {
+  if (p.base >= 0 && blockIdx.x == 0 && threadIdx.x == 0) *p.step_base = p.base + p.n_steps;
 }
 
 // d+ = m X - p d + r fe ;  X+ = X + d+, in FP64: four instructions at the

@@ -143,6 +143,7 @@ struct StepParams {
   int* flags;               // [0] barrier timeout, [1] non-finite state
   unsigned long long timeout_ticks;  // limit of a slab wait (100 MHz clock ticks)
   long long* step_base;     // absolute index of the next step (device)
+  long long base;           // the same where the host knows it, else -1
   float* y;                 // output, y[row * y_stride + s]; NULL = none
   long long y_stride;
   int n_steps;              // steps of this launch
@@ -253,7 +254,8 @@ struct SharedParams {
   float* y;
   long long y_stride;
   int n_steps;
-  const long long* step_base;
+  long long* step_base;
+  long long base;  // as in StepParams
   int* flags;
 };
 // The same with the tensor in registers (shared_class_kernel.hip), for tensors
@@ -281,7 +283,8 @@ struct ScParams {
   float* y;
   long long y_stride;
   int n_steps;
-  const long long* step_base;
+  long long* step_base;
+  long long base;  // as in StepParams
   int* flags;
 };
 
@@ -300,12 +303,6 @@ __host__ __device__ inline size_t shared_lds_bytes(int kt, int kc, int jt, int n
 constexpr int kLinWaves = 4;  // waves per closed-form workgroup
 constexpr int kLinCols = 64;  // samples per row of a wave's tile
 constexpr int kLinConv = 256;  // steps per wave of the window convolution
-
-// A float-float complex number: real and imaginary parts as (high, low)
-// FP32 pairs whose sum carries about 48 bits.
-struct FFc {
-  float rh, rl, ih, il;
-};
 
 // One mode's roots of z^2 - g z - p.  conj: z2 = conj(z1), only root 1 is
 // evaluated (its amplitude carries the factor 2); else both are real.

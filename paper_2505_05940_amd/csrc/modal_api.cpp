@@ -23,6 +23,8 @@
 
 namespace modal {
 hipError_t launch_step(const StepParams& P, int gm, int nw, int n_wg, size_t lds_bytes, hipStream_t s);
+hipError_t launch_reset(double* st, const double* st0, long long n, unsigned int* ctr, int n_ctr, int* dflags,
+                        int* hflags, long long* step, hipStream_t s);
 hipError_t launch_advance(long long* step_base, int n, hipStream_t s);
 hipError_t launch_ctr_fill(const InstDev* inst, int batch, const long long* step_base, unsigned int* ctr,
                            hipStream_t s);
@@ -44,10 +46,10 @@ hipError_t launch_shared(const SharedParams& P, int kt, int kc, int jt, int n_wg
 bool shared_class_shape(int ks, int rows, int& r_tile);
 hipError_t launch_shared_class(const ScParams& P, int ks, int r, int n_wg, hipStream_t s);
 hipError_t launch_row_sum(const float* rrec, int seg_len, int rows, double* acc, hipStream_t s);
-hipError_t launch_tf_response(const float2* coef, const int* mode_off, int batch, const FFc* z, int n_freq,
-                              FFc* H, hipStream_t s);
-hipError_t launch_tf_grad(const float2* coef, const int* mode_off, int batch, int max_modes, const FFc* z,
-                          int n_freq, const FFc* gH, float2* g_coef, hipStream_t s);
+hipError_t launch_tf_response(const double* coef, const int* mode_off, int batch, const double* omega, int n_freq,
+                              double2* H, hipStream_t s);
+hipError_t launch_tf_grad(const double* coef, const int* mode_off, int batch, int max_modes, const double* omega,
+                          int n_freq, const double2* gH, double* g_coef, hipStream_t s);
 hipError_t launch_sym_check(const float* H, int nin, int nt, int* bad, hipStream_t s);
 hipError_t launch_tensor_grad(const TGradJob* jobs, int n_jobs, int max_nin, int max_nt, const float* rec_x,
                               const float* urec, const float* trec, int mode_floats, int rows_total,
@@ -115,20 +117,6 @@ bool finite_all(const double* v, int n) {
 }
 
 int round4(int n) { return (n + 3) & ~3; }
-
-// float-float split of an FP64 value
-void split(double v, float& hi, float& lo) {
-  hi = (float)v;
-  lo = (float)(v - (double)hi);
-}
-
-// FP64 complex -> float-float complex
-FFc ffc(std::complex<double> v) {
-  FFc r;
-  split(v.real(), r.rh, r.rl);
-  split(v.imag(), r.ih, r.il);
-  return r;
-}
 
 struct Coef {
   double m, p, r;
@@ -247,10 +235,21 @@ struct modal_ctx {
   void* dMeta = nullptr;     // InstDev, UnitDev, wg_begin
   double* dCoef = nullptr;   // per-mode arrays: FP64 m, p, r, then FP32 c, lambda, b
   double* dState = nullptr;  // per-unit arrays X, d
+  double* dState0 = nullptr;  // and their initial values
   float* dPart = nullptr;
   unsigned int* dCtr = nullptr;  // arrival words, n_ctr of them (one per slab)
   int n_ctr = 0;
+  // status flags on the device and, for the kernels that only raise them (the
+  // streaming kernels' waits poll them too), from a context's second run on in
+  // pinned host memory, which modal_check reads without a copy (allocated
+  // then: a context that runs once, as in a fit, does not pay for it)
   int* dFlags = nullptr;
+  int* hFlags = nullptr;
+  bool dev_flags = false;  // a launch that may raise the device's is unchecked
+  long long n_runs = 0;
+  // a launch was recorded by a caller's capture: its replays advance the
+  // device's step counter unseen, so every later launch reads that one
+  bool captured = false;
   long long* dStep = nullptr;
   float* dE = nullptr;
   StepParams P{};
@@ -344,13 +343,14 @@ void free_ctx(modal_ctx* c) {
   if (!c) return;
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  void* ptrs[] = {c->dH,   c->dMeta, c->dCoef, c->dState, c->dPart, c->dCtr, c->dFlags,
+  void* ptrs[] = {c->dH,   c->dMeta, c->dCoef, c->dState, c->dPart, c->dCtr, c->dFlags, c->dState0,
                   c->dStep, c->dE,   c->dHd,   c->dCkpt,  c->dRec,  c->dAdj, c->dAcc,
                   c->dGPart, c->dGCtr, c->dShA, c->dShS2, c->dJmap, c->dRrec, c->dRacc,
                   c->dLinModes, c->dLinInit, c->dLinInst, c->dLinAmp, c->dLinZ, c->dLinS, c->dLinForced,
                   c->dLinH, c->dUrec, c->dTrec, c->dTJobs, c->dRecAll, c->dChip};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  if (c->hFlags) (void)hipHostFree(c->hFlags);  // (no launch is left: hipFree waits for the device)
   delete c;
 }
 
@@ -361,6 +361,27 @@ int dalloc(T** p, size_t bytes) {
   if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? MODAL_ENOMEM : MODAL_EHIP,
                                    std::string("hipMalloc: ") + hipGetErrorString(e));
   return MODAL_OK;
+}
+
+// The initial state on the device; every path with a state calls it once
+// state0 is known.
+int alloc_reset(modal_ctx* c, hipStream_t s) {
+  int r = dalloc(&c->dState0, sizeof(double) * c->state0.size());
+  if (r) return r;
+  HIP_TRY(hipMemcpyAsync(c->dState0, c->state0.data(), sizeof(double) * c->state0.size(), hipMemcpyHostToDevice, s));
+  return MODAL_OK;
+}
+
+// Whether the host knows the absolute index of the next step: not where a
+// launch is being captured, or once was.
+bool host_steps(modal_ctx* c, hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    st = hipStreamCaptureStatusActive;
+  }
+  if (st != hipStreamCaptureStatusNone) c->captured = true;
+  return !c->captured;
 }
 
 // Stored rows of a tensor row swept at once: as many as kSweepLoads float4
@@ -1355,6 +1376,7 @@ int init_shared_class(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup
   if (!r) r = dalloc(&c->dShS2, sizeof(float) * s2.size());
   if (!r) r = dalloc(&c->dCoef, sizeof(double) * coef.size() + sizeof(float) * cb.size());
   if (!r) r = dalloc(&c->dState, sizeof(double) * c->state0.size());
+  if (!r) r = alloc_reset(c, stream);
   c->n_ctr = d->batch;
   if (!r) r = dalloc(&c->dCtr, sizeof(unsigned int) * d->batch);
   if (!r) r = dalloc(&c->dFlags, sizeof(int) * 2);
@@ -1389,6 +1411,7 @@ int init_shared_class(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup
   P.b_ext = P.c_out + ncolk;
   P.e_ext = c->dE;
   P.step_base = c->dStep;
+  P.base = -1;
   P.flags = c->dFlags;
   return 1;
 }
@@ -1543,6 +1566,7 @@ int init_shared(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& gro
   if (!r) r = dalloc(&c->dShS2, sizeof(float) * s2.size());
   if (!r) r = dalloc(&c->dCoef, sizeof(double) * coef.size() + sizeof(float) * cb.size());
   if (!r) r = dalloc(&c->dState, sizeof(double) * c->state0.size());
+  if (!r) r = alloc_reset(c, stream);
   c->n_ctr = d->batch;
   if (!r) r = dalloc(&c->dCtr, sizeof(unsigned int) * d->batch);
   if (!r) r = dalloc(&c->dFlags, sizeof(int) * 2);
@@ -1577,6 +1601,7 @@ int init_shared(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup>& gro
   P.b_ext = P.c_out + ncolk;
   P.e_ext = c->dE;
   P.step_base = c->dStep;
+  P.base = -1;
   P.flags = c->dFlags;
   return MODAL_OK;
 }
@@ -2137,6 +2162,10 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     if (e_ != hipSuccess)                                                                 \
       return bail(fail(MODAL_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_)));   \
   } while (0)
+  {
+    int r = alloc_reset(c, stream);
+    if (r) return bail(r);
+  }
   HIP_TRY_C(hipMemsetAsync(c->dH, 0, sizeof(float) * (size_t)(h_floats + 64), stream));
   {
     int r = upload_tensors(c, d, inst, plans, stream);
@@ -2204,6 +2233,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   P.flags = c->dFlags;
   P.timeout_ticks = d->barrier_us > 0 ? 100ull * (unsigned long long)d->barrier_us : kBarrierTicks;
   P.step_base = c->dStep;
+  P.base = -1;
   P.red_floats = red_floats;
   P.mode_floats = mode_floats;
   P.res_stride = c->res_stride;
@@ -2224,11 +2254,8 @@ int modal_reset(modal_ctx* c, void* stream_) {
     c->steps = 0;
     return MODAL_OK;
   }
-  HIP_TRY(hipMemcpyAsync(c->dState, c->state0.data(), sizeof(double) * c->state0.size(),
-                         hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemsetAsync(c->dCtr, 0, sizeof(unsigned int) * c->n_ctr, s));
-  HIP_TRY(hipMemsetAsync(c->dFlags, 0, sizeof(int) * 2, s));
-  HIP_TRY(hipMemsetAsync(c->dStep, 0, sizeof(long long), s));
+  HIP_TRY(launch_reset(c->dState, c->dState0, (long long)c->state0.size(), c->dCtr, c->n_ctr, c->dFlags, c->hFlags,
+                       c->dStep, s));
   c->steps = 0;
   c->ckpt_broken = false;  // checkpoints of [0, ckpt_upto) stay valid
   c->ctr_stale = false;
@@ -2236,7 +2263,10 @@ int modal_reset(modal_ctx* c, void* stream_) {
 }
 
 // One launch of P.n_steps forward steps.
-static int launch_forward(modal_ctx* c, const StepParams& P, hipStream_t s) {
+static int launch_forward(modal_ctx* c, StepParams P, hipStream_t s) {
+  const bool streams = !c->wave_lanes && !c->chip_nt;
+  P.flags = streams || !c->hFlags ? c->dFlags : c->hFlags;
+  c->dev_flags |= P.flags == c->dFlags;
   if (c->wave_lanes)
     HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
   else if (c->chip_nt)
@@ -2248,22 +2278,35 @@ static int launch_forward(modal_ctx* c, const StepParams& P, hipStream_t s) {
 
 static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, hipStream_t s) {
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
+  const bool known = !(c->flags & MODAL_FLAG_GRAPH) && host_steps(c, s);
+  if (known && ++c->n_runs == 2 && !c->hFlags && (c->shared || c->wave_lanes || c->chip_nt)) {
+    HIP_TRY(hipHostMalloc((void**)&c->hFlags, 2 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent));
+    c->hFlags[0] = c->hFlags[1] = 0;
+  }
   for (int64_t done = 0; done < n_steps; done += chunk) {
     const int64_t k = std::min<int64_t>(chunk, n_steps - done);
+    const long long base = known ? c->steps + done : -1;
     if (c->sc_ks) {
       ScParams P = c->SC;
+      P.base = base;
+      P.flags = c->hFlags ? c->hFlags : c->dFlags;
+      c->dev_flags |= !c->hFlags;
       P.y = y + done;
       P.y_stride = y_stride;
       P.n_steps = (int)k;
       HIP_TRY(launch_shared_class(P, c->sc_ks, c->sc_rows, c->sc_wg, s));
     } else if (c->shared) {
       SharedParams P = c->SP;
+      P.flags = c->hFlags ? c->hFlags : c->dFlags;
+      c->dev_flags |= !c->hFlags;
+      P.base = base;
       P.y = y + done;
       P.y_stride = y_stride;
       P.n_steps = (int)k;
       HIP_TRY(launch_shared(P, c->sh_kt, c->sh_kc, c->sh_jt, c->n_wg, s));
     } else {
       StepParams P = c->P;
+      P.base = base;
       P.y = y + done;
       P.y_stride = y_stride;
       P.n_steps = (int)k;
@@ -2279,7 +2322,7 @@ static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride
       int r = launch_forward(c, P, s);
       if (r) return r;
     }
-    HIP_TRY(launch_advance(c->dStep, (int)k, s));
+    if (!known) HIP_TRY(launch_advance(c->dStep, (int)k, s));
   }
   return MODAL_OK;
 }
@@ -2288,8 +2331,15 @@ int modal_check(modal_ctx* c, void* stream_) {
   if (!c) return fail(MODAL_EINVAL, "ctx is NULL");
   hipStream_t s = (hipStream_t)stream_;
   int fl[2] = {0, 0};
-  HIP_TRY(hipMemcpyAsync(fl, c->dFlags, sizeof(fl), hipMemcpyDeviceToHost, s));
+  if (c->dev_flags) HIP_TRY(hipMemcpyAsync(fl, c->dFlags, sizeof(fl), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  if (c->hFlags) {
+    const volatile int* h = c->hFlags;
+    fl[0] |= h[0];
+    fl[1] |= h[1];
+  }
+  // (replays of captured launches come unseen)
+  if (!fl[0] && !fl[1] && !c->captured && !(c->flags & MODAL_FLAG_GRAPH)) c->dev_flags = false;
   if (fl[0]) return fail(MODAL_EHANG, "a per-instance step barrier timed out");
   if (fl[1]) return fail(MODAL_ENONFINITE, "a modal state became non-finite");
   return MODAL_OK;
@@ -2414,18 +2464,20 @@ int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride,
   // context's steps stand (a fill kernel, so a capturing caller records no
   // memset node)
   HIP_TRY(launch_ctr_fill(c->P.inst, c->batch, c->dStep, ctr, s));
+  const bool known = host_steps(c, s);
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
   for (int64_t done = 0; done < n_steps; done += chunk) {
     const int64_t k = std::min<int64_t>(chunk, n_steps - done);
     StepParams P = c->P;
     P.part = part;
     P.ctr = ctr;
+    P.base = known ? c->steps + done : -1;
     P.y = y + done;
     P.y_stride = y_stride;
     P.n_steps = (int)k;
     int r = launch_forward(c, P, s);
     if (r) return r;
-    HIP_TRY(launch_advance(c->dStep, (int)k, s));
+    if (!known) HIP_TRY(launch_advance(c->dStep, (int)k, s));
   }
   // no checkpoints were recorded: a gradient context's recorded checkpoints
   // stop at ckpt_upto, and a later modal_run past them marks them broken
@@ -2456,18 +2508,16 @@ int modal_set_tangent(modal_ctx* c, int32_t b, const float* Hd, void* stream_) {
 
 namespace {
 
-// Device copies of a transfer-function call's inputs as float-float pairs
-// (split from the host's FP64 values) and room for its outputs; freed when
-// the call returns.
+// One transfer-function call's device memory: its inputs, packed by the host
+// and copied at once, and room for its output; freed when the call returns.
 struct TfCall {
-  float2* coef = nullptr;
+  char* mem = nullptr;
+  double *coef = nullptr, *omega = nullptr, *out = nullptr;
+  double2* g = nullptr;
   int* off = nullptr;
-  FFc* z = nullptr;
-  FFc* out = nullptr;  // H, or dL/dH for the gradient
-  float2* g = nullptr;
+  std::vector<double> host;  // the packed inputs, alive until the call's last wait
   ~TfCall() {
-    for (void* p : {(void*)coef, (void*)off, (void*)z, (void*)out, (void*)g})
-      if (p) (void)hipFree(p);
+    if (mem) (void)hipFree(mem);
   }
 };
 
@@ -2479,21 +2529,28 @@ int tf_check(const int32_t* mode_off, int32_t batch, int32_t n_freq, int& modes)
   return MODAL_OK;
 }
 
+// gH: dL/dH, or NULL; n_out: doubles of output.
 int tf_upload(TfCall& t, const double* coef, const int32_t* mode_off, int32_t batch, const double* omega,
-              int32_t n_freq, int modes, hipStream_t s) {
-  std::vector<float2> cf(5 * (size_t)std::max(modes, 1));
-  for (size_t i = 0; i < 5 * (size_t)modes; ++i) split(coef[i], cf[i].x, cf[i].y);
-  std::vector<FFc> zf(n_freq);
-  for (int k = 0; k < n_freq; ++k) zf[k] = ffc(std::polar(1.0, omega[k]));
-  int r = dalloc(&t.coef, sizeof(float2) * cf.size());
-  if (!r) r = dalloc(&t.off, sizeof(int) * (batch + 1));
-  if (!r) r = dalloc(&t.z, sizeof(FFc) * n_freq);
-  if (!r) r = dalloc(&t.out, sizeof(FFc) * (size_t)batch * n_freq);
+              int32_t n_freq, int modes, const double* gH, size_t n_out, hipStream_t s) {
+  const size_t nc = 5 * (size_t)modes, ng = gH ? 2 * (size_t)batch * n_freq : 0;
+  // (the gradients start on a multiple of 16 bytes)
+  const size_t o_g = (nc + n_freq + 1) & ~(size_t)1, o_off = o_g + ng;
+  const size_t n_in = o_off + (size_t)(batch + 2) / 2, o_out = (n_in + 1) & ~(size_t)1;
+  std::vector<double>& h = t.host;
+  h.assign(n_in, 0.);
+  if (modes) std::memcpy(&h[0], coef, sizeof(double) * nc);
+  std::memcpy(&h[nc], omega, sizeof(double) * n_freq);
+  if (gH) std::memcpy(&h[o_g], gH, sizeof(double) * ng);
+  std::memcpy(&h[o_off], mode_off, sizeof(int) * (batch + 1));
+  int r = dalloc(&t.mem, sizeof(double) * (o_out + std::max<size_t>(n_out, 1)));
   if (r) return r;
-  HIP_TRY(hipMemcpyAsync(t.coef, cf.data(), sizeof(float2) * cf.size(), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(t.off, mode_off, sizeof(int) * (batch + 1), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(t.z, zf.data(), sizeof(FFc) * n_freq, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));  // the host vectors go out of scope
+  double* d = reinterpret_cast<double*>(t.mem);
+  t.coef = d;
+  t.omega = d + nc;
+  t.g = reinterpret_cast<double2*>(d + o_g);
+  t.off = reinterpret_cast<int*>(d + o_off);
+  t.out = d + o_out;
+  HIP_TRY(hipMemcpyAsync(d, h.data(), sizeof(double) * n_in, hipMemcpyHostToDevice, s));
   return MODAL_OK;
 }
 
@@ -2507,16 +2564,12 @@ int modal_tf_response(const double* coef, const int32_t* mode_off, int32_t batch
   if (r) return r;
   hipStream_t s = (hipStream_t)stream_;
   TfCall t;
-  r = tf_upload(t, coef, mode_off, batch, omega, n_freq, modes, s);
+  const size_t n = 2 * (size_t)batch * n_freq;
+  r = tf_upload(t, coef, mode_off, batch, omega, n_freq, modes, nullptr, n, s);
   if (r) return r;
-  HIP_TRY(launch_tf_response(t.coef, t.off, batch, t.z, n_freq, t.out, s));
-  std::vector<FFc> h((size_t)batch * n_freq);
-  HIP_TRY(hipMemcpyAsync(h.data(), t.out, sizeof(FFc) * h.size(), hipMemcpyDeviceToHost, s));
+  HIP_TRY(launch_tf_response(t.coef, t.off, batch, t.omega, n_freq, reinterpret_cast<double2*>(t.out), s));
+  HIP_TRY(hipMemcpyAsync(H, t.out, sizeof(double) * n, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  for (size_t i = 0; i < h.size(); ++i) {
-    H[2 * i] = (double)h[i].rh + (double)h[i].rl;
-    H[2 * i + 1] = (double)h[i].ih + (double)h[i].il;
-  }
   return MODAL_OK;
 }
 
@@ -2531,23 +2584,13 @@ int modal_tf_grad(const double* coef, const int32_t* mode_off, int32_t batch, in
     if (mode_off[b + 1] - mode_off[b] > max_modes) return fail(MODAL_EINVAL, "an instance has more than max_modes modes");
   hipStream_t s = (hipStream_t)stream_;
   TfCall t;
-  r = tf_upload(t, coef, mode_off, batch, omega, n_freq, modes, s);
+  r = tf_upload(t, coef, mode_off, batch, omega, n_freq, modes, dL_dH, 5 * (size_t)modes, s);
   if (r) return r;
-  std::vector<FFc> gh((size_t)batch * n_freq);
-  for (size_t i = 0; i < gh.size(); ++i) {
-    split(dL_dH[2 * i], gh[i].rh, gh[i].rl);
-    split(dL_dH[2 * i + 1], gh[i].ih, gh[i].il);
-  }
-  r = dalloc(&t.g, sizeof(float2) * 5 * (size_t)std::max(modes, 1));
-  if (r) return r;
-  HIP_TRY(hipMemcpyAsync(t.out, gh.data(), sizeof(FFc) * gh.size(), hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_tf_grad(t.coef, t.off, batch, max_modes, t.z, n_freq, t.out, t.g, s));
-  std::vector<float2> g(5 * (size_t)std::max(modes, 1));
-  HIP_TRY(hipMemcpyAsync(g.data(), t.g, sizeof(float2) * g.size(), hipMemcpyDeviceToHost, s));
+  HIP_TRY(launch_tf_grad(t.coef, t.off, batch, max_modes, t.omega, n_freq, t.g, t.out, s));
+  // the instances' ranges are contiguous
+  const size_t m0 = (size_t)mode_off[0], n = 5 * ((size_t)modes - m0);
+  if (n) HIP_TRY(hipMemcpyAsync(g_coef + 5 * m0, t.out + 5 * m0, sizeof(double) * n, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
-  for (int b = 0; b < batch; ++b)
-    for (int m = mode_off[b]; m < mode_off[b + 1]; ++m)
-      for (int j = 0; j < 5; ++j) g_coef[5 * (size_t)m + j] = (double)g[5 * (size_t)m + j].x + (double)g[5 * (size_t)m + j].y;
   return MODAL_OK;
 }
 
@@ -2793,7 +2836,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   G.state_floats = sf;
   G.part = c->dGPart;
   G.ctr = c->dGCtr;
-  G.flags = F.flags;
+  G.flags = c->dFlags;
   G.timeout_ticks = F.timeout_ticks;
   G.red_floats = (c->tangent ? 3 : 2) * c->red_floats;
   // on chip unless a tangent tensor is set; there the sums over the rows stay
@@ -2801,6 +2844,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   const bool on_chip = c->wave_lanes || (c->chip_nt && !c->tangent);
   const long long K_rev = on_chip && reuse_rec && !tens_on ? n_steps : K;
   const long long nrev = (n_steps + K_rev - 1) / K_rev;
+  c->dev_flags |= !on_chip;
   G.rrec = rows_on && !on_chip ? c->dRrec : nullptr;
   G.chip = c->dChip;
   G.racc = rows_on ? c->dRacc : nullptr;

@@ -77,7 +77,7 @@ __global__ void __launch_bounds__(kWave* kScWaves) shared_class_kernel(ScParams 
     xs[slot / 4][col][slot % 4] = (float)x[i];
   }
   __syncthreads();
-  const long long base = *P.step_base;
+  const long long base = step_first(P);
   bool bad = false;
   float e = base < sl.n_exc ? P.e_ext[sl.e_off + base] : 0.f;
   for (int s0 = 0; s0 < P.n_steps; s0 += kScChunk) {
@@ -157,7 +157,8 @@ __global__ void __launch_bounds__(kWave* kScWaves) shared_class_kernel(ScParams 
     P.x[o] = x[i];
     P.d[o] = d[i];
   }
-  if (__any(bad) && lane == 0) atomicOr(&P.flags[1], 1);
+  if (__any(bad) && lane == 0) P.flags[1] = 1;
+  step_done(P);
 }
 
 // Tiles with a kernel: KS K steps of the widest class (at most 4: 16 modes)

@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(kWave * kSharedWaves, (KT == 4 && JT == 2) ? 1
 #pragma unroll
   for (int j = 0; j < JT; ++j) sl[j] = P.slot[col0 + 16 * j + col16];
   __syncthreads();
-  const long long base = *P.step_base;
+  const long long base = step_first(P);
 
   for (int s = 0; s < P.n_steps; ++s) {
     const long long nabs = base + s;
@@ -206,9 +206,10 @@ __global__ void __launch_bounds__(kWave * kSharedWaves, (KT == 4 && JT == 2) ? 1
       const float yv = quad_sum(ypart[j]);
       if (quad == 0 && sl[j].out_row >= 0 && P.y) P.y[(long long)sl[j].out_row * P.y_stride + s] = yv;
     }
-    if (__any(bad) && lane == 0) atomicOr(&P.flags[1], 1);
+    if (__any(bad) && lane == 0) P.flags[1] = 1;
     wave_lds_sync();  // the new X is visible to every lane of the wave
   }
+  step_done(P);
 }
 
 // kt: 16-row tiles of the widest group (1..kSharedMaxKT); kc: 4-wide K

@@ -25,6 +25,8 @@
 // cross-lane reduction of V.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 #include "device_common.h"
 
@@ -522,7 +524,7 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
   float* red = L.red + wave * P.red_floats;
   const int u0 = P.wg_begin[blockIdx.x];
   const int u1 = P.wg_begin[blockIdx.x + 1];
-  const long long base = *P.step_base;
+  const long long base = step_first(P);
 
   auto refs = [&](const UnitDev& U, const InstDev& I) {
     ModeRefs M;
@@ -785,6 +787,23 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
     }
   }
   res_copy(false);
+  step_done(P);
+}
+
+// Puts a context back to its initial state: the state's n doubles, n_ctr
+// arrival words, both pairs of status flags (the device's and, if there is one, the host's) and
+// the step counter.
+__global__ void __launch_bounds__(256) reset_kernel(double* st, const double* st0, long long n, unsigned int* ctr,
+                                                    int n_ctr, int* dflags, int* hflags, long long* step) {
+  const long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x, di = (long long)gridDim.x * blockDim.x;
+  for (long long i = i0; i < n / 2; i += di)
+    reinterpret_cast<v2d*>(st)[i] = reinterpret_cast<const v2d*>(st0)[i];
+  for (long long i = i0; i < n_ctr; i += di) ctr[i] = 0u;
+  if (i0 < 2) {
+    dflags[i0] = 0;
+    if (hflags) hflags[i0] = 0;
+  }
+  if (i0 == 0) *step = 0;
 }
 
 __global__ void advance_kernel(long long* step_base, int n_steps) {
@@ -865,6 +884,14 @@ hipError_t launch_step(const StepParams& P, int gm, int nw, int n_wg, size_t lds
     if (gm <= 1) SL(1, 4, false); else if (gm <= 2) SL(2, 4, false); else SL(4, 4, false);
   }
 #undef SL
+  return hipGetLastError();
+}
+// n: even
+hipError_t launch_reset(double* st, const double* st0, long long n, unsigned int* ctr, int n_ctr, int* dflags,
+                        int* hflags, long long* step, hipStream_t s) {
+  const long long want = (std::max<long long>(n / 2, n_ctr) + 255) / 256;
+  hipLaunchKernelGGL(reset_kernel, dim3((unsigned)std::max<long long>(1, std::min<long long>(want, 2048))), dim3(256),
+                     0, s, st, st0, n, ctr, n_ctr, dflags, hflags, step);
   return hipGetLastError();
 }
 hipError_t launch_advance(long long* step_base, int n, hipStream_t s) {

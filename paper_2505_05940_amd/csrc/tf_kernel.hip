@@ -1,6 +1,5 @@
 // Transfer-function response of linear modal systems and its gradient
-// (gfx950, float-float arithmetic on FP32 pairs; the FP64 inputs are split
-// into pairs on the host and the results recombined there).
+// (gfx950, float-float arithmetic on FP32 pairs split from FP64 inputs).
 //
 // With impulse invariance each mode is the discrete system
 // b1 z / (z^2 + a1 z + a2) (paper: Sec. 3.2, transfer function); the linear
@@ -8,22 +7,66 @@
 // free output weights w, and compare the magnitude response on a Bark-scale
 // frequency grid with the target's spectral envelope:
 //   H_b(e^{i Omega_k}) = sum_{mu of b} w_mu (b1_mu z + b2_mu) / (z^2 + a1_mu z + a2_mu).
-// Coefficients per mode are (a1, a2, b1, b2, w), each a float-float pair;
-// z_k = e^{i Omega_k} comes from the host as a float-float complex number.
+// Coefficients per mode are (a1, a2, b1, b2, w).
 //
-// tf_response: one thread per (instance, frequency), modes read as uniform
-// loads.  tf_grad: one wave per mode, lanes over the frequencies, for
+// tf_response: 16 frequencies a workgroup, the modes of each spread over 16
+// lanes.  tf_grad: a workgroup per mode, threads over the frequencies, for
 // L = sum_k Re(conj(g_k) H_k): with N = b1 z + b2, D = z^2 + a1 z + a2,
 //   dH/dw = N/D, dH/db1 = w z/D, dH/db2 = w/D, dH/da1 = -w N z/D^2,
 //   dH/da2 = -w N/D^2.
+// A call is bound by its latency (one allocation, a copy each way, a launch):
+// 40 modes at 512 frequencies took 45 us with one thread a frequency and 22 us
+// with one wave a mode.
 #include <hip/hip_runtime.h>
 
-#include "device_common.h"
 #include "kernels.h"
 
 namespace modal {
 
 namespace {
+
+// Error-free transformations (Knuth's TwoSum, Dekker's Fast2Sum, and the
+// FMA-based exact product).  This file is compiled with -ffp-contract=off so
+// only the explicit fmaf calls fuse.
+struct ff {
+  float hi, lo;
+};
+__device__ __forceinline__ ff two_sum(float a, float b) {
+  float s = a + b;
+  float bb = s - a;
+  float e = (a - (s - bb)) + (b - bb);
+  return {s, e};
+}
+__device__ __forceinline__ ff fast_two_sum(float a, float b) {
+  float s = a + b;
+  float e = b - (s - a);
+  return {s, e};
+}
+__device__ __forceinline__ ff two_prod(float a, float b) {
+  const float p = a * b;
+  return {p, fmaf(a, b, -p)};
+}
+__device__ __forceinline__ ff ff_add(ff a, ff b) {
+  ff s = two_sum(a.hi, b.hi);
+  ff t = two_sum(a.lo, b.lo);
+  float e = s.lo + t.hi;
+  s = fast_two_sum(s.hi, e);
+  e = s.lo + t.lo;
+  return fast_two_sum(s.hi, e);
+}
+__device__ __forceinline__ ff ff_mul(ff a, ff b) {
+  float p = a.hi * b.hi;
+  float e = fmaf(a.hi, b.hi, -p);
+  e = fmaf(a.hi, b.lo, e);
+  e = fmaf(a.lo, b.hi, e);
+  return fast_two_sum(p, e);
+}
+__device__ __forceinline__ ff ff_mul_f(ff a, float b) {
+  float p = a.hi * b;
+  float e = fmaf(a.hi, b, -p);
+  e = fmaf(a.lo, b, e);
+  return fast_two_sum(p, e);
+}
 
 __device__ __forceinline__ ff fneg(ff a) { return {-a.hi, -a.lo}; }
 __device__ __forceinline__ ff fsub(ff a, ff b) { return ff_add(a, fneg(b)); }
@@ -53,96 +96,101 @@ __device__ __forceinline__ cx cinv(cx d) {
   const ff n = ff_add(ff_mul(d.re, d.re), ff_mul(d.im, d.im));
   return {fdiv(d.re, n), fdiv(fneg(d.im), n)};
 }
-__device__ __forceinline__ cx ld(const FFc& v) { return {{v.rh, v.rl}, {v.ih, v.il}}; }
-__device__ __forceinline__ ff ldf(const float2 v) { return {v.x, v.y}; }
-
+__device__ __forceinline__ ff split(double v) {
+  const float h = (float)v;
+  return {h, (float)(v - (double)h)};
+}
+__device__ __forceinline__ double join(ff v) { return (double)v.hi + (double)v.lo; }
+__device__ __forceinline__ cx point(double omega) {
+  double s, c;
+  sincos(omega, &s, &c);
+  return {split(c), split(s)};
+}
 // Re(conj(g) v)
 __device__ __forceinline__ ff re_dot(cx g, cx v) { return ff_add(ff_mul(g.re, v.re), ff_mul(g.im, v.im)); }
-
-__device__ __forceinline__ ff wave_sum_ff(ff v) {
+// sums over groups of W lanes
+template <int W>
+__device__ __forceinline__ ff lanes_sum(ff v) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = ff_add(v, {__shfl_xor(v.hi, o), __shfl_xor(v.lo, o)});
+  for (int o = 1; o < W; o *= 2) v = ff_add(v, {__shfl_xor(v.hi, o, W), __shfl_xor(v.lo, o, W)});
   return v;
 }
 
+constexpr int kTfFreqs = 16, kTfLanes = 16;  // frequencies per workgroup, lanes over modes
+constexpr int kTfThreads = 256;              // threads of a mode's gradient
+
 }  // namespace
 
-// coef [modes][5] float-float (a1, a2, b1, b2, w); z [n_freq]; H [batch][n_freq]
-__global__ void __launch_bounds__(64) tf_response_kernel(const float2* __restrict__ coef,
-                                                         const int* __restrict__ mode_off,
-                                                         const FFc* __restrict__ z, int n_freq,
-                                                         FFc* __restrict__ H) {
+__global__ void __launch_bounds__(kTfFreqs* kTfLanes) tf_response_kernel(const double* __restrict__ coef,
+                                                                         const int* __restrict__ mode_off,
+                                                                         const double* __restrict__ omega, int n_freq,
+                                                                         double2* __restrict__ H) {
+  const int k = blockIdx.x * kTfFreqs + threadIdx.x / kTfLanes, ml = threadIdx.x % kTfLanes;
   const int b = blockIdx.y;
-  const int k = blockIdx.x * 64 + threadIdx.x;
-  if (k >= n_freq) return;
-  const cx zk = ld(z[k]);
-  const cx z2 = cmul(zk, zk);
-  cx acc = {{0.f, 0.f}, {0.f, 0.f}};
-  for (int m = mode_off[b]; m < mode_off[b + 1]; ++m) {
-    const float2* p = coef + 5LL * m;
-    const ff a1 = ldf(p[0]), a2 = ldf(p[1]), b1 = ldf(p[2]), b2 = ldf(p[3]), w = ldf(p[4]);
-    const cx N = cadd(cscale(zk, b1), cx{b2, {0.f, 0.f}});
-    const cx D = cadd(z2, cadd(cscale(zk, a1), cx{a2, {0.f, 0.f}}));
-    acc = cadd(acc, cscale(cmul(N, cinv(D)), w));
+  const cx z = point(omega[min(k, n_freq - 1)]), z2 = cmul(z, z);
+  const ff zero = {0.f, 0.f};
+  cx acc = {zero, zero};
+  for (int m = mode_off[b] + ml; m < mode_off[b + 1]; m += kTfLanes) {
+    const double* c = coef + 5LL * m;
+    const cx N = cadd(cscale(z, split(c[2])), cx{split(c[3]), zero});
+    const cx D = cadd(z2, cadd(cscale(z, split(c[0])), cx{split(c[1]), zero}));
+    acc = cadd(acc, cscale(cmul(N, cinv(D)), split(c[4])));
   }
-  H[(long long)b * n_freq + k] = FFc{acc.re.hi, acc.re.lo, acc.im.hi, acc.im.lo};
+  acc = {lanes_sum<kTfLanes>(acc.re), lanes_sum<kTfLanes>(acc.im)};
+  if (ml == 0 && k < n_freq) H[(long long)b * n_freq + k] = make_double2(join(acc.re), join(acc.im));
 }
 
-// grid: (ceil(max_modes / 4), batch); 4 waves per block, wave = mode
-__global__ void __launch_bounds__(256) tf_grad_kernel(const float2* __restrict__ coef,
-                                                      const int* __restrict__ mode_off,
-                                                      const FFc* __restrict__ z, int n_freq,
-                                                      const FFc* __restrict__ gH,
-                                                      float2* __restrict__ g_coef) {
+__global__ void __launch_bounds__(kTfThreads) tf_grad_kernel(const double* __restrict__ coef,
+                                                             const int* __restrict__ mode_off,
+                                                             const double* __restrict__ omega, int n_freq,
+                                                             const double2* __restrict__ gH,
+                                                             double* __restrict__ g_coef) {
+  __shared__ float2 part[kTfThreads / kWave][5];
   const int b = blockIdx.y;
-  const int lane = threadIdx.x & 63;
-  const int m = mode_off[b] + blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int m = mode_off[b] + blockIdx.x;
   if (m >= mode_off[b + 1]) return;
-  const float2* p = coef + 5LL * m;
-  const ff a1 = ldf(p[0]), a2 = ldf(p[1]), b1 = ldf(p[2]), b2 = ldf(p[3]), w = ldf(p[4]);
-  ff ga1 = {0.f, 0.f}, ga2 = ga1, gb1 = ga1, gb2 = ga1, gw = ga1;
-  for (int k = lane; k < n_freq; k += 64) {
-    const cx zk = ld(z[k]);
-    const cx z2 = cmul(zk, zk);
-    const cx N = cadd(cscale(zk, b1), cx{b2, {0.f, 0.f}});
-    const cx D = cadd(z2, cadd(cscale(zk, a1), cx{a2, {0.f, 0.f}}));
-    const cx iD = cinv(D);
-    const cx ND = cmul(N, iD);    // N / D
-    const cx ND2 = cmul(ND, iD);  // N / D^2
-    const cx g = ld(gH[(long long)b * n_freq + k]);
-    gw = ff_add(gw, re_dot(g, ND));
-    gb1 = ff_add(gb1, ff_mul(w, re_dot(g, cmul(zk, iD))));
-    gb2 = ff_add(gb2, ff_mul(w, re_dot(g, iD)));
-    ga1 = fsub(ga1, ff_mul(w, re_dot(g, cmul(ND2, zk))));
-    ga2 = fsub(ga2, ff_mul(w, re_dot(g, ND2)));
+  const double* c = coef + 5LL * m;
+  const ff zero = {0.f, 0.f};
+  const ff a1 = split(c[0]), a2 = split(c[1]), b1 = split(c[2]), b2 = split(c[3]), w = split(c[4]);
+  ff g[5] = {zero, zero, zero, zero, zero};
+  for (int k = threadIdx.x; k < n_freq; k += kTfThreads) {
+    const cx z = point(omega[k]), z2 = cmul(z, z);
+    const cx N = cadd(cscale(z, b1), cx{b2, zero});
+    const cx iD = cinv(cadd(z2, cadd(cscale(z, a1), cx{a2, zero})));
+    const cx ND = cmul(N, iD), ND2 = cmul(ND, iD);
+    const double2 G2 = gH[(long long)b * n_freq + k];
+    const cx G = {split(G2.x), split(G2.y)};
+    g[0] = ff_add(g[0], fneg(ff_mul(re_dot(G, cmul(ND2, z)), w)));
+    g[1] = ff_add(g[1], fneg(ff_mul(re_dot(G, ND2), w)));
+    g[2] = ff_add(g[2], ff_mul(re_dot(G, cmul(iD, z)), w));
+    g[3] = ff_add(g[3], ff_mul(re_dot(G, iD), w));
+    g[4] = ff_add(g[4], re_dot(G, ND));
   }
-  ga1 = wave_sum_ff(ga1);
-  ga2 = wave_sum_ff(ga2);
-  gb1 = wave_sum_ff(gb1);
-  gb2 = wave_sum_ff(gb2);
-  gw = wave_sum_ff(gw);
-  if (lane == 0) {
-    float2* o = g_coef + 5LL * m;
-    o[0] = make_float2(ga1.hi, ga1.lo);
-    o[1] = make_float2(ga2.hi, ga2.lo);
-    o[2] = make_float2(gb1.hi, gb1.lo);
-    o[3] = make_float2(gb2.hi, gb2.lo);
-    o[4] = make_float2(gw.hi, gw.lo);
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const ff v = lanes_sum<kWave>(g[i]);
+    if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave][i] = make_float2(v.hi, v.lo);
+  }
+  __syncthreads();
+  if (threadIdx.x < 5) {
+    ff s = zero;
+    for (int v = 0; v < kTfThreads / kWave; ++v) s = ff_add(s, {part[v][threadIdx.x].x, part[v][threadIdx.x].y});
+    g_coef[5LL * m + threadIdx.x] = join(s);
   }
 }
 
-hipError_t launch_tf_response(const float2* coef, const int* mode_off, int batch, const FFc* z, int n_freq,
-                              FFc* H, hipStream_t s) {
-  hipLaunchKernelGGL(tf_response_kernel, dim3((n_freq + 63) / 64, batch), dim3(64), 0, s, coef, mode_off, z,
-                     n_freq, H);
+hipError_t launch_tf_response(const double* coef, const int* mode_off, int batch, const double* omega, int n_freq,
+                              double2* H, hipStream_t s) {
+  hipLaunchKernelGGL(tf_response_kernel, dim3((n_freq + kTfFreqs - 1) / kTfFreqs, batch), dim3(kTfFreqs * kTfLanes), 0,
+                     s, coef, mode_off, omega, n_freq, H);
   return hipGetLastError();
 }
 
-hipError_t launch_tf_grad(const float2* coef, const int* mode_off, int batch, int max_modes, const FFc* z,
-                          int n_freq, const FFc* gH, float2* g_coef, hipStream_t s) {
+hipError_t launch_tf_grad(const double* coef, const int* mode_off, int batch, int max_modes, const double* omega,
+                          int n_freq, const double2* gH, double* g_coef, hipStream_t s) {
   if (max_modes < 1) return hipSuccess;
-  hipLaunchKernelGGL(tf_grad_kernel, dim3((max_modes + 3) / 4, batch), dim3(256), 0, s, coef, mode_off, z, n_freq,
-                     gH, g_coef);
+  hipLaunchKernelGGL(tf_grad_kernel, dim3(max_modes, batch), dim3(kTfThreads), 0, s, coef, mode_off, omega, n_freq, gH,
+                     g_coef);
   return hipGetLastError();
 }
 

@@ -54,7 +54,7 @@ __global__ void __launch_bounds__(kWave) wave_step_kernel(StepParams P, int batc
     lam[i] = live && tension ? P.lam[mo] : 0.f;
     xh[i] = (float)x[i];
   }
-  const long long base = *P.step_base;
+  const long long base = step_first(P);
   auto chunk = [&](long long n0) {
     const long long t = n0 + sub;
     return t < I.n_exc ? P.e_ext[I.e_off + t] : 0.f;
@@ -129,7 +129,8 @@ __global__ void __launch_bounds__(kWave) wave_step_kernel(StepParams P, int batc
       P.d[U.state_off + k] = d[i];
     }
   }
-  if (__any(bad) && lane == 0) atomicOr(&P.flags[1], 1);
+  if (__any(bad) && lane == 0) P.flags[1] = 1;
+  step_done(P);
 }
 
 // Reverse sweep of a recorded segment, last step first (the recursion of
