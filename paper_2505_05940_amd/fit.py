@@ -32,8 +32,6 @@ function.
 from __future__ import annotations
 
 import math
-import os
-from concurrent.futures import ThreadPoolExecutor
 from dataclasses import dataclass, field
 
 import numpy as np
@@ -138,11 +136,12 @@ _CLASSES = {}
 def _classes(setup):
     """Parity classes of the setup's transverse modes (one object per setup,
     cached; the batch's instances share it)."""
-    if id(setup) not in _CLASSES:
+    known = _CLASSES.get(id(setup))
+    if known is None or known[0] is not setup.modes:
         if len(_CLASSES) > 256:
             _CLASSES.clear()
-        _CLASSES[id(setup)] = (setup, physics.mode_classes(setup.modes[0], setup.modes[1]))
-    return _CLASSES[id(setup)][1]
+        known = _CLASSES[id(setup)] = (setup.modes, physics.mode_classes(setup.modes[0], setup.modes[1]))
+    return known[1]
 
 
 def plate_instance_shared(setup: PlateSetup, theta):
@@ -160,6 +159,56 @@ def plate_instance_shared(setup: PlateSetup, theta):
     return dict(kind="vk", omega=omega, gamma=gamma, lam=lam, Ht=base_tensor(setup),
                 h_row_scale=pref / zeta2, x0=x0, xm1=x0.copy(), c=c, zeta2=zeta2,
                 mode_class=_classes(setup))
+
+
+def plate_instances_shared(setup: PlateSetup, thetas):
+    """``plate_instance_shared`` of a batch of parameter vectors [B, 5], its
+    per-mode arrays computed together; returns the instances with their
+    eigenvalues and angular frequencies [B, n_t]."""
+    th = np.asarray(thetas, float).reshape(-1, 5)
+    m, q, ai, bi = setup.modes
+    T0h, Dh, a, d1, d3 = (v[:, None] for v in th.T)
+    lam = _lam(m, q, a, setup.area)
+    omega = np.sqrt(Dh * lam ** 2 + T0h * lam)
+    gamma = d1 + d3 * lam
+    zeta2 = _lam(ai, bi, a, setup.area)
+    scale = np.sqrt(6.0 * (1.0 - setup.nu ** 2) * Dh / setup.h ** 2) / zeta2
+    x0, c = excitations(setup, th[:, 2])
+    Ht, cls = base_tensor(setup), _classes(setup)
+    insts = [dict(kind="vk", omega=omega[b], gamma=gamma[b], lam=lam[b], Ht=Ht, h_row_scale=scale[b], x0=x0[b],
+                  xm1=x0[b], c=c[b], zeta2=zeta2[b], mode_class=cls) for b in range(len(th))]
+    return insts, lam, omega
+
+
+def excitations(setup, aspects):
+    """Strike projections and pickup weights [len(aspects), n_t] of ``_excitation``
+    at many aspect ratios at once: the bump is zero outside a few cells around
+    the strike, so only that box of the grid is projected, for all of them in
+    one product (64 plates at two aspects each took 25 ms one by one)."""
+    m, q, _, _ = setup.modes
+    a = np.asarray(aspects, float)
+    Lx, Ly = np.sqrt(setup.area / a), np.sqrt(setup.area * a)
+    xc, yc, amp, rr = setup.strike
+    # sin(k pi (i + 1/2) / n) per axis: the midpoint projection in coordinates
+    # relative to the plate, the same at every aspect ratio
+    sines = [np.sin(np.outer(np.arange(1, int(k.max()) + 1), (np.arange(n) + 0.5) / n) * np.pi)
+             for k, n in zip((m, q), setup.proj_grid)]
+    half = rr * np.minimum(Lx, Ly)
+    d2, box = 0.0, []
+    for L, c, n in ((Lx, xc, setup.proj_grid[0]), (Ly, yc, setup.proj_grid[1])):
+        reach = float(np.max(half / L))
+        lo = max(0, int(np.floor((c - reach) * n - 0.5)))
+        hi = min(n, int(np.ceil((c + reach) * n + 0.5)) + 1)
+        box.append(slice(lo, hi))
+        x = (np.arange(lo, hi) + 0.5) * (L / n)[:, None] - (c * L)[:, None]
+        d2 = d2 + (x * x)[:, :, None] if len(box) == 1 else d2 + (x * x)[:, None, :]
+    r = np.sqrt(d2) / half[:, None, None]
+    w0 = np.where(r < 1.0, 0.5 * amp * (1.0 + np.cos(np.pi * np.minimum(r, 1.0))), 0.0)
+    T = sines[0][:, box[0]] @ w0 @ sines[1][:, box[1]].T
+    norm = (2.0 / np.sqrt(Lx * Ly)) * (Lx * Ly / (setup.proj_grid[0] * setup.proj_grid[1]))
+    x0 = T[:, m - 1, q - 1] * norm[:, None]
+    c = (2.0 / np.sqrt(Lx * Ly))[:, None] * (np.sin(m * np.pi * setup.out[0]) * np.sin(q * np.pi * setup.out[1]))
+    return x0, c
 
 
 def aspect_tangent(setup, inst, a):
@@ -197,6 +246,28 @@ def chain_rule(setup, theta, inst, g, h_rel=1e-6):
     return np.array([dT0, dD, da, dd1, dd3])
 
 
+def chain_rules(setup, th, lam, omega, g, h_rel=1e-6):
+    """dL/dtheta [B, 5] of a batch from modal_grad's per-instance lists:
+    ``chain_rule`` for all instances at once (lam, omega: [B, n_t])."""
+    m, q, ai, bi = setup.modes
+    T0h, Dh, a, d1, d3 = th.T
+    gw, gg, gc, grow = (np.stack(g[k]) for k in ("omega", "gamma", "c", "row"))
+    gx = np.stack(g["x0"]) + np.stack(g["xm1"])
+    A = a[:, None]
+    dlam = _dlam_da(m, q, A, setup.area)
+    kappa = -_dlam_da(ai, bi, A, setup.area) / _lam(ai, bi, A, setup.area)
+    gl = gw / (2 * omega)
+    dT0 = np.sum(gl * lam, 1)
+    dD = np.sum(gl * lam ** 2, 1) + np.asarray(g["scale"]) / Dh
+    da = (np.sum(gl * (2 * Dh[:, None] * lam + T0h[:, None]) * dlam, 1) + np.sum(gg * d3[:, None] * dlam, 1)
+          + np.sum(kappa * grow, 1))
+    eps = h_rel * a
+    x0, c = excitations(setup, np.concatenate([a + eps, a - eps]))
+    B = len(a)
+    da += (np.sum(gx * (x0[:B] - x0[B:]), 1) + np.sum(gc * (c[:B] - c[B:]), 1)) / (2 * eps)
+    return np.stack([dT0, dD, da, np.sum(gg, 1), np.sum(gg * lam, 1)], 1)
+
+
 class ModalFn(torch.autograd.Function):
     """y = simulate(theta) for a batch of parameter vectors (one plate each).
     forward: modal_init + modal_run; backward: modal_grad + chain rule."""
@@ -206,24 +277,19 @@ class ModalFn(torch.autograd.Function):
         th = theta.detach().double().cpu().numpy().reshape(-1, 5)
         # base tensor + row scales: no per-plate tensor build; the library
         # stores each plate's scaled copy for the gradient kernels
-        insts = [plate_instance_shared(setup, t) for t in th]
+        insts, lam, omega = plate_instances_shared(setup, th)
         sim = modal.Sim(insts, setup.fs, flags=modal.FLAG_GRAD)
         y = sim.run(n_steps).clone()
-        ctx.save = (sim, insts, th, setup, n_steps, ckpt)
+        ctx.save = (sim, th, lam, omega, setup, n_steps, ckpt)
         return y
 
     @staticmethod
     def backward(ctx, gy):
-        sim, insts, th, setup, n_steps, ckpt = ctx.save
+        sim, th, lam, omega, setup, n_steps, ckpt = ctx.save
         # the aspect derivative of the tensor is a per-row rescaling, taken
         # from the per-row gradients (no tangent tensor)
         g = sim.grad(n_steps, gy.contiguous().float(), ckpt_every=ckpt)
-        # the per-plate chain rules (each projects the strike at two aspects)
-        # run on host threads; numpy releases the interpreter lock in them
-        def one(b):
-            return chain_rule(setup, th[b], insts[b], {k: v[b] for k, v in g.items()})
-        with ThreadPoolExecutor(max_workers=max(1, min(16, len(insts), os.cpu_count() or 1))) as ex:
-            out = np.stack(list(ex.map(one, range(len(insts)))))
+        out = chain_rules(setup, th, lam, omega, g)
         sim.close()
         return torch.tensor(out, dtype=torch.float64).reshape(-1, 5), None, None, None
 
