@@ -309,7 +309,7 @@ __device__ void vk_rows2_range(const float* __restrict__ Hb, const float* __rest
 
 // Completes the rows vk_rows2_range left to several waves, after a workgroup
 // barrier: the row's eta, V.u, Vd.q and Vd.u are the sums of every sharing
-// wave's partials (in wave order); each sharing wave adds its partial vectors
+// wave's partials; each sharing wave adds its partial vectors
 // times them, and the wave that holds the row's first block (slot 1) writes
 // the row's records and its tangent term.  xv, xr: exchange words of all nw
 // waves (this wave's at 2 wave).
@@ -319,18 +319,23 @@ __device__ void vk_rows2_finish(const float* xv, const int* xr, int nw, int wave
                                 int G, int lane, float* rrow, float* teta, float* tw) {
   constexpr int NR = TAN ? 3 : 2;
   const int nc = ntp >> 2;
+  // the 2 nw <= 16 exchange slots, one a lane of each row of 16 lanes
+  const int i = lane & 15;
+  const bool in = i < 2 * nw;
+  const int ri = in ? xr[i] : -1;
+  const float4 xi = in ? make_float4(xv[i * kXchVals], xv[i * kXchVals + 1], xv[i * kXchVals + 2], xv[i * kXchVals + 3])
+                       : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
   for (int slot = 0; slot < 2; ++slot) {
     const int n = xr[2 * wave + slot];
+    const bool of = ri == n;
+    const float eta = group_sum<16>(of ? xi.x : 0.f), w = group_sum<16>(of ? xi.y : 0.f);
+    float etad = 0.f, vdu = 0.f;
+    if (TAN) {
+      etad = group_sum<16>(of ? xi.z : 0.f);
+      vdu = group_sum<16>(of ? xi.w : 0.f);
+    }
     if (n < 0) continue;
-    float eta = 0.f, w = 0.f, etad = 0.f, vdu = 0.f;
-    for (int i = 0; i < 2 * nw; ++i)
-      if (xr[i] == n) {
-        eta += xv[i * kXchVals];
-        w += xv[i * kXchVals + 1];
-        etad += xv[i * kXchVals + 2];
-        vdu += xv[i * kXchVals + 3];
-      }
     const float* dp = defer + slot * NR * ntp;
 #pragma unroll
     for (int g = 0; g < GM; ++g) {

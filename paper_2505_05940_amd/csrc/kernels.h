@@ -111,6 +111,13 @@ __host__ __device__ inline GradLds grad_lds(float* base) {
   return L;
 }
 
+// Most slabs of an instance that read each other's partial forces directly in
+// the latency kernel; with more, each sums a few modes for all (words read
+// grow with the square of the slabs: a lone 144/144 plate in 72 slabs steps
+// in 7.7 us directly and 6.4 so, a 200/200 in 200 slabs in 12.3 and 7.3,
+// a 128/128 in 128 slabs in 5.3 and 5.6).
+constexpr int kPairSlabs = 64;
+
 // Register layout of one instance on the on-chip path.  Lane p of every
 // wave stands for mode perm[p] (-1: none); modes may be grouped by parity
 // class (each class's lanes contiguous from a multiple of 4).  Wave w holds
@@ -140,6 +147,8 @@ struct StepParams {
   double *x, *d;
   float* part;              // partial forces of split instances
   unsigned int* ctr;        // arrival words of split instances' slabs (InstDev.ctr_off)
+  unsigned long long* pair; // latency kernel: words of step and partial force, as part
+  unsigned long long* pair2;  // and of step and force, [2][mode_floats]
   int* flags;               // [0] barrier timeout, [1] non-finite state
   unsigned long long timeout_ticks;  // limit of a slab wait (100 MHz clock ticks)
   long long* step_base;     // absolute index of the next step (device)

@@ -23,8 +23,12 @@
 
 namespace modal {
 hipError_t launch_step(const StepParams& P, int gm, int nw, int n_wg, size_t lds_bytes, hipStream_t s);
-hipError_t launch_reset(double* st, const double* st0, long long n, unsigned int* ctr, int n_ctr, int* dflags,
-                        int* hflags, long long* step, hipStream_t s);
+hipError_t launch_reset(double* st, const double* st0, long long n, unsigned int* ctr, int n_ctr,
+                        unsigned long long* pair, long long n_pair, int* dflags, int* hflags, long long* step,
+                        hipStream_t s);
+hipError_t launch_pair_fill(unsigned long long* pair, long long n, const long long* step_base, hipStream_t s);
+hipError_t launch_lat(const StepParams& P, int gm, int nw, int nb, int n_wg, size_t lds_bytes, hipStream_t s);
+hipError_t lat_occupancy(int* blocks_per_cu, int gm, int nw, int nb, size_t lds_bytes);
 hipError_t launch_advance(long long* step_base, int n, hipStream_t s);
 hipError_t launch_ctr_fill(const InstDev* inst, int batch, const long long* step_base, unsigned int* ctr,
                            hipStream_t s);
@@ -204,6 +208,14 @@ struct modal_ctx {
   int nw_stream = 4;  // waves and LDS of the streaming kernel, should the
   size_t lds_stream = 0;  // on-chip one be given up (set_tensor)
   int res_stride = 0;  // > 0: LDS-resident state (one unit per workgroup)
+  bool lat = false;    // such a plan of von Karman units only: the latency kernel,
+  int lat_nb = 0;      // with this many row blocks a wave in registers (0: streamed)
+  std::vector<UnitDev> lat_units;       // its units and instances (dLat: both on the device)
+  std::vector<InstDev> lat_inst;
+  char* dLat = nullptr;
+  unsigned long long* dPair = nullptr;  // its exchange words, n_pair of them, n_part for partial forces
+  long long n_part = 0;
+  long long n_pair = 0;
   // > 0: the on-chip kernels (one workgroup per instance, tensor in
   // registers), with chip_nt tensor columns per lane and chip_rows rows per
   // wave, and their register layouts (one ChipMap per instance, with the
@@ -343,7 +355,7 @@ void free_ctx(modal_ctx* c) {
   if (!c) return;
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  void* ptrs[] = {c->dH,   c->dMeta, c->dCoef, c->dState, c->dPart, c->dCtr, c->dFlags, c->dState0,
+  void* ptrs[] = {c->dPair, c->dLat, c->dH,   c->dMeta, c->dCoef, c->dState, c->dPart, c->dCtr, c->dFlags, c->dState0,
                   c->dStep, c->dE,   c->dHd,   c->dCkpt,  c->dRec,  c->dAdj, c->dAcc,
                   c->dGPart, c->dGCtr, c->dShA, c->dShS2, c->dJmap, c->dRrec, c->dRacc,
                   c->dLinModes, c->dLinInit, c->dLinInst, c->dLinAmp, c->dLinZ, c->dLinS, c->dLinForced,
@@ -483,6 +495,26 @@ constexpr int kLatencyMaxSplitBatch = 16;  // larger latency-bound batches keep 
 // 32.8 us against 38.4 and 47.0 us.
 constexpr double kLatencySlabBytes = 256.0 * 1024.0;
 constexpr double kLatencyBigTensor = 16.0 * 1048576.0;
+constexpr int kLatRegBlocks = 8;  // row blocks (4 KB) of a wave that the latency kernel keeps in registers
+
+// Slabs of a split instance whose rows, of nblk blocks each, the latency
+// kernel keeps in registers (0: more than `cap`): of two rows, so that four
+// waves share a row's reduction, or more where that is more slabs than read
+// each other's forces directly; beyond those the fewest.  Lone sine plates in
+// slabs of one, two, four rows and as many as fit, us a step: 80/80 5.3, 4.1,
+// 3.7, 4.8; 100/100 5.6, 4.3, 4.9, 6.0; 128/128 5.6, 4.3, 5.0, 5.0; 160/160
+// 6.3, 6.8 (two fit).
+int lat_slabs(int rows, int nblk, int cap) {
+  const int most = 8 * kLatRegBlocks / nblk;
+  if (most < 1) return 0;
+  int S = (rows + most - 1) / most;
+  for (int m = std::min(2, most); m <= most; ++m)
+    if ((rows + m - 1) / m <= kPairSlabs) {
+      S = (rows + m - 1) / m;
+      break;
+    }
+  return S <= cap ? S : 0;
+}
 
 // Per-step cost of the exchange and barrier of one slab of a split instance,
 // in streamed-byte units (publishing its partial force, arrival, wait and
@@ -1702,6 +1734,58 @@ int modal_tune_key(const modal_desc* d, char* out, int32_t len) {
   return MODAL_OK;
 }
 
+// The latency kernel's own units, one a workgroup: the plan's instances of von
+// Karman kind, whole or in slabs (the plan's, or more that keep their rows in
+// registers).  Every slab starts a launch from the state that the instance's
+// first unit holds, and the first slab writes it back: no slab can end its
+// first step before all have begun theirs.  The reverse sweep keeps the plan's
+// slabs.
+static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::vector<int>& nslab,
+                    const std::vector<int>& qs_of, size_t lds, int cus) {
+  const int batch = (int)inst.size();
+  for (const InstDev& I : inst)
+    if (I.kind != KIND_VK) return MODAL_OK;
+  auto fits = [&](int nb, size_t n) {
+    int o = 0;
+    if (lat_occupancy(&o, c->gm, c->nw, nb, lds) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    return (size_t)o * cus >= n;
+  };
+  for (int regs = c->gm == 1 && c->nw == 8 ? 1 : 0; regs >= 0; --regs) {
+    c->lat_units.clear();
+    c->lat_inst = inst;
+    c->n_part = 0;
+    int share = 0;  // most blocks of a wave
+    for (int b = 0; b < batch; ++b) {
+      InstDev& I = c->lat_inst[b];
+      const int rows = I.nin, nblk = (I.nt + qs_of[b] - 1) / qs_of[b];
+      int S = std::max(1, nslab[b]);
+      if (regs && S > 1 && !I.blk) S = std::max(S, lat_slabs(rows, nblk, cus / batch));
+      I.nslab = S;
+      I.part_off = c->n_part;
+      if (S > 1) c->n_part += 2LL * S * I.ntp;
+      for (int sl = 0; sl < S; ++sl) {
+        UnitDev U{};
+        U.inst = b;
+        U.row0 = (int)((long long)rows * sl / S);
+        U.row1 = (int)((long long)rows * (sl + 1) / S);
+        U.slab = sl;
+        U.state_off = c->unit_state_of_inst[b];
+        U.qs = qs_of[b];
+        c->lat_units.push_back(U);
+        share = std::max(share, I.blk ? kLatRegBlocks + 1 : ((U.row1 - U.row0) * nblk + 7) / 8);
+      }
+    }
+    c->lat_nb = regs ? (share <= 4 ? 4 : 8) : 0;
+    if (regs && share > kLatRegBlocks) continue;
+    c->lat = fits(c->lat_nb, c->lat_units.size());
+    if (c->lat) break;
+  }
+  return MODAL_OK;
+}
+
 int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   if (!out) return fail(MODAL_EINVAL, "out is NULL");
   *out = nullptr;
@@ -2081,6 +2165,11 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     if (S > 0 && o >= 1 && (long long)o * prop.multiProcessorCount >= n_wg) {
       c->res_stride = S;
       c->lds_bytes = lb;
+      int r = plan_lat(c, inst, nslab, qs_of, lb, prop.multiProcessorCount);
+      if (r) {
+        free_ctx(c);
+        return r;
+      }
     }
   }
   c->state_floats = state_floats;
@@ -2146,6 +2235,11 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   ALLOC(c->dState, sizeof(double) * c->state0.size());
   ALLOC(c->dPart, sizeof(float) * (size_t)(part_floats + 64));
   ALLOC(c->dCtr, sizeof(unsigned int) * n_ctr);
+  if (c->lat) {
+    c->n_pair = c->n_part ? c->n_part + 2LL * mode_floats : 0;
+    ALLOC(c->dLat, sizeof(InstDev) * d->batch + sizeof(UnitDev) * c->lat_units.size());
+    ALLOC(c->dPair, sizeof(unsigned long long) * (size_t)(c->n_pair + 1));
+  }
   ALLOC(c->dFlags, sizeof(int) * (2 + 2 * d->batch));
   ALLOC(c->dStep, sizeof(long long));
   ALLOC(c->dE, sizeof(float) * (size_t)(e_floats + 1));
@@ -2185,6 +2279,18 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   UnitDev* dUnit = (UnitDev*)(meta + sizeof(InstDev) * d->batch);
   int* dWg = (int*)(meta + sizeof(InstDev) * d->batch + sizeof(UnitDev) * udev.size());
   HIP_TRY_C(hipMemcpyAsync(dInst, inst.data(), sizeof(InstDev) * d->batch, hipMemcpyHostToDevice, stream));
+  if (c->lat) {
+    for (int b = 0; b < d->batch; ++b) {  // what the plan has filled in since
+      const int ns = c->lat_inst[b].nslab;
+      const long long po = c->lat_inst[b].part_off;
+      c->lat_inst[b] = inst[b];
+      c->lat_inst[b].nslab = ns;
+      c->lat_inst[b].part_off = po;
+    }
+    HIP_TRY_C(hipMemcpyAsync(c->dLat, c->lat_inst.data(), sizeof(InstDev) * d->batch, hipMemcpyHostToDevice, stream));
+    HIP_TRY_C(hipMemcpyAsync(c->dLat + sizeof(InstDev) * d->batch, c->lat_units.data(),
+                             sizeof(UnitDev) * c->lat_units.size(), hipMemcpyHostToDevice, stream));
+  }
   HIP_TRY_C(hipMemcpyAsync(dUnit, udev.data(), sizeof(UnitDev) * udev.size(), hipMemcpyHostToDevice, stream));
   HIP_TRY_C(hipMemcpyAsync(dWg, wg_begin.data(), sizeof(int) * (n_wg + 1), hipMemcpyHostToDevice, stream));
   HIP_TRY_C(hipMemcpyAsync(c->dCoef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice, stream));
@@ -2230,6 +2336,8 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   P.d = P.x + state_floats;
   P.part = c->dPart;
   P.ctr = c->dCtr;
+  P.pair = c->dPair;
+  P.pair2 = c->dPair + c->n_part;
   P.flags = c->dFlags;
   P.timeout_ticks = d->barrier_us > 0 ? 100ull * (unsigned long long)d->barrier_us : kBarrierTicks;
   P.step_base = c->dStep;
@@ -2254,8 +2362,8 @@ int modal_reset(modal_ctx* c, void* stream_) {
     c->steps = 0;
     return MODAL_OK;
   }
-  HIP_TRY(launch_reset(c->dState, c->dState0, (long long)c->state0.size(), c->dCtr, c->n_ctr, c->dFlags, c->hFlags,
-                       c->dStep, s));
+  HIP_TRY(launch_reset(c->dState, c->dState0, (long long)c->state0.size(), c->dCtr, c->n_ctr, c->dPair, c->n_pair,
+                       c->dFlags, c->hFlags, c->dStep, s));
   c->steps = 0;
   c->ckpt_broken = false;  // checkpoints of [0, ckpt_upto) stay valid
   c->ctr_stale = false;
@@ -2271,7 +2379,11 @@ static int launch_forward(modal_ctx* c, StepParams P, hipStream_t s) {
     HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
   else if (c->chip_nt)
     HIP_TRY(launch_chip(P, c->chip_nt, c->chip_rows, c->batch, s));
-  else
+  else if (c->lat) {
+    P.inst = (const InstDev*)c->dLat;
+    P.unit = (const UnitDev*)(c->dLat + sizeof(InstDev) * c->batch);
+    HIP_TRY(launch_lat(P, c->gm, c->nw, c->lat_nb, (int)c->lat_units.size(), c->lds_bytes, s));
+  } else
     HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
   return MODAL_OK;
 }
@@ -2399,6 +2511,7 @@ int modal_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* s
   }
   if (c->ctr_stale) {
     HIP_TRY(launch_ctr_fill(c->P.inst, c->batch, c->dStep, c->dCtr, s));
+    if (c->n_pair) HIP_TRY(launch_pair_fill(c->dPair, c->n_pair, c->dStep, s));
     c->ctr_stale = false;
   }
   if (c->flags & MODAL_FLAG_GRAPH) {
@@ -2464,6 +2577,7 @@ int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride,
   // context's steps stand (a fill kernel, so a capturing caller records no
   // memset node)
   HIP_TRY(launch_ctr_fill(c->P.inst, c->batch, c->dStep, ctr, s));
+  if (c->n_pair) HIP_TRY(launch_pair_fill(c->dPair, c->n_pair, c->dStep, s));
   const bool known = host_steps(c, s);
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
   for (int64_t done = 0; done < n_steps; done += chunk) {
@@ -2860,6 +2974,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
     } else {
       HIP_TRY(launch_restore(c->dCkpt, seg, mf, F.inst, F.unit, c->n_units, c->dState, sf, c->dStep, s0,
                              c->dCtr, s));
+      if (c->n_pair) HIP_TRY(launch_pair_fill(c->dPair, c->n_pair, c->dStep, s));
       StepParams P = c->P;
       P.y = nullptr;
       P.rec_x = c->dRec;

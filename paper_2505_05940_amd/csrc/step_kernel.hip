@@ -252,20 +252,23 @@ __device__ void vk_rows_range(const float* __restrict__ Hb, int nt, int ntp, int
 
 // Completes the rows that vk_rows_range left to several waves, after a
 // workgroup barrier: eta_n is the sum of the partials of every wave that
-// holds row n (in wave order), and each of those waves adds eta_n times its
+// holds row n, and each of those waves adds eta_n times its
 // partial V_n.  xv, xr: the exchange words of all nw waves (this wave's at
 // 2 wave).
 template <int GM>
 __device__ void vk_rows_finish(const float* xv, const int* xr, int nw, int wave, int ntp,
                                const float* defer, float4 (&Fa)[GM], int G, int lane) {
   const int nc = ntp >> 2;
+  // the 2 nw <= 16 words, one a lane of each row of 16 lanes (read in turn by
+  // every lane they cost 1 us of a 100/100 plate's step)
+  const int i = lane & 15;
+  const int ri = i < 2 * nw ? xr[i] : -1;
+  const float vi = i < 2 * nw ? xv[i] : 0.f;
 #pragma unroll
   for (int slot = 0; slot < 2; ++slot) {
     const int n = xr[2 * wave + slot];
+    const float eta = group_sum<16>(ri == n ? vi : 0.f);
     if (n < 0) continue;
-    float eta = 0.f;
-    for (int i = 0; i < 2 * nw; ++i)
-      if (xr[i] == n) eta += xv[i];
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
       const int k4 = lane + kWave * g;
@@ -790,15 +793,376 @@ __global__ void __launch_bounds__(kWave * NW) step_kernel(StepParams P) {
   step_done(P);
 }
 
+// The shared row blocks of vk_rows_range, held in registers for the launch: at
+// most NB blocks of 4 KB a wave.
+template <int NB>
+struct RowRegs {
+  float4 h[NB][kSweepLoads];
+  __device__ __forceinline__ void load(const float* __restrict__ Hb, int nt, int ntp, int qs, int row0, int t0, int t1,
+                                       int lane) {
+    const int nblk = (nt + qs - 1) / qs;
+    const int blk_bytes = 4 * qs * ntp, last_bytes = 4 * (nt - (nblk - 1) * qs) * ntp;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int t = min(t0 + i, t1 - 1), b = t % nblk;
+      const v4i r = buf_rsrc(Hb + (long long)(row0 + t / nblk) * nt * ntp + (long long)b * qs * ntp,
+                             t0 + i < t1 ? (b == nblk - 1 ? last_bytes : blk_bytes) : 0);
+#pragma unroll
+      for (int j = 0; j < kSweepLoads; ++j) h[i][j] = buf_ld4<kKeep>(r, 16 * (lane + kWave * j));
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < kSweepLoads; ++j)
+        asm volatile("" : "+v"(h[i][j].x), "+v"(h[i][j].y), "+v"(h[i][j].z), "+v"(h[i][j].w));
+  }
+  // vk_rows_range on them
+  __device__ __forceinline__ void sweep(int nt, int ntp, int qs, int row0, int t0, int t1, const float* Xs, float* red,
+                                        float4& Fa, int lane, float* defer, float* xv, int* xr) const {
+    constexpr int J = kSweepLoads;
+    if (lane == 0) {
+      xr[0] = -1;
+      xr[1] = -1;
+    }
+    if (t1 <= t0) return;
+    const int nc = ntp >> 2, qsnc = qs * nc, nblk = (nt + qs - 1) / qs;
+    int sub[J];
+    float4 acc[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int v = lane + kWave * j;
+      sub[j] = v < qsnc ? v / nc : 0;
+      acc[j] = f4(0.f);
+    }
+    int n = row0 + t0 / nblk, b = t0 % nblk, bfirst = b;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (t0 + i >= t1) continue;
+      const int q0 = b * qs;
+#pragma unroll
+      for (int j = 0; j < J; ++j) acc[j] = fma4(h[i][j], Xs[min(q0 + sub[j], nt - 1)], acc[j]);
+      if (++b < nblk && t0 + i + 1 < t1) continue;
+      float* rb = red + (n & 1) * qs * ntp;
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (lane + kWave * j < qsnc) st4(rb + 4 * (lane + kWave * j), acc[j]);
+      wave_lds_sync();
+      float4 V = f4(0.f);
+      float eta = 0.f;
+      if (lane < nc) {
+        V = sum_strided4(rb + 4 * lane, qs, ntp);
+        eta = dot4(V, ld4(Xs + 4 * lane));
+      }
+      eta = wave_sum(eta);
+      if (bfirst == 0 && b == nblk) {
+        Fa = fma4(V, eta, Fa);
+      } else {
+        const int slot = bfirst > 0 ? 0 : 1;
+        if (lane < nc) st4(defer + slot * ntp + 4 * lane, V);
+        if (lane == 0) {
+          xv[slot] = eta;
+          xr[slot] = n;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < J; ++j) acc[j] = f4(0.f);
+      b = 0;
+      bfirst = 0;
+      ++n;
+    }
+  }
+};
+
+// ------------------------------------------------------------- latency kernel
+// The step of a plan whose every workgroup owns one von Karman unit for the
+// whole launch: a whole instance, or a slab of a split one.  Such a plan is
+// bound by the chain of one step, not by the tensor's bytes, so the chain is
+// what this kernel shortens against step_kernel:
+//   - a thread owns a mode (or MP), with its state and coefficients in
+//     registers, instead of one wave owning four modes a lane in LDS: the sums
+//     over the waves' partial forces, the update and q^n's FP32 copy are one
+//     pass of all threads;
+//   - slabs exchange their partial forces as 8-byte words of value and step
+//     number, each stored and read whole (agent-scope atomics): what was
+//     stores, a wait for them, an arrival word, a poll of all words and then
+//     the reads is one store and one read, polled until its step is there
+//     (every wave reads every NW-th slab, eight words a lane in flight; twelve
+//     or sixteen measured slower); beyond kPairSlabs slabs each one sums a few
+//     modes' words for all and publishes the sums, two such trips in all;
+//   - the rows stay in registers (NB blocks of 4 KB a wave), where the slabs
+//     are cut so that they fit: a 16 MB tensor is then held by 80 CUs, one of
+//     32 MB by 200, and no step reads it;
+//   - the output sample and the records are written while the words travel.
+// Words of step n live in the half n % 2 of the region: a workgroup can only
+// store step n + 2 after it has read every slab's step n + 1, which each slab
+// stores after it has read step n.  A word of an older run never matches: a
+// reset and a restore clear them to a step that is past.
+// Lone sine plates, us a step in step_kernel and here: 66/66 10.0, 3.8;
+// 100/100 8.0, 4.3; 128/128 10.2, 4.3; 160/160 13.3, 6.6; 200/200 12.0, 7.3.
+// 100/100 without the rows in registers 5.3.  What is left is the exchange
+// (about 2 us, two of them at 200 slabs), the reductions of a row through LDS
+// and three barriers.
+__device__ __forceinline__ void put_word(unsigned long long* p, unsigned int tag, float v) {
+  __hip_atomic_store(p, ((unsigned long long)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long get_word(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int GM, int NW, int NB>
+__global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
+  extern __shared__ float4 lds4[];
+  constexpr int NT = kWave * NW, MP = (4 * kWave * GM + NT - 1) / NT;
+  StepLds L = step_lds(reinterpret_cast<float*>(lds4), NW, P.red_floats);
+  float* Xs = L.xs;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  float* red = L.red + wave * P.red_floats;
+  const UnitDev U = P.unit[blockIdx.x];
+  const InstDev I = P.inst[U.inst];
+  const int ntp = I.ntp, nc = ntp >> 2, G = (nc + kWave - 1) / kWave;
+  const long long base = step_first(P);
+  // after the reduction regions: every wave's sum over its slabs, and its
+  // share of the output sample
+  float* sums = L.res;
+  float* ysum = L.res + NW * P.res_stride;
+  double x[MP], d[MP], m[MP], p[MP], r[MP];
+  float bk[MP], ck[MP];
+#pragma unroll
+  for (int i = 0; i < MP; ++i) {
+    const int k = min(tid + NT * i, ntp - 1);
+    x[i] = P.x[U.state_off + k];
+    d[i] = P.d[U.state_off + k];
+    m[i] = P.m[I.mode_off + k];
+    p[i] = P.p[I.mode_off + k];
+    r[i] = P.r[I.mode_off + k];
+    bk[i] = P.b_ext[I.mode_off + k];
+    ck[i] = P.c_out[I.mode_off + k];
+  }
+  const int R = U.row1 - U.row0, nblk = (I.nt + U.qs - 1) / U.qs, T = R * nblk;
+  const int tw0 = (T * wave) / NW, tw1 = (T * (wave + 1)) / NW;  // the wave's share of the unit's blocks
+  const bool shared_rows = NB > 0 || (!I.blk && 2 * R <= NW);
+  bool cut = false;  // a wave boundary inside a row
+  for (int w = 1; w < NW; ++w) cut |= ((T * w) / NW) % nblk != 0;
+  float* xv = L.xch;
+  int* xr = reinterpret_cast<int*>(L.xch + 2 * NW);
+  float* defer = red + 2 * U.qs * ntp;
+  RowRegs<NB == 0 ? 1 : NB> H;
+  if (NB > 0) H.load(P.H + I.h_off, I.nt, ntp, U.qs, U.row0, tw0, tw1, lane);
+  if (tid == 0) L.flag[0] = 0;
+  bool bad = false;
+  int s = 0;
+  for (; s < P.n_steps; ++s) {
+    const long long n = base + s;
+    float e = 0.f;
+    if (n < I.n_exc) e = P.e_ext[I.e_off + n];
+#pragma unroll
+    for (int i = 0; i < MP; ++i)
+      if (tid + NT * i < ntp) Xs[tid + NT * i] = (float)x[i];
+    __syncthreads();
+    // ---- the unit's rows, as in step_kernel
+    float4 Fa[GM];
+#pragma unroll
+    for (int g = 0; g < GM; ++g) Fa[g] = f4(0.f);
+    if (shared_rows) {
+      if constexpr (NB > 0)
+        H.sweep(I.nt, ntp, U.qs, U.row0, tw0, tw1, Xs, red, Fa[0], lane, defer, xv + 2 * wave, xr + 2 * wave);
+      else
+        vk_rows_range<GM, (NW == 8 && GM <= 2) ? 3 : 2, kKeep>(P.H + I.h_off, I.nt, ntp, U.qs, U.row0, tw0, tw1, Xs,
+                                                               red, Fa, G, lane, defer, xv + 2 * wave, xr + 2 * wave);
+      if (cut) {
+        __syncthreads();  // every wave's partial eta_n of the rows it shares
+        vk_rows_finish<GM>(xv, xr, NW, wave, ntp, defer, Fa, G, lane);
+      }
+    } else {
+      const int r0 = U.row0 + (R * wave) / NW, r1 = U.row0 + (R * (wave + 1)) / NW;
+      if (I.blk)
+        vk_rows_blk<GM>(P.H + I.h_off, P.jmap + I.jmap_off, I, r0, r1, Xs, red, Fa, G, lane);
+      else
+        vk_rows<GM, (NW == 8 && GM <= 2) ? 3 : 2, kKeep>(P.H + I.h_off, I.nt, ntp, U.qs, r0, r1, Xs, red, Fa, G,
+                                                         lane);
+    }
+#pragma unroll
+    for (int g = 0; g < GM; ++g) {
+      const int k4 = lane + kWave * g;
+      if (g < G && k4 < nc) st4(red + 4 * k4, Fa[g]);
+    }
+    __syncthreads();
+    // ---- the unit's force, published
+    const int half = (int)(n & 1);
+    unsigned long long* words = P.pair + I.part_off + half * (long long)I.nslab * ntp;
+    const unsigned int tag = (unsigned int)(n + 1);
+    const bool owners = I.nslab > kPairSlabs;
+    float f[MP];
+#pragma unroll
+    for (int i = 0; i < MP; ++i) {
+      const int k = tid + NT * i;
+      f[i] = 0.f;
+      if (k < ntp) {
+        for (int w = 0; w < NW; ++w) f[i] += L.red[w * P.red_floats + k];
+        if (I.nslab > 1) put_word(words + (owners ? k * I.nslab + U.slab : U.slab * ntp + k), tag, f[i]);
+      }
+    }
+    // ---- output and records of this step's state
+    if (U.slab == 0) {
+      float yp = 0.f;
+#pragma unroll
+      for (int i = 0; i < MP; ++i) {
+        const int k = tid + NT * i;
+        if (k >= ntp) continue;
+        yp = fmaf(ck[i], (float)x[i], yp);
+        if (P.ckpt && n % P.ckpt_every == 0) {
+          double* cp = P.ckpt + (n / P.ckpt_every) * 2LL * P.mode_floats + I.mode_off;
+          cp[k] = x[i];
+          cp[P.mode_floats + k] = d[i];
+        }
+        if (P.rec_x) {
+          const long long ro = (n - P.rec_base) * P.mode_floats + I.mode_off + k;
+          P.rec_x[ro] = (float)x[i];
+          P.rec_d[ro] = (float)d[i];
+        }
+      }
+      yp = wave_sum(yp);
+      if (lane == 0) ysum[wave] = yp;
+    }
+    // ---- every slab's force
+    if (I.nslab > 1) {
+      const unsigned long long t0 = wall_clock64();
+      bool ok = true;
+      // `here`: whether this wave's words have come; else whether to go on
+      auto again = [&](bool here) {
+        if (__all(here)) return false;
+        if (wall_clock64() - t0 > P.timeout_ticks)
+          __hip_atomic_store(&P.flags[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ok = __hip_atomic_load(&P.flags[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+        return ok;
+      };
+      if (owners) {
+        // each slab sums all slabs' words of its own few modes and publishes
+        // the sums, which every slab then reads
+        constexpr int LB = 4;  // 64-slab groups in flight
+        unsigned long long* total = P.pair2 + half * P.mode_floats + I.mode_off;
+        const int seg = (ntp + I.nslab - 1) / I.nslab;
+        const int k1 = min(ntp, (U.slab + 1) * seg);
+        for (int k = U.slab * seg + wave; k < k1 && ok; k += NW) {
+          float a = 0.f;
+          for (int t = lane; t - lane < I.nslab && ok; t += LB * kWave) {
+            unsigned long long v[LB];
+            bool here;
+            do {
+              here = true;
+#pragma unroll
+              for (int b = 0; b < LB; ++b) v[b] = get_word(words + k * I.nslab + min(t + b * kWave, I.nslab - 1));
+#pragma unroll
+              for (int b = 0; b < LB; ++b) here &= (unsigned int)(v[b] >> 32) == tag;
+            } while (again(here));
+#pragma unroll
+            for (int b = 0; b < LB; ++b)
+              if (t + b * kWave < I.nslab) a += __uint_as_float((unsigned int)v[b]);
+          }
+          a = wave_sum(a);
+          if (lane == 0 && ok) put_word(total + k, tag, a);
+        }
+#pragma unroll
+        for (int i = 0; i < MP; ++i) {
+          const int k = tid + NT * i;
+          if (k - lane >= ntp || !ok) continue;
+          unsigned long long v;
+          do {
+            v = get_word(total + min(k, ntp - 1));
+          } while (again((unsigned int)(v >> 32) == tag));
+          f[i] = __uint_as_float((unsigned int)v);
+        }
+      } else {
+        constexpr int TB = 4, JB = 2;  // slabs and 64-mode groups in flight
+        for (int j = 0; j < ntp; j += JB * kWave) {
+          float acc[JB];
+#pragma unroll
+          for (int a = 0; a < JB; ++a) acc[a] = 0.f;
+          for (int t = wave; t < I.nslab && ok; t += TB * NW) {
+            unsigned long long v[TB][JB];
+            bool here;
+            do {
+              here = true;
+#pragma unroll
+              for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int a = 0; a < JB; ++a) {
+                  // past the end: the first slab or the last mode again
+                  const int tt = t + b * NW < I.nslab ? t + b * NW : t, k = min(j + a * kWave + lane, ntp - 1);
+                  v[b][a] = get_word(words + tt * ntp + k);
+                }
+#pragma unroll
+              for (int b = 0; b < TB; ++b)
+#pragma unroll
+                for (int a = 0; a < JB; ++a) here &= (unsigned int)(v[b][a] >> 32) == tag;
+            } while (again(here));
+#pragma unroll
+            for (int b = 0; b < TB; ++b)
+              if (t + b * NW < I.nslab)
+#pragma unroll
+                for (int a = 0; a < JB; ++a) acc[a] += __uint_as_float((unsigned int)v[b][a]);
+          }
+#pragma unroll
+          for (int a = 0; a < JB; ++a) {
+            const int k = j + a * kWave + lane;
+            if (k < ntp) sums[wave * P.res_stride + k] = acc[a];
+          }
+        }
+      }
+      if (!ok && lane == 0) L.flag[0] = 1;
+    }
+    __syncthreads();
+    if (tid == 0 && U.slab == 0 && P.y) {
+      float yv = 0.f;
+      for (int w = 0; w < NW; ++w) yv += ysum[w];
+      P.y[(long long)I.out_row * P.y_stride + s] = yv;
+    }
+    if (L.flag[0]) break;  // a wait was given up; every thread leaves
+    // ---- state
+#pragma unroll
+    for (int i = 0; i < MP; ++i) {
+      const int k = tid + NT * i;
+      if (k >= ntp) continue;
+      if (I.nslab > 1 && !owners) {
+        f[i] = 0.f;
+        for (int w = 0; w < NW; ++w) f[i] += sums[w * P.res_stride + k];
+      }
+      mode_step(x[i], d[i], m[i], p[i], r[i], fmaf(bk[i], e, -f[i]));
+      bad |= !isfinite((float)x[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MP; ++i) {
+    const int k = tid + NT * i;
+    if (k >= ntp || U.slab) continue;
+    P.x[U.state_off + k] = x[i];
+    P.d[U.state_off + k] = d[i];
+  }
+  if (__any(bad) && lane == 0) atomicOr(&P.flags[1], 1);
+  if (s == P.n_steps) step_done(P);
+}
+
+// n words of the latency kernel's exchange, as left by the steps before
+// *step_base.
+__global__ void pair_fill_kernel(unsigned long long* pair, long long n, const long long* step_base) {
+  const unsigned long long v = (unsigned long long)*step_base << 32;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
+    pair[i] = v;
+}
+
 // Puts a context back to its initial state: the state's n doubles, n_ctr
-// arrival words, both pairs of status flags (the device's and, if there is one, the host's) and
+// arrival words, n_pair exchange words, both pairs of status flags (the device's and, if there is one, the host's) and
 // the step counter.
 __global__ void __launch_bounds__(256) reset_kernel(double* st, const double* st0, long long n, unsigned int* ctr,
-                                                    int n_ctr, int* dflags, int* hflags, long long* step) {
+                                                    int n_ctr, unsigned long long* pair, long long n_pair,
+                                                    int* dflags, int* hflags, long long* step) {
   const long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x, di = (long long)gridDim.x * blockDim.x;
   for (long long i = i0; i < n / 2; i += di)
     reinterpret_cast<v2d*>(st)[i] = reinterpret_cast<const v2d*>(st0)[i];
   for (long long i = i0; i < n_ctr; i += di) ctr[i] = 0u;
+  for (long long i = i0; i < n_pair; i += di) pair[i] = 0u;
   if (i0 < 2) {
     dflags[i0] = 0;
     if (hflags) hflags[i0] = 0;
@@ -887,11 +1251,12 @@ hipError_t launch_step(const StepParams& P, int gm, int nw, int n_wg, size_t lds
   return hipGetLastError();
 }
 // n: even
-hipError_t launch_reset(double* st, const double* st0, long long n, unsigned int* ctr, int n_ctr, int* dflags,
-                        int* hflags, long long* step, hipStream_t s) {
-  const long long want = (std::max<long long>(n / 2, n_ctr) + 255) / 256;
+hipError_t launch_reset(double* st, const double* st0, long long n, unsigned int* ctr, int n_ctr,
+                        unsigned long long* pair, long long n_pair, int* dflags, int* hflags, long long* step,
+                        hipStream_t s) {
+  const long long want = (std::max({n / 2, (long long)n_ctr, n_pair}) + 255) / 256;
   hipLaunchKernelGGL(reset_kernel, dim3((unsigned)std::max<long long>(1, std::min<long long>(want, 2048))), dim3(256),
-                     0, s, st, st0, n, ctr, n_ctr, dflags, hflags, step);
+                     0, s, st, st0, n, ctr, n_ctr, pair, n_pair, dflags, hflags, step);
   return hipGetLastError();
 }
 hipError_t launch_advance(long long* step_base, int n, hipStream_t s) {
@@ -902,6 +1267,41 @@ hipError_t launch_ctr_fill(const InstDev* inst, int batch, const long long* step
                            hipStream_t s) {
   hipLaunchKernelGGL(ctr_fill_kernel, dim3((batch + 255) / 256), dim3(256), 0, s, inst, batch, step_base, ctr);
   return hipGetLastError();
+}
+hipError_t launch_pair_fill(unsigned long long* pair, long long n, const long long* step_base, hipStream_t s) {
+  hipLaunchKernelGGL(pair_fill_kernel, dim3((unsigned)std::min<long long>((n + 255) / 256, 1024)), dim3(256), 0, s, pair,
+                     n, step_base);
+  return hipGetLastError();
+}
+// gm, nw, lds_bytes as launch_step's with resident state; nb: blocks a wave of
+// the launch's units keeps in registers (0: streamed; else 4 or 8, with gm 1
+// and nw 8)
+hipError_t launch_lat(const StepParams& P, int gm, int nw, int nb, int n_wg, size_t lds_bytes, hipStream_t s) {
+#define LL(G, W, B) hipLaunchKernelGGL((lat_kernel<G, W, B>), dim3(n_wg), dim3(kWave * W), lds_bytes, s, P)
+  if (nb == 4) LL(1, 8, 4);
+  else if (nb == 8) LL(1, 8, 8);
+  else if (nw == 8) {
+    if (gm <= 1) LL(1, 8, 0); else if (gm <= 2) LL(2, 8, 0); else LL(4, 8, 0);
+  } else {
+    if (gm <= 1) LL(1, 4, 0); else if (gm <= 2) LL(2, 4, 0); else LL(4, 4, 0);
+  }
+#undef LL
+  return hipGetLastError();
+}
+hipError_t lat_occupancy(int* blocks_per_cu, int gm, int nw, int nb, size_t lds_bytes) {
+#define LO(G, W, B) \
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, lat_kernel<G, W, B>, kWave * W, lds_bytes)
+  if (nb == 4) LO(1, 8, 4);
+  if (nb == 8) LO(1, 8, 8);
+  if (nw == 8) {
+    if (gm <= 1) LO(1, 8, 0);
+    if (gm <= 2) LO(2, 8, 0);
+    LO(4, 8, 0);
+  }
+  if (gm <= 1) LO(1, 4, 0);
+  if (gm <= 2) LO(2, 4, 0);
+  LO(4, 4, 0);
+#undef LO
 }
 hipError_t launch_check(const float* H, const InstDev* inst, int batch, int* out, hipStream_t s) {
   hipLaunchKernelGGL(check_kernel, dim3(64, batch), dim3(256), 0, s, H, inst, out);
