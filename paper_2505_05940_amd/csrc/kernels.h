@@ -111,6 +111,27 @@ __host__ __device__ inline GradLds grad_lds(float* base) {
   return L;
 }
 
+// LDS of the latency kernel's reverse step: q^n, u^n, a flag word, the exchange
+// words of the waves that share a row, per wave red_floats for a row's sums of
+// V and W and two parked rows, and per wave a sum over its slabs.
+struct LatGradLds {
+  float *xs, *us, *xch, *red, *sums;
+  int* flag;
+};
+__host__ __device__ inline size_t lat_grad_lds_bytes(int nw, int red_floats) {
+  return sizeof(float) * (2 * 4 * (size_t)kWave + 4 + 6 * (size_t)nw + (size_t)nw * (red_floats + 4 * kWave));
+}
+__host__ __device__ inline LatGradLds lat_grad_lds(float* base, int nw, int red_floats) {
+  LatGradLds L;
+  L.xs = base;
+  L.us = base + 4 * kWave;
+  L.flag = reinterpret_cast<int*>(base + 8 * kWave);
+  L.xch = base + 8 * kWave + 4;
+  L.red = L.xch + 6 * nw;
+  L.sums = L.red + (size_t)nw * red_floats;
+  return L;
+}
+
 // Most slabs of an instance that read each other's partial forces directly in
 // the latency kernel; with more, each sums a few modes for all (words read
 // grow with the square of the slabs: a lone 144/144 plate in 72 slabs steps
@@ -194,6 +215,8 @@ struct GradParams {
   // m, p, r, c, s (u.F per mode), theta (per mode)
   double* acc;
   int state_floats;
+  unsigned long long *pair, *pair2;  // latency kernel: as StepParams'
+  double* gs;            // and each unit's sums of dbar F, 256 a unit
   float* part;           // partial (J u, F) of split instances, [2][nslab][2 ntp] at 2 part_off
   unsigned int* ctr;
   int* flags;

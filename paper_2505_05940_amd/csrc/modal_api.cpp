@@ -29,6 +29,10 @@ hipError_t launch_reset(double* st, const double* st0, long long n, unsigned int
 hipError_t launch_pair_fill(unsigned long long* pair, long long n, const long long* step_base, hipStream_t s);
 hipError_t launch_lat(const StepParams& P, int gm, int nw, int nb, int n_wg, size_t lds_bytes, hipStream_t s);
 hipError_t lat_occupancy(int* blocks_per_cu, int gm, int nw, int nb, size_t lds_bytes);
+hipError_t launch_lat_grad(const GradParams& P, int nb, int n_wg, size_t lds_bytes, hipStream_t s);
+hipError_t lat_grad_occupancy(int* blocks_per_cu, int nb, size_t lds_bytes);
+hipError_t launch_lat_sum(const InstDev* inst, const UnitDev* unit, int n_units, const double* gs, const double* r,
+                          double* acc, int state_floats, hipStream_t s);
 hipError_t launch_advance(long long* step_base, int n, hipStream_t s);
 hipError_t launch_ctr_fill(const InstDev* inst, int batch, const long long* step_base, unsigned int* ctr,
                            hipStream_t s);
@@ -209,10 +213,14 @@ struct modal_ctx {
   size_t lds_stream = 0;  // on-chip one be given up (set_tensor)
   int res_stride = 0;  // > 0: LDS-resident state (one unit per workgroup)
   bool lat = false;    // such a plan of von Karman units only: the latency kernel,
+  int lat_share = 0;   // blocks of a wave, and where the reverse step runs so too the
+  int lat_red = 0;     // LDS floats of a wave there (0: it does not)
   int lat_nb = 0;      // with this many row blocks a wave in registers (0: streamed)
   std::vector<UnitDev> lat_units;       // its units and instances (dLat: both on the device)
   std::vector<InstDev> lat_inst;
   char* dLat = nullptr;
+  double* dLatG = nullptr;              // the reverse step's sums and exchange words
+  unsigned long long* dGPair = nullptr;
   unsigned long long* dPair = nullptr;  // its exchange words, n_pair of them, n_part for partial forces
   long long n_part = 0;
   long long n_pair = 0;
@@ -355,7 +363,7 @@ void free_ctx(modal_ctx* c) {
   if (!c) return;
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  void* ptrs[] = {c->dPair, c->dLat, c->dH,   c->dMeta, c->dCoef, c->dState, c->dPart, c->dCtr, c->dFlags, c->dState0,
+  void* ptrs[] = {c->dPair, c->dLat, c->dLatG, c->dGPair, c->dH,   c->dMeta, c->dCoef, c->dState, c->dPart, c->dCtr, c->dFlags, c->dState0,
                   c->dStep, c->dE,   c->dHd,   c->dCkpt,  c->dRec,  c->dAdj, c->dAcc,
                   c->dGPart, c->dGCtr, c->dShA, c->dShS2, c->dJmap, c->dRrec, c->dRacc,
                   c->dLinModes, c->dLinInit, c->dLinInst, c->dLinAmp, c->dLinZ, c->dLinS, c->dLinForced,
@@ -1781,7 +1789,15 @@ static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::v
     c->lat_nb = regs ? (share <= 4 ? 4 : 8) : 0;
     if (regs && share > kLatRegBlocks) continue;
     c->lat = fits(c->lat_nb, c->lat_units.size());
-    if (c->lat) break;
+    if (!c->lat) continue;
+    if (regs) {
+      int rf = 0, o = 0;
+      for (const UnitDev& U : c->lat_units) rf = std::max(rf, (2 * U.qs + 4) * inst[U.inst].ntp);
+      c->lat_share = share;
+      if (lat_grad_occupancy(&o, share, lat_grad_lds_bytes(8, rf)) != hipSuccess) (void)hipGetLastError();
+      else if ((size_t)o * cus >= c->lat_units.size()) c->lat_red = rf;
+    }
+    break;
   }
   return MODAL_OK;
 }
@@ -2928,6 +2944,21 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   HIP_TRY(hipMemsetAsync(c->dAdj, 0, sizeof(double) * 2 * (size_t)sf, s));
   HIP_TRY(hipMemsetAsync(c->dAcc, 0, sizeof(double) * 6 * (size_t)sf, s));
   HIP_TRY(hipMemsetAsync(c->dGCtr, 0, sizeof(unsigned int) * c->n_ctr, s));
+  const bool lat_rev = c->lat && c->lat_red && !c->chip_nt && !c->tangent;
+  if (lat_rev) {
+    const size_t g_bytes = sizeof(double) * 4 * kWave * c->lat_units.size();
+    const size_t w_bytes = sizeof(unsigned long long) * (size_t)(c->n_pair + 1);
+    if (!c->dLatG) {
+      r = dalloc(&c->dLatG, g_bytes);
+      if (r) return r;
+    }
+    if (!c->dGPair) {
+      r = dalloc(&c->dGPair, w_bytes);
+      if (r) return r;
+    }
+    HIP_TRY(hipMemsetAsync(c->dLatG, 0, g_bytes, s));
+    HIP_TRY(hipMemsetAsync(c->dGPair, 0, w_bytes, s));
+  }
   const bool rows_on = g_row && c->rows_total > 0;
   if (rows_on) HIP_TRY(hipMemsetAsync(c->dRacc, 0, sizeof(double) * (size_t)c->rows_total, s));
   GradParams G{};
@@ -2953,6 +2984,14 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   G.flags = c->dFlags;
   G.timeout_ticks = F.timeout_ticks;
   G.red_floats = (c->tangent ? 3 : 2) * c->red_floats;
+  if (lat_rev) {
+    G.inst = (const InstDev*)c->dLat;
+    G.unit = (const UnitDev*)(c->dLat + sizeof(InstDev) * c->batch);
+    G.red_floats = c->lat_red;
+    G.pair = c->dGPair;
+    G.pair2 = c->dGPair + c->n_part;
+    G.gs = c->dLatG;
+  }
   // on chip unless a tangent tensor is set; there the sums over the rows stay
   // in the kernel, and with the whole trajectory recorded one launch sweeps it
   const bool on_chip = c->wave_lanes || (c->chip_nt && !c->tangent);
@@ -2993,6 +3032,8 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
       HIP_TRY(launch_wave_grad(G, c->wave_lanes, c->wave_m, c->batch, s));
     else if (on_chip)
       HIP_TRY(launch_chip_grad(G, c->chip_nt, c->chip_rows, c->batch, s));
+    else if (lat_rev)
+      HIP_TRY(launch_lat_grad(G, c->lat_share, (int)c->lat_units.size(), lat_grad_lds_bytes(8, c->lat_red), s));
     else
       HIP_TRY(launch_grad(G, c->gm, c->tangent, c->nw_grad[c->tangent],
                           c->res_stride > 0 && c->nw_grad[c->tangent] > 1, c->n_wg, c->grad_lds_v[c->tangent], s));
@@ -3001,6 +3042,8 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
       HIP_TRY(launch_tensor_grad(c->dTJobs, (int)tjobs.size(), tj_nin, tj_nt, G.rec_x, c->dUrec, c->dTrec, mf,
                                  c->rows_total, len, s));
   }
+  if (lat_rev)
+    HIP_TRY(launch_lat_sum(G.inst, G.unit, (int)c->lat_units.size(), G.gs, G.r, c->dAcc, sf, s));
   r = modal_check(c, stream_);
   if (r) return r;
   if (g_row) {

@@ -871,6 +871,82 @@ struct RowRegs {
       ++n;
     }
   }
+  // the same for the reverse sweep (vk_rows2_range of the streaming kernel):
+  // V = H q, W = H u, eta = V.q, w = V.u; J u += 2 w V + eta W, F += eta V
+  __device__ __forceinline__ void sweep2(int nt, int ntp, int qs, int row0, int t0, int t1, const float* Xs,
+                                         const float* Us, float* red, float4& Ju, float4& Fa, int lane, float* rrow,
+                                         float* teta, float* tw, float* defer, float* xv, int* xr) const {
+    constexpr int J = kSweepLoads;
+    if (lane == 0) {
+      xr[0] = -1;
+      xr[1] = -1;
+    }
+    if (t1 <= t0) return;
+    const int nc = ntp >> 2, qsnc = qs * nc, nblk = (nt + qs - 1) / qs, slab = qs * ntp;
+    int sub[J];
+    float4 aV[J], aW[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int v = lane + kWave * j;
+      sub[j] = v < qsnc ? v / nc : 0;
+      aV[j] = aW[j] = f4(0.f);
+    }
+    int n = row0 + t0 / nblk, b = t0 % nblk, bfirst = b;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (t0 + i >= t1) continue;
+      const int q0 = b * qs;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int qi = min(q0 + sub[j], nt - 1);
+        aV[j] = fma4(h[i][j], Xs[qi], aV[j]);
+        aW[j] = fma4(h[i][j], Us[qi], aW[j]);
+      }
+      if (++b < nblk && t0 + i + 1 < t1) continue;
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (lane + kWave * j < qsnc) {
+          st4(red + 4 * (lane + kWave * j), aV[j]);
+          st4(red + slab + 4 * (lane + kWave * j), aW[j]);
+        }
+      wave_lds_sync();
+      float4 V = f4(0.f), W = f4(0.f);
+      float eta = 0.f, w = 0.f;
+      if (lane < nc) {
+        V = sum_strided4(red + 4 * lane, qs, ntp);
+        W = sum_strided4(red + slab + 4 * lane, qs, ntp);
+        eta = dot4(V, ld4(Xs + 4 * lane));
+        w = dot4(V, ld4(Us + 4 * lane));
+      }
+      eta = wave_sum(eta);
+      w = wave_sum(w);
+      if (bfirst == 0 && b == nblk) {
+        if (lane == 0) {
+          if (rrow) rrow[n] = -2.f * eta * w;
+          if (teta) teta[n] = eta, tw[n] = w;
+        }
+        Ju = fma4(V, 2.f * w, fma4(W, eta, Ju));
+        Fa = fma4(V, eta, Fa);
+      } else {
+        const int slot = bfirst > 0 ? 0 : 1;
+        if (lane < nc) {
+          st4(defer + 2 * slot * ntp + 4 * lane, V);
+          st4(defer + (2 * slot + 1) * ntp + 4 * lane, W);
+        }
+        if (lane == 0) {
+          xv[2 * slot] = eta;
+          xv[2 * slot + 1] = w;
+          xr[slot] = n;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < J; ++j) aV[j] = aW[j] = f4(0.f);
+      b = 0;
+      bfirst = 0;
+      ++n;
+      wave_lds_sync();  // red is read before the next row's sums replace it
+    }
+  }
 };
 
 // ------------------------------------------------------------- latency kernel
@@ -908,6 +984,102 @@ __device__ __forceinline__ void put_word(unsigned long long* p, unsigned int tag
 }
 __device__ __forceinline__ unsigned long long get_word(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every slab's partial force of the step `tag`: with up to kPairSlabs slabs each
+// wave's sum over its slabs to sums[wave][stride] (to be added after a
+// barrier), else the whole sum to f, thread by thread.  False if the wait was
+// given up, here or elsewhere.
+template <int NW, int MP>
+__device__ __forceinline__ bool lat_gather(unsigned long long* words, unsigned long long* total, const InstDev& I,
+                                           const UnitDev& U, unsigned int tag, float (&f)[MP], float* sums, int stride,
+                                           int* flags, unsigned long long timeout) {
+  constexpr int NT = kWave * NW;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), ntp = I.ntp;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const unsigned long long t0 = wall_clock64();
+  bool ok = true;
+  // `here`: whether this wave's words have come; else whether to go on
+  auto again = [&](bool here) {
+    if (__all(here)) return false;
+    if (wall_clock64() - t0 > timeout)
+      __hip_atomic_store(&flags[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ok = __hip_atomic_load(&flags[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    return ok;
+  };
+  if (I.nslab > kPairSlabs) {
+    // each slab sums all slabs' words of its own few modes and publishes the
+    // sums, which every slab then reads
+    constexpr int LB = 4;  // 64-slab groups in flight
+    const int seg = (ntp + I.nslab - 1) / I.nslab;
+    const int k1 = min(ntp, (U.slab + 1) * seg);
+    for (int k = U.slab * seg + wave; k < k1 && ok; k += NW) {
+      float a = 0.f;
+      for (int t = lane; t - lane < I.nslab && ok; t += LB * kWave) {
+        unsigned long long v[LB];
+        bool here;
+        do {
+          here = true;
+#pragma unroll
+          for (int b = 0; b < LB; ++b) v[b] = get_word(words + k * I.nslab + min(t + b * kWave, I.nslab - 1));
+#pragma unroll
+          for (int b = 0; b < LB; ++b) here &= (unsigned int)(v[b] >> 32) == tag;
+        } while (again(here));
+#pragma unroll
+        for (int b = 0; b < LB; ++b)
+          if (t + b * kWave < I.nslab) a += __uint_as_float((unsigned int)v[b]);
+      }
+      a = wave_sum(a);
+      if (lane == 0 && ok) put_word(total + k, tag, a);
+    }
+#pragma unroll
+    for (int i = 0; i < MP; ++i) {
+      const int k = tid + NT * i;
+      if (k - lane >= ntp || !ok) continue;
+      unsigned long long v;
+      do {
+        v = get_word(total + min(k, ntp - 1));
+      } while (again((unsigned int)(v >> 32) == tag));
+      f[i] = __uint_as_float((unsigned int)v);
+    }
+    return ok;
+  }
+  constexpr int TB = 4, JB = 2;  // slabs and 64-mode groups in flight
+  for (int j = 0; j < ntp; j += JB * kWave) {
+    float acc[JB];
+#pragma unroll
+    for (int a = 0; a < JB; ++a) acc[a] = 0.f;
+    for (int t = wave; t < I.nslab && ok; t += TB * NW) {
+      unsigned long long v[TB][JB];
+      bool here;
+      do {
+        here = true;
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+          for (int a = 0; a < JB; ++a) {
+            // past the end: the first slab or the last mode again
+            const int tt = t + b * NW < I.nslab ? t + b * NW : t, k = min(j + a * kWave + lane, ntp - 1);
+            v[b][a] = get_word(words + tt * ntp + k);
+          }
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+          for (int a = 0; a < JB; ++a) here &= (unsigned int)(v[b][a] >> 32) == tag;
+      } while (again(here));
+#pragma unroll
+      for (int b = 0; b < TB; ++b)
+        if (t + b * NW < I.nslab)
+#pragma unroll
+          for (int a = 0; a < JB; ++a) acc[a] += __uint_as_float((unsigned int)v[b][a]);
+    }
+#pragma unroll
+    for (int a = 0; a < JB; ++a) {
+      const int k = j + a * kWave + lane;
+      if (k < ntp) sums[wave * stride + k] = acc[a];
+    }
+  }
+  return ok;
 }
 
 template <int GM, int NW, int NB>
@@ -1027,92 +1199,9 @@ __global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
       if (lane == 0) ysum[wave] = yp;
     }
     // ---- every slab's force
-    if (I.nslab > 1) {
-      const unsigned long long t0 = wall_clock64();
-      bool ok = true;
-      // `here`: whether this wave's words have come; else whether to go on
-      auto again = [&](bool here) {
-        if (__all(here)) return false;
-        if (wall_clock64() - t0 > P.timeout_ticks)
-          __hip_atomic_store(&P.flags[0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ok = __hip_atomic_load(&P.flags[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
-        return ok;
-      };
-      if (owners) {
-        // each slab sums all slabs' words of its own few modes and publishes
-        // the sums, which every slab then reads
-        constexpr int LB = 4;  // 64-slab groups in flight
-        unsigned long long* total = P.pair2 + half * P.mode_floats + I.mode_off;
-        const int seg = (ntp + I.nslab - 1) / I.nslab;
-        const int k1 = min(ntp, (U.slab + 1) * seg);
-        for (int k = U.slab * seg + wave; k < k1 && ok; k += NW) {
-          float a = 0.f;
-          for (int t = lane; t - lane < I.nslab && ok; t += LB * kWave) {
-            unsigned long long v[LB];
-            bool here;
-            do {
-              here = true;
-#pragma unroll
-              for (int b = 0; b < LB; ++b) v[b] = get_word(words + k * I.nslab + min(t + b * kWave, I.nslab - 1));
-#pragma unroll
-              for (int b = 0; b < LB; ++b) here &= (unsigned int)(v[b] >> 32) == tag;
-            } while (again(here));
-#pragma unroll
-            for (int b = 0; b < LB; ++b)
-              if (t + b * kWave < I.nslab) a += __uint_as_float((unsigned int)v[b]);
-          }
-          a = wave_sum(a);
-          if (lane == 0 && ok) put_word(total + k, tag, a);
-        }
-#pragma unroll
-        for (int i = 0; i < MP; ++i) {
-          const int k = tid + NT * i;
-          if (k - lane >= ntp || !ok) continue;
-          unsigned long long v;
-          do {
-            v = get_word(total + min(k, ntp - 1));
-          } while (again((unsigned int)(v >> 32) == tag));
-          f[i] = __uint_as_float((unsigned int)v);
-        }
-      } else {
-        constexpr int TB = 4, JB = 2;  // slabs and 64-mode groups in flight
-        for (int j = 0; j < ntp; j += JB * kWave) {
-          float acc[JB];
-#pragma unroll
-          for (int a = 0; a < JB; ++a) acc[a] = 0.f;
-          for (int t = wave; t < I.nslab && ok; t += TB * NW) {
-            unsigned long long v[TB][JB];
-            bool here;
-            do {
-              here = true;
-#pragma unroll
-              for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int a = 0; a < JB; ++a) {
-                  // past the end: the first slab or the last mode again
-                  const int tt = t + b * NW < I.nslab ? t + b * NW : t, k = min(j + a * kWave + lane, ntp - 1);
-                  v[b][a] = get_word(words + tt * ntp + k);
-                }
-#pragma unroll
-              for (int b = 0; b < TB; ++b)
-#pragma unroll
-                for (int a = 0; a < JB; ++a) here &= (unsigned int)(v[b][a] >> 32) == tag;
-            } while (again(here));
-#pragma unroll
-            for (int b = 0; b < TB; ++b)
-              if (t + b * NW < I.nslab)
-#pragma unroll
-                for (int a = 0; a < JB; ++a) acc[a] += __uint_as_float((unsigned int)v[b][a]);
-          }
-#pragma unroll
-          for (int a = 0; a < JB; ++a) {
-            const int k = j + a * kWave + lane;
-            if (k < ntp) sums[wave * P.res_stride + k] = acc[a];
-          }
-        }
-      }
-      if (!ok && lane == 0) L.flag[0] = 1;
-    }
+    if (I.nslab > 1 && !lat_gather<NW, MP>(words, P.pair2 + half * P.mode_floats + I.mode_off, I, U, tag, f, sums,
+                                           P.res_stride, P.flags, P.timeout_ticks) && lane == 0)
+      L.flag[0] = 1;
     __syncthreads();
     if (tid == 0 && U.slab == 0 && P.y) {
       float yv = 0.f;
@@ -1142,6 +1231,153 @@ __global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
   }
   if (__any(bad) && lane == 0) atomicOr(&P.flags[1], 1);
   if (s == P.n_steps) step_done(P);
+}
+
+// The reverse (adjoint) step in the same way, for the units whose rows stay in
+// registers.  Only J u is exchanged: F enters the gradients alone, which are
+// linear in it, so each slab sums dbar F over the steps for its own part (gs)
+// and lat_sum_kernel adds the slabs.  Lone sine plates, us a step of a
+// gradient less its forward pass, with grad_kernel and here: 66/66 17.8, 6.6;
+// 100/100 15.0, 7.5; 128/128 18.2, 8.3; 200/200 24.5, 14.8.
+template <int NW, int NB>
+__global__ void __launch_bounds__(kWave * NW) lat_grad_kernel(GradParams P) {
+  extern __shared__ float4 lds4[];
+  const LatGradLds L = lat_grad_lds(reinterpret_cast<float*>(lds4), NW, P.red_floats);
+  float *Xs = L.xs, *Us = L.us;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), k = tid;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  float* red = L.red + wave * P.red_floats;
+  const UnitDev U = P.unit[blockIdx.x];
+  const InstDev I = P.inst[U.inst];
+  const int ntp = I.ntp, nc = ntp >> 2;  // ntp <= 256, one mode a thread
+  const bool mine = k < ntp, first = U.slab == 0;
+  const int so = U.state_off + min(k, ntp - 1), mo = I.mode_off + min(k, ntp - 1);
+  double qb = P.qb[so], db = P.db[so];
+  const double m = P.m[mo], p = P.p[mo], r = P.r[mo];
+  const float bk = P.b_ext[mo], ck = P.c_out[mo];
+  double a0 = 0., a1 = 0., a2 = 0., a3 = 0., gs = 0.;
+  const int R = U.row1 - U.row0, nblk = (I.nt + U.qs - 1) / U.qs, T = R * nblk;
+  const int tw0 = (T * wave) / NW, tw1 = (T * (wave + 1)) / NW;
+  bool cut = false;
+  for (int w = 1; w < NW; ++w) cut |= ((T * w) / NW) % nblk != 0;
+  float* xv = L.xch;
+  int* xr = reinterpret_cast<int*>(L.xch + 4 * NW);
+  float* defer = red + 2 * U.qs * ntp;
+  RowRegs<NB> H;
+  H.load(P.H + I.h_off, I.nt, ntp, U.qs, U.row0, tw0, tw1, lane);
+  if (tid == 0) L.flag[0] = 0;
+  const float* rx = P.rec_x + mo;
+  const float* rd = P.rec_d + mo;
+  const float* yrow = P.ybar + (long long)I.out_row * P.ybar_stride + P.seg_base;
+  // a step's record is fetched a step ahead
+  float xn = rx[(long long)(P.seg_len - 1) * P.mode_floats], dn_ = rd[(long long)(P.seg_len - 1) * P.mode_floats];
+  float yn = yrow[P.seg_len - 1];
+  for (int s = 0; s < P.seg_len; ++s) {
+    const int row = P.seg_len - 1 - s;
+    const long long n = P.seg_base + row, rstep = P.done_before + s;
+    const float x = xn, dd = dn_, yb = yn;
+    const float e = n < I.n_exc ? P.e_ext[I.e_off + n] : 0.f;
+    const int next = max(row - 1, 0);
+    xn = rx[(long long)next * P.mode_floats];
+    dn_ = rd[(long long)next * P.mode_floats];
+    yn = yrow[next];
+    const double dbar = fma(-p, db, qb);  // db^{n+1}
+    const float u = (float)(r * dbar);
+    if (mine) {
+      Xs[k] = x;
+      Us[k] = u;
+      if (P.urec && first) P.urec[(long long)row * P.mode_floats + mo] = u;
+    }
+    __syncthreads();
+    float4 Ju = f4(0.f), Fa = f4(0.f);
+    float* rrow = P.rrec ? P.rrec + (long long)s * P.rows_total + I.row_off : nullptr;
+    float* teta = P.trec ? P.trec + row * 2LL * P.rows_total + I.row_off : nullptr;
+    float* tw = teta ? teta + P.rows_total : nullptr;
+    H.sweep2(I.nt, ntp, U.qs, U.row0, tw0, tw1, Xs, Us, red, Ju, Fa, lane, rrow, teta, tw, defer, xv + 4 * wave,
+             xr + 2 * wave);
+    if (cut) {
+      __syncthreads();  // every wave's partials of the rows it shares
+      const int i = lane & 15;
+      const bool in = i < 2 * NW;
+      const int ri = in ? xr[i] : -1;
+      const float ei = in ? xv[2 * i] : 0.f, wi = in ? xv[2 * i + 1] : 0.f;
+#pragma unroll
+      for (int slot = 0; slot < 2; ++slot) {
+        const int nr = xr[2 * wave + slot];
+        const float eta = group_sum<16>(ri == nr ? ei : 0.f), w = group_sum<16>(ri == nr ? wi : 0.f);
+        if (nr < 0) continue;
+        if (lane < nc) {
+          const float4 V = ld4(defer + 2 * slot * ntp + 4 * lane), W = ld4(defer + (2 * slot + 1) * ntp + 4 * lane);
+          Ju = fma4(V, 2.f * w, fma4(W, eta, Ju));
+          Fa = fma4(V, eta, Fa);
+        }
+        if (slot == 1 && lane == 0) {  // the wave that holds the row's first block
+          if (rrow) rrow[nr] = -2.f * eta * w;
+          if (teta) teta[nr] = eta, tw[nr] = w;
+        }
+      }
+    }
+    if (lane < nc) {
+      st4(red + 4 * lane, Ju);
+      st4(red + ntp + 4 * lane, Fa);
+    }
+    __syncthreads();
+    const int half = (int)(rstep & 1);
+    unsigned long long* words = P.pair + I.part_off + half * (long long)I.nslab * ntp;
+    const unsigned int tag = (unsigned int)(rstep + 1);
+    const bool owners = I.nslab > kPairSlabs;
+    float ju[1] = {0.f}, f = 0.f;
+    if (mine) {
+      for (int w = 0; w < NW; ++w) ju[0] += L.red[w * P.red_floats + k];
+      if (I.nslab > 1) put_word(words + (owners ? k * I.nslab + U.slab : U.slab * ntp + k), tag, ju[0]);
+      for (int w = 0; w < NW; ++w) f += L.red[w * P.red_floats + ntp + k];
+    }
+    gs = fma(dbar, (double)f, gs);
+    if (first) {
+      a0 = fma(dbar, (double)x, a0);
+      a1 = fma(-dbar, (double)dd, a1);
+      a2 = fma(dbar, (double)(bk * e), a2);
+      a3 = fma((double)yb, (double)x, a3);
+    }
+    if (I.nslab > 1 && !lat_gather<NW, 1>(words, P.pair2 + half * P.mode_floats + I.mode_off, I, U, tag, ju, L.sums,
+                                          kWave * 4, P.flags, P.timeout_ticks) && lane == 0)
+      L.flag[0] = 1;
+    __syncthreads();
+    if (L.flag[0]) return;  // a wait was given up; every thread leaves
+    if (mine && I.nslab > 1 && !owners) {
+      ju[0] = 0.f;
+      for (int w = 0; w < NW; ++w) ju[0] += L.sums[w * kWave * 4 + k];
+    }
+    // qb^n = ybar c + qb^{n+1} + m db^{n+1} - (J u)
+    qb = fma(m, dbar, qb) + fma((double)yb, (double)ck, -(double)ju[0]);
+    db = dbar;
+  }
+  if (!mine) return;
+  P.gs[(long long)blockIdx.x * kWave * 4 + k] += gs;
+  if (first) {
+    P.qb[so] = qb;
+    P.db[so] = db;
+    const long long sf = P.state_floats;
+    P.acc[so] += a0;
+    P.acc[sf + so] += a1;
+    P.acc[2 * sf + so] += a2;
+    P.acc[3 * sf + so] += a3;
+  }
+}
+
+// Adds the slabs' sums of dbar F to the accumulators of each instance, in the
+// order of the slabs.
+__global__ void lat_sum_kernel(const InstDev* inst, const UnitDev* unit, int n_units, const double* gs, const double* r,
+                               double* acc, int state_floats) {
+  const UnitDev U = unit[blockIdx.x];
+  const InstDev I = inst[U.inst];
+  const int k = threadIdx.x;
+  if (U.slab != 0 || k >= I.ntp) return;
+  double g = 0.;
+#pragma unroll 8
+  for (int t = 0; t < I.nslab; ++t) g += gs[(long long)(blockIdx.x + t) * kWave * 4 + k];
+  acc[2LL * state_floats + U.state_off + k] -= g;
+  acc[4LL * state_floats + U.state_off + k] -= r[I.mode_off + k] * g;
 }
 
 // n words of the latency kernel's exchange, as left by the steps before
@@ -1302,6 +1538,27 @@ hipError_t lat_occupancy(int* blocks_per_cu, int gm, int nw, int nb, size_t lds_
   if (gm <= 2) LO(2, 4, 0);
   LO(4, 4, 0);
 #undef LO
+}
+// nb: 4, 6 or 8
+hipError_t launch_lat_grad(const GradParams& P, int nb, int n_wg, size_t lds_bytes, hipStream_t s) {
+#define LG(B) hipLaunchKernelGGL((lat_grad_kernel<8, B>), dim3(n_wg), dim3(kWave * 8), lds_bytes, s, P)
+  if (nb <= 4) LG(4); else if (nb <= 6) LG(6); else LG(8);
+#undef LG
+  return hipGetLastError();
+}
+hipError_t launch_lat_sum(const InstDev* inst, const UnitDev* unit, int n_units, const double* gs, const double* r,
+                          double* acc, int state_floats, hipStream_t s) {
+  hipLaunchKernelGGL(lat_sum_kernel, dim3(n_units), dim3(kWave * 4), 0, s, inst, unit, n_units, gs, r, acc,
+                     state_floats);
+  return hipGetLastError();
+}
+hipError_t lat_grad_occupancy(int* blocks_per_cu, int nb, size_t lds_bytes) {
+#define LG(B) \
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, lat_grad_kernel<8, B>, kWave * 8, lds_bytes)
+  if (nb <= 4) LG(4);
+  if (nb <= 6) LG(6);
+  LG(8);
+#undef LG
 }
 hipError_t launch_check(const float* H, const InstDev* inst, int batch, int* out, hipStream_t s) {
   hipLaunchKernelGGL(check_kernel, dim3(64, batch), dim3(256), 0, s, H, inst, out);

@@ -61,3 +61,32 @@ def test_latency_plates(shapes):
     parts = [sim.run(k).cpu().numpy() for k in (1, 2, 50, STEPS - 53)]
     assert np.array_equal(np.concatenate(parts, 1), whole)
     sim.close()
+
+
+@pytest.mark.parametrize("shapes", [[(65, 3)], [(72, 9), (68, 33), (97, 64)], [(131, 129)], [(196, 130)], [(250, 66)],
+                                    [(66, 5)] * 18])
+def test_latency_gradients(shapes):
+    """The reverse step with rows in registers against the streaming reverse
+    kernel on an explicit launch shape, every gradient; the same reasoning."""
+    import torch
+    from paper_2505_05940_amd import modal
+    rng = np.random.default_rng(sum(a * b for a, b in shapes))
+    plates = [_plate(rng, nt, nin, i % 2 == 0) for i, (nt, nin) in enumerate(shapes)]
+    ybar = torch.tensor(rng.normal(size=(len(plates), STEPS)), dtype=torch.float32, device="cuda")
+    got = []
+    for kw in ({}, dict(waves=4, max_workgroups=32)):
+        sim = modal.Sim(plates, FS, flags=modal.FLAG_GRAD, **kw)
+        got.append([sim.grad(STEPS, ybar, tensor=t) for t in (False, True)])
+        sim.close()
+
+    def flat(v):
+        v = v if isinstance(v, (list, tuple)) else [v]
+        return np.concatenate([np.asarray(a.cpu() if torch.is_tensor(a) else a, dtype=float).ravel() for a in v])
+
+    for a, b in zip(*got):
+        assert a.keys() == b.keys()
+        for key in a:
+            if a[key] is None:
+                continue
+            x, y = flat(a[key]), flat(b[key])
+            assert np.linalg.norm(x - y) <= 1e-5 * np.linalg.norm(y), key
