@@ -202,24 +202,6 @@ __device__ __forceinline__ float4 sum_strided4(const float* p, int n, int stride
   return add4(add4(s0, s1), add4(s2, s3));
 }
 
-// Sum over t = t0, t0 + dt, ... (t < n) of the float4 at p + t * stride
-// (global memory written by other workgroups), with eight loads issued
-// before the first add so that their latencies overlap; a fixed order, so
-// every caller gets the same bits.
-__device__ __forceinline__ float4 sum_slabs4(const float* p, int t0, int dt, int n, long long stride) {
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  int t = t0;
-  for (; t + 7 * dt < n; t += 8 * dt) {
-    float4 a[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = *reinterpret_cast<const float4*>(p + (long long)(t + i * dt) * stride);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s = add4(s, a[i]);
-  }
-  for (; t < n; t += dt) s = add4(s, *reinterpret_cast<const float4*>(p + (long long)t * stride));
-  return s;
-}
-
 // sum of n consecutive floats (LDS), four partial sums
 __device__ __forceinline__ float sum_run(const float* p, int n) {
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
@@ -232,11 +214,6 @@ __device__ __forceinline__ float sum_run(const float* p, int n) {
   }
   for (; c < n; ++c) s0 += p[c];
   return (s0 + s1) + (s2 + s3);
-}
-// streaming 16-byte load with the non-temporal hint (read once per step)
-__device__ __forceinline__ float4 ldnt4(const float* p) {
-  const v4f v = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p));
-  return make_float4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ void st4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
 
