@@ -536,9 +536,16 @@ constexpr double kSplitSyncCost = 32768.0;
 double split_cost(const modal_desc* d) {
   return d->split_cost_kb > 0 ? 1024.0 * d->split_cost_kb : kSplitSyncCost;
 }
-// Instances below this cost are never split: their tensors stay L2-resident
-// from step to step and a whole-instance workgroup outruns any slab barrier.
-constexpr double kMinSplitCost = 4.0 * 1048576.0;
+// Instances below this cost are never split: a whole-instance workgroup then
+// outruns its slabs' exchange (2-4 us a step).  128 plates of 50-400 modes, us
+// a step with 4, 2, 1, 0.5 MB: 341, 299, 301, 300; 128 of 50-200: 323, 179,
+// 90, 63 (109 to 768 workgroups); 32 of 50-400: 281, 178, 128, 129; 256 of
+// 60-120: 125, 106, 95, 95.  The larger bound left CUs idle: a batch's
+// capacity is at least its largest whole instance.
+constexpr double kMinSplitCost = 0.5 * 1048576.0;
+// A batch of at most one instance per CU whose instances all cost less than
+// this is bound by a step's latency: eight waves a workgroup.
+constexpr double kSmallCost = 4.0 * 1048576.0;
 
 // ------------------------------------------------------ parity-blocked tensors
 // Internal layout of an instance whose tensor splits by mode class: modes
@@ -1994,7 +2001,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     bool small = true;
     if (!latency)
       for (int b = 0; b < d->batch && small; ++b)
-        small = row_cost[b] * (inst[b].kind == KIND_VK ? inst[b].nin : 1) < kMinSplitCost;
+        small = row_cost[b] * (inst[b].kind == KIND_VK ? inst[b].nin : 1) < kSmallCost;
     int o8 = 0;
     if (small) HIP_TRY(step_occupancy(&o8, c->gm, 8, step_lds_bytes(8, red_floats)));
     if (o8 >= 1) c->nw = 8;
