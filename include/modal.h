@@ -221,7 +221,9 @@ int modal_run(modal_ctx *c, int64_t n_steps, float *y, int64_t y_stride,
  * hipFree, graph creation or checkpoint recording.  A small kernel first sets
  * the scratch arrival words to this context's step count, so calls of different
  * contexts may follow each other in any order; calls that overlap on one GPU
- * (two streams at once) race on the scratch and must not be issued.
+ * (two streams at once) race on the scratch and must not be issued.  A few
+ * large plates on the latency kernel exchange through words that the context
+ * holds; the scratch they would need is checked all the same.
  * y, y_stride and the return values as modal_run; the launches go straight
  * to `stream` (MODAL_FLAG_GRAPH is not used here; a caller may capture them
  * itself, with MODAL_FLAG_ASYNC so that no status read-back is made).
@@ -258,7 +260,8 @@ int modal_get_state(modal_ctx *c, double *x, double *xm1, void *stream);
  * recursion, 1 shared tensor (then [1] is the number of instance columns
  * and [2], [8], [9] are 0), 2 linear closed form, 3 on-chip recursion
  * (one workgroup of 8 waves per instance, or without tensors one-wave
- * workgroups of 1, 2 or 4 instances; [6] 0); a context with
+ * workgroups of 1, 2 or 4 instances; [6] 0); the units that the latency
+ * kernel cuts for itself are not reported; a context with
  * MODAL_FLAG_GRAD reports its persistent plan here, also where it steps on
  * chip,
  * [11] FP32 operations of the force per step (sum over VK instances of
