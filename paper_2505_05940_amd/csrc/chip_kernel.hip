@@ -61,6 +61,14 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
   const int k = M.perm[lane];  // this lane's mode (-1: none)
   const int jb = M.jb[wave][lane];
   const int jl = M.jl[wave][lane];
+  // the mode this lane records: its own, or for the first lanes without one
+  // the zeros between nt and ntp, which a reverse sweep on the streaming
+  // kernel reads with the modes (64 lanes hold nt modes and that many zeros)
+  int kr = k;
+  if (REC && k < 0) {
+    const int idle = __popcll(__ballot(k < 0) & ((1ull << lane) - 1));
+    if (idle < I.ntp - I.nt) kr = I.nt + idle;
+  }
 
   float h[R][W];
   chip_load<W, R>(M, I, P.H, wave, k, jb, jl, [&](int i, int t, float v) { h[i][t] = v; });
@@ -100,15 +108,15 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
       if (wave == kChipWaves - 1) ys[j][lane] = cw * xh;
       if constexpr (REC) {
         const long long n = base + s0 + j;
-        if (wave == kChipWaves - 2 && P.rec_x && k >= 0) {
-          const long long ro = (n - P.rec_base) * P.mode_floats + I.mode_off + k;
+        if (wave == kChipWaves - 2 && P.rec_x && kr >= 0) {
+          const long long ro = (n - P.rec_base) * P.mode_floats + I.mode_off + kr;
           P.rec_x[ro] = xh;
           P.rec_d[ro] = (float)d;
         }
         if (P.ckpt) {
           if (to_ckpt == 0) {
-            if (wave == kChipWaves - 2 && k >= 0) {
-              double* cp = P.ckpt + (n / P.ckpt_every) * 2LL * P.mode_floats + I.mode_off + k;
+            if (wave == kChipWaves - 2 && kr >= 0) {
+              double* cp = P.ckpt + (n / P.ckpt_every) * 2LL * P.mode_floats + I.mode_off + kr;
               cp[0] = x;
               cp[P.mode_floats] = d;
             }
