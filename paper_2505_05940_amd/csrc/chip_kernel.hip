@@ -88,6 +88,9 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
     cw = P.c_out[mo];
     lam = P.lam[mo];
   }
+  // every wave has its copy of the state before the first one to finish writes
+  // it back (steps of an instance without a tensor have no barrier)
+  __syncthreads();
   float xh = (float)x;
   const long long base = step_first(P);
   auto chunk = [&](long long n0) {
