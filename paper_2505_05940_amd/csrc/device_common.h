@@ -161,7 +161,8 @@ __device__ __forceinline__ float4 ld4_coherent(v4i r, int byte_off) {
 // cannot be seen before them.  A workgroup-scope release fence emits no such
 // wait when a workgroup's waves share one CU, and an agent-scope one would
 // also write back the XCD's whole L2; the wait on the vector-memory counter
-// alone is what the exchange needs.  It is also a compiler barrier.
+// alone is what the exchange needs.  It is also a compiler barrier, and waits
+// for loads as well.
 __device__ __forceinline__ void publish_fence() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // Before reading partials (ld4_coherent) once the words have been seen:
 // keeps the compiler from moving the reads above the words' loads (the

@@ -1123,6 +1123,9 @@ __global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
   RowRegs<NB == 0 ? 1 : NB> H;
   if (NB > 0) H.load(P.H + I.h_off, I.nt, ntp, U.qs, U.row0, tw0, tw1, lane);
   if (tid == 0) L.flag[0] = 0;
+  // the state is in registers before this slab's first word goes out: with
+  // every slab's words the first one may end its launch and write it back
+  publish_fence();
   bool bad = false;
   int s = 0;
   for (; s < P.n_steps; ++s) {
