@@ -265,7 +265,8 @@ struct modal_ctx {
   // then: a context that runs once, as in a fit, does not pay for it)
   int* dFlags = nullptr;
   int* hFlags = nullptr;
-  bool dev_flags = false;  // a launch that may raise the device's is unchecked
+  bool dev_flags = false;  // a launch that may raise the device's is unchecked,
+  hipStream_t flag_stream = nullptr;  // the last of them on this stream
   long long n_runs = 0;
   // a launch was recorded by a caller's capture: its replays advance the
   // device's step counter unseen, so every later launch reads that one
@@ -2396,11 +2397,17 @@ int modal_reset(modal_ctx* c, void* stream_) {
   return MODAL_OK;
 }
 
+// A launch on s may raise the device's flags: the next check on s reads them.
+static void raises_dev_flags(modal_ctx* c, hipStream_t s) {
+  c->dev_flags = true;
+  c->flag_stream = s;
+}
+
 // One launch of P.n_steps forward steps.
 static int launch_forward(modal_ctx* c, StepParams P, hipStream_t s) {
   const bool streams = !c->wave_lanes && !c->chip_nt;
   P.flags = streams || !c->hFlags ? c->dFlags : c->hFlags;
-  c->dev_flags |= P.flags == c->dFlags;
+  if (P.flags == c->dFlags) raises_dev_flags(c, s);
   if (c->wave_lanes)
     HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
   else if (c->chip_nt)
@@ -2428,7 +2435,7 @@ static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride
       ScParams P = c->SC;
       P.base = base;
       P.flags = c->hFlags ? c->hFlags : c->dFlags;
-      c->dev_flags |= !c->hFlags;
+      if (!c->hFlags) raises_dev_flags(c, s);
       P.y = y + done;
       P.y_stride = y_stride;
       P.n_steps = (int)k;
@@ -2436,7 +2443,7 @@ static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride
     } else if (c->shared) {
       SharedParams P = c->SP;
       P.flags = c->hFlags ? c->hFlags : c->dFlags;
-      c->dev_flags |= !c->hFlags;
+      if (!c->hFlags) raises_dev_flags(c, s);
       P.base = base;
       P.y = y + done;
       P.y_stride = y_stride;
@@ -2476,8 +2483,9 @@ int modal_check(modal_ctx* c, void* stream_) {
     fl[0] |= h[0];
     fl[1] |= h[1];
   }
-  // (replays of captured launches come unseen)
-  if (!fl[0] && !fl[1] && !c->captured && !(c->flags & MODAL_FLAG_GRAPH)) c->dev_flags = false;
+  // (replays of captured launches come unseen, and another stream's launch may
+  // still be running)
+  if (!fl[0] && !fl[1] && !c->captured && !(c->flags & MODAL_FLAG_GRAPH) && s == c->flag_stream) c->dev_flags = false;
   if (fl[0]) return fail(MODAL_EHANG, "a per-instance step barrier timed out");
   if (fl[1]) return fail(MODAL_ENONFINITE, "a modal state became non-finite");
   return MODAL_OK;
@@ -3007,7 +3015,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   const bool on_chip = c->wave_lanes || (c->chip_nt && !c->tangent);
   const long long K_rev = on_chip && reuse_rec && !tens_on ? n_steps : K;
   const long long nrev = (n_steps + K_rev - 1) / K_rev;
-  c->dev_flags |= !on_chip;
+  if (!on_chip) raises_dev_flags(c, s);
   G.rrec = rows_on && !on_chip ? c->dRrec : nullptr;
   G.chip = c->dChip;
   G.racc = rows_on ? c->dRacc : nullptr;
