@@ -2397,6 +2397,20 @@ int modal_reset(modal_ctx* c, void* stream_) {
   return MODAL_OK;
 }
 
+// Pinned flags, if there are any to be had: without them a context goes on
+// with the device's.  Another stream of the process may be under capture, which
+// the allocation has nothing to do with and must not end.
+static void alloc_host_flags(modal_ctx* c) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  if (hipHostMalloc((void**)&c->hFlags, 2 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess)
+    c->hFlags[0] = c->hFlags[1] = 0;
+  else
+    c->hFlags = nullptr;
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  (void)hipGetLastError();
+}
+
 // A launch on s may raise the device's flags: the next check on s reads them.
 static void raises_dev_flags(modal_ctx* c, hipStream_t s) {
   c->dev_flags = true;
@@ -2424,10 +2438,7 @@ static int launch_forward(modal_ctx* c, StepParams P, hipStream_t s) {
 static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, hipStream_t s) {
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
   const bool known = !(c->flags & MODAL_FLAG_GRAPH) && host_steps(c, s);
-  if (known && ++c->n_runs == 2 && !c->hFlags && (c->shared || c->wave_lanes || c->chip_nt)) {
-    HIP_TRY(hipHostMalloc((void**)&c->hFlags, 2 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent));
-    c->hFlags[0] = c->hFlags[1] = 0;
-  }
+  if (known && ++c->n_runs == 2 && !c->hFlags && (c->shared || c->wave_lanes || c->chip_nt)) alloc_host_flags(c);
   for (int64_t done = 0; done < n_steps; done += chunk) {
     const int64_t k = std::min<int64_t>(chunk, n_steps - done);
     const long long base = known ? c->steps + done : -1;
