@@ -29,6 +29,15 @@
  *    soon as it returns.  A context owns all device memory it allocates and
  *    frees it in modal_destroy.  A context is not thread safe: use one
  *    context per stream.
+ *  - Plates of more than 64 modes may be cut into slabs (modal_info [2], and
+ *    the latency kernel's), whose workgroups wait for each other's forces on
+ *    every step and so must all be resident on the GPU at once.  Launches of
+ *    such contexts on several streams or threads of a process are ordered by
+ *    the library where they would not fit side by side: the later one starts
+ *    when earlier ones have ended.  It cannot order what it does not launch:
+ *    replays of launches that a caller captured, and other processes, must not
+ *    overlap with another such context's launches; workgroups that miss their
+ *    partners for barrier_us report MODAL_EHANG.
  */
 #ifndef MODAL_H
 #define MODAL_H

@@ -11,6 +11,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <optional>
 #include <queue>
 #include <atomic>
 #include <string>
@@ -350,6 +351,11 @@ struct modal_ctx {
   int sc_ks = 0, sc_rows = 0, sc_wg = 0;
   ScParams SC{};
   hipStream_t cap_stream = nullptr;  // private stream used only for graph capture
+  // > 0: the plan's workgroups wait for each other, on this share of the GPU
+  // (workgroups over co-resident ones, the widest of its kernels); the event
+  // marks the end of the last such launches
+  double together = 0.;
+  hipEvent_t together_done = nullptr;
   struct Graph {
     int64_t n, stride;
     float* y;
@@ -360,8 +366,86 @@ struct modal_ctx {
 
 namespace {
 
+// Launches whose workgroups wait for each other's words end only if all of
+// them are resident at once.  Two such launches on two streams could each get
+// half of what it needs, and both would then run into the wait limit, so a
+// launch waits (on the GPU) for as many earlier ones of the process as it takes
+// for those that may run beside it to need at most half of the GPU together
+// with it.  Half, because a CU that holds workgroups of several kernels may
+// refuse all of them when it is little more than half full.  Launches recorded
+// by a caller's capture are not ordered.  Held by the enqueuing thread from
+// before the first launch until after the last.
+class Together {
+ public:
+  Together(modal_ctx* c, bool waits, hipStream_t s) : c_(c), s_(s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!waits || !(c->together > 0.) || c->device >= kMaxScratchDevices ||
+        hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+      if (waits) (void)hipGetLastError();
+      c_ = nullptr;
+      return;
+    }
+    lock_ = std::unique_lock<std::mutex>(mu_);
+    std::vector<Live>& live = list(c);
+    live.reserve(live.size() + 1);
+    drop(live, c);  // (a context's own launches are on one stream, or ordered by the caller)
+    double sum = c->together;
+    for (const Live& l : live) sum += l.share;
+    if (sum <= 0.5) return;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another stream may be under capture)
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    sum = c->together;
+    live.erase(std::remove_if(live.begin(), live.end(), [](const Live& l) { return hipEventQuery(l.done) == hipSuccess; }),
+               live.end());
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipGetLastError();
+    for (const Live& l : live) sum += l.share;
+    for (const Live& l : live) {
+      if (sum <= 0.5) break;
+      if (hipStreamWaitEvent(s, l.done, 0) != hipSuccess) (void)hipGetLastError();
+      sum -= l.share;
+    }
+  }
+  ~Together() {
+    if (!c_) return;
+    if (hipEventRecord(c_->together_done, s_) == hipSuccess)
+      list(c_).push_back({c_, c_->together_done, c_->together});
+    else
+      (void)hipGetLastError();
+  }
+  Together(const Together&) = delete;
+  Together& operator=(const Together&) = delete;
+  static void forget(const modal_ctx* c) {
+    if (!(c->together > 0.) || c->device >= kMaxScratchDevices) return;
+    std::lock_guard<std::mutex> lock(mu_);
+    drop(list(c), c);
+  }
+
+ private:
+  struct Live {
+    const modal_ctx* c;
+    hipEvent_t done;
+    double share;
+  };
+  static void drop(std::vector<Live>& live, const modal_ctx* c) {
+    live.erase(std::remove_if(live.begin(), live.end(), [c](const Live& l) { return l.c == c; }), live.end());
+  }
+  // the last launches of each context, oldest first (never destroyed: a
+  // context may be freed while the process ends)
+  static std::vector<Live>& list(const modal_ctx* c) {
+    static auto* live = new std::array<std::vector<Live>, kMaxScratchDevices>();
+    return (*live)[c->device];
+  }
+  static std::mutex mu_;
+  modal_ctx* c_;
+  hipStream_t s_;
+  std::unique_lock<std::mutex> lock_;
+};
+std::mutex Together::mu_;
+
 void free_ctx(modal_ctx* c) {
   if (!c) return;
+  Together::forget(c);
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   void* ptrs[] = {c->dPair, c->dLat, c->dLatG, c->dGPair, c->dH,   c->dMeta, c->dCoef, c->dState, c->dPart, c->dCtr, c->dFlags, c->dState0,
@@ -372,6 +456,7 @@ void free_ctx(modal_ctx* c) {
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->hFlags) (void)hipHostFree(c->hFlags);  // (no launch is left: hipFree waits for the device)
+  if (c->together_done) (void)hipEventDestroy(c->together_done);
   delete c;
 }
 
@@ -1761,8 +1846,8 @@ static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::v
   const int batch = (int)inst.size();
   for (const InstDev& I : inst)
     if (I.kind != KIND_VK) return MODAL_OK;
+  int o = 0;  // workgroups a CU
   auto fits = [&](int nb, size_t n) {
-    int o = 0;
     if (lat_occupancy(&o, c->gm, c->nw, nb, lds) != hipSuccess) {
       (void)hipGetLastError();
       return false;
@@ -1798,12 +1883,18 @@ static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::v
     if (regs && share > kLatRegBlocks) continue;
     c->lat = fits(c->lat_nb, c->lat_units.size());
     if (!c->lat) continue;
+    const double n = (double)c->lat_units.size() / cus;
+    if (c->n_part) c->together = std::max(c->together, n / o);
     if (regs) {
-      int rf = 0, o = 0;
+      int rf = 0;
       for (const UnitDev& U : c->lat_units) rf = std::max(rf, (2 * U.qs + 4) * inst[U.inst].ntp);
       c->lat_share = share;
-      if (lat_grad_occupancy(&o, share, lat_grad_lds_bytes(8, rf)) != hipSuccess) (void)hipGetLastError();
-      else if ((size_t)o * cus >= c->lat_units.size()) c->lat_red = rf;
+      if (lat_grad_occupancy(&o, share, lat_grad_lds_bytes(8, rf)) != hipSuccess) {
+        (void)hipGetLastError();
+      } else if ((size_t)o * cus >= c->lat_units.size()) {
+        c->lat_red = rf;
+        if (c->n_part) c->together = std::max(c->together, n / o);
+      }
     }
     break;
   }
@@ -2176,6 +2267,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   c->chip_rows = chip_rows;
   c->nw_stream = c->nw;
   c->lds_stream = c->lds_bytes;
+  if (c->n_split > 0) c->together = (double)n_wg / ((double)occ * prop.multiProcessorCount);
   if (chip_nt && !grad) {
     c->nw = kChipWaves;
     c->lds_bytes = 0;
@@ -2192,6 +2284,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     if (S > 0 && o >= 1 && (long long)o * prop.multiProcessorCount >= n_wg) {
       c->res_stride = S;
       c->lds_bytes = lb;
+      if (c->n_split > 0) c->together = std::max(c->together, (double)n_wg / ((double)o * prop.multiProcessorCount));
       int r = plan_lat(c, inst, nslab, qs_of, lb, prop.multiProcessorCount);
       if (r) {
         free_ctx(c);
@@ -2283,6 +2376,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     if (e_ != hipSuccess)                                                                 \
       return bail(fail(MODAL_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_)));   \
   } while (0)
+  if (c->together > 0.) HIP_TRY_C(hipEventCreateWithFlags(&c->together_done, hipEventDisableTiming));
   {
     int r = alloc_reset(c, stream);
     if (r) return bail(r);
@@ -2409,6 +2503,11 @@ static void alloc_host_flags(modal_ctx* c) {
     c->hFlags = nullptr;
   if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
   (void)hipGetLastError();
+}
+
+// Whether forward launches have workgroups that wait for each other.
+static bool forward_waits(const modal_ctx* c) {
+  return !c->shared && !c->wave_lanes && !c->chip_nt && (c->lat ? c->n_part > 0 : c->n_split > 0);
 }
 
 // A launch on s may raise the device's flags: the next check on s reads them.
@@ -2578,9 +2677,11 @@ int modal_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* s
       if (e != hipSuccess) return fail(MODAL_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
       c->graphs.push_back({n_steps, y_stride, y, exec});
     }
+    Together room(c, forward_waits(c), s);
     HIP_TRY(hipGraphLaunch(exec, s));
   } else {
     const bool recorded = c->run_ckpt, recorded_all = c->run_rec;
+    Together room(c, forward_waits(c), s);
     int r = enqueue_run(c, n_steps, y, y_stride, s);
     c->run_ckpt = false;
     c->run_rec = false;
@@ -2625,18 +2726,21 @@ int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride,
   if (c->n_pair) HIP_TRY(launch_pair_fill(c->dPair, c->n_pair, c->dStep, s));
   const bool known = host_steps(c, s);
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
-  for (int64_t done = 0; done < n_steps; done += chunk) {
-    const int64_t k = std::min<int64_t>(chunk, n_steps - done);
-    StepParams P = c->P;
-    P.part = part;
-    P.ctr = ctr;
-    P.base = known ? c->steps + done : -1;
-    P.y = y + done;
-    P.y_stride = y_stride;
-    P.n_steps = (int)k;
-    int r = launch_forward(c, P, s);
-    if (r) return r;
-    if (!known) HIP_TRY(launch_advance(c->dStep, (int)k, s));
+  {
+    Together room(c, forward_waits(c), s);
+    for (int64_t done = 0; done < n_steps; done += chunk) {
+      const int64_t k = std::min<int64_t>(chunk, n_steps - done);
+      StepParams P = c->P;
+      P.part = part;
+      P.ctr = ctr;
+      P.base = known ? c->steps + done : -1;
+      P.y = y + done;
+      P.y_stride = y_stride;
+      P.n_steps = (int)k;
+      int r = launch_forward(c, P, s);
+      if (r) return r;
+      if (!known) HIP_TRY(launch_advance(c->dStep, (int)k, s));
+    }
   }
   // no checkpoints were recorded: a gradient context's recorded checkpoints
   // stop at ckpt_upto, and a later modal_run past them marks them broken
@@ -2940,6 +3044,10 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   // recorded them)
   int r = modal_reset(c, stream_);
   if (r) return r;
+  // on chip unless a tangent tensor is set; there the sums over the rows stay
+  // in the kernel, and with the whole trajectory recorded one launch sweeps it
+  const bool on_chip = c->wave_lanes || (c->chip_nt && !c->tangent);
+  std::optional<Together> room(std::in_place, c, forward_waits(c) || (!on_chip && (c->n_split > 0 || c->n_part > 0)), s);
   // the forward pass also records the whole trajectory while it fits, so
   // that the reverse sweep needs no segment recomputes
   bool rec_now = false;
@@ -3021,9 +3129,6 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
     G.pair2 = c->dGPair + c->n_part;
     G.gs = c->dLatG;
   }
-  // on chip unless a tangent tensor is set; there the sums over the rows stay
-  // in the kernel, and with the whole trajectory recorded one launch sweeps it
-  const bool on_chip = c->wave_lanes || (c->chip_nt && !c->tangent);
   const long long K_rev = on_chip && reuse_rec && !tens_on ? n_steps : K;
   const long long nrev = (n_steps + K_rev - 1) / K_rev;
   if (!on_chip) raises_dev_flags(c, s);
@@ -3073,6 +3178,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   }
   if (lat_rev)
     HIP_TRY(launch_lat_sum(G.inst, G.unit, (int)c->lat_units.size(), G.gs, G.r, c->dAcc, sf, s));
+  room.reset();
   r = modal_check(c, stream_);
   if (r) return r;
   if (g_row) {
