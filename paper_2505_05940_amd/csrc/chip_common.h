@@ -129,11 +129,7 @@ __device__ __forceinline__ float wave_join(const float (*red)[kWave], int lane) 
   float v[kChipWaves];
 #pragma unroll
   for (int w = 0; w < kChipWaves; ++w) v[w] = red[w][lane];
-#pragma unroll
-  for (int s = kChipWaves / 2; s > 0; s /= 2)
-#pragma unroll
-    for (int w = 0; w < s; ++w) v[w] += v[w + s];
-  return v[0];
+  return tree_sum(v);
 }
 
 // Lane stride of a vector of modes in LDS: a run of W <= 64 columns from any

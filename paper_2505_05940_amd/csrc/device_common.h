@@ -69,6 +69,26 @@ __device__ __forceinline__ float group_sum(float v) {
   }
   return v;
 }
+// c . x of each quad of lanes, on its last lane (zero on the others), rounded
+// as dot4 rounds four elements of one lane
+__device__ __forceinline__ float quad_dot(float c, float x, int lane) {
+  float v = c * x;
+#pragma unroll
+  for (int j = 1; j < 4; ++j) {
+    const float t = fmaf(c, x, dpp_mov<0x90>(v));  // quad_perm [0,0,1,2]: the lane before
+    v = (lane & 3) == j ? t : v;
+  }
+  return (lane & 3) == 3 ? v : 0.f;
+}
+// Sum of N values (a power of two) as a tree.
+template <int N>
+__device__ __forceinline__ float tree_sum(float (&v)[N]) {
+#pragma unroll
+  for (int s = N / 2; s > 0; s /= 2)
+#pragma unroll
+    for (int w = 0; w < s; ++w) v[w] += v[w + s];
+  return v[0];
+}
 // Sum of v over the four lanes l, l^16, l^32, l^48 (gfx950 lane swaps).
 __device__ __forceinline__ float quad_sum(float v) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);

@@ -129,11 +129,7 @@ __global__ void __launch_bounds__(kWave* kScWaves) shared_class_kernel(ScParams 
         float f[kScWaves];
 #pragma unroll
         for (int w = 0; w < kScWaves; ++w) f[w] = red[w][slot / 16][(slot % 16 / 4) * 16 + col][slot % 4];
-#pragma unroll
-        for (int h = kScWaves / 2; h > 0; h /= 2)
-#pragma unroll
-          for (int w = 0; w < h; ++w) f[w] += f[w + h];
-        mode_step(x[i], d[i], m[i], p[i], rr[i], fmaf(bx[i], e, -f[0]));
+        mode_step(x[i], d[i], m[i], p[i], rr[i], fmaf(bx[i], e, -tree_sum(f)));
         const float xh = (float)x[i];
         bad |= !isfinite(xh);
         xs[slot / 4][col][slot % 4] = xh;
@@ -145,9 +141,10 @@ __global__ void __launch_bounds__(kWave* kScWaves) shared_class_kernel(ScParams 
       const int c = i / kScChunk, j = i % kScChunk;
       const int row = P.slot[blockIdx.x * 16 + c].out_row;
       if (j >= js || row < 0 || !P.y) continue;
-      float v = 0.f;
-      for (int w = 0; w < kScWaves; ++w) v += ys[j][w][c];
-      P.y[(long long)row * P.y_stride + s0 + j] = v;
+      float v[kScWaves];
+#pragma unroll
+      for (int w = 0; w < kScWaves; ++w) v[w] = ys[j][w][c];
+      P.y[(long long)row * P.y_stride + s0 + j] = tree_sum(v);
     }
     block_lds_sync();  // the outputs are read
   }

@@ -1186,7 +1186,7 @@ __global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
       for (int i = 0; i < MP; ++i) {
         const int k = tid + NT * i;
         if (k >= ntp) continue;
-        yp = fmaf(ck[i], (float)x[i], yp);
+        yp += quad_dot(ck[i], (float)x[i], lane);  // (ntp is a multiple of 4)
         if (P.ckpt && n % P.ckpt_every == 0) {
           double* cp = P.ckpt + (n / P.ckpt_every) * 2LL * P.mode_floats + I.mode_off;
           cp[k] = x[i];
@@ -1207,9 +1207,14 @@ __global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
       L.flag[0] = 1;
     __syncthreads();
     if (tid == 0 && U.slab == 0 && P.y) {
-      float yv = 0.f;
-      for (int w = 0; w < NW; ++w) yv += ysum[w];
-      P.y[(long long)I.out_row * P.y_stride + s] = yv;
+      float yv[NW];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) yv[w] = ysum[w];
+#pragma unroll
+      for (int h = 1; h < NW; h *= 2)
+#pragma unroll
+        for (int w = 0; w < NW; w += 2 * h) yv[w] += yv[w + h];  // (as wave_sum pairs the rows of a wave)
+      P.y[(long long)I.out_row * P.y_stride + s] = yv[0];
     }
     if (L.flag[0]) break;  // a wait was given up; every thread leaves
     // ---- state
