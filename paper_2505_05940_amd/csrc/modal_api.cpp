@@ -742,30 +742,50 @@ void analyze_blocks(const modal_instance& I, BlockPlan& bp) {
   bp.ok = true;
 }
 
+bool device_pointer(const void* p) {
+  hipPointerAttribute_t attr;
+  if (hipPointerGetAttributes(&attr, p) == hipSuccess) return attr.type == hipMemoryTypeDevice;
+  (void)hipGetLastError();
+  return false;
+}
+
+// The class structures of a batch's tensors.  Instances that pass the same
+// tensor and classes are analysed once.
+struct BlockPlans {
+  std::vector<int> of;           // per instance: its plan, -1: a tensor without classes, or none
+  std::vector<BlockPlan> plans;
+  const BlockPlan& operator[](int b) const {
+    static const BlockPlan none;
+    return of.empty() || of[b] < 0 ? none : plans[of[b]];
+  }
+};
+
 // Analyses every VK instance that carries mode classes and host tensors, on
 // all host threads (largest first).
-void plan_blocks(const modal_desc* d, std::vector<BlockPlan>& plans) {
-  plans.assign(d->batch, BlockPlan{});
-  if (d->flags & (MODAL_FLAG_GRAD | MODAL_FLAG_NO_BLOCK)) return;
-  std::vector<int> todo;
+void plan_blocks(const modal_desc* d, BlockPlans& bp) {
+  bp.of.assign(d->batch, -1);
+  std::map<std::tuple<const float*, int, int>, std::vector<int>> seen;
+  std::vector<int> todo;  // the first instance of each plan
   for (int b = 0; b < d->batch; ++b) {
     const modal_instance& I = d->inst[b];
     if (I.kind != MODAL_KIND_VK || !I.mode_class) continue;
-    hipPointerAttribute_t attr;
-    bool on_device = false;
-    if (hipPointerGetAttributes(&attr, I.H) == hipSuccess)
-      on_device = attr.type == hipMemoryTypeDevice;
-    else
-      (void)hipGetLastError();
-    if (!on_device) todo.push_back(b);
+    std::vector<int>& same = seen[std::make_tuple(I.H, I.n_t, I.n_in)];
+    for (int o : same)
+      if (!std::memcmp(d->inst[o].mode_class, I.mode_class, I.n_t)) bp.of[b] = bp.of[o];
+    if (bp.of[b] >= 0) continue;
+    same.push_back(b);
+    if (device_pointer(I.H)) continue;
+    bp.of[b] = (int)todo.size();
+    todo.push_back(b);
   }
+  bp.plans.assign(todo.size(), BlockPlan{});
   std::stable_sort(todo.begin(), todo.end(), [&](int a, int b) {
     return (double)d->inst[a].n_in * d->inst[a].n_t * d->inst[a].n_t >
            (double)d->inst[b].n_in * d->inst[b].n_t * d->inst[b].n_t;
   });
   std::atomic<size_t> next{0};
   auto work = [&]() {
-    for (size_t i = next++; i < todo.size(); i = next++) analyze_blocks(d->inst[todo[i]], plans[todo[i]]);
+    for (size_t i = next++; i < todo.size(); i = next++) analyze_blocks(d->inst[todo[i]], bp.plans[bp.of[todo[i]]]);
   };
   const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
   const unsigned nth = (unsigned)std::min<size_t>(hw, todo.size());
@@ -898,39 +918,27 @@ bool chip_map(const modal_instance& I, const BlockPlan& bp, ChipMap& m, int& w_n
 }
 
 // The layouts of a batch whose instances all fit one workgroup's registers,
-// in a common tile; false if they do not.  Instances that pass the same
-// tensor and classes are analysed once.
-bool chip_plan(const modal_desc* d, std::vector<modal_ctx::Chip>& chips, int& w_tile, int& rows) {
+// in a common tile; false if they do not.  `plans` gets the batch's class
+// structures, once they are needed.
+bool chip_plan(const modal_desc* d, BlockPlans& plans, std::vector<modal_ctx::Chip>& chips, int& w_tile, int& rows) {
   for (int b = 0; b < d->batch; ++b) {  // before any analysis
     const modal_instance& I = d->inst[b];
     if (I.n_t > kWave || (I.kind == MODAL_KIND_VK && I.n_in > kChipWaves * kChipMaxRows)) return false;
   }
+  plan_blocks(d, plans);
   chips.resize(d->batch);
-  std::map<std::tuple<const float*, int, int>, std::vector<int>> seen;
-  std::vector<BlockPlan> plans(d->batch);
+  std::vector<int> mapped(plans.plans.size(), -1);  // the first instance of each plan
   int max_w = 0, max_r = 0;
   for (int b = 0; b < d->batch; ++b) {
-    const modal_instance& I = d->inst[b];
-    int like = -1;
-    if (I.kind == MODAL_KIND_VK && I.mode_class) {
-      auto& same = seen[std::make_tuple(I.H, I.n_t, I.n_in)];
-      for (int o : same)
-        if (!std::memcmp(d->inst[o].mode_class, I.mode_class, I.n_t)) like = o;
-      if (like < 0) {
-        hipPointerAttribute_t attr;
-        bool on_device = false;
-        if (hipPointerGetAttributes(&attr, I.H) == hipSuccess)
-          on_device = attr.type == hipMemoryTypeDevice;
-        else
-          (void)hipGetLastError();
-        if (!on_device) analyze_blocks(I, plans[b]);
-        same.push_back(b);
-      }
-    }
     modal_ctx::Chip& c = chips[b];
-    if (like >= 0) c = chips[like];
-    else if (!chip_map(I, plans[b], c.map, c.w, c.r)) return false;
-    else c.grouped = plans[b].ok;
+    const int p = plans.of[b];
+    if (p >= 0 && mapped[p] >= 0) {
+      c = chips[mapped[p]];
+    } else {
+      if (!chip_map(d->inst[b], plans[b], c.map, c.w, c.r)) return false;
+      c.grouped = plans[b].ok;
+      if (p >= 0) mapped[p] = b;
+    }
     max_w = std::max(max_w, c.w);
     max_r = std::max(max_r, c.r);
   }
@@ -1044,7 +1052,7 @@ bool plan_batch(const modal_desc* d, const std::vector<double>& row_cost,
 // floats).  Device sources are copied directly; host sources are padded into
 // two pinned staging buffers that alternate with the asynchronous copies.
 int upload_tensors(modal_ctx* c, const modal_desc* d, const std::vector<InstDev>& inst,
-                   const std::vector<BlockPlan>& plans, hipStream_t stream) {
+                   const BlockPlans& plans, hipStream_t stream) {
   const size_t kStage = 64u << 20;
   float* stage[2] = {nullptr, nullptr};
   hipEvent_t done[2] = {nullptr, nullptr};
@@ -1998,14 +2006,15 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   // between workgroups; so does its reverse sweep, unless a tangent tensor is
   // set.
   int chip_nt = 0, chip_rows = 0;
+  BlockPlans plans;
   if (d->waves == 0 && d->max_workgroups == 0 && !(d->flags & MODAL_FLAG_SPLIT_ANY) && !wave_lanes &&
-      !chip_plan(d, c->chips, chip_nt, chip_rows)) {
+      !chip_plan(d, plans, c->chips, chip_nt, chip_rows)) {
     chip_nt = chip_rows = 0;
     c->chips.clear();
   }
-  std::vector<BlockPlan> plans;
-  if (!latency && !chip_nt) plan_blocks(d, plans);
-  else plans.assign(d->batch, BlockPlan{});
+  const bool may_block = !latency && !(d->flags & (MODAL_FLAG_GRAD | MODAL_FLAG_NO_BLOCK));
+  if (chip_nt || !may_block) plans = BlockPlans{};  // held dense
+  else if (plans.of.empty()) plan_blocks(d, plans);
   std::vector<int> jmap_pool;
   c->mode_slot.assign(d->batch, {});
   for (int b = 0; b < d->batch; ++b) {
