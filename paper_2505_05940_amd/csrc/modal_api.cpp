@@ -2012,7 +2012,25 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     chip_nt = chip_rows = 0;
     c->chips.clear();
   }
+  // The on-chip plan holds tensors dense, up to six times the memory of their
+  // blocks.  A batch that would take more than half of what is free that way
+  // streams its blocks instead.
   const bool may_block = !latency && !(d->flags & (MODAL_FLAG_GRAD | MODAL_FLAG_NO_BLOCK));
+  if (chip_nt && may_block) {
+    double dense = 0., stored = 0.;
+    for (int b = 0; b < d->batch; ++b)
+      if (d->inst[b].kind == MODAL_KIND_VK) {
+        const double whole = 4.0 * d->inst[b].n_in * (double)d->inst[b].n_t * round4(d->inst[b].n_t);
+        dense += whole;
+        stored += plans[b].ok ? 4.0 * (double)plans[b].floats : whole;
+      }
+    size_t free_bytes = 0, total_bytes = 0;
+    if (dense > 1073741824.0 && stored < dense && hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess &&
+        dense > 0.5 * (double)free_bytes) {
+      chip_nt = chip_rows = 0;
+      c->chips.clear();
+    }
+  }
   if (chip_nt || !may_block) plans = BlockPlans{};  // held dense
   else if (plans.of.empty()) plan_blocks(d, plans);
   std::vector<int> jmap_pool;
