@@ -149,7 +149,9 @@ typedef struct {
                                    waves and max_workgroups 0, a batch whose
                                    key (modal_tune_key) is listed takes that
                                    launch shape; a missing file or key
-                                   leaves the defaults.  NULL = none.  An
+                                   leaves the defaults, and so does an entry
+                                   of zeros (they were the fastest).  NULL =
+                                   none.  An
                                    entry's optional "split_cost_kb" applies
                                    when split_cost_kb below is 0.           */
   int32_t split_cost_kb;        /* the per-step cost the planner charges each
@@ -383,8 +385,9 @@ int modal_tf_grad(const double *coef, const int32_t *mode_off, int32_t batch, in
 int modal_plan(const modal_desc *d, int32_t n_workgroups, int64_t out[4]);
 
 /* The autotuner's key of a batch: 16 hexadecimal digits of a hash of the
- * device name, the scheme, the planning flags and every instance's kind,
- * mode counts and block-structure hint (no tensor values).  out: host
+ * device name, the set of plans that modal_init knows, the scheme, the
+ * planning flags and every instance's kind, mode counts and block-structure
+ * hint (no tensor values).  out: host
  * memory of at least 17 chars.  EINVAL for a description modal_init would
  * reject, or len < 17. */
 int modal_tune_key(const modal_desc *d, char *out, int32_t len);

@@ -1768,6 +1768,11 @@ struct Fnv {
   void add_int(int32_t v) { add(&v, sizeof v); }
 };
 
+// Counts the sets of plans that modal_init chooses from by itself: a shape
+// tuned against another set would keep a batch from a plan that is new since
+// (batches without a tensor, and of small plates, streamed in set 1).
+constexpr int32_t kPlanSet = 2;
+
 int tune_key(const modal_desc* d, std::string& key) {
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
@@ -1775,6 +1780,7 @@ int tune_key(const modal_desc* d, std::string& key) {
   HIP_TRY(hipGetDeviceProperties(&prop, dev));
   Fnv f;
   f.add(prop.name, strnlen(prop.name, sizeof(prop.name)));
+  f.add_int(kPlanSet);
   f.add_int(d->batch);
   f.add_int(d->scheme);
   f.add_int(d->flags & ~(MODAL_FLAG_ASYNC | MODAL_FLAG_GRAPH));
@@ -1806,7 +1812,8 @@ bool json_int(const std::string& text, size_t from, size_t to, const char* name,
   return true;
 }
 
-// Launch shape for `d` from the autotuner's cache, if listed.
+// Launch shape for `d` from the autotuner's cache, if listed (an entry of
+// zeros: the default plan was the fastest).
 bool tuned_shape(const modal_desc* d, int& waves, int& max_wg, int& split_kb) {
   FILE* fp = std::fopen(d->tune_cache, "rb");
   if (!fp) return false;

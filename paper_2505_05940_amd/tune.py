@@ -6,12 +6,15 @@ charges a split instance (``split_cost_kb``), which decides which instances
 are cut into row slabs and how the units are packed; the slab sizes and the
 packing follow from them.  Each candidate (waves, workgroups per CU) is timed
 on the actual batch for a few hundred samples with HIP events, then each
-exchange cost with the best shape; the best is written to a JSON file under
+exchange cost with the best shape, and the plan that ``modal_init`` chooses by
+itself: an explicit shape always runs the step kernel, while many batches
+(without a tensor, of small plates, of a few large ones) have a faster kernel
+of their own.  The best, zeros for the default plan, is written to a JSON file under
 the batch's key (``modal.tune_key``: a hash of the device name and the
 batch's shapes), which ``modal_init`` reads when a context is created with
 ``tune_cache`` set and no explicit launch shape:
     {"<key>": {"waves": W, "max_workgroups": M, "split_cost_kb": S,
-               "ms_per_sample": ..., "trials": {"WxM": ms, "WxM/S": ms, ...}}, ...}
+               "ms_per_sample": ..., "trials": {"default": ms, "WxM": ms, "WxM/S": ms, ...}}, ...}
 """
 from __future__ import annotations
 
@@ -54,7 +57,8 @@ def autotune(insts, fs, shapes=SHAPES, samples=200, cache=CACHE, log=None, flags
     """The best (waves per workgroup, max_workgroups, split_cost_kb) for this
     batch: the shape among `shapes` = (waves, workgroups per CU) pairs, then
     the exchange cost among `split_costs` (KiB) with that shape, timed, and
-    recorded in `cache` (a cached entry is returned without timing)."""
+    recorded in `cache` (a cached entry is returned without timing); (0, 0, 0)
+    where none is faster than the default plan."""
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     key = modal.tune_key(insts, fs, flags=flags)
@@ -74,15 +78,20 @@ def autotune(insts, fs, shapes=SHAPES, samples=200, cache=CACHE, log=None, flags
         trials[f"{waves}x{mw}"] = ms
         if best_ms is None or ms < best_ms:
             best, best_ms = (waves, mw, 0), ms
-    if best is None:
+    default_ms = _time(insts, fs, flags, samples, log)
+    if best is None and default_ms is None:
         raise RuntimeError("autotune: no candidate launch shape fits the batch")
-    for sk in split_costs:
+    for sk in split_costs if best is not None else ():
         ms = _time(insts, fs, flags, samples, log, max_workgroups=best[1], waves=best[0], split_cost_kb=sk)
         if ms is None:
             continue
         trials[f"{best[0]}x{best[1]}/{sk}"] = ms
         if ms < best_ms:
             best, best_ms = (best[0], best[1], sk), ms
+    if default_ms is not None:
+        trials["default"] = default_ms
+        if best is None or default_ms <= best_ms:
+            best, best_ms = (0, 0, 0), default_ms
     # the optional cost is written before the trials: modal_init reads an
     # entry's fields up to its first closing brace
     table[key] = dict(waves=best[0], max_workgroups=best[1], split_cost_kb=best[2], ms_per_sample=best_ms,
