@@ -154,14 +154,22 @@ __global__ void __launch_bounds__(kWave * kChipWaves) chip_kernel(StepParams P) 
     }
     if (wave == kChipWaves - 1) {
       wave_lds_sync();
-      // as a tree, so that 64 modes cost six roundings
-      float4 t[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float* q = &ys[lane][16 * i];
-        t[i] = add4(add4(ld4(q), ld4(q + 4)), add4(ld4(q + 8), ld4(q + 12)));
+      // as a tree, so that 64 modes cost six roundings; in loops, which leave
+      // the tile its registers
+      float4 a = f4(0.f);
+#pragma unroll 1
+      for (int i = 0; i < kWave; i += 32) {
+        float4 t = f4(0.f);
+#pragma unroll 1
+        for (int g = i; g < i + 32; g += 16) {
+          const float* q = &ys[lane][g];
+          float4 u = ld4(q);
+          u = add4(u, ld4(q + 4));
+          asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w));
+          t = add4(t, add4(u, add4(ld4(q + 8), ld4(q + 12))));
+        }
+        a = add4(a, t);
       }
-      const float4 a = add4(add4(t[0], t[1]), add4(t[2], t[3]));
       if (lane < js && P.y) P.y[(long long)I.out_row * P.y_stride + s0 + lane] = (a.x + a.y) + (a.z + a.w);
       wave_lds_sync();
     }
