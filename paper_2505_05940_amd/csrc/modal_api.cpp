@@ -1878,7 +1878,7 @@ static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::v
       InstDev& I = c->lat_inst[b];
       const int rows = I.nin, nblk = (I.nt + qs_of[b] - 1) / qs_of[b];
       int S = std::max(1, nslab[b]);
-      if (regs && S > 1 && !I.blk) S = std::max(S, lat_slabs(rows, nblk, cus / batch));
+      if (regs && S > 1) S = std::max(S, lat_slabs(rows, nblk, cus / batch));
       I.nslab = S;
       I.part_off = c->n_part;
       if (S > 1) c->n_part += 2LL * S * I.ntp;
@@ -1891,7 +1891,7 @@ static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::v
         U.state_off = c->unit_state_of_inst[b];
         U.qs = qs_of[b];
         c->lat_units.push_back(U);
-        share = std::max(share, I.blk ? kLatRegBlocks + 1 : ((U.row1 - U.row0) * nblk + 7) / 8);
+        share = std::max(share, ((U.row1 - U.row0) * nblk + 7) / 8);
       }
     }
     c->lat_nb = regs ? (share <= 4 ? 4 : 8) : 0;

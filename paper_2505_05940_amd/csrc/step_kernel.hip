@@ -951,7 +951,8 @@ struct RowRegs {
 
 // ------------------------------------------------------------- latency kernel
 // The step of a plan whose every workgroup owns one von Karman unit for the
-// whole launch: a whole instance, or a slab of a split one.  Such a plan is
+// whole launch: a whole instance, or a slab of a split one, its tensor dense
+// (latency plans store no blocks).  Such a plan is
 // bound by the chain of one step, not by the tensor's bytes, so the chain is
 // what this kernel shortens against step_kernel:
 //   - a thread owns a mode (or MP), with its state and coefficients in
@@ -1114,7 +1115,7 @@ __global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
   }
   const int R = U.row1 - U.row0, nblk = (I.nt + U.qs - 1) / U.qs, T = R * nblk;
   const int tw0 = (T * wave) / NW, tw1 = (T * (wave + 1)) / NW;  // the wave's share of the unit's blocks
-  const bool shared_rows = NB > 0 || (!I.blk && 2 * R <= NW);
+  const bool shared_rows = NB > 0 || 2 * R <= NW;
   bool cut = false;  // a wave boundary inside a row
   for (int w = 1; w < NW; ++w) cut |= ((T * w) / NW) % nblk != 0;
   float* xv = L.xch;
@@ -1152,11 +1153,7 @@ __global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
       }
     } else {
       const int r0 = U.row0 + (R * wave) / NW, r1 = U.row0 + (R * (wave + 1)) / NW;
-      if (I.blk)
-        vk_rows_blk<GM>(P.H + I.h_off, P.jmap + I.jmap_off, I, r0, r1, Xs, red, Fa, G, lane);
-      else
-        vk_rows<GM, (NW == 8 && GM <= 2) ? 3 : 2, kKeep>(P.H + I.h_off, I.nt, ntp, U.qs, r0, r1, Xs, red, Fa, G,
-                                                         lane);
+      vk_rows<GM, (NW == 8 && GM <= 2) ? 3 : 2, kKeep>(P.H + I.h_off, I.nt, ntp, U.qs, r0, r1, Xs, red, Fa, G, lane);
     }
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
