@@ -592,22 +592,25 @@ constexpr double kLatencyBigTensor = 16.0 * 1048576.0;
 constexpr int kLatRegBlocks = 8;  // row blocks (4 KB) of a wave that the latency kernel keeps in registers
 
 // Slabs of a split instance whose rows, of nblk blocks each, the latency
-// kernel keeps in registers (0: more than `cap`): of two rows, so that four
-// waves share a row's reduction, or more where that is more slabs than read
-// each other's forces directly; beyond those the fewest.  Lone sine plates in
-// slabs of one, two, four rows and as many as fit, us a step: 80/80 5.3, 4.1,
-// 3.7, 4.8; 100/100 5.6, 4.3, 4.9, 6.0; 128/128 5.6, 4.3, 5.0, 5.0; 160/160
-// 6.3, 6.8 (two fit).
+// kernel keeps in registers (0: more than `cap`).  Four, two or one row a slab
+// gives each row a whole number of the eight waves; the most of them whose
+// blocks are at most four a wave (the smaller register tile), four only where
+// the rows divide by it.  Where even one row takes more, or the slabs are more
+// than `cap`, the fewest more rows a slab that fit.  Lone sine plates in slabs
+// of one, two and four rows, us a step: 66/66 5.0, 3.7, 4.2 (17 uneven slabs);
+// 72/72 5.1, 3.9, 3.6; 80/80 5.3, 4.1, 3.7; 100/100 5.4, 4.3, 4.5; 112/112 5.4,
+// 4.2, 4.7; 128/128 5.7, 4.3, 4.8 (the last three over four blocks a wave with
+// four rows); 144/144 and 160/160 5.9 and 6.4 with one, 6.2 and 6.7 with two
+// (five blocks and more); gradients alike.
 int lat_slabs(int rows, int nblk, int cap) {
   const int most = 8 * kLatRegBlocks / nblk;
   if (most < 1) return 0;
-  int S = (rows + most - 1) / most;
-  for (int m = std::min(2, most); m <= most; ++m)
-    if ((rows + m - 1) / m <= kPairSlabs) {
-      S = (rows + m - 1) / m;
-      break;
-    }
-  return S <= cap ? S : 0;
+  int m = 1;
+  if (2 * nblk <= 4 * 8) m = 2;
+  if (4 * nblk <= 4 * 8 && rows % 4 == 0) m = 4;
+  for (; m <= most; ++m)
+    if ((rows + m - 1) / m <= cap) return (rows + m - 1) / m;
+  return 0;
 }
 
 // Per-step cost of the exchange and barrier of one slab of a split instance,
