@@ -271,10 +271,11 @@ int modal_get_state(modal_ctx *c, double *x, double *xm1, void *stream);
  * recursion, 1 shared tensor (then [1] is the number of instance columns
  * and [2], [8], [9] are 0), 2 linear closed form, 3 on-chip recursion
  * (one workgroup of 8 waves per instance, or without tensors one-wave
- * workgroups of 1, 2 or 4 instances; [6] 0); the units that the latency
- * kernel cuts for itself are not reported; a context with
- * MODAL_FLAG_GRAD reports its persistent plan here, also where it steps on
- * chip,
+ * workgroups of 1, 2 or 4 instances; [6] 0).  [0]..[2], [4], [6]..[9] and
+ * [14] describe the plan; which kernels run on it or beside it (the latency
+ * kernel on slabs of its own, the kernel of shared tensors by class in place
+ * of the dense tiling described here, the on-chip kernels in a context with
+ * MODAL_FLAG_GRAD) is reported by modal_launches,
  * [11] FP32 operations of the force per step (sum over VK instances of
  * 2 n_in n_t^2 + 4 n_in n_t), [12] instances stored parity-blocked,
  * [13] dense-equivalent tensor bytes per step (sum of 4 n_in n_t^2),
@@ -284,6 +285,19 @@ int modal_get_state(modal_ctx *c, double *x, double *xm1, void *stream);
  * [3] counts the entries of the stored representation: for a blocked
  * instance, 4 bytes per entry of its stored blocks without padding. */
 int modal_info(const modal_ctx *c, int64_t info[15]);
+
+/* The kernels that modal_run and modal_grad launch now (a tangent or a
+ * replaced tensor may change them):
+ * out[0] the kernel that modal_run steps on: 0 streaming, 1 streaming with
+ * the state resident in LDS, 2 on chip, 3 wave, 4 latency, 5 shared tensor,
+ * 6 shared tensor by class, 7 linear closed form, [1] its workgroups (0 for
+ * the closed form, whose grid depends on the steps), [2] waves per
+ * workgroup, [3] dynamic LDS bytes, [4] most workgroups of one instance,
+ * [5] row blocks of 4 KB per wave that the latency kernel keeps in registers
+ * (0: streamed) or tensor columns per lane of the on-chip kernel, else 0,
+ * [6] the kernel of modal_grad's reverse sweep (0..4 as above, -1 without
+ * MODAL_FLAG_GRAD) and [7] its workgroups. */
+int modal_launches(const modal_ctx *c, int64_t out[8]);
 
 void modal_destroy(modal_ctx *c);
 

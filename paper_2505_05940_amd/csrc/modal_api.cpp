@@ -2547,6 +2547,8 @@ static bool forward_waits(const modal_ctx* c) {
   return !c->shared && !c->wave_lanes && !c->chip_nt && (c->lat ? c->n_part > 0 : c->n_split > 0);
 }
 
+static bool reverse_on_lat(const modal_ctx* c) { return c->lat && c->lat_red && !c->chip_nt && !c->tangent; }
+
 // A launch on s may raise the device's flags: the next check on s reads them.
 static void raises_dev_flags(modal_ctx* c, hipStream_t s) {
   c->dev_flags = true;
@@ -3118,7 +3120,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   HIP_TRY(hipMemsetAsync(c->dAdj, 0, sizeof(double) * 2 * (size_t)sf, s));
   HIP_TRY(hipMemsetAsync(c->dAcc, 0, sizeof(double) * 6 * (size_t)sf, s));
   HIP_TRY(hipMemsetAsync(c->dGCtr, 0, sizeof(unsigned int) * c->n_ctr, s));
-  const bool lat_rev = c->lat && c->lat_red && !c->chip_nt && !c->tangent;
+  const bool lat_rev = reverse_on_lat(c);
   if (lat_rev) {
     const size_t g_bytes = sizeof(double) * 4 * kWave * c->lat_units.size();
     const size_t w_bytes = sizeof(unsigned long long) * (size_t)(c->n_pair + 1);
@@ -3321,6 +3323,38 @@ int modal_info(const modal_ctx* c, int64_t info[15]) {
   info[12] = c->n_blocked;
   info[13] = c->shared ? c->coupling_bytes : c->dense_bytes;
   info[14] = c->res_stride;
+  return MODAL_OK;
+}
+
+int modal_launches(const modal_ctx* c, int64_t out[8]) {
+  if (!c || !out) return fail(MODAL_EINVAL, "NULL argument");
+  enum { STREAM, RESIDENT, CHIP, WAVE, LAT, SHARED, SHARED_CLASS, LINEAR };
+  auto most_of = [](const std::vector<InstDev>& inst) {
+    int n = 1;
+    for (const InstDev& I : inst) n = std::max(n, I.nslab);
+    return n;
+  };
+  const int plan = c->res_stride > 0 ? RESIDENT : STREAM;
+  const int wave_wg = c->wave_lanes ? (c->batch + kWave / c->wave_lanes - 1) / (kWave / c->wave_lanes) : 0;
+  for (int i = 0; i < 8; ++i) out[i] = 0;
+  auto forward = [&](int kernel, int64_t wg, int waves, size_t lds, int most, int tile) {
+    const int64_t v[6] = {kernel, wg, waves, (int64_t)lds, most, tile};
+    std::copy(v, v + 6, out);
+  };
+  if (c->linear) forward(LINEAR, 0, kLinWaves, 0, 1, 0);
+  else if (c->sc_ks) forward(SHARED_CLASS, c->sc_wg, kScWaves, 0, 1, 0);
+  else if (c->shared) forward(SHARED, c->n_wg, kSharedWaves, c->lds_bytes, 1, 0);
+  else if (c->wave_lanes) forward(WAVE, wave_wg, 1, 0, 1, 0);
+  else if (c->chip_nt) forward(CHIP, c->batch, kChipWaves, 0, 1, c->chip_nt);
+  else if (c->lat) forward(LAT, (int64_t)c->lat_units.size(), c->nw, c->lds_bytes, most_of(c->lat_inst), c->lat_nb);
+  else forward(plan, c->n_wg, c->nw, c->lds_bytes, most_of(c->inst_host), 0);
+  out[6] = -1;
+  if (c->flags & MODAL_FLAG_GRAD) {
+    if (c->wave_lanes) out[6] = WAVE, out[7] = wave_wg;
+    else if (c->chip_nt && !c->tangent) out[6] = CHIP, out[7] = c->batch;
+    else if (reverse_on_lat(c)) out[6] = LAT, out[7] = (int64_t)c->lat_units.size();
+    else out[6] = plan, out[7] = c->n_wg;
+  }
   return MODAL_OK;
 }
 

@@ -68,6 +68,7 @@ def _load():
     lib.modal_reset.argtypes = [vp, vp]
     lib.modal_get_state.argtypes = [vp, _dp, _dp, vp]
     lib.modal_info.argtypes = [vp, C.POINTER(C.c_int64)]
+    lib.modal_launches.argtypes = [vp, C.POINTER(C.c_int64)]
     lib.modal_destroy.argtypes = [vp]
     lib.modal_destroy.restype = None
     lib.modal_last_error.restype = C.c_char_p
@@ -88,7 +89,7 @@ def _load():
     lib.modal_tf_response.argtypes = [vp, vp, C.c_int32, vp, C.c_int32, vp, vp]
     lib.modal_tf_grad.argtypes = [vp, vp, C.c_int32, C.c_int32, vp, C.c_int32, vp, vp, vp]
     for f in ("modal_init", "modal_run", "modal_run_noalloc", "modal_check", "modal_reset", "modal_get_state",
-              "modal_info", "modal_vk_coupling_sine", "modal_tf_response", "modal_tf_grad"):
+              "modal_info", "modal_launches", "modal_vk_coupling_sine", "modal_tf_response", "modal_tf_grad"):
         getattr(lib, f).restype = C.c_int
     return lib
 
@@ -361,6 +362,14 @@ class Sim:
         out = dict(zip(keys, list(v)))
         out["shared"] = int(out["path"] == 1)  # 0 recursion, 1 shared tensor, 2 linear closed form
         return out
+
+    def launches(self):
+        """The kernels that ``run`` and ``grad`` launch now (``modal_launches``)."""
+        v = (C.c_int64 * 8)()
+        _check(lib.modal_launches(self._ctx, v))
+        names = ("streaming", "resident", "on-chip", "wave", "latency", "shared", "shared by class", "linear")
+        return dict(kernel=names[v[0]], workgroups=v[1], waves=v[2], lds_bytes=v[3], instance_workgroups=v[4],
+                    tile=v[5], reverse=names[v[6]] if v[6] >= 0 else None, reverse_workgroups=v[7])
 
     def close(self):
         if self._ctx:
