@@ -629,8 +629,12 @@ double split_cost(const modal_desc* d) {
 // outruns its slabs' exchange (2-4 us a step).  128 plates of 50-400 modes, us
 // a step with 4, 2, 1, 0.5 MB: 341, 299, 301, 300; 128 of 50-200: 323, 179,
 // 90, 63 (109 to 768 workgroups); 32 of 50-400: 281, 178, 128, 129; 256 of
-// 60-120: 125, 106, 95, 95.  The larger bound left CUs idle: a batch's
-// capacity is at least its largest whole instance.
+// 60-120: 125, 106, 95, 95.  Gradient contexts, whose tensors are dense,
+// forward and reverse: 64 of 65-100 122+153, 58+75, 31+40, 31+40; 128 of
+// 50-120 130+158, 78+101, 74+101, 74+101; 40 of 80 40+47, then 16+20; batches
+// that fill the GPU with whole instances (300 of 80, 800 of 66) the same with
+// any.  The larger bound left CUs idle: a batch's capacity is at least its
+// largest whole instance.
 constexpr double kMinSplitCost = 0.5 * 1048576.0;
 // A batch of at most one instance per CU whose instances all cost less than
 // this is bound by a step's latency: eight waves a workgroup.
