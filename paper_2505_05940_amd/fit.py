@@ -156,9 +156,13 @@ def plate_instance_shared(setup: PlateSetup, theta):
     zeta2 = _lam(ai, bi, a, setup.area)
     pref = math.sqrt(6.0 * (1.0 - setup.nu ** 2) * Dh / setup.h ** 2)
     x0, c = _excitation_cached(setup, a)
-    return dict(kind="vk", omega=omega, gamma=gamma, lam=lam, Ht=base_tensor(setup),
-                h_row_scale=pref / zeta2, x0=x0, xm1=x0.copy(), c=c, zeta2=zeta2,
-                mode_class=_classes(setup))
+    inst = dict(kind="vk", omega=omega, gamma=gamma, lam=lam, Ht=base_tensor(setup),
+                h_row_scale=pref / zeta2, x0=x0, xm1=x0.copy(), c=c, zeta2=zeta2)
+    # the kernels of at most 64 modes use the classes; a larger plate's tensor
+    # would be stored by class, and could then not be replaced
+    if len(m) <= 64:
+        inst["mode_class"] = _classes(setup)
+    return inst
 
 
 def plate_instances_shared(setup: PlateSetup, thetas):
@@ -174,9 +178,10 @@ def plate_instances_shared(setup: PlateSetup, thetas):
     zeta2 = _lam(ai, bi, a, setup.area)
     scale = np.sqrt(6.0 * (1.0 - setup.nu ** 2) * Dh / setup.h ** 2) / zeta2
     x0, c = excitations(setup, th[:, 2])
-    Ht, cls = base_tensor(setup), _classes(setup)
+    Ht = base_tensor(setup)
+    extra = dict(mode_class=_classes(setup)) if len(m) <= 64 else {}
     insts = [dict(kind="vk", omega=omega[b], gamma=gamma[b], lam=lam[b], Ht=Ht, h_row_scale=scale[b], x0=x0[b],
-                  xm1=x0[b], c=c[b], zeta2=zeta2[b], mode_class=cls) for b in range(len(th))]
+                  xm1=x0[b], c=c[b], zeta2=zeta2[b], **extra) for b in range(len(th))]
     return insts, lam, omega
 
 
