@@ -355,9 +355,13 @@ int modal_grad(modal_ctx *c, int64_t n_steps, const float *dL_dy, int64_t y_stri
  * be exactly symmetric in its last two indices, as the coupling coefficients
  * are (checked; the kernels contract rows by that symmetry); a fit keeps it
  * so by stepping with the symmetric part of g_H.  The state is left as it
- * is.  ESTATE on the shared-tensor and linear paths and for parity-blocked
- * instances (MODAL_FLAG_GRAD keeps tensors dense); EINVAL for a bad index or
- * an asymmetric tensor (the stored tensor is then unchanged). */
+ * is, and replays of launches that a caller captured go on with the new
+ * tensor.  ESTATE on the shared-tensor and linear paths, for parity-blocked
+ * instances (MODAL_FLAG_GRAD keeps tensors dense), and for a tensor that has
+ * entries outside its mode_class structure where captured launches hold it
+ * on chip by class (only without MODAL_FLAG_GRAD and MODAL_FLAG_NO_BLOCK);
+ * EINVAL for a bad index or an asymmetric tensor (the stored tensor is then
+ * unchanged). */
 int modal_set_tensor(modal_ctx *c, int32_t inst, const float *H, void *stream);
 
 /* Transfer-function response of linear modal systems (paper: Sec. 3.2,

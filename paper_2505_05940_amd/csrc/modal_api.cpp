@@ -37,6 +37,8 @@ hipError_t launch_lat_sum(const InstDev* inst, const UnitDev* unit, int n_units,
 hipError_t launch_advance(long long* step_base, int n, hipStream_t s);
 hipError_t launch_ctr_fill(const InstDev* inst, int batch, const long long* step_base, unsigned int* ctr,
                            hipStream_t s);
+hipError_t launch_spread(const InstDev* inst, const UnitDev* unit, int n_units, double* state, int state_floats,
+                         unsigned int* ctr, const long long* step_base, hipStream_t s);
 hipError_t launch_check(const float* H, const InstDev* inst, int batch, int* out, hipStream_t s);
 hipError_t step_occupancy(int* blocks_per_cu, int gm, int nw, size_t lds_bytes, bool res = false);
 hipError_t launch_chip(const StepParams& P, int nt_tile, int rows, int n_wg, hipStream_t s);
@@ -232,6 +234,14 @@ struct modal_ctx {
   // the tensor's mode classes make zero)
   int chip_nt = 0, chip_rows = 0;
   ChipMap* dChip = nullptr;
+  // Where chip_nt is a tile of mode classes, launches that a caller captures
+  // in contexts that keep tensors dense (gradients, no blocks) take another
+  // kernel, so that their replays hold for any tensor that replaces one: the
+  // tile in which every tensor fits whole, with layouts for it, or if there is
+  // none the streaming plan.
+  int whole_nt = 0, whole_rows = 0;
+  ChipMap* dChipWhole = nullptr;
+  bool capture_streams = false;
   struct Chip {
     ChipMap map;
     int w, r;
@@ -272,6 +282,7 @@ struct modal_ctx {
   // a launch was recorded by a caller's capture: its replays advance the
   // device's step counter unseen, so every later launch reads that one
   bool captured = false;
+  bool capturing = false;  // the launches being enqueued are
   long long* dStep = nullptr;
   float* dE = nullptr;
   StepParams P{};
@@ -452,7 +463,7 @@ void free_ctx(modal_ctx* c) {
                   c->dStep, c->dE,   c->dHd,   c->dCkpt,  c->dRec,  c->dAdj, c->dAcc,
                   c->dGPart, c->dGCtr, c->dShA, c->dShS2, c->dJmap, c->dRrec, c->dRacc,
                   c->dLinModes, c->dLinInit, c->dLinInst, c->dLinAmp, c->dLinZ, c->dLinS, c->dLinForced,
-                  c->dLinH, c->dUrec, c->dTrec, c->dTJobs, c->dRecAll, c->dChip};
+                  c->dLinH, c->dUrec, c->dTrec, c->dTJobs, c->dRecAll, c->dChip, c->dChipWhole};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->hFlags) (void)hipHostFree(c->hFlags);  // (no launch is left: hipFree waits for the device)
@@ -486,7 +497,8 @@ bool host_steps(modal_ctx* c, hipStream_t s) {
     (void)hipGetLastError();
     st = hipStreamCaptureStatusActive;
   }
-  if (st != hipStreamCaptureStatusNone) c->captured = true;
+  c->capturing = st != hipStreamCaptureStatusNone;
+  c->captured |= c->capturing;
   return !c->captured;
 }
 
@@ -1212,6 +1224,21 @@ int upload_tensors(modal_ctx* c, const modal_desc* d, const std::vector<InstDev>
 #undef UP_TRY
   cleanup();
   return MODAL_OK;
+}
+
+// The layouts in which every tensor of the batch is held whole; false if it
+// does not fit so.
+bool chip_plan_whole(const modal_ctx* c, const modal_desc* d, std::vector<ChipMap>& maps, int& w_tile, int& rows) {
+  maps.resize(d->batch);
+  int max_w = 0, max_r = 0;
+  for (int b = 0; b < d->batch; ++b) {
+    int w = 0, r = 0;
+    if (!chip_map(d->inst[b], BlockPlan{}, maps[b], w, r)) return false;
+    maps[b].unit = c->chips[b].map.unit;
+    max_w = std::max(max_w, w);
+    max_r = std::max(max_r, r);
+  }
+  return chip_shape(max_w, max_r, w_tile, rows);
 }
 
 // The register layouts of the on-chip kernels, to the device.
@@ -2434,6 +2461,19 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
         if (udev[u].slab == 0) c->chips[udev[u].inst].map.unit = u;
       r = upload_chips(c, stream);
       if (r) return bail(r);
+      const bool grouped = std::any_of(c->chips.begin(), c->chips.end(), [](const modal_ctx::Chip& h) { return h.grouped; });
+      std::vector<ChipMap> whole;
+      if (grouped && (d->flags & (MODAL_FLAG_GRAD | MODAL_FLAG_NO_BLOCK))) {
+        if (chip_plan_whole(c, d, whole, c->whole_nt, c->whole_rows)) {
+          r = dalloc(&c->dChipWhole, sizeof(ChipMap) * whole.size());
+          if (r) return bail(r);
+          HIP_TRY_C(hipMemcpyAsync(c->dChipWhole, whole.data(), sizeof(ChipMap) * whole.size(), hipMemcpyHostToDevice, stream));
+          HIP_TRY_C(hipStreamSynchronize(stream));
+        } else {
+          c->whole_nt = c->whole_rows = 0;
+          c->capture_streams = true;
+        }
+      }
     }
   }
   char* meta = (char*)c->dMeta;
@@ -2564,21 +2604,35 @@ static int launch_forward(modal_ctx* c, StepParams P, hipStream_t s) {
   const bool streams = !c->wave_lanes && !c->chip_nt;
   P.flags = streams || !c->hFlags ? c->dFlags : c->hFlags;
   if (P.flags == c->dFlags) raises_dev_flags(c, s);
+  const bool captured_stream = c->chip_nt && c->capturing && c->capture_streams;
+  if (captured_stream) {
+    P.flags = c->dFlags;
+    raises_dev_flags(c, s);
+    // the on-chip kernel keeps the state of slab 0 and no words
+    HIP_TRY(launch_spread(c->P.inst, c->P.unit, c->n_units, c->dState, c->state_floats, P.ctr, c->dStep, s));
+    if (c->n_pair) HIP_TRY(launch_pair_fill(c->dPair, c->n_pair, c->dStep, s));
+  }
   if (c->wave_lanes)
     HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
-  else if (c->chip_nt)
+  else if (c->chip_nt && c->capturing && c->whole_nt) {
+    P.chip = c->dChipWhole;
+    HIP_TRY(launch_chip(P, c->whole_nt, c->whole_rows, c->batch, s));
+  } else if (c->chip_nt && !captured_stream)
     HIP_TRY(launch_chip(P, c->chip_nt, c->chip_rows, c->batch, s));
   else if (c->lat) {
     P.inst = (const InstDev*)c->dLat;
     P.unit = (const UnitDev*)(c->dLat + sizeof(InstDev) * c->batch);
     HIP_TRY(launch_lat(P, c->gm, c->nw, c->lat_nb, (int)c->lat_units.size(), c->lds_bytes, s));
-  } else
+  } else if (captured_stream && !(c->flags & MODAL_FLAG_GRAD))
+    HIP_TRY(launch_step(P, c->gm, c->nw_stream, c->n_wg, c->lds_stream, s));
+  else
     HIP_TRY(launch_step(P, c->gm, c->nw, c->n_wg, c->lds_bytes, s));
   return MODAL_OK;
 }
 
 static int enqueue_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, hipStream_t s) {
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
+  c->capturing = false;  // (the context's own graphs end where the layouts they launch do)
   const bool known = !(c->flags & MODAL_FLAG_GRAPH) && host_steps(c, s);
   if (known && ++c->n_runs == 2 && !c->hFlags && (c->shared || c->wave_lanes || c->chip_nt)) alloc_host_flags(c);
   for (int64_t done = 0; done < n_steps; done += chunk) {
@@ -2900,8 +2954,32 @@ int modal_tf_grad(const double* coef, const int32_t* mode_off, int32_t batch, in
   return MODAL_OK;
 }
 
+// Whether tensor H (host memory) of instance b has entries that its on-chip
+// layout leaves out.
+static bool chip_leaves_out(const modal_ctx* c, int b, const float* H) {
+  const ChipMap& M = c->chips[b].map;
+  const int nt = c->inst_host[b].nt, lanes = kWave;
+  std::vector<char> held(nt);
+  for (int w = 0; w < kChipWaves; ++w)
+    for (int p = 0; p < lanes; ++p) {
+      const int k = M.perm[p];
+      if (k < 0) continue;
+      std::fill(held.begin(), held.end(), 0);
+      for (int t = 0; t < M.jl[w][p]; ++t)
+        if (M.perm[M.jb[w][p] + t] >= 0) held[M.perm[M.jb[w][p] + t]] = 1;
+      for (int r = 0; r < kChipMaxRows; ++r) {
+        const int n = M.row[w][r];
+        if (n < 0) continue;
+        const float* row = H + ((size_t)n * nt + k) * nt;
+        for (int j = 0; j < nt; ++j)
+          if (!held[j] && row[j] != 0.f) return true;
+      }
+    }
+  return false;
+}
+
 // A tensor about to replace one whose on-chip layout leaves out the entries
-// that mode classes make zero may have entries there: instance b's tensor is
+// that mode classes make zero has entries there: instance b's tensor is
 // held whole from now on, where the tile allows it; else the batch goes back
 // to the streaming kernel, every slab of an instance starting from the state
 // that its slab 0 holds.
@@ -2979,8 +3057,22 @@ int modal_set_tensor(modal_ctx* c, int32_t b, const float* H, void* stream_) {
   }
   if (!symmetric) return fail(MODAL_EINVAL, "tensor is not symmetric in its last two indices");
   if (c->chip_nt && c->chips[b].grouped) {
-    int r = chip_ungroup(c, b, s);
-    if (r) return r;
+    std::vector<float> copy;
+    const float* host = H;
+    if (on_device) {
+      copy.resize((size_t)D.nin * D.nt * D.nt);
+      HIP_TRY(hipMemcpyAsync(copy.data(), H, sizeof(float) * copy.size(), hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
+      host = copy.data();
+    }
+    if (chip_leaves_out(c, b, host)) {
+      // (replays would go on without the entries)
+      if (c->captured && !c->whole_nt && !c->capture_streams)
+        return fail(MODAL_ESTATE, "launches that were captured hold the instance's tensor by mode class, and this one "
+                                  "has other entries");
+      int r = chip_ungroup(c, b, s);
+      if (r) return r;
+    }
   }
   HIP_TRY(hipMemcpy2DAsync(c->dH + D.h_off, sizeof(float) * D.ntp, H, sizeof(float) * D.nt,
                            sizeof(float) * D.nt, (size_t)D.nin * D.nt, hipMemcpyDefault, s));
@@ -3090,6 +3182,7 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   // on chip unless a tangent tensor is set; there the sums over the rows stay
   // in the kernel, and with the whole trajectory recorded one launch sweeps it
   const bool on_chip = c->wave_lanes || (c->chip_nt && !c->tangent);
+  c->capturing = false;
   std::optional<Together> room(std::in_place, c, forward_waits(c) || (!on_chip && (c->n_split > 0 || c->n_part > 0)), s);
   // the forward pass also records the whole trajectory while it fits, so
   // that the reverse sweep needs no segment recomputes

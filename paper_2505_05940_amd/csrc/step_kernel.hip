@@ -1426,6 +1426,23 @@ __global__ void ctr_fill_kernel(const InstDev* inst, int batch, const long long*
   for (int t = 0; t < inst[b].nslab; ++t) ctr[inst[b].ctr_off + t] = v;
 }
 
+// Every slab's copy of the state from its instance's slab 0, and the arrival
+// words as ctr_fill_kernel sets them: what the streaming kernel needs after
+// steps on chip.
+__global__ void spread_kernel(const InstDev* inst, const UnitDev* unit, int n_units, double* state, int state_floats,
+                              unsigned int* ctr, const long long* step_base) {
+  const UnitDev U = unit[blockIdx.x];
+  const InstDev I = inst[U.inst];
+  if (threadIdx.x == 0) ctr[I.ctr_off + U.slab] = (unsigned int)(unsigned long long)*step_base;
+  if (U.slab == 0) return;
+  int from = 0;  // the instance's slab 0
+  for (int u = 0; u < n_units; ++u)
+    if (unit[u].inst == U.inst && unit[u].slab == 0) from = unit[u].state_off;
+  for (int k = threadIdx.x; k < I.ntp; k += blockDim.x)
+    for (int a = 0; a < 2; ++a)
+      state[(long long)a * state_floats + U.state_off + k] = state[(long long)a * state_floats + from + k];
+}
+
 // Symmetry and finiteness of each instance's Ht: out[2b] = max |H - H^T|,
 // out[2b+1] = max |H|, both as float bits (non-negative floats order like
 // their bit patterns); a non-finite entry reports +inf in both.
@@ -1512,6 +1529,12 @@ hipError_t launch_ctr_fill(const InstDev* inst, int batch, const long long* step
 hipError_t launch_pair_fill(unsigned long long* pair, long long n, const long long* step_base, hipStream_t s) {
   hipLaunchKernelGGL(pair_fill_kernel, dim3((unsigned)std::min<long long>((n + 255) / 256, 1024)), dim3(256), 0, s, pair,
                      n, step_base);
+  return hipGetLastError();
+}
+hipError_t launch_spread(const InstDev* inst, const UnitDev* unit, int n_units, double* state, int state_floats,
+                         unsigned int* ctr, const long long* step_base, hipStream_t s) {
+  hipLaunchKernelGGL(spread_kernel, dim3(n_units), dim3(kWave), 0, s, inst, unit, n_units, state, state_floats, ctr,
+                     step_base);
   return hipGetLastError();
 }
 // gm, nw, lds_bytes as launch_step's with resident state; nb: blocks a wave of
