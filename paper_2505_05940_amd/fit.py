@@ -189,9 +189,14 @@ def excitations(setup, aspects):
     """Strike projections and pickup weights [len(aspects), n_t] of ``_excitation``
     at many aspect ratios at once: the bump is zero outside a few cells around
     the strike, so only that box of the grid is projected, for all of them in
-    one product (64 plates at two aspects each took 25 ms one by one)."""
+    one product (64 plates at two aspects each took 25 ms one by one), as many
+    at a time as keep the boxes to about 100 MB."""
     m, q, _, _ = setup.modes
     a = np.asarray(aspects, float)
+    per = max(1, 2_500_000 // (setup.proj_grid[0] * setup.proj_grid[1]))  # a box is at most the grid
+    if len(a) > per:
+        parts = [excitations(setup, a[i:i + per]) for i in range(0, len(a), per)]
+        return tuple(np.concatenate(p) for p in zip(*parts))
     Lx, Ly = np.sqrt(setup.area / a), np.sqrt(setup.area * a)
     xc, yc, amp, rr = setup.strike
     # sin(k pi (i + 1/2) / n) per axis: the midpoint projection in coordinates
