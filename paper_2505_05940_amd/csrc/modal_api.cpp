@@ -2940,13 +2940,16 @@ int modal_tf_grad(const double* coef, const int32_t* mode_off, int32_t batch, in
   int r = tf_check(mode_off, batch, n_freq, modes);
   if (r) return r;
   if (max_modes < 0) return fail(MODAL_EINVAL, "max_modes");
-  for (int b = 0; b < batch; ++b)
+  int most = 0;
+  for (int b = 0; b < batch; ++b) {
     if (mode_off[b + 1] - mode_off[b] > max_modes) return fail(MODAL_EINVAL, "an instance has more than max_modes modes");
+    most = std::max(most, mode_off[b + 1] - mode_off[b]);
+  }
   hipStream_t s = (hipStream_t)stream_;
   TfCall t;
   r = tf_upload(t, coef, mode_off, batch, omega, n_freq, modes, dL_dH, 5 * (size_t)modes, s);
   if (r) return r;
-  HIP_TRY(launch_tf_grad(t.coef, t.off, batch, max_modes, t.omega, n_freq, t.g, t.out, s));
+  HIP_TRY(launch_tf_grad(t.coef, t.off, batch, most, t.omega, n_freq, t.g, t.out, s));
   // the instances' ranges are contiguous
   const size_t m0 = (size_t)mode_off[0], n = 5 * ((size_t)modes - m0);
   if (n) HIP_TRY(hipMemcpyAsync(g_coef + 5 * m0, t.out + 5 * m0, sizeof(double) * n, hipMemcpyDeviceToHost, s));

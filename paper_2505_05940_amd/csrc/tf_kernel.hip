@@ -19,6 +19,8 @@
 // with one wave a mode.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace modal {
@@ -118,16 +120,18 @@ __device__ __forceinline__ ff lanes_sum(ff v) {
 
 constexpr int kTfFreqs = 16, kTfLanes = 16;  // frequencies per workgroup, lanes over modes
 constexpr int kTfThreads = 256;              // threads of a mode's gradient
+constexpr int kTfBlocks = 1 << 23;           // workgroups along x of a launch: 2^31 threads, a grid takes under 2^32
 
 }  // namespace
 
 __global__ void __launch_bounds__(kTfFreqs* kTfLanes) tf_response_kernel(const double* __restrict__ coef,
                                                                          const int* __restrict__ mode_off,
-                                                                         const double* __restrict__ omega, int n_freq,
-                                                                         double2* __restrict__ H) {
-  const int k = blockIdx.x * kTfFreqs + threadIdx.x / kTfLanes, ml = threadIdx.x % kTfLanes;
+                                                                         const double* __restrict__ omega, int k0,
+                                                                         int n_freq, double2* __restrict__ H) {
+  const int i = blockIdx.x * kTfFreqs + threadIdx.x / kTfLanes, left = n_freq - k0, ml = threadIdx.x % kTfLanes;
+  const int k = k0 + min(i, left - 1);
   const int b = blockIdx.y;
-  const cx z = point(omega[min(k, n_freq - 1)]), z2 = cmul(z, z);
+  const cx z = point(omega[k]), z2 = cmul(z, z);
   const ff zero = {0.f, 0.f};
   cx acc = {zero, zero};
   for (int m = mode_off[b] + ml; m < mode_off[b + 1]; m += kTfLanes) {
@@ -137,18 +141,19 @@ __global__ void __launch_bounds__(kTfFreqs* kTfLanes) tf_response_kernel(const d
     acc = cadd(acc, cscale(cmul(N, cinv(D)), split(c[4])));
   }
   acc = {lanes_sum<kTfLanes>(acc.re), lanes_sum<kTfLanes>(acc.im)};
-  if (ml == 0 && k < n_freq) H[(long long)b * n_freq + k] = make_double2(join(acc.re), join(acc.im));
+  if (ml == 0 && i < left) H[(long long)b * n_freq + k] = make_double2(join(acc.re), join(acc.im));
 }
 
 __global__ void __launch_bounds__(kTfThreads) tf_grad_kernel(const double* __restrict__ coef,
                                                              const int* __restrict__ mode_off,
-                                                             const double* __restrict__ omega, int n_freq,
+                                                             const double* __restrict__ omega, int m0, int n_freq,
                                                              const double2* __restrict__ gH,
                                                              double* __restrict__ g_coef) {
   __shared__ float2 part[kTfThreads / kWave][5];
   const int b = blockIdx.y;
-  const int m = mode_off[b] + blockIdx.x;
-  if (m >= mode_off[b + 1]) return;
+  const int i = m0 + blockIdx.x;
+  if (i >= mode_off[b + 1] - mode_off[b]) return;
+  const int m = mode_off[b] + i;
   const double* c = coef + 5LL * m;
   const ff zero = {0.f, 0.f};
   const ff a1 = split(c[0]), a2 = split(c[1]), b1 = split(c[2]), b2 = split(c[3]), w = split(c[4]);
@@ -181,17 +186,26 @@ __global__ void __launch_bounds__(kTfThreads) tf_grad_kernel(const double* __res
 
 hipError_t launch_tf_response(const double* coef, const int* mode_off, int batch, const double* omega, int n_freq,
                               double2* H, hipStream_t s) {
-  hipLaunchKernelGGL(tf_response_kernel, dim3((n_freq + kTfFreqs - 1) / kTfFreqs, batch), dim3(kTfFreqs * kTfLanes), 0,
-                     s, coef, mode_off, omega, n_freq, H);
-  return hipGetLastError();
+  for (int k0 = 0, n; k0 < n_freq; k0 += n) {
+    n = std::min(n_freq - k0, kTfBlocks * kTfFreqs);
+    hipLaunchKernelGGL(tf_response_kernel, dim3((n + kTfFreqs - 1) / kTfFreqs, batch), dim3(kTfFreqs * kTfLanes), 0, s,
+                       coef, mode_off, omega, k0, n_freq, H);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_tf_grad(const double* coef, const int* mode_off, int batch, int max_modes, const double* omega,
                           int n_freq, const double2* gH, double* g_coef, hipStream_t s) {
-  if (max_modes < 1) return hipSuccess;
-  hipLaunchKernelGGL(tf_grad_kernel, dim3(max_modes, batch), dim3(kTfThreads), 0, s, coef, mode_off, omega, n_freq, gH,
-                     g_coef);
-  return hipGetLastError();
+  for (int m0 = 0, n; m0 < max_modes; m0 += n) {
+    n = std::min(max_modes - m0, kTfBlocks);
+    hipLaunchKernelGGL(tf_grad_kernel, dim3(n, batch), dim3(kTfThreads), 0, s, coef, mode_off, omega, m0, n_freq, gH,
+                       g_coef);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace modal
