@@ -43,6 +43,8 @@
 // ones, it took 0.40 ms; rows of 64 a wave (one wave per SIMD) 0.50.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -204,16 +206,17 @@ __global__ void __launch_bounds__(kWave* kLinWaves) lin_sum_kernel(LinParams P, 
 // powers of the two roots of a real pair), and s64[k][32] = (z^64)^a.
 __global__ void lin_tab_kernel(const LinMode* __restrict__ modes, int M, double* __restrict__ z,
                                double2* __restrict__ s64) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long k = i / (kLinCols + 32);
-  const int t = (int)(i % (kLinCols + 32));
-  if (k >= M) return;
-  if (t < kLinCols) {
-    const double2 v = mode_pow(modes[k], t);
-    z[(2 * k) * kLinCols + t] = v.x;
-    z[(2 * k + 1) * kLinCols + t] = v.y;
-  } else {
-    s64[k * 32 + t - kLinCols] = mode_pow(modes[k], (long long)kLinCols * (t - kLinCols));
+  const long long n = (long long)M * (kLinCols + 32), step = (long long)gridDim.x * blockDim.x;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) {
+    const long long k = i / (kLinCols + 32);
+    const int t = (int)(i % (kLinCols + 32));
+    if (t < kLinCols) {
+      const double2 v = mode_pow(modes[k], t);
+      z[(2 * k) * kLinCols + t] = v.x;
+      z[(2 * k + 1) * kLinCols + t] = v.y;
+    } else {
+      s64[k * 32 + t - kLinCols] = mode_pow(modes[k], (long long)kLinCols * (t - kLinCols));
+    }
   }
 }
 
@@ -320,8 +323,8 @@ hipError_t launch_lin_impulse(const LinParams& P, int n_forced, long long max_le
 hipError_t launch_lin_init(const LinInit* init, const LinMode* modes, int M, const float* e_ext, double2* amp,
                            double* z, double2* s64, hipStream_t s) {
   if (M < 1) return hipSuccess;
-  hipLaunchKernelGGL(lin_tab_kernel, dim3((unsigned)(((kLinCols + 32LL) * M + 255) / 256)), dim3(256), 0, s, modes, M,
-                     z, s64);
+  const long long tab_blocks = std::min(((kLinCols + 32LL) * M + 255) / 256, 1LL << 16);
+  hipLaunchKernelGGL(lin_tab_kernel, dim3((unsigned)tab_blocks), dim3(256), 0, s, modes, M, z, s64);
   hipLaunchKernelGGL(lin_amp_kernel, dim3((M + 63) / 64), dim3(64), 0, s, init, modes, M, e_ext, amp);
   return hipGetLastError();
 }

@@ -38,6 +38,8 @@
 // gradients), of which a batch of 128 rows still takes 6.4 us on average.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "mlp_kernels.h"
 
 namespace modal {
@@ -136,13 +138,14 @@ __device__ __forceinline__ void product(const MlpJob& J, int m0, int n0, int n1,
 __global__ void __launch_bounds__(kMlpThreads, 4) mlp_phase(MlpPhase P) {
   __shared__ __attribute__((aligned(16))) float T[kMlpSlices][32][kTS];
   const int t = threadIdx.x;
-  int blk = blockIdx.x, j = 0;
+  int blk = blockIdx.x + gridDim.x * blockIdx.y, j = 0;
 #pragma unroll
   for (int i = 0; i + 1 < kMlpJobs; ++i)
     if (blk >= P.job[i].blocks && j == i) blk -= P.job[i].blocks, ++j;
   // the whole job at once: its fields come from far away, and each one that
   // is fetched where it is used adds its latency to the launch's
   const MlpJob J = P.job[j];
+  if (blk >= J.blocks) return;  // (past the last row of a grid of several)
   asm volatile("" ::"s"(J.M), "s"(J.N), "s"(J.nk), "s"(J.width), "s"(J.mt), "s"(J.inv_mt), "s"(J.slices), "s"(J.ks), "s"(J.akt), "s"(J.bkt), "s"(J.mkt), "s"(J.o1kt), "s"(J.o2kt),
                "s"(J.vec), "s"(J.relu), "s"(J.A), "s"(J.B), "s"(J.src), "s"(J.idx), "s"(J.bias), "s"(J.mask),
                "s"(J.C), "s"(J.Z), "s"(J.zidx), "s"(J.p), "s"(J.m), "s"(J.v), "s"(J.o1), "s"(J.o2), "s"(J.csum),
@@ -151,7 +154,7 @@ __global__ void __launch_bounds__(kMlpThreads, 4) mlp_phase(MlpPhase P) {
   int tn = __umulhi(blk, J.inv_mt), tm = blk - tn * J.mt;  // tn is one too small at most
   if (tm >= J.mt) tm -= J.mt, ++tn;
   const int m0 = 32 * tm, n0 = J.width * tn, n1 = min(J.N, n0 + J.width);
-  if (P.loss && blockIdx.x == 0) {  // the previous launch's partial losses, in order
+  if (P.loss && blockIdx.x + blockIdx.y == 0) {  // the previous launch's partial losses, in order
     float s = 0.f;
     for (int i = t; i < P.n_lpart; i += kMlpThreads) s += P.lpart[i];
     float* red = &T[0][0][0];
@@ -311,7 +314,9 @@ __global__ void __launch_bounds__(kMlpThreads, 4) mlp_phase(MlpPhase P) {
 hipError_t launch_mlp_phase(const MlpPhase& P, hipStream_t s) {
   long long n = 0;
   for (const MlpJob& j : P.job) n += j.blocks;
-  hipLaunchKernelGGL(mlp_phase, dim3((unsigned)n), dim3(kMlpThreads), 0, s, P);
+  // a grid's row holds less than 2^32 threads: large phases take several
+  const long long x = std::min(n, 1LL << 15);
+  hipLaunchKernelGGL(mlp_phase, dim3((unsigned)x, (unsigned)((n + x - 1) / x)), dim3(kMlpThreads), 0, s, P);
   return hipGetLastError();
 }
 

@@ -200,6 +200,11 @@ bool stable(const Coef& c) {
   return std::fabs(c.p) <= 1.0 + tol && std::fabs(g) <= 1.0 - c.p + tol;
 }
 
+// Instances of a batch that may have a workgroup each: a grid holds less than
+// 2^32 threads, and the on-chip kernel takes 512 an instance.  Larger batches
+// stream.
+constexpr int kMaxOwnWgs = 1 << 22;
+
 struct Unit {
   int inst, row0, row1, slab;
   double cost;
@@ -940,6 +945,7 @@ bool chip_map(const modal_instance& I, const BlockPlan& bp, ChipMap& m, int& w_n
 // in a common tile; false if they do not.  `plans` gets the batch's class
 // structures, once they are needed.
 bool chip_plan(const modal_desc* d, BlockPlans& plans, std::vector<modal_ctx::Chip>& chips, int& w_tile, int& rows) {
+  if (d->batch > kMaxOwnWgs) return false;
   for (int b = 0; b < d->batch; ++b) {  // before any analysis
     const modal_instance& I = d->inst[b];
     if (I.n_t > kWave || (I.kind == MODAL_KIND_VK && I.n_in > kChipWaves * kChipMaxRows)) return false;
@@ -2039,7 +2045,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
       plain = d->inst[b].kind != MODAL_KIND_VK;
       nt_max = std::max(nt_max, d->inst[b].n_t);
     }
-    if (plain) wave_shape(nt_max, d->batch, prop0.multiProcessorCount, wave_lanes, wave_m);
+    if (plain && d->batch <= kMaxOwnWgs) wave_shape(nt_max, d->batch, prop0.multiProcessorCount, wave_lanes, wave_m);
   }
   // On-chip plan: a batch of any size whose instances each fit one
   // workgroup's registers (at most 64 modes; chip_plan) steps every instance
