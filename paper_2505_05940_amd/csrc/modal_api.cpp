@@ -284,8 +284,9 @@ struct modal_ctx {
   bool dev_flags = false;  // a launch that may raise the device's is unchecked,
   hipStream_t flag_stream = nullptr;  // the last of them on this stream
   long long n_runs = 0;
-  // a launch was recorded by a caller's capture: its replays advance the
-  // device's step counter unseen, so every later launch reads that one
+  // a launch was recorded by a caller's capture: its replays advance (or, a
+  // reset's, rewind) the device's step counter unseen, so every later launch
+  // reads that one
   bool captured = false;
   bool capturing = false;  // the launches being enqueued are
   long long* dStep = nullptr;
@@ -2570,6 +2571,7 @@ int modal_reset(modal_ctx* c, void* stream_) {
     c->steps = 0;
     return MODAL_OK;
   }
+  (void)host_steps(c, s);  // (a captured reset rewinds the device's counter when it is replayed)
   HIP_TRY(launch_reset(c->dState, c->dState0, (long long)c->state0.size(), c->dCtr, c->n_ctr, c->dPair, c->n_pair,
                        c->dFlags, c->hFlags, c->dStep, s));
   c->steps = 0;
