@@ -18,6 +18,7 @@ namespace {
 thread_local std::string g_mlp_err;
 int mfail(int code, const std::string& m) {
   g_mlp_err = m;
+  if (code == MODAL_EHIP || code == MODAL_ENOMEM) (void)hipGetLastError();  // the launches read the last error
   return code;
 }
 #define MHIP(expr)                                                                     \

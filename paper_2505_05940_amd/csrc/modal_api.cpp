@@ -114,11 +114,14 @@ int fail(int code, const std::string& msg) {
   return code;
 }
 
+// (an error that is reported is also cleared: the launches read the last one)
 #define HIP_TRY(expr)                                                               \
   do {                                                                              \
     hipError_t e_ = (expr);                                                         \
-    if (e_ != hipSuccess)                                                           \
+    if (e_ != hipSuccess) {                                                         \
+      (void)hipGetLastError();                                                      \
       return fail(MODAL_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_));  \
+    }                                                                               \
   } while (0)
 
 bool finite_all(const double* v, int n) {
@@ -481,8 +484,10 @@ template <class T>
 int dalloc(T** p, size_t bytes) {
   if (bytes == 0) bytes = 256;
   hipError_t e = hipMalloc((void**)p, bytes);
-  if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? MODAL_ENOMEM : MODAL_EHIP,
-                                   std::string("hipMalloc: ") + hipGetErrorString(e));
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(e == hipErrorOutOfMemory ? MODAL_ENOMEM : MODAL_EHIP, std::string("hipMalloc: ") + hipGetErrorString(e));
+  }
   return MODAL_OK;
 }
 
