@@ -2909,14 +2909,15 @@ int tf_upload(TfCall& t, const double* coef, const int32_t* mode_off, int32_t ba
   // (the gradients start on a multiple of 16 bytes)
   const size_t o_g = (nc + n_freq + 1) & ~(size_t)1, o_off = o_g + ng;
   const size_t n_in = o_off + (size_t)(batch + 2) / 2, o_out = (n_in + 1) & ~(size_t)1;
+  // the device's memory first: what it cannot hold is not packed on the host
+  int r = dalloc(&t.mem, sizeof(double) * (o_out + std::max<size_t>(n_out, 1)));
+  if (r) return r;
   std::vector<double>& h = t.host;
   h.assign(n_in, 0.);
   if (modes) std::memcpy(&h[0], coef, sizeof(double) * nc);
   std::memcpy(&h[nc], omega, sizeof(double) * n_freq);
   if (gH) std::memcpy(&h[o_g], gH, sizeof(double) * ng);
   std::memcpy(&h[o_off], mode_off, sizeof(int) * (batch + 1));
-  int r = dalloc(&t.mem, sizeof(double) * (o_out + std::max<size_t>(n_out, 1)));
-  if (r) return r;
   double* d = reinterpret_cast<double*>(t.mem);
   t.coef = d;
   t.omega = d + nc;

@@ -1,6 +1,6 @@
 """Transfer-function calls at the ends of their ranges: a bound on the modes of
-an instance far above what there is, and more frequencies than one launch takes
-(2^27).  The response of one mode is a closed form in numpy; the device's
+an instance far above what there is, more frequencies than one launch takes
+(2^27), and a gradient that the GPU's memory cannot hold.  The response of one mode is a closed form in numpy; the device's
 float-float arithmetic keeps about 48 bits of it."""
 import ctypes as C
 
@@ -61,3 +61,16 @@ def test_more_frequencies_than_a_launch_takes():
     rest = np.random.default_rng(2).integers(0, n, 100000)
     rest = rest[~np.isin(rest, at)]
     assert np.allclose(H[rest, 0], base.real, rtol=1e-11, atol=0) and np.allclose(H[rest, 1], base.imag, rtol=1e-11, atol=0)
+
+
+def test_gradient_beyond_the_memory():
+    """1.1 TB of dL/dH: refused before the host copies any of it (so the array
+    given for it need not exist)."""
+    import torch
+    from paper_2505_05940_amd import modal
+    n, batch = 1 << 20, 65535
+    off = np.zeros(batch + 1, np.int32)
+    off[1:] = 1
+    w, out = np.full(n, 1.0), np.zeros((1, 5))
+    code = modal.lib.modal_tf_grad(_ptr(COEF[:1].copy()), _ptr(off), batch, 1, _ptr(w), n, _ptr(np.zeros(2)), _ptr(out), None)
+    assert modal.STATUS[code] == "ENOMEM"
