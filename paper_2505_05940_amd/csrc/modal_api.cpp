@@ -9,12 +9,14 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <map>
 #include <mutex>
 #include <optional>
 #include <queue>
 #include <atomic>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <tuple>
 #include <vector>
@@ -114,7 +116,15 @@ int fail(int code, const std::string& msg) {
   return code;
 }
 
+// The end of a C entry that is a function-try-block: nothing throws across it
+// (what is thrown here is memory or threads running out).
+#define ENTRY_END                                                \
+  catch (const std::exception& e) {                              \
+    return fail(MODAL_ENOMEM, std::string("host: ") + e.what()); \
+  }
+
 // (an error that is reported is also cleared: the launches read the last one)
+
 #define HIP_TRY(expr)                                                               \
   do {                                                                              \
     hipError_t e_ = (expr);                                                         \
@@ -772,6 +782,34 @@ void analyze_blocks(const modal_instance& I, BlockPlan& bp) {
   bp.ok = true;
 }
 
+// f(t) for every t < n, each on a thread of its own, the first (and those that
+// get none) on the caller's.  An exception of any is thrown here once all have
+// ended.
+template <class F>
+void on_threads(unsigned n, F f) {
+  std::exception_ptr failed;
+  std::mutex mu;
+  auto run = [&](unsigned t) {
+    try {
+      f(t);
+    } catch (...) {
+      std::lock_guard<std::mutex> lock(mu);
+      failed = std::current_exception();
+    }
+  };
+  std::vector<std::thread> th;
+  th.reserve(n);
+  unsigned t = 1;
+  try {
+    for (; t < n; ++t) th.emplace_back(run, t);
+  } catch (const std::system_error&) {  // no more threads to be had
+  }
+  if (n > 0) run(0);
+  for (; t < n; ++t) run(t);
+  for (auto& x : th) x.join();
+  if (failed) std::rethrow_exception(failed);
+}
+
 bool device_pointer(const void* p) {
   hipPointerAttribute_t attr;
   if (hipPointerGetAttributes(&attr, p) == hipSuccess) return attr.type == hipMemoryTypeDevice;
@@ -814,15 +852,11 @@ void plan_blocks(const modal_desc* d, BlockPlans& bp) {
            (double)d->inst[b].n_in * d->inst[b].n_t * d->inst[b].n_t;
   });
   std::atomic<size_t> next{0};
-  auto work = [&]() {
+  auto work = [&](unsigned) {
     for (size_t i = next++; i < todo.size(); i = next++) analyze_blocks(d->inst[todo[i]], bp.plans[bp.of[todo[i]]]);
   };
   const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-  const unsigned nth = (unsigned)std::min<size_t>(hw, todo.size());
-  std::vector<std::thread> th;
-  for (unsigned t = 1; t < nth; ++t) th.emplace_back(work);
-  work();
-  for (auto& t : th) t.join();
+  on_threads((unsigned)std::min<size_t>(hw, todo.size()), work);
 }
 
 // A class-structured tensor's in-plane rows dealt to the waves of a
@@ -1168,10 +1202,7 @@ int upload_tensors(modal_ctx* c, const modal_desc* d, const std::vector<InstDev>
         };
         const int nr = n1 - n0;
         const unsigned nth = (unsigned)std::max(1, std::min({16, nr, (int)std::thread::hardware_concurrency()}));
-        std::vector<std::thread> th;
-        for (unsigned t = 1; t < nth; ++t) th.emplace_back(fill_rows, n0 + (int)(nr * t / nth), n0 + (int)(nr * (t + 1) / nth));
-        fill_rows(n0, n0 + (int)(nr / nth));
-        for (auto& t : th) t.join();
+        on_threads(nth, [&](unsigned t) { fill_rows(n0 + (int)(nr * t / nth), n0 + (int)(nr * (t + 1) / nth)); });
         UP_TRY(hipMemcpyAsync(c->dH + D.h_off + rs[n0], dst, sizeof(float) * (size_t)(rs[n1] - rs[n0]),
                               hipMemcpyHostToDevice, stream));
         UP_TRY(hipEventRecord(done[slot], stream));
@@ -1542,10 +1573,7 @@ int init_shared_class(modal_ctx* c, const modal_desc* d, std::vector<SharedGroup
     };
     const size_t nm = G.members.size();
     const size_t nth = std::min<size_t>({16, std::max(1u, std::thread::hardware_concurrency()), (nm + 1023) / 1024});
-    std::vector<std::thread> th;
-    for (size_t t = 1; t < nth; ++t) th.emplace_back(fill, nm * t / nth, nm * (t + 1) / nth);
-    fill(0, nm / nth);
-    for (auto& t : th) t.join();
+    on_threads((unsigned)nth, [&](unsigned t) { fill(nm * t / nth, nm * (t + 1) / nth); });
   }
   for (int b = 0; b < d->batch; ++b) {
     c->kind.push_back(d->inst[b].kind);
@@ -1885,7 +1913,7 @@ bool tuned_shape(const modal_desc* d, int& waves, int& max_wg, int& split_kb) {
 
 }  // namespace
 
-int modal_tune_key(const modal_desc* d, char* out, int32_t len) {
+int modal_tune_key(const modal_desc* d, char* out, int32_t len) try {
   if (!out || len < 17) return fail(MODAL_EINVAL, "out NULL or len < 17");
   int rc = validate(d);
   if (rc) return rc;
@@ -1894,7 +1922,7 @@ int modal_tune_key(const modal_desc* d, char* out, int32_t len) {
   if (rc) return rc;
   std::memcpy(out, key.c_str(), 17);
   return MODAL_OK;
-}
+} ENTRY_END
 
 // The latency kernel's own units, one a workgroup: the plan's instances of von
 // Karman kind, whole or in slabs (the plan's, or more that keep their rows in
@@ -1962,7 +1990,7 @@ static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::v
   return MODAL_OK;
 }
 
-int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
+static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, modal_ctx*& c) {
   if (!out) return fail(MODAL_EINVAL, "out is NULL");
   *out = nullptr;
   g_err.clear();
@@ -1981,7 +2009,7 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
     void* sp = nullptr;  // modal_run_noalloc's scratch, once per device
     HIP_TRY(resolve_scratch(device, &sp));
   }
-  modal_ctx* c = new modal_ctx();
+  c = new modal_ctx();
   c->device = device;
   c->batch = d->batch;
   c->scheme = d->scheme;
@@ -2568,7 +2596,17 @@ int modal_init(modal_ctx** out, const modal_desc* d_in, void* stream_) {
   return MODAL_OK;
 }
 
-int modal_reset(modal_ctx* c, void* stream_) {
+int modal_init(modal_ctx** out, const modal_desc* d, void* stream) {
+  modal_ctx* c = nullptr;
+  try {
+    return init_ctx(out, d, stream, c);
+  } catch (const std::exception& e) {
+    free_ctx(c);
+    return fail(MODAL_ENOMEM, std::string("host: ") + e.what());
+  }
+}
+
+int modal_reset(modal_ctx* c, void* stream_) try {
   if (!c) return fail(MODAL_EINVAL, "ctx is NULL");
   hipStream_t s = (hipStream_t)stream_;
   if (c->linear) {
@@ -2583,7 +2621,7 @@ int modal_reset(modal_ctx* c, void* stream_) {
   c->ckpt_broken = false;  // checkpoints of [0, ckpt_upto) stay valid
   c->ctr_stale = false;
   return MODAL_OK;
-}
+} ENTRY_END
 
 // Pinned flags, if there are any to be had: without them a context goes on
 // with the device's.  Another stream of the process may be under capture, which
@@ -2711,7 +2749,7 @@ int modal_check(modal_ctx* c, void* stream_) {
   return MODAL_OK;
 }
 
-int modal_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* stream_) {
+int modal_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* stream_) try {
   if (!c) return fail(MODAL_EINVAL, "ctx is NULL");
   if (n_steps < 0 || n_steps > (1LL << 31) - 1) return fail(MODAL_EINVAL, "n_steps out of range");
   if (n_steps == 0) return MODAL_OK;
@@ -2802,9 +2840,9 @@ int modal_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* s
   c->steps += n_steps;
   if (c->flags & MODAL_FLAG_ASYNC) return MODAL_OK;
   return modal_check(c, stream_);
-}
+} ENTRY_END
 
-int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* stream_) {
+int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* stream_) try {
   if (!c) return fail(MODAL_EINVAL, "ctx is NULL");
   if (n_steps < 0 || n_steps > (1LL << 31) - 1) return fail(MODAL_EINVAL, "n_steps out of range");
   if (n_steps == 0) return MODAL_OK;
@@ -2858,7 +2896,7 @@ int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride,
   c->ctr_stale = true;
   if (c->flags & MODAL_FLAG_ASYNC) return MODAL_OK;
   return modal_check(c, stream_);
-}
+} ENTRY_END
 
 int modal_set_tangent(modal_ctx* c, int32_t b, const float* Hd, void* stream_) {
   if (!c || !Hd) return fail(MODAL_EINVAL, "NULL argument");
@@ -2931,7 +2969,7 @@ int tf_upload(TfCall& t, const double* coef, const int32_t* mode_off, int32_t ba
 }  // namespace
 
 int modal_tf_response(const double* coef, const int32_t* mode_off, int32_t batch, const double* omega,
-                      int32_t n_freq, double* H, void* stream_) {
+                      int32_t n_freq, double* H, void* stream_) try {
   if (!coef || !mode_off || !omega || !H) return fail(MODAL_EINVAL, "NULL argument");
   int modes = 0;
   int r = tf_check(mode_off, batch, n_freq, modes);
@@ -2945,10 +2983,10 @@ int modal_tf_response(const double* coef, const int32_t* mode_off, int32_t batch
   HIP_TRY(hipMemcpyAsync(H, t.out, sizeof(double) * n, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   return MODAL_OK;
-}
+} ENTRY_END
 
 int modal_tf_grad(const double* coef, const int32_t* mode_off, int32_t batch, int32_t max_modes,
-                  const double* omega, int32_t n_freq, const double* dL_dH, double* g_coef, void* stream_) {
+                  const double* omega, int32_t n_freq, const double* dL_dH, double* g_coef, void* stream_) try {
   if (!coef || !mode_off || !omega || !dL_dH || !g_coef) return fail(MODAL_EINVAL, "NULL argument");
   int modes = 0;
   int r = tf_check(mode_off, batch, n_freq, modes);
@@ -2969,7 +3007,7 @@ int modal_tf_grad(const double* coef, const int32_t* mode_off, int32_t batch, in
   if (n) HIP_TRY(hipMemcpyAsync(g_coef + 5 * m0, t.out + 5 * m0, sizeof(double) * n, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   return MODAL_OK;
-}
+} ENTRY_END
 
 // Whether tensor H (host memory) of instance b has entries that its on-chip
 // layout leaves out.
@@ -3038,7 +3076,7 @@ static int chip_ungroup(modal_ctx* c, int b, hipStream_t s) {
   return MODAL_OK;
 }
 
-int modal_set_tensor(modal_ctx* c, int32_t b, const float* H, void* stream_) {
+int modal_set_tensor(modal_ctx* c, int32_t b, const float* H, void* stream_) try {
   if (!c || !H) return fail(MODAL_EINVAL, "NULL argument");
   if (c->shared || c->linear) return fail(MODAL_ESTATE, "the context keeps no per-instance tensor");
   if (b < 0 || b >= c->batch || c->kind[b] != MODAL_KIND_VK)
@@ -3097,11 +3135,11 @@ int modal_set_tensor(modal_ctx* c, int32_t b, const float* H, void* stream_) {
   c->ckpt_upto = 0;  // recorded checkpoints and trajectory belong to the old tensor
   c->rec_upto = 0;
   return MODAL_OK;
-}
+} ENTRY_END
 
 int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_stride, int32_t ckpt_every,
                double* g_omega, double* g_gamma, double* g_c, double* g_x0, double* g_xm1,
-               double* g_scale, double* g_theta, double* g_row, float* const* g_H, void* stream_) {
+               double* g_scale, double* g_theta, double* g_row, float* const* g_H, void* stream_) try {
   if (!c) return fail(MODAL_EINVAL, "ctx is NULL");
   if (!(c->flags & MODAL_FLAG_GRAD)) return fail(MODAL_ESTATE, "context not created with MODAL_FLAG_GRAD");
   if (n_steps < 1 || n_steps > (1LL << 31) - 1 || !ybar || y_stride < n_steps)
@@ -3375,9 +3413,9 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
     if (g_theta) g_theta[b] = theta[b];
   }
   return modal_reset(c, stream_);
-}
+} ENTRY_END
 
-int modal_get_state(modal_ctx* c, double* x, double* xm1, void* stream_) {
+int modal_get_state(modal_ctx* c, double* x, double* xm1, void* stream_) try {
   if (!c || !x || !xm1) return fail(MODAL_EINVAL, "NULL argument");
   hipStream_t s = (hipStream_t)stream_;
   if (c->linear) {
@@ -3417,7 +3455,7 @@ int modal_get_state(modal_ctx* c, double* x, double* xm1, void* stream_) {
     }
   }
   return MODAL_OK;
-}
+} ENTRY_END
 
 int modal_info(const modal_ctx* c, int64_t info[15]) {
   if (!c || !info) return fail(MODAL_EINVAL, "NULL argument");
@@ -3474,7 +3512,7 @@ int modal_launches(const modal_ctx* c, int64_t out[8]) {
 
 void modal_destroy(modal_ctx* c) { free_ctx(c); }
 
-int modal_plan(const modal_desc* d, int32_t n_workgroups, int64_t out[4]) {
+int modal_plan(const modal_desc* d, int32_t n_workgroups, int64_t out[4]) try {
   g_err.clear();
   if (!out || n_workgroups < 1) return fail(MODAL_EINVAL, "out NULL or n_workgroups < 1");
   int rc = validate(d);
@@ -3495,6 +3533,6 @@ int modal_plan(const modal_desc* d, int32_t n_workgroups, int64_t out[4]) {
   out[2] = (int64_t)*std::max_element(load.begin(), load.end());
   out[3] = (int64_t)(total / n_workgroups);
   return MODAL_OK;
-}
+} ENTRY_END
 
 }  // extern "C"
