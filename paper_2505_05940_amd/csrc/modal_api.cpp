@@ -218,6 +218,8 @@ bool stable(const Coef& c) {
 // stream.
 constexpr int kMaxOwnWgs = 1 << 22;
 
+constexpr int kXcds = 8;  // dies of the GPU, to which a grid's workgroups are dealt in turn
+
 struct Unit {
   int inst, row0, row1, slab;
   double cost;
@@ -381,10 +383,25 @@ struct modal_ctx {
   int sc_ks = 0, sc_rows = 0, sc_wg = 0;
   ScParams SC{};
   hipStream_t cap_stream = nullptr;  // private stream used only for graph capture
-  // > 0: the plan's workgroups wait for each other, on this share of the GPU
-  // (workgroups over co-resident ones, the widest of its kernels); the event
-  // marks the end of the last such launches
-  double together = 0.;
+  // The share of the GPU that launches need whose workgroups wait for each
+  // other (zero: none do), of the plan's kernels and of the latency kernels;
+  // the event marks the end of the last such launches.
+  struct Share {
+    double part = 0.;
+    bool whole_cu = true;  // each workgroup takes more than half a CU
+    // n workgroups, o a CU: they are dealt to the XCDs in turn, so an XCD gets
+    // up to n / 8 rounded up
+    void need(int n, int o, int cus) {
+      part = std::max(part, (n + kXcds - 1) / kXcds * kXcds / ((double)o * cus));
+      whole_cu = whole_cu && o == 1;
+    }
+    void need(const Share& s) {
+      if (!(s.part > 0.)) return;
+      part = std::max(part, s.part);
+      whole_cu = whole_cu && s.whole_cu;
+    }
+  };
+  Share plan_share, lat_share_gpu;
   hipEvent_t together_done = nullptr;
   struct Graph {
     int64_t n, stride;
@@ -400,18 +417,21 @@ namespace {
 // them are resident at once.  Two such launches on two streams could each get
 // half of what it needs, and both would then run into the wait limit, so a
 // launch waits (on the GPU) for as many earlier ones of the process as it takes
-// for those that may run beside it to need at most half of the GPU together
-// with it.  Half, because a CU that holds workgroups of several kernels may
-// refuse all of them when it is little more than half full.  Launches recorded
-// by a caller's capture are not ordered.  Held by the enqueuing thread from
-// before the first launch until after the last.
+// for those that may run beside it to fit with it: where each workgroup of all
+// of them takes more than half a CU, in the whole GPU, else in half of it,
+// because a CU that holds workgroups of several kernels may refuse all of them
+// when it is little more than half full.  Launches recorded by a caller's
+// capture are not ordered.  Held by the enqueuing thread from before the first
+// launch until after the last.  Lone 100/100 plates on
+// one, two and eight streams: 4.2, 4.3 and 8.9 us for a step of all; 200/200 on
+// one and two: 7.1 and 14.2.
 class Together {
  public:
-  Together(modal_ctx* c, bool waits, hipStream_t s) : c_(c), s_(s) {
+  Together(modal_ctx* c, const modal_ctx::Share& need, hipStream_t s) : c_(c), s_(s), need_(need) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (!waits || !(c->together > 0.) || c->device >= kMaxScratchDevices ||
+    if (!(need.part > 0.) || !c->together_done || c->device >= kMaxScratchDevices ||
         hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
-      if (waits) (void)hipGetLastError();
+      if (need.part > 0.) (void)hipGetLastError();
       c_ = nullptr;
       return;
     }
@@ -419,34 +439,27 @@ class Together {
     std::vector<Live>& live = list(c);
     live.reserve(live.size() + 1);
     drop(live, c);  // (a context's own launches are on one stream, or ordered by the caller)
-    double sum = c->together;
-    for (const Live& l : live) sum += l.share;
-    if (sum <= 0.5) return;
+    if (fits(live, 0)) return;
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another stream may be under capture)
     const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-    sum = c->together;
     live.erase(std::remove_if(live.begin(), live.end(), [](const Live& l) { return hipEventQuery(l.done) == hipSuccess; }),
                live.end());
     if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     (void)hipGetLastError();
-    for (const Live& l : live) sum += l.share;
-    for (const Live& l : live) {
-      if (sum <= 0.5) break;
-      if (hipStreamWaitEvent(s, l.done, 0) != hipSuccess) (void)hipGetLastError();
-      sum -= l.share;
-    }
+    for (size_t i = 0; i < live.size() && !fits(live, i); ++i)
+      if (hipStreamWaitEvent(s, live[i].done, 0) != hipSuccess) (void)hipGetLastError();
   }
   ~Together() {
     if (!c_) return;
     if (hipEventRecord(c_->together_done, s_) == hipSuccess)
-      list(c_).push_back({c_, c_->together_done, c_->together});
+      list(c_).push_back({c_, c_->together_done, need_});
     else
       (void)hipGetLastError();
   }
   Together(const Together&) = delete;
   Together& operator=(const Together&) = delete;
   static void forget(const modal_ctx* c) {
-    if (!(c->together > 0.) || c->device >= kMaxScratchDevices) return;
+    if (!c->together_done || c->device >= kMaxScratchDevices) return;
     std::lock_guard<std::mutex> lock(mu_);
     drop(list(c), c);
   }
@@ -455,8 +468,18 @@ class Together {
   struct Live {
     const modal_ctx* c;
     hipEvent_t done;
-    double share;
+    modal_ctx::Share need;
   };
+  // whether the launch fits beside those from the i-th on
+  bool fits(const std::vector<Live>& live, size_t i) const {
+    double sum = need_.part;
+    bool whole = need_.whole_cu;
+    for (; i < live.size(); ++i) {
+      sum += live[i].need.part;
+      whole = whole && live[i].need.whole_cu;
+    }
+    return sum <= (whole ? 1.0 : 0.5);
+  }
   static void drop(std::vector<Live>& live, const modal_ctx* c) {
     live.erase(std::remove_if(live.begin(), live.end(), [c](const Live& l) { return l.c == c; }), live.end());
   }
@@ -469,6 +492,7 @@ class Together {
   static std::mutex mu_;
   modal_ctx* c_;
   hipStream_t s_;
+  modal_ctx::Share need_;
   std::unique_lock<std::mutex> lock_;
 };
 std::mutex Together::mu_;
@@ -1972,8 +1996,8 @@ static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::v
     if (regs && share > kLatRegBlocks) continue;
     c->lat = fits(c->lat_nb, c->lat_units.size());
     if (!c->lat) continue;
-    const double n = (double)c->lat_units.size() / cus;
-    if (c->n_part) c->together = std::max(c->together, n / o);
+    const int n = (int)c->lat_units.size();
+    if (c->n_part) c->lat_share_gpu.need(n, o, cus);
     if (regs) {
       int rf = 0;
       for (const UnitDev& U : c->lat_units) rf = std::max(rf, (2 * U.qs + 4) * inst[U.inst].ntp);
@@ -1982,7 +2006,7 @@ static int plan_lat(modal_ctx* c, const std::vector<InstDev>& inst, const std::v
         (void)hipGetLastError();
       } else if ((size_t)o * cus >= c->lat_units.size()) {
         c->lat_red = rf;
-        if (c->n_part) c->together = std::max(c->together, n / o);
+        if (c->n_part) c->lat_share_gpu.need(n, o, cus);
       }
     }
     break;
@@ -2375,7 +2399,7 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
   c->chip_rows = chip_rows;
   c->nw_stream = c->nw;
   c->lds_stream = c->lds_bytes;
-  if (c->n_split > 0) c->together = (double)n_wg / ((double)occ * prop.multiProcessorCount);
+  if (c->n_split > 0) c->plan_share.need(n_wg, occ, prop.multiProcessorCount);
   if (chip_nt && !grad) {
     c->nw = kChipWaves;
     c->lds_bytes = 0;
@@ -2392,7 +2416,7 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
     if (S > 0 && o >= 1 && (long long)o * prop.multiProcessorCount >= n_wg) {
       c->res_stride = S;
       c->lds_bytes = lb;
-      if (c->n_split > 0) c->together = std::max(c->together, (double)n_wg / ((double)o * prop.multiProcessorCount));
+      if (c->n_split > 0) c->plan_share.need(n_wg, o, prop.multiProcessorCount);
       int r = plan_lat(c, inst, nslab, qs_of, lb, prop.multiProcessorCount);
       if (r) {
         free_ctx(c);
@@ -2484,7 +2508,7 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
     if (e_ != hipSuccess)                                                                 \
       return bail(fail(MODAL_EHIP, std::string(#expr) + ": " + hipGetErrorString(e_)));   \
   } while (0)
-  if (c->together > 0.) HIP_TRY_C(hipEventCreateWithFlags(&c->together_done, hipEventDisableTiming));
+  if (c->plan_share.part + c->lat_share_gpu.part > 0.) HIP_TRY_C(hipEventCreateWithFlags(&c->together_done, hipEventDisableTiming));
   {
     int r = alloc_reset(c, stream);
     if (r) return bail(r);
@@ -2637,9 +2661,10 @@ static void alloc_host_flags(modal_ctx* c) {
   (void)hipGetLastError();
 }
 
-// Whether forward launches have workgroups that wait for each other.
-static bool forward_waits(const modal_ctx* c) {
-  return !c->shared && !c->wave_lanes && !c->chip_nt && (c->lat ? c->n_part > 0 : c->n_split > 0);
+// What forward launches whose workgroups wait for each other need.
+static modal_ctx::Share forward_share(const modal_ctx* c) {
+  if (c->shared || c->wave_lanes || c->chip_nt) return {};
+  return c->lat ? c->lat_share_gpu : c->plan_share;
 }
 
 static bool reverse_on_lat(const modal_ctx* c) { return c->lat && c->lat_red && !c->chip_nt && !c->tangent; }
@@ -2825,11 +2850,11 @@ int modal_run(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride, void* s
       if (e != hipSuccess) return fail(MODAL_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
       c->graphs.push_back({n_steps, y_stride, y, exec});
     }
-    Together room(c, forward_waits(c), s);
+    Together room(c, forward_share(c), s);
     HIP_TRY(hipGraphLaunch(exec, s));
   } else {
     const bool recorded = c->run_ckpt, recorded_all = c->run_rec;
-    Together room(c, forward_waits(c), s);
+    Together room(c, forward_share(c), s);
     int r = enqueue_run(c, n_steps, y, y_stride, s);
     c->run_ckpt = false;
     c->run_rec = false;
@@ -2875,7 +2900,7 @@ int modal_run_noalloc(modal_ctx* c, int64_t n_steps, float* y, int64_t y_stride,
   const bool known = host_steps(c, s);
   const int64_t chunk = c->chunk > 0 ? c->chunk : n_steps;
   {
-    Together room(c, forward_waits(c), s);
+    Together room(c, forward_share(c), s);
     for (int64_t done = 0; done < n_steps; done += chunk) {
       const int64_t k = std::min<int64_t>(chunk, n_steps - done);
       StepParams P = c->P;
@@ -3238,7 +3263,9 @@ int modal_grad(modal_ctx* c, int64_t n_steps, const float* ybar, int64_t y_strid
   // in the kernel, and with the whole trajectory recorded one launch sweeps it
   const bool on_chip = c->wave_lanes || (c->chip_nt && !c->tangent);
   c->capturing = false;
-  std::optional<Together> room(std::in_place, c, forward_waits(c) || (!on_chip && (c->n_split > 0 || c->n_part > 0)), s);
+  modal_ctx::Share share = forward_share(c);
+  if (!on_chip) share.need(reverse_on_lat(c) ? c->lat_share_gpu : c->plan_share);
+  std::optional<Together> room(std::in_place, c, share, s);
   // the forward pass also records the whole trajectory while it fits, so
   // that the reverse sweep needs no segment recomputes
   bool rec_now = false;
