@@ -133,6 +133,8 @@ def dense_path(batch, n_modes, samples, launches, seed):
     # of the nonzero entries (mode classes leave most of the tensor zero)
     flops = info["flops_per_step"] * nonzero * samples
     achieved = flops / (launch_ms * 1e-3) / 1e12
+    ran = sim.launches()
+    assert ran["kernel"] == "shared by class"
     sim.close()
     return {
         "workload": f"proposal-prior von Karman plates sharing one coupling tensor up to per-row "
@@ -145,7 +147,7 @@ def dense_path(batch, n_modes, samples, launches, seed):
                      "unit": "TFLOP/s", "frac": achieved / FP32_MFMA_PEAK_TFLOPS, "traffic": None,
                      "kernel": "modal::shared_class_kernel", "launch_ms": launch_ms,
                      "algorithmic_flops_per_launch": flops},
-        "workgroups": info["workgroups"],
+        "workgroups": ran["workgroups"],
     }
 
 
@@ -184,7 +186,7 @@ def linear_path(batch, n_modes, seed):
                     f"{batch // 8} with a 1000-sample forcing",
         "value": modes * 44100 / t, "unit": "instance*mode*samples/s",
         "seconds": t, "recursion_seconds": res["recursion"],
-        "time_basis": "whole closed-form run (sum and convolution kernels, segment upload)",
+        "time_basis": "whole closed-form run (sum and convolution kernels)",
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": FP64_MFMA_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / FP64_MFMA_PEAK_TFLOPS, "traffic": None,
                      "kernel": "modal::lin_sum_kernel (FP64)"},
@@ -229,9 +231,9 @@ def single_instance_rates():
     """One instance at a time, as in the paper's benchmark (Sec. 4.2, Fig. 2):
     wall time of one modal_run over 1 s of audio at 44.1 kHz (the KC string:
     0.5 s) after a 441-step warm-up, HIP events on the launch stream, the
-    real-time factor (audio seconds per wall second) and the plan the library
-    chose (on-chip: one workgroup, tensor in registers; streaming: row slabs
-    on several workgroups)."""
+    real-time factor (audio seconds per wall second) and the kernel that ran
+    (on-chip: one workgroup, tensor in registers; wave: 16 to 64 lanes of one;
+    latency: row slabs on several workgroups, rows in registers)."""
     import torch
     import workloads as W
     from paper_2505_05940_amd import modal, physics
@@ -256,8 +258,7 @@ def single_instance_rates():
         t = a.elapsed_time(b) * 1e-3
         out.append({"case": name, "audio_s": steps / 44100.0, "wall_s": t,
                     "realtime_factor": steps / 44100.0 / t, "us_per_step": 1e6 * t / steps,
-                    "plan": {0: "streaming", 3: "on-chip"}.get(sim.info()["path"], "other"),
-                    "workgroups": sim.info()["workgroups"]})
+                    "plan": sim.launches()["kernel"], "workgroups": sim.launches()["workgroups"]})
         sim.close()
     return {"runs": out}
 
@@ -269,10 +270,12 @@ def adjoint_200():
     (forward with checkpoints and the trajectory record, then the reverse
     sweep), and apart, the forward pass (a recording modal_run) and the
     reverse sweep that reuses its record, each bracketed by HIP events on
-    the stream the context launches on.  Roofline of the reverse sweep: its
-    algorithmic bytes are the dense tensor, 4 n_in n_t^2, streamed once per
-    step (two right-hand sides per row), against the HBM peak; the plate is
-    bound by each step's latency across 200 slab workgroups, not by bytes."""
+    the stream the context launches on.  Roofline of the reverse sweep: the
+    dense tensor's bytes, 4 n_in n_t^2 a step (two right-hand sides per row),
+    against the HBM peak.  The latency kernel holds the rows in the registers
+    of 200 slab workgroups and streams nothing, so this is the rate at which
+    memory would have to deliver them; a step is bound by the exchange between
+    the slabs."""
     import torch
     import workloads as W
     from paper_2505_05940_amd import modal, physics
@@ -298,17 +301,18 @@ def adjoint_200():
     sim.reset()
     fwd = timed(lambda: sim.run(steps, out=y))
     rev = timed(lambda: sim.grad(steps, g))  # reuses the run's checkpoints and record
-    workgroups = sim.info()["workgroups"]
+    ran = sim.launches()
+    assert ran["reverse"] == "latency"
     sim.close()
     tensor_bytes = 4.0 * n * n * n
     achieved = tensor_bytes * steps / rev / 1e9
     return {"workload": f"gradient of a {n}/{n}-mode sine von Karman plate over 1 s ({steps} steps) "
                         "from the initial state, constant dL/dy",
-            "wall_s": wall, "forward_s": fwd, "reverse_s": rev, "workgroups": workgroups,
+            "wall_s": wall, "forward_s": fwd, "reverse_s": rev, "workgroups": ran["reverse_workgroups"],
             "forward_us_per_step": 1e6 * fwd / steps, "reverse_us_per_step": 1e6 * rev / steps,
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                         "kernel": "modal::grad_kernel (reverse sweep)",
+                         "kernel": "modal::lat_grad_kernel (reverse sweep)",
                          "algorithmic_bytes_per_step": tensor_bytes}}
 
 
