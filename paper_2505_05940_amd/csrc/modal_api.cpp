@@ -260,7 +260,7 @@ struct modal_ctx {
   // tile in which every tensor fits whole, with layouts for it, or if there is
   // none the streaming plan.
   int whole_nt = 0, whole_rows = 0;
-  ChipMap* dChipWhole = nullptr;
+  std::vector<ChipMap> chips_whole;  // (on the device behind dChip's)
   bool capture_streams = false;
   struct Chip {
     ChipMap map;
@@ -506,7 +506,7 @@ void free_ctx(modal_ctx* c) {
                   c->dStep, c->dE,   c->dHd,   c->dCkpt,  c->dRec,  c->dAdj, c->dAcc,
                   c->dGPart, c->dGCtr, c->dShA, c->dShS2, c->dJmap, c->dRrec, c->dRacc,
                   c->dLinModes, c->dLinInit, c->dLinInst, c->dLinAmp, c->dLinZ, c->dLinS, c->dLinForced,
-                  c->dLinH, c->dUrec, c->dTrec, c->dTJobs, c->dRecAll, c->dChip, c->dChipWhole};
+                  c->dLinH, c->dUrec, c->dTrec, c->dTJobs, c->dRecAll, c->dChip};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->hFlags) (void)hipHostFree(c->hFlags);  // (no launch is left: hipFree waits for the device)
@@ -1295,13 +1295,12 @@ int upload_tensors(modal_ctx* c, const modal_desc* d, const std::vector<InstDev>
 
 // The layouts in which every tensor of the batch is held whole; false if it
 // does not fit so.
-bool chip_plan_whole(const modal_ctx* c, const modal_desc* d, std::vector<ChipMap>& maps, int& w_tile, int& rows) {
+bool chip_plan_whole(const modal_desc* d, std::vector<ChipMap>& maps, int& w_tile, int& rows) {
   maps.resize(d->batch);
   int max_w = 0, max_r = 0;
   for (int b = 0; b < d->batch; ++b) {
     int w = 0, r = 0;
     if (!chip_map(d->inst[b], BlockPlan{}, maps[b], w, r)) return false;
-    maps[b].unit = c->chips[b].map.unit;
     max_w = std::max(max_w, w);
     max_r = std::max(max_r, r);
   }
@@ -1312,6 +1311,10 @@ bool chip_plan_whole(const modal_ctx* c, const modal_desc* d, std::vector<ChipMa
 int upload_chips(modal_ctx* c, hipStream_t s) {
   std::vector<ChipMap> m(c->chips.size());
   for (size_t b = 0; b < m.size(); ++b) m[b] = c->chips[b].map;
+  for (size_t b = 0; b < c->chips_whole.size(); ++b) {
+    c->chips_whole[b].unit = m[b].unit;
+    m.push_back(c->chips_whole[b]);
+  }
   HIP_TRY(hipMemcpyAsync(c->dChip, m.data(), sizeof(ChipMap) * m.size(), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));
   return MODAL_OK;
@@ -2496,7 +2499,16 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
   ALLOC(c->dStep, sizeof(long long));
   ALLOC(c->dE, sizeof(float) * (size_t)(e_floats + 1));
   ALLOC(c->dJmap, sizeof(int) * (jmap_pool.size() + 4));
-  if (c->chip_nt) ALLOC(c->dChip, sizeof(ChipMap) * d->batch);
+  if (c->chip_nt) {
+    const bool grouped = std::any_of(c->chips.begin(), c->chips.end(), [](const modal_ctx::Chip& h) { return h.grouped; });
+    if (grouped && (d->flags & (MODAL_FLAG_GRAD | MODAL_FLAG_NO_BLOCK)) &&
+        !chip_plan_whole(d, c->chips_whole, c->whole_nt, c->whole_rows)) {
+      c->chips_whole.clear();
+      c->whole_nt = c->whole_rows = 0;
+      c->capture_streams = true;
+    }
+    ALLOC(c->dChip, sizeof(ChipMap) * (d->batch + c->chips_whole.size()));
+  }
 #undef ALLOC
   auto bail = [&](int r) {
     free_ctx(c);
@@ -2525,19 +2537,6 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
         if (udev[u].slab == 0) c->chips[udev[u].inst].map.unit = u;
       r = upload_chips(c, stream);
       if (r) return bail(r);
-      const bool grouped = std::any_of(c->chips.begin(), c->chips.end(), [](const modal_ctx::Chip& h) { return h.grouped; });
-      std::vector<ChipMap> whole;
-      if (grouped && (d->flags & (MODAL_FLAG_GRAD | MODAL_FLAG_NO_BLOCK))) {
-        if (chip_plan_whole(c, d, whole, c->whole_nt, c->whole_rows)) {
-          r = dalloc(&c->dChipWhole, sizeof(ChipMap) * whole.size());
-          if (r) return bail(r);
-          HIP_TRY_C(hipMemcpyAsync(c->dChipWhole, whole.data(), sizeof(ChipMap) * whole.size(), hipMemcpyHostToDevice, stream));
-          HIP_TRY_C(hipStreamSynchronize(stream));
-        } else {
-          c->whole_nt = c->whole_rows = 0;
-          c->capture_streams = true;
-        }
-      }
     }
   }
   char* meta = (char*)c->dMeta;
@@ -2691,7 +2690,7 @@ static int launch_forward(modal_ctx* c, StepParams P, hipStream_t s) {
   if (c->wave_lanes)
     HIP_TRY(launch_wave_step(P, c->wave_lanes, c->wave_m, c->batch, s));
   else if (c->chip_nt && c->capturing && c->whole_nt) {
-    P.chip = c->dChipWhole;
+    P.chip = c->dChip + c->batch;
     HIP_TRY(launch_chip(P, c->whole_nt, c->whole_rows, c->batch, s));
   } else if (c->chip_nt && !captured_stream)
     HIP_TRY(launch_chip(P, c->chip_nt, c->chip_rows, c->batch, s));
