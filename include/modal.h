@@ -357,7 +357,8 @@ int modal_grad(modal_ctx *c, int64_t n_steps, const float *dL_dy, int64_t y_stri
  * so by stepping with the symmetric part of g_H.  The state is left as it
  * is, and replays of launches that a caller captured go on with the new
  * tensor.  ESTATE on the shared-tensor and linear paths, for parity-blocked
- * instances (MODAL_FLAG_GRAD keeps tensors dense), and for a tensor that has
+ * instances and those of a batch that stores them so where it does not step
+ * on chip (MODAL_FLAG_GRAD keeps tensors dense), and for a tensor that has
  * entries outside its mode_class structure where captured launches hold it
  * on chip by class (only without MODAL_FLAG_GRAD and MODAL_FLAG_NO_BLOCK);
  * EINVAL for a bad index or an asymmetric tensor (the stored tensor is then

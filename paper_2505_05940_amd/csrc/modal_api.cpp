@@ -266,6 +266,7 @@ struct modal_ctx {
     ChipMap map;
     int w, r;
     bool grouped;
+    bool fixed = false;  // stored by class where the batch streams: set_tensor refuses it
   };
   std::vector<Chip> chips;
   // > 0: the wave kernels (no instance has a tensor), with this many lanes
@@ -2139,6 +2140,9 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
       c->chips.clear();
     }
   }
+  // such a batch's tensors cannot be replaced, however there is memory for them
+  if (chip_nt && may_block)
+    for (int b = 0; b < d->batch; ++b) c->chips[b].fixed = plans[b].ok;
   if (chip_nt || !may_block) plans = BlockPlans{};  // held dense
   else if (plans.of.empty()) plan_blocks(d, plans);
   std::vector<int> jmap_pool;
@@ -3106,7 +3110,8 @@ int modal_set_tensor(modal_ctx* c, int32_t b, const float* H, void* stream_) try
   if (b < 0 || b >= c->batch || c->kind[b] != MODAL_KIND_VK)
     return fail(MODAL_EINVAL, "set_tensor needs a VK instance index");
   const InstDev& D = c->inst_host[b];
-  if (D.blk) return fail(MODAL_ESTATE, "the instance's tensor is stored parity-blocked");
+  if (D.blk || (c->chip_nt && c->chips[b].fixed))
+    return fail(MODAL_ESTATE, "the instance's tensor is stored parity-blocked");
   hipStream_t s = (hipStream_t)stream_;
   // the kernels use the symmetry of every row in its last two indices
   hipPointerAttribute_t attr;
