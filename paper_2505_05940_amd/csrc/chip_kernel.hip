@@ -32,7 +32,7 @@
 //
 // Bound by vector issue (two waves per SIMD, W R multiply-adds a wave) and
 // the latency of the LDS round trips and the barrier: a 40/40 plate by class
-// (a tile of 12 columns and 5 or 6 rows) steps in 0.60 us.  With wave 0 alone
+// (a tile of 12 columns and 5 or 6 rows) steps in 0.57 us.  With wave 0 alone
 // keeping the state, a second barrier for q^n, a full wave sum per row and the
 // output summed every step it took 0.84 us (0.95 with a float-float state).
 #include <hip/hip_runtime.h>

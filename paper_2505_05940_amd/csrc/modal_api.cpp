@@ -622,29 +622,32 @@ constexpr double kRecAllBytes = 2.0 * 1073741824.0;
 // instance cut into slabs of about kLatencyRows in-plane rows (at most
 // no more than CUs / batch, and only in batches of at most
 // kLatencyMaxSplitBatch instances), one slab per workgroup.
-// Measured on single sine-family plates: 100/100 modes step in 11.0 us this
-// way (13 slabs), against 82 us blocked on the byte-balanced plan; 50/50 in
-// 9.1 us against 39.6 us.  About 8 rows, one per wave, was the best slab size
-// of 5, 6, 8 and 10 (100/100: 13.2, 11.8, 11.0, 13.5 us): smaller slabs add
-// workgroups to every step's exchange, larger ones give some waves two rows.
-// Default limit of a wait for the other slabs of a split instance, in ticks
-// of the device's 100 MHz clock (4 s).
-constexpr unsigned long long kBarrierTicks = 400000000ull;
+// Plates alone then step on the latency kernel, on at least as many slabs of its
+// own (lat_slabs); the streaming kernel with resident state steps this plan
+// where a string is beside them, and reverse sweeps with a tangent.  There a
+// plate and a 12-mode string take 8.9 us a step (72/72 modes), 8.0 (100/100)
+// and 11.1 (200/200), against 24, 31 and 68 us on the byte-balanced plan of 256
+// workgroups.  About 8 rows, one per wave, was the best slab size of 5, 6, 8 and
+// 10 when all lone plates stepped so (100/100: 13.2, 11.8, 11.0, 13.5 us, 8.0
+// since): smaller slabs add workgroups to every step's exchange, larger ones
+// give some waves two rows.
 constexpr double kLatencyBytes = 64.0 * 1048576.0;
 constexpr int kLatencyRows = 8;
 constexpr int kLatencyMaxSplitBatch = 16;  // larger latency-bound batches keep instances whole
+// Default limit of a wait for the other slabs of a split instance, in ticks
+// of the device's 100 MHz clock (4 s).
+constexpr unsigned long long kBarrierTicks = 400000000ull;
 // A large instance of such a batch is also cut so that no slab streams more
 // than about this many tensor bytes per step (the waves of a one-unit
 // workgroup share its row blocks, so slabs of fewer rows than waves keep
 // every wave busy); half as many for a tensor larger than kLatencyBigTensor,
 // which no longer stays in the XCDs' L2 caches, so that more CUs stream it
-// from the last-level cache.  Measured on lone sine plates with the partial
-// forces exchanged as 16-byte coherent accesses: a 100/100 plate (4 MB)
-// steps in 9.0 us with 256 KB slabs (16) against 11.5 us at 128 KB (31) and
-// 11.7 us at 384 KB (13); a 200/200 plate (32 MB) steps forward in 14.1 us
-// with 128 KB slabs (one in-plane row each, 200) against 16.9 us at 256 KB
-// (123) and 21.2 us at 512 KB (62), its forward and reverse step together in
-// 32.8 us against 38.4 and 47.0 us.
+// from the last-level cache.  Measured on lone sine plates when the streaming
+// kernel stepped them: a 100/100 plate (4 MB) 9.0 us with 256 KB slabs (16),
+// 11.5 us at 128 KB (31) and 11.7 us at 384 KB (13); a 200/200 plate (32 MB)
+// forward 14.1 us with 128 KB slabs (one in-plane row each, 200), 16.9 us at
+// 256 KB (123) and 21.2 us at 512 KB (62), its forward and reverse step
+// together 32.8, 38.4 and 47.0 us.
 constexpr double kLatencySlabBytes = 256.0 * 1024.0;
 constexpr double kLatencyBigTensor = 16.0 * 1048576.0;
 constexpr int kLatRegBlocks = 8;  // row blocks (4 KB) of a wave that the latency kernel keeps in registers
@@ -2224,9 +2227,9 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
   HIP_TRY(hipGetDeviceProperties(&prop, dev));
   // Waves per workgroup.  A batch of small instances, at most one per CU, is
   // bound by the latency of each step rather than by bytes: eight waves share
-  // a unit's rows when their reduction space fits the LDS (a single 40/40
-  // plate steps in 10.4 us instead of 16.2 us).  Larger batches stream with
-  // four waves and three workgroups per CU.
+  // a unit's rows when their reduction space fits the LDS (30 plates at 72/72
+  // on 240 workgroups: 13.2 us with eight waves, 15.1 with four).  Larger
+  // batches stream with four waves and three workgroups per CU.
   c->nw = d->waves == 0 ? 4 : d->waves;
   if (d->waves == 0 && d->batch <= prop.multiProcessorCount) {
     bool small = true;
@@ -2393,12 +2396,11 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
   // A latency-bound plan gives every workgroup one unit; its state and
   // coefficients then stay in LDS for the whole launch, which takes the
   // global round trips of the output and the update out of every step (a
-  // lone 100/100 plate in 15 slabs steps in 12.0 us instead of 12.5, a
-  // Berger plate in 2.4 us instead of 2.9).  Only
+  // 100/100 plate, in 15 slabs when it took one, 12.0 us instead of 12.5).  Only
   // when the variant still fits every planned workgroup on the chip at once.
   // Where all instances are von Karman plates the latency kernel takes them
-  // (100/100: 4.3 us), on units of its own; this plan is what a reverse sweep
-  // with a tangent steps on and what modal_info reports.
+  // (100/100: 4.2 us), on units of its own; this plan is what mixed batches and
+  // reverse sweeps with a tangent step on and what modal_info reports.
   c->res_stride = 0;
   c->wave_lanes = wave_lanes;
   c->wave_m = wave_m;

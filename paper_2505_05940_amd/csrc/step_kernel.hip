@@ -974,8 +974,8 @@ struct RowRegs {
 // store step n + 2 after it has read every slab's step n + 1, which each slab
 // stores after it has read step n.  A word of an older run never matches: a
 // reset and a restore clear them to a step that is past.
-// Lone sine plates, us a step in step_kernel and here: 66/66 10.0, 3.8;
-// 100/100 8.0, 4.3; 128/128 10.2, 4.3; 160/160 13.3, 6.6; 200/200 12.0, 7.3.
+// Lone sine plates, us a step in step_kernel and here: 66/66 10.0, 3.7;
+// 100/100 8.0, 4.2; 128/128 10.2, 4.3; 160/160 13.3, 6.4; 200/200 12.0, 7.1.
 // 100/100 without the rows in registers 5.3.  What is left is the exchange
 // (about 2 us, two of them at 200 slabs), the reductions of a row through LDS
 // and three barriers.
@@ -1243,7 +1243,9 @@ __global__ void __launch_bounds__(kWave * NW) lat_kernel(StepParams P) {
 // linear in it, so each slab sums dbar F over the steps for its own part (gs)
 // and lat_sum_kernel adds the slabs.  Lone sine plates, us a step of a
 // gradient less its forward pass, with grad_kernel and here: 66/66 17.8, 6.6;
-// 100/100 15.0, 7.5; 128/128 18.2, 8.3; 200/200 24.5, 14.8.
+// 100/100 15.0, 7.5; 128/128 18.2, 8.3; 200/200 24.5, 14.8; of a reverse sweep
+// that reuses the forward run's record 5.5, 6.0, 5.8 and 8.0.  The variant of
+// eight blocks spills 68 bytes a lane.
 template <int NW, int NB>
 __global__ void __launch_bounds__(kWave * NW) lat_grad_kernel(GradParams P) {
   extern __shared__ float4 lds4[];
