@@ -700,6 +700,20 @@ constexpr double kMinSplitCost = 0.5 * 1048576.0;
 // A batch of at most one instance per CU whose instances all cost less than
 // this is bound by a step's latency: eight waves a workgroup.
 constexpr double kSmallCost = 4.0 * 1048576.0;
+// Rows that a slab of an instance below kSmallCost holds at least: four, or
+// 128 KB of them.  Every slab adds up all slabs' partial forces, so where few
+// instances meet many workgroups, slabs of one row are slower than slabs of
+// four and, with 8 waves, than the whole instance: lone plates of 50, 64 and
+// 80 modes, us a step in one-row slabs, four-row slabs and whole, 4 waves 17.8,
+// 8.8, 20.4; 20.5, 9.8, 28.4; 25.5, 11.5, 45.7; 8 waves 18.1, 9.3, 13.4; 20.9,
+// 10.4, 17.0; 25.8, 12.2, 27.4.  Six rows gain more with 8 waves and less with
+// 4.  Batches that fill the GPU are cut no finer than this anyway.
+constexpr int kSlabRows = 4;
+constexpr double kSlabBytes = 131072.0;
+int slab_rows_least(const modal_desc* d, double whole, double row_cost) {
+  if ((d->flags & MODAL_FLAG_SPLIT_ANY) || whole >= kSmallCost) return 1;
+  return std::min(kSlabRows, (int)std::ceil(kSlabBytes / row_cost));
+}
 
 // ------------------------------------------------------ parity-blocked tensors
 // Internal layout of an instance whose tensor splits by mode class: modes
@@ -1075,7 +1089,7 @@ int pack(const modal_desc* d, const std::vector<double>& row_cost,
     if (I.kind == MODAL_KIND_VK && whole > cap && may_split) {
       const double sync = (d->flags & MODAL_FLAG_SPLIT_ANY) ? 0.0 : split_cost(d);
       const int per = (int)std::floor((cap - sync - fixed_cost[b]) / row_cost[b]);
-      if (per < 1) return n_bins + 1;
+      if (per < slab_rows_least(d, whole, row_cost[b])) return n_bins + 1;
       S = (rows + per - 1) / per;
     }
     if (S > n_bins) return n_bins + 1;
@@ -1123,7 +1137,8 @@ bool plan_batch(const modal_desc* d, const std::vector<double>& row_cost,
   for (int b = 0; b < d->batch; ++b) {
     const double whole = fixed_cost[b] + (d->inst[b].kind == MODAL_KIND_VK ? d->inst[b].n_in : 1) * row_cost[b];
     const double one_row = ((d->flags & MODAL_FLAG_SPLIT_ANY) ? 0.0 : split_cost(d)) + fixed_cost[b] +
-                           (d->inst[b].kind == MODAL_KIND_VK ? row_cost[b] : 0.0);
+                           (d->inst[b].kind == MODAL_KIND_VK
+                                ? row_cost[b] * slab_rows_least(d, whole, row_cost[b]) : 0.0);
     const bool may_split = (d->flags & MODAL_FLAG_SPLIT_ANY) || whole >= kMinSplitCost;
     max_item = std::max(max_item, may_split ? std::min(whole, one_row) : whole);
   }
