@@ -26,6 +26,10 @@ from . import modal
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_tune_cache.json")
 SHAPES = ((4, 2), (4, 3), (8, 1), (8, 2), (1, 6), (1, 8))
 SPLIT_COSTS_KB = (8, 16, 32, 64, 128)  # the planner's default is 32
+# Timed runs of a candidate, of which the fastest counts: a batch of strings
+# runs 100 samples in 0.03 ms on its own kernel, less than the host may pause
+# between the events, and one run alone has kept a plan five times slower.
+REPEATS = 4
 
 
 def _time(insts, fs, flags, samples, log, **kw):
@@ -39,14 +43,17 @@ def _time(insts, fs, flags, samples, log, **kw):
         return None
     y = torch.empty((len(insts), samples), device="cuda")
     sim.run(samples, out=y)
-    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    a.record()
-    sim.run(samples, out=y)
-    b.record()
-    torch.cuda.synchronize()
+    ms = None
+    for _ in range(REPEATS):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        sim.run(samples, out=y)
+        b.record()
+        torch.cuda.synchronize()
+        t = a.elapsed_time(b) / samples
+        ms = t if ms is None else min(ms, t)
     sim.check()
     sim.close()
-    ms = a.elapsed_time(b) / samples
     if log:
         log(f"autotune: {kw} -> {ms:.4f} ms/sample")
     return ms
