@@ -2948,6 +2948,8 @@ int modal_set_tangent(modal_ctx* c, int32_t b, const float* Hd, void* stream_) {
   if (c->shared) return fail(MODAL_ESTATE, "tangents need a context created with MODAL_FLAG_GRAD");
   if (b < 0 || b >= c->batch || c->kind[b] != MODAL_KIND_VK)
     return fail(MODAL_EINVAL, "tangent needs a VK instance index");
+  // (the copy below is as large as the dense tensor)
+  if (c->inst_host[b].blk) return fail(MODAL_ESTATE, "the instance's tensor is stored parity-blocked");
   hipStream_t s = (hipStream_t)stream_;
   if (!c->dHd) {
     int r = dalloc(&c->dHd, sizeof(float) * (size_t)(c->h_floats + 64));
