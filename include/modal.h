@@ -303,7 +303,9 @@ void modal_destroy(modal_ctx *c);
 
 /* Tangent tensor of instance `inst` (VK only): Hd = dHt/dtheta for one
  * scalar parameter theta, [n_in][n_t][n_t] like H, host or device memory,
- * copied.  modal_grad then also returns dL/dtheta through the tensor. */
+ * copied.  modal_grad then also returns dL/dtheta through the tensor.
+ * MODAL_ESTATE where the instance's tensor is stored by class (contexts with
+ * MODAL_FLAG_GRAD keep tensors dense). */
 int modal_set_tangent(modal_ctx *c, int32_t inst, const float *Hd, void *stream);
 
 /* Reverse-mode gradient of a loss L(y) over the first n_steps outputs of
