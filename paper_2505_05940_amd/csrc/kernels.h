@@ -36,8 +36,8 @@ struct InstDev {
   // the columns of class j = jmap[n][i] & 7 (or nothing if jmap < 0), as wide
   // as class j, at float offset boff[n][i] from the instance's start; w is
   // the widest class.  A map entry also holds bit 3 (the block stands for its
-  // transpose too), the rows per piece qs = min(rows, 256 / (width / 4)) in
-  // bits 4..12 and the number of pieces from bit 13.
+  // transpose too), the rows per piece qs = min(rows, 256 / (width / 4)),
+  // at most 64 with bit 3, in bits 4..12 and the number of pieces from bit 13.
   int blk, w;
   int cls[5];
   int row_off;         // VK: offset of its in-plane rows in per-row pools

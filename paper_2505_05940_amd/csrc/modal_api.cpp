@@ -2185,7 +2185,8 @@ static int init_ctx(modal_ctx** out, const modal_desc* d_in, void* stream_, moda
         const int R = bp.cls[i + 1] - bp.cls[i];
         if (je >= 0 && R > 0) {
           const int tlen = (bp.cls[(je & 7) + 1] - bp.cls[je & 7]) / 4;
-          const int qs = std::min(R, (kSweepLoads * kWave) / tlen);
+          // (a paired block's row sums are one a lane)
+          const int qs = std::min({R, (kSweepLoads * kWave) / tlen, je & 8 ? kWave : R});
           je |= (qs << 4) | (((R + qs - 1) / qs) << 13);
         }
         jmap_pool.push_back(je);

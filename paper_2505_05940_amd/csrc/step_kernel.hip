@@ -284,7 +284,8 @@ __device__ void vk_rows_finish(const float* xv, const int* xr, int nw, int wave,
 // j = jmap[n][i] only (every other entry of those rows is zero), as a block
 // as wide as class j (padded to 4) at its own offset (the second int4 of the
 // row's map entry).  The sweep is the dense one applied to each (n, i) block
-// in turn: pieces of qs = min(rows, 256 / (width / 4)) stored rows, lane slot
+// in turn: pieces of qs = min(rows, 256 / (width / 4)) stored rows (at most 64 of
+// a block that stands for its transpose, whose row sums are one a lane), lane slot
 // v = lane + 64 j reading float4 v of the piece (sub-row v / (width / 4)),
 // buffer resources sized to the valid rows, the next piece's loads issued
 // before the current one is used.  Accumulating along the
@@ -307,7 +308,7 @@ struct BlkMeta {
   int flags;  // 1: last block of its class, 2: last of its row, 4: last overall,
               // 8: the block also stands for its transpose (row dot products)
   int rows;   // valid stored rows in the block
-  int qs;     // sub-rows of the block's slot layout (256 / tlen, at most the class)
+  int qs;     // sub-rows of the block's slot layout (256 / tlen, at most the class; 64 if flag 8)
 };
 
 __device__ __forceinline__ int sel4(const int4 v, int i) {
@@ -367,7 +368,7 @@ __device__ void vk_rows_blk(const float* __restrict__ Hb, const int4* __restrict
       const int tj = je & 7;
       m.tc = co(tj) >> 2;
       m.tlen = (co(tj + 1) - co(tj)) >> 2;
-      m.qs = (je >> 4) & 511;  // min(R, 256 / tlen), from the map entry
+      m.qs = (je >> 4) & 511;  // from the map entry
       const int nb = je >> 13;  // pieces of the block
       m.q0 = co(li) + lb * m.qs;
       m.rows = min(m.qs, R - lb * m.qs);
